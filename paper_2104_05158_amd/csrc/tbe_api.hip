@@ -43,6 +43,16 @@ const char* const kSlotNames[SLOT_COUNT] = {"forward",       "sort_plan",  "radi
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 constexpr int kDenseGrid = 1024;
+// Lookups from which a wavefront of the update kernel owns 128 sorted positions instead of 64.  A small call needs
+// the shorter spans to have wavefronts enough (0.13 M lookups, dims 4..512: 62 us with 64, 112 with 128, 206 with
+// 256; 0.65 M: 156 / 170 / 169); a large one fills the steps of the length classes better with the longer ones
+// (5.5 M lookups, 16-bit rows: 303 us with 128, 319 with 64, 334 with 256; 127 M: 3.84 / 3.87 / 3.88 ms).
+constexpr int64_t kWideSpanMin = 2 << 20;
+// Largest gradient block of a table (bytes) up to which long runs are cut by position.  While the block fits the
+// 4 MiB of an L2 the windows bring no locality, and counts x gradient block has too few slices to fill the chip:
+// batch 611, dims to 512: 28 us for all long runs instead of 245; batch 8191, 128 bf16 columns (2 MiB): 81 instead
+// of 236.  Beyond it gathering loses: batch 16384, 128 fp32 columns (8 MiB): 754 us instead of 410.
+constexpr int64_t kPositionBlock = 4 << 20;
 constexpr int kWindowGrid = 1024;  // persistent workgroups of window_runs_kernel: 8 wavefronts per CU, a multiple of 8
 constexpr int kDenseBagsPerLookup = 8;   // persistent workgroups of dense_rows_kernel: 4 per CU, a multiple of 8
 
@@ -88,7 +98,7 @@ struct tbe_s {
     size_t off_meta = 0, off_rowbase = 0, off_counters = 0, off_keys[2] = {0, 0}, off_vals[2] = {0, 0};
     size_t off_tile_base = 0, off_tstart = 0, off_tile_table = 0;
     int64_t max_tiles = 1;
-    size_t off_hist = 0, off_scan_tmp = 0, off_rl_counts = 0, off_chunk_first = 0, off_partials = 0;
+    size_t off_hist = 0, off_scan_tmp = 0, off_rl_counts = 0, off_unit_first = 0, off_partials = 0;
     size_t off_long_list = 0, off_zero = 0, workspace_bytes = 0;
     size_t off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
     size_t off_dense_dirty = 0, off_dense_cnt = 0, off_dense_list = 0, off_drun = 0, off_dgroup = 0, off_dbounds = 0;
@@ -214,10 +224,10 @@ void plan_workspace(tbe_s* h)
     h->off_scan_tmp = take(4 * (size_t)(scan_blocks + 1));
     h->off_rl_counts = take(4 * (size_t)(rl_tiles + 16));
     const int64_t chunks = std::max<int64_t>(1, ceil_div(nmax, kChunk));
-    h->off_chunk_first = take(4 * (size_t)(chunks + 1));
+    h->off_unit_first = take(4 * (size_t)(ceil_div(nmax, kSpanUnit) + 1));
     const int dpad = (int)align_up((size_t)h->dmax, 4);
     h->off_partials = take(4 * (size_t)chunks * 2 * (size_t)dpad);
-    h->off_long_list = take(4 * (size_t)(nmax / kLongRun + 2));
+    h->off_long_list = take(sizeof(LongRun) * (size_t)(nmax / kPosPiece + 2));
     // dense hot rows: per-table queues, compact run list, groups, and the runs' positions at every
     // kDenseSlice-th bag.  The threshold is never below kDenseMinRun, which bounds the number of dense runs.
     const int64_t dense_runs_max = nmax / kDenseMinRun + h->T + 2;
@@ -615,8 +625,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     // of the sort holds unique_keys / seg_offsets)
     uint32_t* unique_keys = keys[cur ^ 1];
     int32_t* seg_offsets = vals[cur ^ 1];
-    int32_t* chunk_first = h->ws<int32_t>(h->off_chunk_first);
-    const int num_chunks = (int)ceil_div(n, kChunk);
+    int32_t* unit_first = h->ws<int32_t>(h->off_unit_first);
     {
         ScopedTimer tm(h, SLOT_RUNLENGTH, st);
         const int rl_tiles = (int)ceil_div(n, kRlTile);
@@ -627,7 +636,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         if (rc != TBE_OK)
             return rc;
         hipLaunchKernelGGL(runlength_write_kernel, dim3(rl_tiles), dim3(kRlThreads), 0, st, keys[cur],
-                           rl_counts, unique_keys, seg_offsets, chunk_first, counters, n, num_chunks);
+                           rl_counts, unique_keys, seg_offsets, unit_first, counters, n);
         TBE_LAUNCH_CHECK(h, "runlength kernels");
     }
 
@@ -637,22 +646,31 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
 // a5 + a6 on the artefacts left by enqueue_sort
 extern "C++" {
 template <typename WT, typename GT, int OPT>
-static void launch_update(const BwdArgs& a, dim3 grid, dim3 grid_fix, hipStream_t st, tbe_s* h)
+static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s* h)
 {
     {
         ScopedTimer tm(h, SLOT_REDUCE_UPDATE, st);
-        hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT>), grid, dim3(kBwdThreads), 0, st, a);
+        const int per_block = kBwdThreads / kWave;
+        if (a.n >= kWideSpanMin)
+            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, 128>), dim3((unsigned)ceil_div(ceil_div(a.n, 128), per_block)),
+                               dim3(kBwdThreads), 0, st, a);
+        else
+            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, 64>), dim3((unsigned)ceil_div(ceil_div(a.n, 64), per_block)),
+                               dim3(kBwdThreads), 0, st, a);
     }
     Counters* counters = h->ws<Counters>(h->off_counters);
-    if (a.n > kLongRun) {
+    if (a.n > a.long_run) {
         // the long runs below the dense threshold: plan -> window-border positions -> pieces, window by window
         ScopedTimer tm(h, SLOT_WINDOW_RUNS, st);
         uint32_t* wpre = h->ws<uint32_t>(h->off_wrun);
         uint32_t* ppre = wpre + (h->T + 1);
-        WinPiece* pieces = h->ws<WinPiece>(h->off_wbounds);
-        hipLaunchKernelGGL(window_plan_kernel, dim3(1), dim3(256), 0, st, a, wpre, ppre);
-        hipLaunchKernelGGL(window_pieces_kernel, dim3(1024), dim3(256), 0, st, a, wpre, ppre, pieces);
-        hipLaunchKernelGGL((window_runs_kernel<GT>), dim3(kWindowGrid), dim3(kBwdThreads), 0, st, a, pieces);
+        if (!a.by_position) {
+            hipLaunchKernelGGL(window_plan_kernel, dim3(1), dim3(256), 0, st, a, wpre, ppre);
+            hipLaunchKernelGGL(window_pieces_kernel, dim3(1024), dim3(256), 0, st, a, wpre, ppre);
+        }
+        // by position there are at most 2 n / kPosPiece pieces: one per wavefront
+        const int64_t need = a.by_position ? align_up((size_t)ceil_div(2 * ((int64_t)a.n / kPosPiece + 1), kBwdThreads / kWave), 8) : kWindowGrid;
+        hipLaunchKernelGGL((window_runs_kernel<GT>), dim3((unsigned)std::min<int64_t>(kWindowGrid, need)), dim3(kBwdThreads), 0, st, a);
     }
     if (a.dense_thr != INT32_MAX) {
         // the runs the update kernel queued as dense: plan -> bag-slice positions -> counts x gradient block
@@ -671,32 +689,32 @@ static void launch_update(const BwdArgs& a, dim3 grid, dim3 grid_fix, hipStream_
         hipLaunchKernelGGL(run_bounds_kernel, dim3(512), dim3(256), 0, st, d);
         hipLaunchKernelGGL((dense_rows_kernel<GT>), dim3(kDenseGrid), dim3(kDenseThreads), 0, st, d);
     }
-    {
+    if (a.n > a.long_run) {
         ScopedTimer tm(h, SLOT_LONG_FIXUP, st);
         hipLaunchKernelGGL((long_run_fixup_kernel<WT, GT, OPT>), grid_fix, dim3(kBwdThreads), 0, st, a);
     }
 }
 
 template <typename WT, typename GT>
-static void launch_update_opt(const BwdArgs& a, dim3 grid, dim3 grid_fix, hipStream_t st, tbe_s* h)
+static void launch_update_opt(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s* h)
 {
     if (h->optimizer == TBE_OPT_ROWWISE_ADAGRAD)
-        launch_update<WT, GT, kOptRowwiseAdagrad>(a, grid, grid_fix, st, h);
+        launch_update<WT, GT, kOptRowwiseAdagrad>(a, grid_fix, st, h);
     else if (h->optimizer == TBE_OPT_ADAGRAD)
-        launch_update<WT, GT, kOptAdagrad>(a, grid, grid_fix, st, h);
+        launch_update<WT, GT, kOptAdagrad>(a, grid_fix, st, h);
     else
-        launch_update<WT, GT, kOptAdam>(a, grid, grid_fix, st, h);
+        launch_update<WT, GT, kOptAdam>(a, grid_fix, st, h);
 }
 
 template <typename WT>
-static void launch_update_grad(const BwdArgs& a, dim3 grid, dim3 grid_fix, hipStream_t st, tbe_s* h)
+static void launch_update_grad(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s* h)
 {
     if (h->grad_dtype == TBE_DTYPE_FP32)
-        launch_update_opt<WT, float>(a, grid, grid_fix, st, h);
+        launch_update_opt<WT, float>(a, grid_fix, st, h);
     else if (h->grad_dtype == TBE_DTYPE_FP16)
-        launch_update_opt<WT, __half>(a, grid, grid_fix, st, h);
+        launch_update_opt<WT, __half>(a, grid_fix, st, h);
     else
-        launch_update_opt<WT, __hip_bfloat16>(a, grid, grid_fix, st, h);
+        launch_update_opt<WT, __hip_bfloat16>(a, grid_fix, st, h);
 }
 }  // extern "C++"
 
@@ -720,8 +738,7 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     int32_t* vals[2] = {h->ws<int32_t>(h->off_vals[0]), h->ws<int32_t>(h->off_vals[1])};
     uint32_t* unique_keys = keys[cur ^ 1];
     int32_t* seg_offsets = vals[cur ^ 1];
-    int32_t* chunk_first = h->ws<int32_t>(h->off_chunk_first);
-    const int num_chunks = (int)ceil_div(n, kChunk);
+    int32_t* unit_first = h->ws<int32_t>(h->off_unit_first);
     // a5 + a6: on-chip aggregation per run, one AdaGrad step per touched row
     BwdArgs a;
     a.meta = h->ws<TableMeta>(h->off_meta);
@@ -730,23 +747,26 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     a.sorted_vals = vals[cur];
     a.unique_keys = unique_keys;
     a.seg_offsets = seg_offsets;
-    a.chunk_first_run = chunk_first;
+    a.unit_first_run = unit_first;
     a.counters = counters;
     a.grad_out = d_grad_out;
     a.weights = h->d_weights;
     a.partials = h->ws<float>(h->off_partials);
-    a.long_list = h->ws<uint32_t>(h->off_long_list);
+    a.long_list = h->ws<LongRun>(h->off_long_list);
+    a.pieces = h->ws<WinPiece>(h->off_wbounds);
     a.zero_row = h->ws<float>(h->off_zero);
     a.n = n;
-    a.num_chunks = num_chunks;
     a.T = h->T;
     a.sumD = (int32_t)h->sumD;
     a.dpad = (int32_t)align_up((size_t)h->dmax, 4);
     a.batch = h->sorted_batch;
     a.table_major = h->layout;
+    // Long runs: by position while every table's gradient block fits an L2, by bag window and as dense rows beyond
+    a.by_position = (int64_t)a.batch * a.dpad * (h->grad_dtype == TBE_DTYPE_FP32 ? 4 : 2) <= kPositionBlock;
+    a.long_run = a.by_position ? kPosPiece : kLongRun;
     // dense hot rows: only when a run can exceed the threshold and the bounds table of this call fits
     const int thr = dense_threshold(h->sorted_batch);
-    const bool dense_on = n > thr && dense_bounds_entries(n, h->sorted_batch, h->T) <= h->dbounds_cap &&
+    const bool dense_on = !a.by_position && n > thr && dense_bounds_entries(n, h->sorted_batch, h->T) <= h->dbounds_cap &&
                           n / thr + h->T + 2 <= h->max_indices / kDenseMinRun + h->T + 2;
     a.dense_thr = dense_on ? thr : INT32_MAX;
     a.dense_slices = (int32_t)ceil_div(std::max(h->sorted_batch, 1), kDenseSlice);
@@ -771,13 +791,12 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
         a.opt.inv_bc2 = (float)(1.0 / (1.0 - std::pow((double)oc.beta2, (double)oc.step)));
     }
     const int per_block = kBwdThreads / kWave;
-    const dim3 grid((unsigned)ceil_div(ceil_div(num_chunks, kSpanChunks), per_block));   // a wavefront per span of chunks
-    const int64_t max_long = n / kLongRun + 1;
+    const int64_t max_long = n / a.long_run + 1;
     const dim3 grid_fix((unsigned)std::min<int64_t>(2048, ceil_div(max_long, per_block)));
     if (h->dtype == TBE_DTYPE_FP32)
-        launch_update_grad<float>(a, grid, grid_fix, st, h);
+        launch_update_grad<float>(a, grid_fix, st, h);
     else
-        launch_update_grad<__half>(a, grid, grid_fix, st, h);
+        launch_update_grad<__half>(a, grid_fix, st, h);
     TBE_LAUNCH_CHECK(h, "reduce_update / long_run_fixup kernels");
     return TBE_OK;
 }

@@ -32,8 +32,11 @@ constexpr int kScanTile = kScanThreads * kScanPerThread;      // 4096
 constexpr int kRlThreads = 256;
 constexpr int kRlPerThread = 16;
 constexpr int kRlTile = kRlThreads * kRlPerThread;            // 4096 sorted positions
-constexpr int kChunk = 128;               // sorted positions owned by one wavefront in the update
+constexpr int kChunk = 128;               // sorted positions per pair of partial-row slots
+constexpr int kSpanUnit = 64;             // a span of the update kernel is a multiple of this many sorted positions
 constexpr int kLongRun = 512;             // runs longer than this are summed in pieces by other kernels (window / dense path)
+constexpr int kPosPiece = 128;            // shortest piece of a run that is cut by position; also the threshold in that mode
+constexpr int kPosPiecesMax = 256;        // most pieces of such a run (longer runs take longer pieces)
 constexpr int kWinMax = 16;               // most bag windows a long run is cut into
 constexpr int kWinBatch = 8;               // pieces a workgroup of window_runs_kernel claims at a time
 constexpr int kBwdThreads = 256;          // 4 wavefronts = 4 chunks per workgroup
@@ -59,12 +62,12 @@ struct TableMeta {      // 32 bytes, one per table, in the workspace head
 
 struct Counters {       // workspace scalars
     int64_t num_unique;         // written by the run-length pass of every sort
-    // Number of long runs queued by the update kernel for the fix-up kernel.  Zero between update
-    // launches: the last workgroup of the fix-up kernel to finish clears it (and fixup_done), so every
-    // update starts from an empty queue -- also a second update after one sort, and every replay of a
-    // captured graph.
+    // Long runs (and, when they are cut by position, their pieces) queued by the update kernel.  Zero between
+    // updates, also before a second update after one sort and every replay of a captured graph: the window kernel
+    // hands the number of runs over to the fix-up kernel (long_todo) and clears it, the fix-up kernel clears the
+    // number of pieces.  Each is cleared by one workgroup of a kernel in which no other reads it.
     uint32_t long_count;
-    uint32_t fixup_done;        // workgroups of the running fix-up kernel that have finished
+    uint32_t long_todo;
     uint32_t check_flags;       // written only by tbe_check_inputs
     uint32_t dense_runs;        // written by the plan kernels: dense runs / groups, windowed runs of this update
     uint32_t dense_groups;
@@ -900,7 +903,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply_kernel(
 //
 // A sorted position q is a run head when q == 0 or key[q] != key[q-1].  Pass 1 counts heads per
 // tile, a scan turns the counts into the index of each tile's first run, pass 2 writes
-// unique_keys / seg_offsets and, for every kChunk-aligned position, the number of heads before it.
+// unique_keys / seg_offsets and, for every kSpanUnit-aligned position, the number of heads before it.
 
 __device__ __forceinline__ void rl_load(const uint32_t* __restrict__ keys, int32_t n, int base,
                                         uint32_t (&k)[kRlPerThread], uint32_t& prev)
@@ -943,8 +946,7 @@ __global__ __launch_bounds__(kRlThreads) void runlength_count_kernel(
 __global__ __launch_bounds__(kRlThreads) void runlength_write_kernel(
     const uint32_t* __restrict__ keys, const uint32_t* __restrict__ tile_first_run,
     uint32_t* __restrict__ unique_keys, int32_t* __restrict__ seg_offsets,
-    int32_t* __restrict__ chunk_first_run, Counters* __restrict__ counters, int32_t n,
-    int32_t num_chunks)
+    int32_t* __restrict__ unit_first_run, Counters* __restrict__ counters, int32_t n)
 {
     __shared__ uint32_t s_wave[4];
     const int base = blockIdx.x * kRlTile + threadIdx.x * kRlPerThread;
@@ -964,8 +966,8 @@ __global__ __launch_bounds__(kRlThreads) void runlength_write_kernel(
     for (int i = 0; i < kRlPerThread; ++i) {
         const int q = base + i;
         if (q < n) {
-            if ((q & (kChunk - 1)) == 0)
-                chunk_first_run[q / kChunk] = (int32_t)r;
+            if ((q & (kSpanUnit - 1)) == 0)
+                unit_first_run[q / kSpanUnit] = (int32_t)r;
             if (head[i]) {
                 unique_keys[r] = k[i];
                 seg_offsets[r] = q;
@@ -973,7 +975,7 @@ __global__ __launch_bounds__(kRlThreads) void runlength_write_kernel(
             }
             if (q == n - 1) {
                 seg_offsets[r] = n;
-                chunk_first_run[num_chunks] = (int32_t)r;
+                unit_first_run[(n + kSpanUnit - 1) / kSpanUnit] = (int32_t)r;
                 counters->num_unique = (int64_t)r;
             }
         }
@@ -985,7 +987,7 @@ __global__ __launch_bounds__(kRlThreads) void runlength_write_kernel(
 // Section 5.1: all gradients of one row are aggregated on chip and the optimizer runs once per row.
 // Section 5.2: m += mean_d(G_d^2); w -= lr * G / (sqrt(m) + eps)  (updated moment, eps outside the root).
 //
-// Each wavefront owns a span of kSpan consecutive sorted positions and every run that STARTS inside it.
+// Each wavefront owns a span of SPAN consecutive sorted positions and every run that STARTS inside it.
 // The span's run descriptors and payloads are staged in LDS once.  Lane mapping: a row of D floats
 // is covered by LPR = pow2ceil(D/8) lanes, two float4 blocks per lane, so G = 64/LPR rows are
 // fetched per load instruction.  The runs of the span are sorted by length class (a counting sort with
@@ -995,12 +997,13 @@ __global__ __launch_bounds__(kRlThreads) void runlength_write_kernel(
 //     of a step are requested before anything is consumed, and all groups apply their update together;
 //   * runs of up to 4 x 2^j lookups, 2^j <= G: teams of 2^j lane groups, G / 2^j runs per step, the
 //     members' sums combined with an xor butterfly;
-//   * longer runs use the whole wavefront in several steps (groups take alternate lookups); up to
-//     kLongRun lookups the owner follows the run past its span and finishes it;
-//   * a run longer than kLongRun is not summed here: it is queued, per table, for window_runs_kernel
-//     (pieces by bag window) or, beyond the call's dense threshold, for dense_rows_kernel (counts x
-//     gradient block); those write fp32 partial rows to the workspace, and the fix-up kernel adds a
-//     run's partial rows in a fixed order and applies the single update.
+//   * longer runs use the whole wavefront in several steps (groups take alternate lookups); up to the
+//     call's long_run lookups the owner follows the run past its span and finishes it;
+//   * a longer run is not summed here.  While a table's gradient block fits an L2 (by_position) its
+//     pieces of kPosPiece lookups are listed for window_runs_kernel right away; beyond that the run is
+//     queued, per table, for window_runs_kernel (pieces by bag window) or, past the call's dense
+//     threshold, for dense_rows_kernel (counts x gradient block).  Those write fp32 partial rows to the
+//     workspace, and the fix-up kernel adds a run's partial rows in a fixed order and applies the update.
 // The single-lookup rows of the tail of the index distribution move a row, its moment and one gradient row
 // each and run at the rate of the memory system; the steps of the longer runs are bound by how fast gradient
 // rows come out of the caches, so nothing here is arranged around instruction counts.
@@ -1011,17 +1014,21 @@ __global__ __launch_bounds__(kRlThreads) void runlength_write_kernel(
 // workspace, column offsets past D are clamped) so that the loads of a step are issued back to
 // back and waited for once.
 
+// Table of a linear row id, for a whole wavefront (key uniform): 64 borders per step instead of one per step of a
+// bisection, whose dependent loads the start of every span would wait for one after the other.
 __device__ __forceinline__ int find_table(const uint32_t* __restrict__ row_base, int T, uint32_t key)
 {
-    int a = 0, c = T;  // row_base[a] <= key < row_base[c]
-    while (c - a > 1) {
-        const int mid = (a + c) >> 1;
-        if (row_base[mid] <= key)
-            a = mid;
-        else
-            c = mid;
+    const int lane = threadIdx.x & (kWave - 1);
+    int lo = 0, n = T;  // row_base[lo] <= key < row_base[lo + n]
+    while (n > 1) {
+        const int step = (n + kWave - 1) / kWave;
+        const int i = lane * step;
+        const uint64_t le = __ballot(i < n && row_base[lo + min(i, n - 1)] <= key);
+        const int k = (__popcll(le) - 1) * step;
+        lo += k;
+        n = min(step, n - k);
     }
-    return a;
+    return lo;
 }
 
 // Optimizer of the fused epilogue (Section 5.1 names AdaGrad and Adam next to the row-wise AdaGrad of
@@ -1050,15 +1057,17 @@ struct BwdArgs {
     const int32_t* sorted_vals;
     const uint32_t* unique_keys;
     const int32_t* seg_offsets;
-    const int32_t* chunk_first_run;
+    const int32_t* unit_first_run;   // runs that start before position i * kSpanUnit
     Counters* counters;
     const void* grad_out;   // [B, sumD] in the gradient type (float, __half or __hip_bfloat16)
     void* weights;
     float* partials;      // [num_chunks][2][dpad]
-    uint32_t* long_list;
+    struct LongRun* long_list;   // long runs for the fix-up kernel
+    struct WinPiece* pieces;
     const float* zero_row;  // >= 2 KiB of zeros
     int32_t n;
-    int32_t num_chunks;
+    int32_t long_run;      // runs longer than this are long: kLongRun, or kPosPiece when they are cut by position
+    int32_t by_position;   // long runs are cut by position (their pieces are listed by the update kernel), not by bag window
     int32_t T;
     int32_t sumD;
     int32_t dpad;
@@ -1077,6 +1086,57 @@ struct BwdArgs {
     int32_t grad_bytes;    // bytes per gradient element (sizes the bag windows)
     OptParams opt;
 };
+
+struct WinPiece {        // 16 bytes: what a wavefront needs to sum one piece, in one load
+    int32_t p0, p1;      // sorted positions of the piece
+    int32_t slot;        // partial row it writes; < 0: merged into the piece that starts at an earlier window
+    int32_t t;           // table
+};
+
+struct LongRun {         // 32 bytes: what a wavefront of the fix-up kernel needs to finish a run
+    uint32_t key;        // linear row id
+    int32_t t;           // table
+    int32_t s, e;        // sorted positions of the run
+    uint32_t base;       // cut by position: the run's first partial row
+    uint32_t pad[3];
+};
+
+// Pieces of a run of `len` lookups that is cut by position.
+__device__ __forceinline__ int position_piece(int len)
+{
+    const int per = (len + kPosPiecesMax - 1) / kPosPiecesMax;
+    return max(kPosPiece, (per + kPosPiece - 1) / kPosPiece * kPosPiece);
+}
+
+// Lists the long runs of the lanes in `todo` (one run per lane: length, first position, row id, table) for the
+// fix-up kernel and their pieces for window_runs_kernel.  Partial row = index of the piece in the list: which rows
+// a run gets depends on the order of the atomics, what they hold and the order they are added in does not.
+__device__ __forceinline__ void list_position_pieces(const BwdArgs& a, uint64_t todo, int len, int first, uint32_t key, int t)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    while (todo != 0ull) {
+        const int src = __ffsll((unsigned long long)todo) - 1;
+        todo &= todo - 1;
+        const int L = __shfl(len, src), s = __shfl(first, src), k = __shfl((int)key, src);
+        const int piece = position_piece(L);
+        const int np = (L + piece - 1) / piece;
+        uint32_t base = 0;
+        if (lane == 0) {
+            base = atomicAdd(&a.counters->win_pieces, (uint32_t)np);
+            const uint32_t slot = atomicAdd(&a.counters->long_count, 1u);
+            a.long_list[slot] = LongRun{(uint32_t)k, t, s, s + L, base, {0, 0, 0}};
+        }
+        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+        for (int i = lane; i < np; i += kWave) {
+            WinPiece p;
+            p.p0 = s + i * piece;
+            p.p1 = min(s + L, p.p0 + piece);
+            p.slot = (int)base + i;
+            p.t = t;
+            a.pieces[base + i] = p;
+        }
+    }
+}
 
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ void acc4(float (&a)[4], const float4 v)
@@ -1387,46 +1447,42 @@ __device__ __forceinline__ void run_batch(const BwdArgs& a, WT* __restrict__ wta
     }
 }
 
-constexpr int kSpanChunks = 2;                  // chunks owned by one wavefront of the update kernel
-constexpr int kSpan = kSpanChunks * kChunk;     // 256 sorted positions
-
-template <typename WT, typename GT, int OPT>
+// SPAN: sorted positions owned by one wavefront
+template <typename WT, typename GT, int OPT, int SPAN>
 __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
 {
     using IO = RowIO<WT, 4>;
     const GT* __restrict__ grad_out = static_cast<const GT*>(a.grad_out);
     constexpr int kWaves = kBwdThreads / kWave;
-    constexpr int kRounds = kSpan / kWave;         // staging rounds of one entry per lane
-    constexpr int kSegCap = (kRounds + 1) * kWave; // >= kSpan + 1
-    constexpr int kValCap = kSpan + kLongRun;      // a run owned by the span ends within this window
+    constexpr int kRounds = SPAN / kWave;         // staging rounds of one entry per lane
+    constexpr int kSegCap = (kRounds + 1) * kWave; // >= SPAN + 1
+    constexpr int kValCap = SPAN + kLongRun;      // a run owned by the span ends within this window
     // row-wise AdaGrad keeps one moment per row, so several runs per lane group fit in registers; the
     // element-wise optimizers carry whole state rows and take one run per group
     constexpr int kNB1 = OPT != kOptRowwiseAdagrad ? 1 : sizeof(WT) == 2 ? 4 : 2;   // runs of one lookup per group
     constexpr int kNB2 = OPT != kOptRowwiseAdagrad ? 1 : 2;                          // runs of two lookups per group
-    static_assert(kSpan <= 256, "run indices of a span are kept in bytes");
+    static_assert(SPAN <= 256, "run indices of a span are kept in bytes");
     static_assert(kShortRun == 4, "run_batch is instantiated for 1..4 lookups");
     __shared__ int32_t s_seg_all[kWaves][kSegCap];
-    __shared__ uint32_t s_key_all[kWaves][kSpan];
+    __shared__ uint32_t s_key_all[kWaves][SPAN];
     __shared__ int32_t s_val_all[kWaves][kValCap];
-    __shared__ uint8_t s_list_all[kWaves][kSpan];
+    __shared__ uint8_t s_list_all[kWaves][SPAN];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x >> 6;
     const int k = uniform(blockIdx.x * kWaves + wv);
-    const int ch0 = k * kSpanChunks;
-    if (ch0 >= a.num_chunks)
+    const int q0 = k * SPAN;
+    if (q0 >= a.n)
         return;
-    const int ch1 = min(ch0 + kSpanChunks, a.num_chunks);
     int32_t* s_seg = s_seg_all[wv];
     uint32_t* s_key = s_key_all[wv];
     int32_t* s_val = s_val_all[wv];
     uint8_t* s_list = s_list_all[wv];
 
-    const int q0 = ch0 * kChunk;
-    const int q1 = min(a.n, q0 + kSpan);
-    const int ub = a.chunk_first_run[ch0];
-    const int ue = a.chunk_first_run[ch1];
-    const int nruns = ue - ub;  // runs that start in [q0, q1): at most kSpan
+    const int q1 = min(a.n, q0 + SPAN);
+    const int ub = a.unit_first_run[q0 / kSpanUnit];
+    const int ue = a.unit_first_run[(q1 + kSpanUnit - 1) / kSpanUnit];
+    const int nruns = ue - ub;  // runs that start in [q0, q1): at most SPAN
     if (nruns == 0)
         return;     // the span lies inside one run: its owner, or (long runs) another kernel, sums all of it
     WT* __restrict__ weights = static_cast<WT*>(a.weights);
@@ -1462,7 +1518,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     {
         const int e_last = uniform(s_seg[nruns]);
         const int s_last = uniform(s_seg[nruns - 1]);
-        if (e_last > q1 && e_last - s_last <= kLongRun) {
+        if (e_last > q1 && e_last - s_last <= a.long_run) {
             for (int p = q1 + lane; p < e_last; p += kWave)
                 s_val[p - q0] = vals[p];
             __threadfence_block();
@@ -1528,14 +1584,16 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
             int cl;
             if (len <= kShortRun) {
                 cl = len - 1;
-            } else if (len > kLongRun) {
+            } else if (len > a.long_run) {
                 cl = 15;
             } else {
                 const int tl = 32 - __clz((len - 1) >> 2);     // smallest tl with (4 << tl) >= len
                 cl = tl <= lgG ? 3 + tl : 14;
             }
             cls[i] = valid ? cl : -1;
-            if (valid && cl == 15) {
+            if (a.by_position) {
+                list_position_pieces(a, __ballot(valid && cl == 15), len, s_seg[rc], s_key[rc], t);
+            } else if (valid && cl == 15) {
                 if (len > a.dense_thr) {
                     const uint32_t dslot = atomicAdd(&a.dense_cnt[t], 1u);
                     a.dense_list[a.tstart[t] / a.dense_thr + t + (int)dslot] = (uint32_t)(ub + run);
@@ -1544,7 +1602,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
                     a.win_list[a.tstart[t] / kLongRun + t + (int)wslot] = (uint32_t)(ub + run);
                 }
                 const uint32_t slot = atomicAdd(&a.counters->long_count, 1u);
-                a.long_list[slot] = (uint32_t)(ub + run);
+                a.long_list[slot] = LongRun{s_key[rc], t, s_seg[rc], s_seg[rc + 1], 0, {0, 0, 0}};
             }
         }
 
@@ -2040,8 +2098,13 @@ __global__ __launch_bounds__(kDenseThreads, 4) void dense_rows_kernel(DenseArgs 
     }
 }
 
-// ---------------------------------------------------------------- long runs, window by window
+// ---------------------------------------------------------------- long runs in pieces
 //
+// By position (the gradient block fits an L2): pieces of kPosPiece lookups, one wavefront each.  In a call of this
+// size what counts is the length of the chain a wavefront follows -- four rows in flight per lane group, so 128
+// lookups of a 512-column row are 32 trips to the L2, about 20 us -- and that there are pieces for every CU.
+//
+// By bag window, beyond that:
 // A run of kLongRun < L <= dense threshold lookups is cut into pieces by bag window (the batch is divided
 // into at most kWinMax windows of win_bags bags); the payloads of a run ascend by bag, so a piece is a
 // contiguous part of the run.  One wavefront sums one piece (one gathered gradient row per lookup) and
@@ -2083,12 +2146,6 @@ __device__ __forceinline__ int window_step(int s, int e, int nwin)
     return step;
 }
 
-struct WinPiece {        // 16 bytes: what a wavefront needs to sum one piece, in one load
-    int32_t p0, p1;      // sorted positions of the piece
-    int32_t slot;        // partial row it writes; < 0: merged into the piece that starts at an earlier window
-    int32_t t;           // table
-};
-
 // one workgroup: exclusive prefixes of the per-table queue lengths (wpre[T] = number of windowed runs) and of
 // the per-table piece counts, runs x windows (ppre[T] = number of pieces); clears the queue lengths and the
 // piece-claim counters for this update
@@ -2128,8 +2185,7 @@ __global__ __launch_bounds__(256) void window_plan_kernel(BwdArgs a, uint32_t* _
 // wpre[t + 1] and is entry ri - wpre[t] of that table's queue; the pieces of table t are
 // [ppre[t], ppre[t + 1]), window-major, run-minor.
 __global__ __launch_bounds__(256) void window_pieces_kernel(BwdArgs a, const uint32_t* __restrict__ wpre,
-                                                            const uint32_t* __restrict__ ppre,
-                                                            WinPiece* __restrict__ pieces)
+                                                            const uint32_t* __restrict__ ppre)
 {
     static_assert(kWinMax == 16, "one 16-lane group per run");
     const int lane = threadIdx.x & (kWave - 1);
@@ -2175,27 +2231,93 @@ __global__ __launch_bounds__(256) void window_pieces_kernel(BwdArgs a, const uin
             p.p1 = sub + step >= nwin ? e : up;
             p.slot = sub % step == 0 ? (s / kChunk + 1) * 2 + sub / step : -1;
             p.t = t0;
-            pieces[(int64_t)ppre[t0] + (int64_t)sub * ng + (ri - gbase)] = p;
+            a.pieces[(int64_t)ppre[t0] + (int64_t)sub * ng + (ri - gbase)] = p;
         }
     }
 }
 
+// One wavefront sums the gradient rows of one piece and writes its partial row.
 template <typename GT>
-__global__ __launch_bounds__(kBwdThreads) void window_runs_kernel(BwdArgs a, const WinPiece* __restrict__ pieces)
+__device__ __forceinline__ void sum_piece(const BwdArgs& a, const int4 rec /* p0, p1, slot, t */)
 {
     using GIO = GradIO<GT>;
     const int lane = threadIdx.x & (kWave - 1);
-    const int total = (int)a.counters->win_pieces;
     const GT* __restrict__ grad_out = static_cast<const GT*>(a.grad_out);
     const GT* zero_row = reinterpret_cast<const GT*>(a.zero_row);
     const int32_t* __restrict__ vals = a.sorted_vals;
-    // The workgroups that share an L2 (every 8th block) take the pieces of one eighth of the list, kWinBatch
-    // consecutive unclaimed ones at a time (one integer atomic per batch; the wavefronts of the workgroup then
-    // share the batch out through LDS): whatever the pieces' lengths, the wavefronts of an L2 domain are always
-    // at work on neighbouring pieces.  Which wavefront sums a piece has no influence on the result.
-    __shared__ int s_batch, s_taken;
+    const int p0 = rec.x, p1 = rec.y;
+    const TableMeta m = a.meta[rec.w];
+    const int64_t stride = a.table_major ? m.dim : a.sumD;
+    const GT* gb = a.table_major ? grad_out + (int64_t)a.batch * m.col : grad_out + m.col;
+    const Cols c(m.dim, m.lpr_bwd, lane);
+    const int G = kWave >> c.lprl;
+    float acc[2][4];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            acc[k][x] = 0.f;
+    for (int base = p0; base < p1; base += kWave) {
+        const int cnt = min(kWave, p1 - base);
+        const int myv = vals[min(base + lane, p1 - 1)];     // 64 payloads with one coalesced load
+        for (int i0 = 0; i0 < cnt; i0 += G * kBwdUnroll) {
+            typename GIO::Vec v[kBwdUnroll][2];
+            const GT* rp[kBwdUnroll];
+#pragma unroll
+            for (int x = 0; x < kBwdUnroll; ++x) {
+                const int i = i0 + x * G + c.grp;
+                const int b = __shfl(myv, min(i, cnt - 1));
+                rp[x] = i < cnt ? gb + (int64_t)b * stride : zero_row;
+            }
+#pragma unroll
+            for (int x = 0; x < kBwdUnroll; ++x) {
+                v[x][0] = GIO::ldv(rp[x] + c.e0);
+                v[x][1] = GIO::ldv(rp[x] + c.e1);
+            }
+#pragma unroll
+            for (int x = 0; x < kBwdUnroll; ++x) {
+                GIO::add(acc[0], v[x][0]);
+                GIO::add(acc[1], v[x][1]);
+            }
+        }
+    }
+    for (int sft = 1 << c.lprl; sft < kWave; sft <<= 1) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                acc[k][x] += __shfl_xor(acc[k][x], sft);
+    }
+    store_partial(a.partials + (int64_t)rec.z * a.dpad, acc, c);
+}
+
+template <typename GT>
+__global__ __launch_bounds__(kBwdThreads) void window_runs_kernel(BwdArgs a)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int total = (int)a.counters->win_pieces;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        a.counters->long_todo = a.counters->long_count;
+        a.counters->long_count = 0;
+    }
+    // The workgroups that share an L2 (every 8th block) take the pieces of one eighth of the list.
     const int xcd = blockIdx.x & 7;
     const int per_xcd = (total + 7) / 8;
+    if (a.by_position) {
+        // pieces of equal length over a gradient block that fits an L2: a fixed assignment, wavefront by wavefront
+        const int step = (int)(gridDim.x >> 3) * (kBwdThreads / kWave);
+        for (int w = uniform((int)(blockIdx.x >> 3) * (kBwdThreads / kWave) + (int)(threadIdx.x >> 6)); w < per_xcd; w += step) {
+            const int piece = xcd * per_xcd + w;
+            if (piece >= total)
+                break;
+            sum_piece<GT>(a, *reinterpret_cast<const int4*>(&a.pieces[piece]));
+        }
+        return;
+    }
+    // By bag window: kWinBatch consecutive unclaimed pieces at a time (one integer atomic per batch; the wavefronts
+    // of the workgroup then share the batch out through LDS): whatever the pieces' lengths, the wavefronts of an L2
+    // domain are always at work on neighbouring pieces.  Which wavefront sums a piece has no influence on the result.
+    __shared__ int s_batch, s_taken;
     for (;;) {
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -2206,64 +2328,20 @@ __global__ __launch_bounds__(kBwdThreads) void window_runs_kernel(BwdArgs a, con
         const int batch0 = s_batch;
         if (batch0 >= per_xcd)
             break;
-      for (;;) {
-        int w = 0;
-        if (lane == 0)
-            w = atomicAdd(&s_taken, 1);
-        w = uniform(w);
-        if (w >= kWinBatch || batch0 + w >= per_xcd)
-            break;
-        const int piece = xcd * per_xcd + batch0 + w;
-        if (piece >= total)
-            break;
-        const int4 rec = *reinterpret_cast<const int4*>(&pieces[piece]);   // p0, p1, slot, t
-        if (rec.z < 0)
-            continue;                                           // merged into the piece that starts earlier
-        const int p0 = rec.x, p1 = rec.y;
-        const TableMeta m = a.meta[rec.w];
-        const int64_t stride = a.table_major ? m.dim : a.sumD;
-        const GT* gb = a.table_major ? grad_out + (int64_t)a.batch * m.col : grad_out + m.col;
-        const Cols c(m.dim, m.lpr_bwd, lane);
-        const int G = kWave >> c.lprl;
-        float acc[2][4];
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-#pragma unroll
-            for (int x = 0; x < 4; ++x)
-                acc[k][x] = 0.f;
-        for (int base = p0; base < p1; base += kWave) {
-            const int cnt = min(kWave, p1 - base);
-            const int myv = vals[min(base + lane, p1 - 1)];     // 64 payloads with one coalesced load
-            for (int i0 = 0; i0 < cnt; i0 += G * kBwdUnroll) {
-                typename GIO::Vec v[kBwdUnroll][2];
-                const GT* rp[kBwdUnroll];
-#pragma unroll
-                for (int x = 0; x < kBwdUnroll; ++x) {
-                    const int i = i0 + x * G + c.grp;
-                    const int b = __shfl(myv, min(i, cnt - 1));
-                    rp[x] = i < cnt ? gb + (int64_t)b * stride : zero_row;
-                }
-#pragma unroll
-                for (int x = 0; x < kBwdUnroll; ++x) {
-                    v[x][0] = GIO::ldv(rp[x] + c.e0);
-                    v[x][1] = GIO::ldv(rp[x] + c.e1);
-                }
-#pragma unroll
-                for (int x = 0; x < kBwdUnroll; ++x) {
-                    GIO::add(acc[0], v[x][0]);
-                    GIO::add(acc[1], v[x][1]);
-                }
-            }
+        for (;;) {
+            int w = 0;
+            if (lane == 0)
+                w = atomicAdd(&s_taken, 1);
+            w = uniform(w);
+            if (w >= kWinBatch || batch0 + w >= per_xcd)
+                break;
+            const int piece = xcd * per_xcd + batch0 + w;
+            if (piece >= total)
+                break;
+            const int4 rec = *reinterpret_cast<const int4*>(&a.pieces[piece]);
+            if (rec.z >= 0)          // < 0: merged into the piece that starts at an earlier window
+                sum_piece<GT>(a, rec);
         }
-        for (int sft = 1 << c.lprl; sft < kWave; sft <<= 1) {
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-#pragma unroll
-                for (int x = 0; x < 4; ++x)
-                    acc[k][x] += __shfl_xor(acc[k][x], sft);
-        }
-        store_partial(a.partials + (int64_t)rec.z * a.dpad, acc, c);
-      }
     }
 }
 
@@ -2276,16 +2354,16 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
     const int lane = threadIdx.x & (kWave - 1);
     const int wave_global = uniform(blockIdx.x * (kBwdThreads / kWave) + (threadIdx.x >> 6));
     const int wave_total = gridDim.x * (kBwdThreads / kWave);
-    const int cnt = (int)a.counters->long_count;
+    const int cnt = (int)a.counters->long_todo;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        a.counters->win_pieces = 0;
     WT* __restrict__ weights = static_cast<WT*>(a.weights);
     float acc[2][4];
     for (int i = wave_global; i < cnt; i += wave_total) {
-        const int u = (int)a.long_list[i];
-        const int s = a.seg_offsets[u];
-        const int e = a.seg_offsets[u + 1];
+        const LongRun rec = a.long_list[i];
+        const int s = rec.s, e = rec.e, t = rec.t;
+        const uint32_t key = rec.key;
         const bool dense = e - s > a.dense_thr;
-        const uint32_t key = a.unique_keys[u];
-        const int t = find_table(a.row_base, a.T, key);
         const TableMeta m = a.meta[t];
         const Cols c(m.dim, m.lpr_bwd, lane);
         const int k0 = s / kChunk;
@@ -2298,7 +2376,11 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
         wvv[1] = IO::ldv(wrow + c.e1);
         OptRow<OPT> st;
         st.load(a.opt, key, wel, c);
-        if (dense && a.dense_dirty[t] != 0u) {
+        if (a.by_position) {
+            const int piece = position_piece(e - s);
+            wave_gather_sum<float>([&](int cc) { return pbase + ((int64_t)rec.base + cc) * dpad; }, 0,
+                                   (e - s + piece - 1) / piece, a.zero_row, c, acc);
+        } else if (dense && a.dense_dirty[t] != 0u) {
             // the table's gradient block holds Inf / NaN, which the dense sums leave out: this run is
             // summed the plain way, one gathered gradient row per lookup (a rare, slow path)
             const GT* gb = a.table_major ? static_cast<const GT*>(a.grad_out) + (int64_t)a.batch * m.col
@@ -2317,17 +2399,6 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
                                    (nwin + step - 1) / step, a.zero_row, c, acc);
         }
         optimizer_epilogue<WT, OPT>(wrow, wvv, acc, m.dim, c, c.grp == 0, a.opt, key, wel, st);
-    }
-    // Leave the queue empty for the next update launch.  Every wavefront read the count before its
-    // loop (the loop bound depends on it), the barrier orders those reads before this workgroup's
-    // arrival, and only the workgroup that arrives last -- after all others have arrived -- clears.
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t arrived = atomicAdd(&a.counters->fixup_done, 1u);
-        if (arrived == gridDim.x - 1) {
-            a.counters->long_count = 0;
-            a.counters->fixup_done = 0;
-        }
     }
 }
 

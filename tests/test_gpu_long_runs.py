@@ -1,0 +1,32 @@
+"""GPU parity of the two ways long runs are cut: by position while the largest gradient block of a table
+(batch x dim x bytes) fits 4 MiB, by bag window and as dense rows beyond.  Run lengths lie on both sides of every
+border: the threshold (128 by position, 512 by window, 1024 dense), whole pieces, and the length from which
+pieces grow (128 x 256 lookups).  Tolerances are the suite's (tbe_testlib)."""
+import numpy as np
+import pytest
+
+import tbe_testlib as tl
+from paper_2104_05158_amd import workloads as wl
+from test_gpu_run_classes import _explicit_case
+
+pytestmark = pytest.mark.gpu
+
+CASES = {
+    # name: (batch, dims, run lengths of every table)
+    "by_position": (53, [4, 64, 512], [127, 128, 129, 255, 256, 257, 385, 3000, 1, 1, 2]),
+    "by_position_long_pieces": (700, [64, 8], [128 * 256 - 1, 128 * 256, 128 * 256 + 1, 70000, 5]),
+    "block_of_exactly_4_MiB": (2048, [512, 4], [129, 511, 513, 1024, 1025, 5000] + [1] * 70),
+    "block_beyond_4_MiB": (2200, [512, 4, 64, 128], [129, 511, 512, 513, 600, 1023, 1024, 1025, 3000, 5000] + [1] * 70),
+}
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_long_runs_on_both_sides_of_every_border(gpu_device, case, dtype):
+    batch, dims, lens = CASES[case]
+    spec, idx, off = _explicit_case(dims, [np.array(lens) for _ in dims], batch=batch, seed=41 + dtype, dtype=dtype)
+    w = wl.make_weights(spec, "cpu", seed=42).numpy()
+    g = wl.make_grad(spec, "cpu", seed=43).numpy()
+    m0 = np.random.default_rng(44).uniform(0, 1, spec.total_rows).astype(np.float32)
+    print(f"{case}: N={idx.size} dtype={dtype}", flush=True)
+    tl.full_parity_step(spec, idx, off, w, g, gpu_device, lr=0.03, m0=m0, what=case)
