@@ -153,8 +153,8 @@ TBE_API tbe_status_t tbe_forward(tbe_handle_t h, const int32_t* d_indices, const
  *   m[t,r]  += (1/D_t) * sum_d G[t,r,d]^2
  *   W_t[r,:] -= lr * G[t,r,:] / (sqrt(m[t,r]) + eps)
  * computed in fp32 and rounded to the storage type (nearest even).  Rows not looked up are not
- * written.  Implementation: the lookups are radix-sorted by (table, row) (stable; the sort is
- * segmented by table and reads the caller's indices directly) and run-length segmented in the
+ * written.  Implementation: the lookups are sorted by (table, row) (stable; every table is
+ * partitioned by sampled row borders and its buckets are sorted on chip) and run-length segmented in the
  * workspace, then every run is reduced on chip and its row updated once.
  * The integer artefacts stay in the workspace until the next backward call (tbe_backward_artifacts).
  * d_grad_out holds batch * sumD elements of the configured gradient type, laid out like d_out.
@@ -187,7 +187,7 @@ TBE_API tbe_status_t tbe_backward_adam(tbe_handle_t h, const int32_t* d_indices,
 /*
  * The same backward pass in two calls, for callers that overlap work (Section 4.2 pipelines
  * independent stages on separate streams).  tbe_backward_sort enqueues the part that needs only the
- * batch's (indices, offsets): sort plan, radix sort, run-length segmentation (Section 5.1 "gradient
+ * batch's (indices, offsets): sort plan, sort, run-length segmentation (Section 5.1 "gradient
  * sorting by rows"); it may run on another stream, concurrently with tbe_forward or with dense
  * layers.  tbe_backward_update_<optimizer> enqueues the aggregation + optimizer step
  * (Sections 5.1, 5.2) for the batch sorted last; the caller must order it after that sort (same
@@ -239,7 +239,8 @@ TBE_API tbe_status_t tbe_check_inputs(tbe_handle_t h, const int32_t* d_indices, 
 TBE_API tbe_status_t tbe_profile_enable(tbe_handle_t h, int32_t max_calls);
 
 /*
- * Synchronises the recorded events and returns, per kernel slot, the number of timed launches and
+ * Synchronises the recorded events and returns, per kernel slot, the number of timed launches (of the sort itself,
+ * slot "radix_scatter": eight-bit digits of the tallest table's row index per call, however few launches order them) and
  * their total duration in milliseconds since the last read; then resets the pool.  names receives
  * pointers to static strings.  capacity = length of the three host arrays; *num_slots = entries filled.
  */

@@ -3,7 +3,7 @@
 //
 // Section 5.1 of arxiv 2104.05158 asks for one forward launch and one fused backward+optimizer
 // step for all tables of a GPU; here the forward is literally one kernel and the backward is a
-// fixed sequence (sort plan, radix sort passes, run-length, fused reduce+optimizer, long-run fix-up)
+// fixed sequence (partition, bucket sort, run-length, fused reduce+optimizer, long runs)
 // enqueued on the caller's stream without any host synchronisation.
 #include "tbe.h"
 
@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "tbe_kernels.hip.h"
+#include "tbe_sort_kernels.hip.h"
 
 using namespace tbe;
 
@@ -42,6 +43,14 @@ const char* const kSlotNames[SLOT_COUNT] = {"forward",       "sort_plan",  "radi
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// Lookups per bucket: about 512 units in a small call, so that every CU has one or two, and no more than 7/16 of a tile
+// in a large one.  A bucket spreads by 1/4 around that; beyond a tile it takes the slow path through memory, which
+// one bucket in 1,000 did at half a tile (64 tables, 5.5 M lookups: 76 us for the units, 55 without such a straggler).
+constexpr int kSortTargetMin = 1024, kSortTargetMax = 3584;
+// Tiles per chunk of the partition: a histogram of up to 4 KiB is written and read per chunk, but there should be
+// some 4096 chunks for 512 resident workgroups (98 M lookups: histogram + partition 622 us with up to 4, 660 with 8).
+constexpr int64_t kSortChunksWanted = 4096;
+constexpr int kSortTilesPerChunk = 4;
 constexpr int kDenseGrid = 1024;
 // Lookups from which a wavefront of the update kernel owns 128 sorted positions instead of 64.  A small call needs
 // the shorter spans to have wavefronts enough (0.13 M lookups, dims 4..512: 62 us with 64, 112 with 128, 206 with
@@ -66,6 +75,7 @@ inline int pow2ceil_log2(int x)
 
 struct ProfRec {
     int slot;
+    int count;   // what the record adds to the slot's number of launches
     hipEvent_t start, stop;
 };
 
@@ -88,7 +98,7 @@ struct tbe_s {
     int fwd_epl = 4;
     int fwd_kmax = 1;
     int key_bits = 1;                   // bits of the tallest table's row index
-    std::vector<int> pass_digit_bits;   // per sort launch: the widest digit any table sorts in it
+    int64_t max_rows = 1;
     std::vector<int64_t> woff;      // T+1, elements
     std::vector<int64_t> soff;      // T+1, rows
     std::vector<int32_t> coloff;    // T+1
@@ -96,9 +106,9 @@ struct tbe_s {
 
     // workspace layout (byte offsets)
     size_t off_meta = 0, off_rowbase = 0, off_counters = 0, off_keys[2] = {0, 0}, off_vals[2] = {0, 0};
-    size_t off_tile_base = 0, off_tstart = 0, off_tile_table = 0;
-    int64_t max_tiles = 1;
-    size_t off_hist = 0, off_scan_tmp = 0, off_rl_counts = 0, off_unit_first = 0, off_partials = 0;
+    size_t off_tstart = 0, off_stables = 0, off_schunks = 0, off_sunits = 0, off_split = 0, off_lut = 0, off_bstart = 0;
+    size_t off_hist = 0, off_tile_bag = 0, off_unit_cnt = 0, off_unit_base = 0, off_unit_runs = 0, off_table_runs = 0, off_words64[2] = {0, 0};
+    size_t off_unit_first = 0, off_partials = 0;
     size_t off_long_list = 0, off_zero = 0, workspace_bytes = 0;
     size_t off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
     size_t off_dense_dirty = 0, off_dense_cnt = 0, off_dense_list = 0, off_drun = 0, off_dgroup = 0, off_dbounds = 0;
@@ -135,10 +145,11 @@ struct ScopedTimer {
     hipStream_t st;
     ProfRec rec;
     bool on = false;
-    ScopedTimer(tbe_s* h_, int slot, hipStream_t st_) : h(h_), st(st_)
+    ScopedTimer(tbe_s* h_, int slot, hipStream_t st_, int count = 1) : h(h_), st(st_)
     {
         if (h->profiling && h->ev_used + 2 <= h->ev_pool.size()) {
             rec.slot = slot;
+            rec.count = count;
             rec.start = h->ev_pool[h->ev_used++];
             rec.stop = h->ev_pool[h->ev_used++];
             on = hipEventRecord(rec.start, st) == hipSuccess;
@@ -192,6 +203,29 @@ int64_t dense_bounds_entries(int64_t n, int64_t batch, int T)
     return runs * (ceil_div(batch, kDenseSlice) + 1);
 }
 
+// Shape of a call's sort: how many bits of a packed word hold the bag number and how many the row offset inside a
+// bucket, and whether words of 32 bits do (the tallest table then needs at most kMaxRangeCuts buckets for that alone).
+struct SortShape {
+    int vb, kb;
+    bool wide;
+    int target, tiles_per_chunk;
+};
+
+SortShape sort_shape(const tbe_s* h, int64_t batch, int64_t n)
+{
+    SortShape s;
+    s.vb = 1;
+    while (((int64_t)1 << s.vb) < batch)
+        ++s.vb;
+    s.kb = 32 - s.vb;
+    s.wide = ceil_div(h->max_rows, (int64_t)1 << s.kb) > kMaxRangeCuts;
+    if (s.wide)
+        s.vb = s.kb = 32;
+    s.target = (int)std::min<int64_t>(kSortTargetMax, std::max<int64_t>(kSortTargetMin, n / 512));
+    s.tiles_per_chunk = (int)std::min<int64_t>(kSortTilesPerChunk, std::max<int64_t>(1, n / (kSortTile * kSortChunksWanted)));
+    return s;
+}
+
 void plan_workspace(tbe_s* h)
 {
     const int64_t nmax = h->max_indices;
@@ -212,17 +246,34 @@ void plan_workspace(tbe_s* h)
         h->off_keys[i] = take(4 * nelem);
         h->off_vals[i] = take(4 * nelem);
     }
-    // tiles never cross a table border: at most one partly filled tile per table on top of nmax / tile
-    h->max_tiles = ceil_div(nmax, kSortTile) + h->T;
-    h->off_tile_base = take(4 * (size_t)(h->T + 1));
+    // sort: sizes for the worst call (chunks and buckets never cross a table border; small calls use smaller ones)
+    const SortShape ss = sort_shape(h, h->max_batch, nmax);
+    int64_t slots = 2 * (int64_t)h->T + 513 + ceil_div(nmax, kSortTargetMax) + nmax / kSortTile;
+    // fewest row-offset bits a call with 32-bit words can have (a smaller batch may use them where the largest does not)
+    int kb = ss.wide ? 0 : ss.kb;
+    while (ceil_div(h->max_rows, (int64_t)1 << kb) > kMaxRangeCuts)
+        ++kb;
+    for (int t = 0; t < h->T; ++t) {
+        const bool tall = h->meta[t].key_bits > kb;
+        slots += tall ? ceil_div(h->rows[t], (int64_t)1 << kb) : 1;
+    }
+    const int64_t parts = std::min<int64_t>(h->T, nmax);
+    const int64_t sort_chunks = std::min<int64_t>(ceil_div(nmax, kSortTile), 2 * kSortChunksWanted + nmax / (kSortTile * kSortTilesPerChunk)) + h->T;
     h->off_tstart = take(4 * (size_t)(h->T + 1));
-    h->off_tile_table = take(sizeof(TileDesc) * (size_t)h->max_tiles);
-    const int64_t hist_len = 256 * h->max_tiles;
-    h->off_hist = take(4 * (size_t)hist_len);
-    const int64_t rl_tiles = std::max<int64_t>(1, ceil_div(nmax, kRlTile));
-    const int64_t scan_blocks = std::max(ceil_div(hist_len, kScanTile), ceil_div(rl_tiles, kScanTile));
-    h->off_scan_tmp = take(4 * (size_t)(scan_blocks + 1));
-    h->off_rl_counts = take(4 * (size_t)(rl_tiles + 16));
+    h->off_stables = take(sizeof(SortTable) * (size_t)h->T);
+    h->off_schunks = take(sizeof(SortChunk) * (size_t)sort_chunks);
+    h->off_sunits = take(sizeof(SortUnit) * (size_t)slots);
+    h->off_split = take(4 * (size_t)kMaxBuckets * parts);
+    h->off_lut = take(2 * (size_t)kLutSize * parts);
+    h->off_bstart = take(4 * (size_t)kMaxBuckets * parts);
+    h->off_hist = take(4 * (size_t)kMaxBuckets * sort_chunks);
+    h->off_tile_bag = take(4 * (size_t)(ceil_div(nmax, kSortTile) + (kSortTilesPerChunk + 1) * (int64_t)(h->T + 1)));
+    h->off_unit_cnt = take(4 * (size_t)h->T);
+    h->off_unit_base = take(4 * (size_t)(h->T + 1));
+    h->off_unit_runs = take(4 * (size_t)slots);
+    h->off_table_runs = take(4 * (size_t)h->T);
+    for (int i = 0; i < 2; ++i)
+        h->off_words64[i] = ss.wide ? take(8 * nelem) : 0;
     const int64_t chunks = std::max<int64_t>(1, ceil_div(nmax, kChunk));
     h->off_unit_first = take(4 * (size_t)(ceil_div(nmax, kSpanUnit) + 1));
     const int dpad = (int)align_up((size_t)h->dmax, 4);
@@ -252,20 +303,6 @@ void plan_workspace(tbe_s* h)
     h->off_wrun = take(4 * 2 * (size_t)(h->T + 1));   // prefixes of the per-table queue lengths and piece counts
     h->off_wbounds = take(sizeof(WinPiece) * (size_t)win_runs_max * kWinMax);   // the runs' piece records
     h->workspace_bytes = off;
-}
-
-// exclusive scan of a uint32 device array in place (three launches)
-tbe_status_t device_scan(tbe_s* h, uint32_t* data, int64_t n, int64_t* total_out, hipStream_t st)
-{
-    if (n <= 0)
-        return TBE_OK;
-    const int nb = (int)ceil_div(n, kScanTile);
-    uint32_t* tmp = h->ws<uint32_t>(h->off_scan_tmp);
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3(nb), dim3(kScanThreads), 0, st, data, tmp, n);
-    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(kScanThreads), 0, st, tmp, nb, total_out);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(nb), dim3(kScanThreads), 0, st, data, tmp, n);
-    TBE_LAUNCH_CHECK(h, "device_scan");
-    return TBE_OK;
 }
 
 tbe_status_t check_call(tbe_s* h, const void* d_indices, const void* d_offsets, int64_t num_indices,
@@ -391,28 +428,13 @@ tbe_status_t tbe_create(const tbe_config_t* cfg, tbe_handle_t* out_handle)
     h->dmax = dmax;
     h->fwd_epl = (h->dtype == TBE_DTYPE_FP16 && all8) ? 8 : 4;
     h->fwd_kmax = (int)ceil_div(dmax, h->fwd_epl * kWave);
-    // the sort is segmented by table, so only the bits of the tallest table's row index are sorted
-    int64_t max_rows = 1;
-    for (int t = 0; t < cfg->num_tables; ++t)
-        max_rows = std::max(max_rows, cfg->rows[t]);
-    h->key_bits = 1;
-    while (h->key_bits < 32 && ((int64_t)1 << h->key_bits) < max_rows)
-        ++h->key_bits;
-    // per-table sort geometry: table t orders ceil(log2 H_t) bits in P_t = ceil(bits / 8) passes during the
-    // last P_t of the P launches, bits split as evenly as possible (wider digits first)
-    const int P = (int)ceil_div(h->key_bits, 8);
-    h->pass_digit_bits.assign(P, 1);
+    // the sort is segmented by table: only the bits of a table's own row index are sorted
     std::vector<int> table_bits(cfg->num_tables, 1);
     for (int t = 0; t < cfg->num_tables; ++t) {
-        int b = 1;
-        while (b < 32 && ((int64_t)1 << b) < cfg->rows[t])
-            ++b;
-        table_bits[t] = b;
-        const int pt = (b + 7) / 8, q = b / pt, rem = b - q * pt;
-        for (int lp = 0; lp < pt; ++lp) {
-            int& w = h->pass_digit_bits[P - pt + lp];
-            w = std::max(w, q + (lp < rem ? 1 : 0));
-        }
+        while (table_bits[t] < 31 && ((int64_t)1 << table_bits[t]) < cfg->rows[t])
+            ++table_bits[t];
+        h->max_rows = std::max(h->max_rows, cfg->rows[t]);
+        h->key_bits = std::max(h->key_bits, table_bits[t]);
     }
 
     h->woff.resize(h->T + 1);
@@ -545,7 +567,6 @@ tbe_status_t tbe_forward(tbe_handle_t h, const int32_t* d_indices, const int64_t
 static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64_t* d_offsets, int32_t n,
                                  int32_t batch, hipStream_t st)
 {
-    tbe_status_t rc = TBE_OK;
     Counters* counters = h->ws<Counters>(h->off_counters);
     h->sorted_n = n;
     h->sorted_batch = batch;
@@ -555,91 +576,86 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         h->final_buf = 0;
         return TBE_OK;
     }
-    const uint32_t* row_base = h->ws<uint32_t>(h->off_rowbase);
-    uint32_t* keys[2] = {h->ws<uint32_t>(h->off_keys[0]), h->ws<uint32_t>(h->off_keys[1])};
-    int32_t* vals[2] = {h->ws<int32_t>(h->off_vals[0]), h->ws<int32_t>(h->off_vals[1])};
-
-    SortPlan pl;
-    pl.tile_base = h->ws<int32_t>(h->off_tile_base);
-    pl.tstart = h->ws<int32_t>(h->off_tstart);
-    pl.tiles = h->ws<TileDesc>(h->off_tile_table);
-    // upper bound of the number of tiles for THIS call (the exact number is only known on the device)
-    const int max_tiles = (int)std::min<int64_t>(h->max_tiles, ceil_div(n, kSortTile) + h->T);
-    {   // a2: table borders -> tile plan (keys are the caller's indices; payloads are made in the first pass)
+    const SortShape ss = sort_shape(h, batch, n);
+    SortArgs a;
+    a.offsets = d_offsets;
+    a.indices = reinterpret_cast<const uint32_t*>(d_indices);
+    a.meta = h->ws<TableMeta>(h->off_meta);
+    a.row_base = h->ws<uint32_t>(h->off_rowbase);
+    a.tables = h->ws<SortTable>(h->off_stables);
+    a.chunks = h->ws<SortChunk>(h->off_schunks);
+    a.units = h->ws<SortUnit>(h->off_sunits);
+    a.split = h->ws<uint32_t>(h->off_split);
+    a.lut = h->ws<uint16_t>(h->off_lut);
+    a.bstart = h->ws<uint32_t>(h->off_bstart);
+    a.hist = h->ws<uint32_t>(h->off_hist);
+    a.tile_bag = h->ws<int32_t>(h->off_tile_bag);
+    a.unit_cnt = h->ws<uint32_t>(h->off_unit_cnt);
+    a.unit_base = h->ws<uint32_t>(h->off_unit_base);
+    a.unit_runs = h->ws<uint32_t>(h->off_unit_runs);
+    a.table_runs = h->ws<uint32_t>(h->off_table_runs);
+    a.tstart = h->ws<int32_t>(h->off_tstart);
+    a.counters = counters;
+    a.keys = h->ws<uint32_t>(h->off_keys[0]);
+    a.vals = h->ws<int32_t>(h->off_vals[0]);
+    a.unique_keys = h->ws<uint32_t>(h->off_keys[1]);
+    a.seg_offsets = h->ws<int32_t>(h->off_vals[1]);
+    a.unit_first_run = h->ws<int32_t>(h->off_unit_first);
+    // a unit reads its words before it writes its keys and payloads to the same positions: 32-bit words share
+    // the memory of the result
+    for (int i = 0; i < 2; ++i)
+        a.words[i] = ss.wide ? h->ws<void>(h->off_words64[i]) : i == 0 ? static_cast<void*>(a.keys) : static_cast<void*>(a.vals);
+    a.n = n;
+    a.B = batch;
+    a.T = h->T;
+    a.vb = ss.vb;
+    a.kb = ss.kb;
+    a.target = ss.target;
+    a.tiles_per_chunk = ss.tiles_per_chunk;
+    const int passes = (int)ceil_div(h->key_bits, 8);    // what the profile counts for the sort itself
+    h->final_buf = 0;
+    if (n <= kSortTile && (int64_t)h->T * batch <= kSmallBags) {
+        ScopedTimer tm(h, SLOT_RADIX_SCATTER, st, passes);
+        int bits = 1;                                    // of the linear row ids
+        while (bits < 32 && ((int64_t)1 << bits) < h->soff[h->T])
+            ++bits;
+        hipLaunchKernelGGL(sort_small_kernel, dim3(1), dim3(kSortThreads), 0, st, a, bits);
+        TBE_LAUNCH_CHECK(h, "sort_small_kernel");
+        return TBE_OK;
+    }
+    const unsigned chunk_grid = (unsigned)(ceil_div(n, (int64_t)kSortTile * ss.tiles_per_chunk) + h->T);
+    {   // a2: samples, bucket borders and chunks
         ScopedTimer tm(h, SLOT_SORT_PLAN, st);
-        hipLaunchKernelGGL(sort_plan_tables_kernel, dim3(1), dim3(256), 0, st, d_offsets, batch, h->T,
-                           h->ws<int32_t>(h->off_tile_base), h->ws<int32_t>(h->off_tstart), counters);
-        hipLaunchKernelGGL(sort_plan_tiles_kernel, dim3((unsigned)ceil_div(max_tiles, 256)), dim3(256), 0, st,
-                           pl.tile_base, pl.tstart, d_offsets, batch, h->T, h->ws<TileDesc>(h->off_tile_table),
-                           max_tiles);
-        TBE_LAUNCH_CHECK(h, "sort_plan kernels");
+        hipLaunchKernelGGL(sort_plan_kernel, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
+        TBE_LAUNCH_CHECK(h, "sort_plan_kernel");
     }
-
-    // a3: stable LSD radix sort, segmented by table; every table over the bits of its own row index, in its own
-    // number of passes, all tables finishing in the last launch (tables with fewer passes sit out the first ones)
-    const int passes = (int)ceil_div(h->key_bits, 8);
-    uint32_t* hist = h->ws<uint32_t>(h->off_hist);
-    const TableMeta* meta = h->ws<TableMeta>(h->off_meta);
-    const uint32_t* indices = reinterpret_cast<const uint32_t*>(d_indices);
-    int cur = -1;  // pair that holds the current order (-1 = nothing sorted yet)
-    for (int p = 0; p < passes; ++p) {
-        const int nd_bits = h->pass_digit_bits[p];   // widest digit any table sorts in this launch
-        const int out = cur < 0 ? 0 : cur ^ 1;
-        const uint32_t* keys_cur = cur < 0 ? indices : keys[cur];
-        const int32_t* vals_cur = cur < 0 ? nullptr : vals[cur];
-        {
-            ScopedTimer tm(h, SLOT_RADIX_HIST, st);
-            hipLaunchKernelGGL(radix_hist_kernel, dim3(max_tiles), dim3(kSortThreads), 0, st, pl, meta, keys_cur,
-                               indices, hist, p, passes, nd_bits);
-            TBE_LAUNCH_CHECK(h, "radix_hist_kernel");
-        }
-        {
-            ScopedTimer tm(h, SLOT_RADIX_SCAN, st);
-            rc = device_scan(h, hist, (int64_t)max_tiles << nd_bits, nullptr, st);
-            if (rc != TBE_OK)
-                return rc;
-        }
-        {
-            ScopedTimer tm(h, SLOT_RADIX_SCATTER, st);
-            // a bag number below 2^16 travels as 16 bits between the passes
-            auto launch = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(max_tiles), dim3(kSortThreads), 0, st, pl, meta, keys_cur, vals_cur,
-                                   indices, keys[out], vals[out], hist, d_offsets, row_base, batch, p, passes, nd_bits);
-            };
-            const bool last = p == passes - 1, v16 = batch <= 65536;
-            if (last && v16)
-                launch(radix_scatter_kernel<true, true>);
-            else if (last)
-                launch(radix_scatter_kernel<true, false>);
-            else if (v16)
-                launch(radix_scatter_kernel<false, true>);
-            else
-                launch(radix_scatter_kernel<false, false>);
-            TBE_LAUNCH_CHECK(h, "radix_scatter_kernel");
-        }
-        cur = out;
-    }
-    h->final_buf = cur;
-
-    // a4: run heads -> unique keys, segment offsets, per-chunk first run (the free ping-pong pair
-    // of the sort holds unique_keys / seg_offsets)
-    uint32_t* unique_keys = keys[cur ^ 1];
-    int32_t* seg_offsets = vals[cur ^ 1];
-    int32_t* unit_first = h->ws<int32_t>(h->off_unit_first);
     {
-        ScopedTimer tm(h, SLOT_RUNLENGTH, st);
-        const int rl_tiles = (int)ceil_div(n, kRlTile);
-        uint32_t* rl_counts = h->ws<uint32_t>(h->off_rl_counts);
-        hipLaunchKernelGGL(runlength_count_kernel, dim3(rl_tiles), dim3(kRlThreads), 0, st, keys[cur],
-                           rl_counts, n);
-        rc = device_scan(h, rl_counts, rl_tiles, nullptr, st);
-        if (rc != TBE_OK)
-            return rc;
-        hipLaunchKernelGGL(runlength_write_kernel, dim3(rl_tiles), dim3(kRlThreads), 0, st, keys[cur],
-                           rl_counts, unique_keys, seg_offsets, unit_first, counters, n);
-        TBE_LAUNCH_CHECK(h, "runlength kernels");
+        ScopedTimer tm(h, SLOT_RADIX_HIST, st);
+        hipLaunchKernelGGL(sort_hist_kernel, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
+        TBE_LAUNCH_CHECK(h, "sort_hist_kernel");
     }
-
+    {
+        ScopedTimer tm(h, SLOT_RADIX_SCAN, st);
+        hipLaunchKernelGGL(sort_units_kernel, dim3((unsigned)h->T), dim3(kUnitsThreads), 0, st, a);
+        TBE_LAUNCH_CHECK(h, "sort_units_kernel");
+    }
+    {   // a3: the partition and the sort of the buckets in LDS
+        ScopedTimer tm(h, SLOT_RADIX_SCATTER, st, passes);
+        auto launch = [&](auto scatter, auto local, int per_cu) {
+            hipLaunchKernelGGL(scatter, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
+            hipLaunchKernelGGL(local, dim3(256 * per_cu), dim3(kSortThreads), 0, st, a);
+        };
+        if (ss.wide)
+            launch(sort_scatter_kernel<uint64_t>, sort_local_kernel<uint64_t>, 2);
+        else
+            launch(sort_scatter_kernel<uint32_t>, sort_local_kernel<uint32_t>, 3);
+        TBE_LAUNCH_CHECK(h, "sort_local_kernel");
+    }
+    {   // a4: run heads -> unique keys, segment offsets, first run of every span unit
+        ScopedTimer tm(h, SLOT_RUNLENGTH, st);
+        hipLaunchKernelGGL(sort_runs_kernel, dim3(1024), dim3(kRunThreads), 0, st, a);
+        TBE_LAUNCH_CHECK(h, "sort_runs_kernel");
+    }
     return TBE_OK;
 }
 
@@ -984,7 +1000,7 @@ tbe_status_t tbe_profile_read(tbe_handle_t h, int32_t capacity, const char** nam
         TBE_HIP_CHECK(h, hipEventSynchronize(r.stop));
         float ms = 0.f;
         TBE_HIP_CHECK(h, hipEventElapsedTime(&ms, r.start, r.stop));
-        launches[r.slot] += 1;
+        launches[r.slot] += r.count;
         total_ms[r.slot] += ms;
     }
     h->recs.clear();

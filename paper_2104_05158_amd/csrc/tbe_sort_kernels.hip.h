@@ -1,0 +1,1291 @@
+// Sort by (table, row) and run-length segmentation of a batch's lookups (Section 5.1 of arxiv 2104.05158,
+// "gradient sorting by rows"), for gfx950.
+//
+// The input is table-major, so the lookups of a table already occupy one contiguous range of positions: only the
+// row index has to be sorted, table by table.  Every table is partitioned once into buckets that fit a workgroup's
+// LDS, and every bucket is sorted there -- the lookups cross HBM twice, whatever the number of index bits, where a
+// digit-by-digit radix sort crosses it once per eight bits and once more for the run lengths.
+//
+//   sort_plan_kernel     one workgroup per table: sorts a sample of its indices and picks the borders of its
+//                        buckets so that a bucket holds about `target` lookups whatever their distribution.  A row
+//                        that is looked up more often than that gets a bucket of its own, which needs no sorting.
+//   sort_hist_kernel     lookups per bucket and chunk (a chunk is a few tiles of kSortTile positions)
+//   sort_units_kernel    bucket starts, positions of every chunk inside its buckets, and the list of work units
+//   sort_scatter_kernel  stable partition: a lookup becomes one word, (row - first row of the bucket) and bag
+//                        number packed in 32 bits
+//   sort_local_kernel    one workgroup per unit: sorts the words in LDS, writes keys and payloads, counts the runs
+//   sort_runs_kernel     bucket borders are run borders, so a unit's runs start at a known index: unique_keys,
+//                        seg_offsets, and the first run of every span unit
+// A call of at most kSortTile lookups is sorted by (table, row) at once, by one workgroup (sort_small_kernel).
+//
+// (The runs' first index could also come from a look-back over the units' counts inside sort_local_kernel; at
+// 38,000 units its polling took 6 ms where the extra kernel takes 0.2.)
+//
+// The word is 32 bits while the rows of every table can be cut into at most kMaxRangeCuts ranges whose row offset
+// and bag number fit 32 bits (always for batch <= 65536 and tables below 2^25 rows); otherwise 64 bits.
+//
+// Stability (equal rows keep the order of their bags) comes from ranks formed by ballots in position order; nothing
+// depends on scheduling: the artefacts are bit-identical run to run.
+#pragma once
+
+#include <type_traits>
+
+#include "tbe_kernels.hip.h"
+
+namespace tbe {
+
+constexpr int kSortThreads = 512;                 // 8 wavefronts
+constexpr int kSortWaves = kSortThreads / kWave;
+constexpr int kSortPerThread = 16;
+constexpr int kSortTile = kSortThreads * kSortPerThread;   // 8192 words: what a workgroup sorts in LDS
+constexpr int kMaxBuckets = 1024;                 // per table
+constexpr int kMaxRangeCuts = 512;                // of those, bucket borders at multiples of the packed key range
+constexpr int kLutBits = 12;
+constexpr int kLutSize = (1 << kLutBits) + 8;
+constexpr int kSamplesPerBucket = 16;             // a bucket's size then spreads by 1/4 around the target
+constexpr int kLocalDigits = 256;
+constexpr int kUnitsThreads = 1024;
+
+struct SortTable {       // 32 bytes
+    int32_t start, n;    // first position, lookups
+    int32_t slot_base;   // first unit slot
+    int32_t chunk_base;  // first chunk
+    int32_t nchunks;
+    int32_t nb;          // buckets (0: no lookups)
+    int32_t part;        // index of its border / lookup tables
+    int32_t lut;         // lookup-table shift | most borders inside a cell << 8
+};
+
+struct SortChunk {       // 16 bytes
+    int32_t t, first, cnt, pad;
+};
+
+struct SortUnit {        // 32 bytes
+    int32_t start, m;    // positions
+    uint32_t key0;       // linear row id that row offset 0 stands for
+    int32_t bits;        // bits of the row offsets to sort
+    int32_t t;
+    int32_t flags;
+    int32_t pad[2];
+};
+constexpr int kUnitContinued = 1;     // further part of a one-row bucket: its first lookup starts no run
+
+struct SortArgs {
+    const int64_t* offsets;
+    const uint32_t* indices;
+    const TableMeta* meta;
+    const uint32_t* row_base;
+    SortTable* tables;       // [T]
+    SortChunk* chunks;
+    SortUnit* units;
+    uint32_t* split;         // [parts][kMaxBuckets] first row of every bucket
+    uint16_t* lut;           // [parts][kLutSize] bucket of the first row of every cell of rows (and of the row past the last)
+    uint32_t* bstart;        // [parts][kMaxBuckets] first position of every bucket
+    uint32_t* hist;          // [chunks][kMaxBuckets]
+    int32_t* tile_bag;       // [chunks * tiles_per_chunk] bag of the first position of every tile
+    uint32_t* unit_cnt;      // [T]
+    uint32_t* unit_base;     // [T + 1]
+    uint32_t* unit_runs;     // [slots] runs of every unit
+    uint32_t* table_runs;    // [T]
+    int32_t* tstart;         // [T + 1]
+    Counters* counters;
+    void* words[2];          // words, and the second buffer of units larger than a tile
+    uint32_t* keys;
+    int32_t* vals;
+    uint32_t* unique_keys;
+    int32_t* seg_offsets;
+    int32_t* unit_first_run;
+    int32_t n, B, T;
+    int32_t vb;              // bits of the bag number in a word
+    int32_t kb;              // bits left for the row offset
+    int32_t target;          // lookups per bucket
+    int32_t tiles_per_chunk;
+};
+
+// ---------------------------------------------------------------- wavefront and workgroup primitives
+
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v)     // lanes without a source get 0
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v)   // inclusive
+{
+    v += dpp0<0x111, 0xf>(v);
+    v += dpp0<0x112, 0xf>(v);
+    v += dpp0<0x114, 0xf>(v);
+    v += dpp0<0x118, 0xf>(v);
+    v += dpp0<0x142, 0xa>(v);
+    v += dpp0<0x143, 0xc>(v);
+    return v;
+}
+
+__device__ __forceinline__ uint32_t wave_scan_max(uint32_t v)   // inclusive
+{
+    v = max(v, dpp0<0x111, 0xf>(v));
+    v = max(v, dpp0<0x112, 0xf>(v));
+    v = max(v, dpp0<0x114, 0xf>(v));
+    v = max(v, dpp0<0x118, 0xf>(v));
+    v = max(v, dpp0<0x142, 0xa>(v));
+    v = max(v, dpp0<0x143, 0xc>(v));
+    return v;
+}
+
+__device__ __forceinline__ uint32_t last_lane(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+// exclusive scan over the workgroup's NT threads; one barrier (s_wsum must not be in use), total to all threads
+template <int NT>
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* s_wsum, uint32_t& total)
+{
+    const uint32_t incl = wave_scan_add(v);
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1)
+        s_wsum[wave] = incl;
+    __syncthreads();
+    uint32_t off = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w) {
+        const uint32_t c = s_wsum[w];
+        off += w < wave ? c : 0u;
+        tot += c;
+    }
+    total = tot;
+    return off + incl - v;
+}
+
+// last i in [0, n) with p[i] <= q for a whole wavefront (p[0] <= q, ascending): 64 probes per step
+__device__ __forceinline__ int wave_upper(const int64_t* __restrict__ p, int n, int64_t q)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    int lo = 0;
+    while (n > 1) {
+        const int step = (n + kWave - 1) / kWave;
+        const int i = lane * step;
+        const uint64_t le = __ballot(i < n && p[lo + min(i, n - 1)] <= q);
+        const int k = (__popcll(le) - 1) * step;
+        lo += k;
+        n = min(step, n - k);
+    }
+    return lo;
+}
+
+__device__ __forceinline__ int ceil_log2(uint32_t x) { return x <= 1 ? 0 : 32 - __clz((int)(x - 1)); }
+
+// The digit counters are counted as words and read as their halves.
+typedef uint16_t __attribute__((may_alias)) u16_alias;
+typedef uint32_t __attribute__((may_alias)) u32_alias;
+
+// element i of an array: 32-bit byte offset to a uniform base, so that unrolled accesses share one address register
+template <typename T>
+__device__ __forceinline__ T load_at(const T* base, uint32_t i, uint32_t plus)
+{
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + i * (uint32_t)sizeof(T) + plus * sizeof(T));
+}
+template <typename T>
+__device__ __forceinline__ void store_at(T* base, uint32_t i, uint32_t plus, T v)
+{
+    *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (uint32_t)sizeof(T) + plus * sizeof(T)) = v;
+}
+
+// digit of `width` bits from `sh` on
+__device__ __forceinline__ uint32_t digit_of(uint32_t w, int sh, int width) { return __builtin_amdgcn_ubfe(w, sh, width); }
+__device__ __forceinline__ uint32_t digit_of(uint64_t w, int sh, int width) { return __builtin_amdgcn_ubfe((uint32_t)(w >> sh), 0, width); }
+
+// A value the compiler may not carry over from one phase to the next: sixteen positions per thread, or the masks
+// of their comparisons, kept in registers across the phases of a tile spill.
+__device__ __forceinline__ int opaque(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Ranks of the wavefront's words among those of the same digit, in position order: rank[r] counts the earlier
+// words of the wavefront's own row of counters.  Lanes with the same digit find each other with one ballot per
+// digit bit; the first of them adds the count.  The counters are 16-bit halves of words, read and added to by LDS
+// operations, which execute in order.
+// Rounds come in groups whose counter reads are waited for together.  Every position of every round counts: positions past the end hold words whose digit is the largest, so they
+// come out last.  BITS is a template parameter: with a test per bit and round the kernels spend as long on scalar
+// branches as on ballots.
+template <int BITS, int GROUP, int ND, int PER, typename Digit>
+__device__ __forceinline__ void rank_bits(Digit digit, int groups, uint16_t (&s_cnt)[kSortWaves][ND], uint32_t (&rank)[PER])
+{
+    const int wave = uniform(threadIdx.x >> 6);
+#pragma unroll
+    for (int r0 = 0; r0 < PER; r0 += GROUP) {
+        if (r0 >= groups * GROUP)
+            break;
+        uint32_t lo[GROUP], hi[GROUP], dg[GROUP];
+#pragma unroll
+        for (int x = 0; x < GROUP; ++x) {
+            dg[x] = digit(r0 + x);
+            lo[x] = hi[x] = ~0u;
+#pragma unroll
+            for (int b = 0; b < BITS; ++b) {
+                int32_t mk;                                  // all ones if bit b is set
+                asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(mk) : "v"(dg[x]), "n"(b));
+                const uint64_t bal = __ballot(mk != 0);
+                // x &= ~(ballot ^ mk): lanes whose bit differs drop out (left to itself the compiler takes 3/2 as many)
+                lo[x] = __builtin_amdgcn_bitop3_b32(lo[x], (uint32_t)bal, (uint32_t)mk, 0x90);
+                hi[x] = __builtin_amdgcn_bitop3_b32(hi[x], (uint32_t)(bal >> 32), (uint32_t)mk, 0x90);
+            }
+        }
+        uint32_t pre[GROUP];
+#pragma unroll
+        for (int x = 0; x < GROUP; ++x) {
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi[x], __builtin_amdgcn_mbcnt_lo(lo[x], 0u));
+            pre[x] = reinterpret_cast<const u16_alias*>(s_cnt[wave])[dg[x]];
+            if (below == 0)
+                atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s_cnt[wave]) + (2u * dg[x] & ~3u)),
+                          (uint32_t)(__popc(lo[x]) + __popc(hi[x])) << ((dg[x] & 1u) * 16u));
+            rank[r0 + x] = below;
+        }
+#pragma unroll
+        for (int x = 0; x < GROUP; ++x)
+            rank[r0 + x] += pre[x];
+    }
+}
+
+// groups: of GROUP rounds each
+template <int GROUP, int ND, int PER, typename Digit>
+__device__ __forceinline__ void rank_rounds(Digit digit, int groups, int bits, uint16_t (&s_cnt)[kSortWaves][ND],
+                                            uint32_t (&rank)[PER])
+{
+    static_assert(ND == 256 || ND == 1024, "digit tables");
+    switch (bits) {
+        case 0:
+        case 1: rank_bits<1, GROUP>(digit, groups, s_cnt, rank); break;
+        case 2: rank_bits<2, GROUP>(digit, groups, s_cnt, rank); break;
+        case 3: rank_bits<3, GROUP>(digit, groups, s_cnt, rank); break;
+        case 4: rank_bits<4, GROUP>(digit, groups, s_cnt, rank); break;
+        case 5: rank_bits<5, GROUP>(digit, groups, s_cnt, rank); break;
+        case 6: rank_bits<6, GROUP>(digit, groups, s_cnt, rank); break;
+        case 7: rank_bits<7, GROUP>(digit, groups, s_cnt, rank); break;
+        case 8: rank_bits<8, GROUP>(digit, groups, s_cnt, rank); break;
+        default:
+            if constexpr (ND > 256) {
+                if (bits == 9)
+                    rank_bits<9, GROUP>(digit, groups, s_cnt, rank);
+                else
+                    rank_bits<10, GROUP>(digit, groups, s_cnt, rank);
+            }
+    }
+}
+
+// Turns the wavefronts' digit counts into the slots of their first words (digit-major, wavefront by wavefront):
+// slot = s_cnt[wave][digit] + rank.  A thread owns two neighbouring digits as the halves of one word (no count
+// exceeds kSortTile).  Returns the thread's pair of digit starts; counts: its pair of digit totals.  One barrier
+// inside; the caller synchronises before the slots are read.
+template <int ND>
+__device__ __forceinline__ uint32_t digit_starts(uint16_t (&s_cnt)[kSortWaves][ND], uint32_t* s_wsum, uint32_t& counts)
+{
+    uint32_t c[kSortWaves], sum = 0;
+    const bool mine = 2 * (int)threadIdx.x < ND;
+    if (mine) {
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) {
+            c[w] = reinterpret_cast<const u32_alias*>(s_cnt[w])[threadIdx.x];
+            sum += c[w];
+        }
+    }
+    uint32_t total;
+    const uint32_t ex = block_scan<kSortThreads>((sum & 0xffffu) + (sum >> 16), s_wsum, total);
+    uint32_t run = ex | ((ex + (sum & 0xffffu)) << 16);
+    const uint32_t starts = run;
+    if (mine) {
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) {
+            reinterpret_cast<u32_alias*>(s_cnt[w])[threadIdx.x] = run;
+            run += c[w];
+        }
+    }
+    counts = sum;
+    return starts;
+}
+
+template <int ND>
+__device__ __forceinline__ void zero_counts(uint16_t (&s_cnt)[kSortWaves][ND])
+{
+    for (int i = threadIdx.x; i < kSortWaves * ND / 8; i += kSortThreads)
+        reinterpret_cast<uint4*>(&s_cnt[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+constexpr int kSortGroup = 2;      // rounds per group of the sorts in LDS (units differ in size) ...
+constexpr int kPartGroup = 4;      // ... and of the partition (tiles are full)
+
+// rounds of 64 words per wavefront that hold m words, in whole groups
+template <int GROUP>
+__device__ __forceinline__ int group_count(int m) { return (m + kSortThreads * GROUP - 1) / (kSortThreads * GROUP); }
+
+// One pass of a stable sort of the words w, in registers at positions wavefront * rounds * 64 + r * 64 + lane: by
+// `width` bits from `sh` on; the result is in s_w, barrier included.  s_cnt: cleared, and synchronised since.
+template <typename W>
+__device__ __forceinline__ void block_sort_pass(W (&w)[kSortPerThread], int groups, int sh, int width, W* s_w,
+                                                uint16_t (&s_cnt)[kSortWaves][kLocalDigits], uint32_t* s_wsum)
+{
+    const int wave = uniform(threadIdx.x >> 6);
+    uint32_t rank[kSortPerThread];
+    rank_rounds<kSortGroup>([&](int r) { return digit_of(w[r], sh, width); }, groups, width, s_cnt, rank);
+    __syncthreads();
+    uint32_t counts;
+    (void)digit_starts<kLocalDigits>(s_cnt, s_wsum, counts);
+    __syncthreads();
+#pragma unroll
+    for (int r0 = 0; r0 < kSortPerThread; r0 += kSortGroup)
+        if (r0 < groups * kSortGroup) {
+#pragma unroll
+            for (int r = r0; r < r0 + kSortGroup; ++r)
+                rank[r] += s_cnt[wave][digit_of(w[r], sh, width)];
+        }
+#pragma unroll
+    for (int r = 0; r < kSortPerThread; ++r)
+        if (r < groups * kSortGroup)
+            s_w[rank[r]] = w[r];
+    __syncthreads();
+}
+
+// the digits of pass p of P over `bits` bits
+__device__ __forceinline__ int pass_width(int bits, int P, int p) { return bits / P + (p < bits % P ? 1 : 0); }
+
+template <typename W>
+__device__ __forceinline__ void block_sort(W (&w)[kSortPerThread], int groups, int shift, int bits, W* s_w,
+                                           uint16_t (&s_cnt)[kSortWaves][kLocalDigits], uint32_t* s_wsum)
+{
+    const int p0 = (int)(threadIdx.x >> 6) * groups * kSortGroup * kWave + (int)(threadIdx.x & (kWave - 1));
+    const int passes = (bits + 7) >> 3;
+    for (int p = 0; p < passes; ++p) {
+        const int width = pass_width(bits, passes, p);
+        zero_counts(s_cnt);
+        if (p > 0) {
+            const int q = opaque(p0);
+#pragma unroll
+            for (int r = 0; r < kSortPerThread; ++r)
+                if (r < groups * kSortGroup)
+                    w[r] = s_w[q + r * kWave];
+        }
+        __syncthreads();
+        block_sort_pass<W>(w, groups, shift, width, s_w, s_cnt, s_wsum);
+        shift += width;
+    }
+}
+
+// Bags of the positions [first, first + m) of a table (offsets: its B + 1 bag borders; bags lo..hi are the ones
+// that can hold them): every bag that is not empty marks its first position, and a position's bag is the largest
+// mark at or before it, for position p = wavefront * rounds * 64 + r * 64 + lane
+//     max(s_mark[p], returned carry of the wavefront) - 1.
+// s_mark: rounds * kSortThreads words of LDS, rounds a multiple of 2.  Barriers inside, the last one before the
+// caller may read.
+__device__ __forceinline__ uint32_t bags_of_positions(const int64_t* __restrict__ offsets, int lo, int hi, int first, int m,
+                                                      int rounds, uint32_t* s_mark, uint32_t* s_wsum)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x >> 6;
+    const int p0 = wave * rounds * kWave + lane;
+    for (int i = threadIdx.x; i < rounds * (kSortThreads / 4); i += kSortThreads)
+        reinterpret_cast<uint4*>(s_mark)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    for (int i = lo + (int)threadIdx.x; i <= hi; i += kSortThreads) {
+        const int o = (int)offsets[i], e = (int)offsets[i + 1];
+        const int p = max(o - first, 0);
+        if (e > o && e > first && p < m)
+            s_mark[p] = (uint32_t)i + 1u;
+    }
+    __syncthreads();
+    uint32_t top = 0;
+    for (int r = 0; r < rounds; r += 2) {
+        const uint32_t v = wave_scan_max(s_mark[p0 + r * kWave]), x = wave_scan_max(s_mark[p0 + (r + 1) * kWave]);
+        const uint32_t mid = max(top, last_lane(v));
+        s_mark[p0 + r * kWave] = max(v, top);
+        s_mark[p0 + (r + 1) * kWave] = max(x, mid);
+        top = max(mid, last_lane(x));
+    }
+    if (lane == 0)
+        s_wsum[wave] = top;
+    __syncthreads();
+    uint32_t carry = 0;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w)
+        carry = max(carry, w < wave ? s_wsum[w] : 0u);
+    return carry;
+}
+
+// ---------------------------------------------------------------- plan
+
+struct TablePlan {
+    int want, cuts;      // buckets asked for, ranges of the packed key
+    int slots, chunks;
+};
+
+__device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32_t rows)
+{
+    TablePlan p;
+    p.cuts = a.kb >= 31 ? 1 : (int)((rows + (1u << a.kb) - 1) >> a.kb);
+    p.want = min(max((n + a.target - 1) / a.target, 1), kMaxBuckets - p.cuts);
+    p.slots = n == 0 ? 0 : p.want + p.cuts + n / kSortTile;
+    p.chunks = n == 0 ? 0 : (n + kSortTile * a.tiles_per_chunk - 1) / (kSortTile * a.tiles_per_chunk);
+    return p;
+}
+
+__device__ __forceinline__ uint32_t mix_bits(uint32_t x)
+{
+    x ^= x >> 16; x *= 0x7feb352du;
+    x ^= x >> 15; x *= 0x846ca68bu;
+    return x ^ (x >> 16);
+}
+
+// first i in [0, n) with p[i] >= v (n if none); p ascending, in LDS
+__device__ __forceinline__ int lds_lower(const uint32_t* p, int n, uint32_t v)
+{
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (p[mid] < v)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+__global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
+{
+    __shared__ __align__(16) uint32_t s_key[kSortTile];
+    __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
+    __shared__ uint32_t s_list[kMaxBuckets + 2], s_cut[kMaxRangeCuts];
+    __shared__ uint32_t s_wsum[kSortWaves];
+    __shared__ uint32_t s_sum[4];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int t = blockIdx.x;
+    if (tid < 4)
+        s_sum[tid] = 0;
+    __syncthreads();
+    {   // what the tables before this one take
+        uint32_t slots = 0, chunks = 0, parts = 0;
+        for (int i = tid; i < t; i += kSortThreads) {
+            const int n = (int)(a.offsets[(int64_t)(i + 1) * a.B] - a.offsets[(int64_t)i * a.B]);
+            const TablePlan p = table_plan(a, n, a.row_base[i + 1] - a.row_base[i]);
+            slots += p.slots; chunks += p.chunks; parts += n > 0;
+        }
+        slots = last_lane(wave_scan_add(slots));
+        chunks = last_lane(wave_scan_add(chunks));
+        parts = last_lane(wave_scan_add(parts));
+        if (lane == 0 && slots > 0) {
+            atomicAdd(&s_sum[0], slots); atomicAdd(&s_sum[1], chunks); atomicAdd(&s_sum[2], parts);
+        }
+    }
+    __syncthreads();
+    const int64_t o0 = a.offsets[(int64_t)t * a.B], o1 = a.offsets[(int64_t)(t + 1) * a.B];
+    const int start = (int)o0, n = (int)(o1 - o0);
+    const uint32_t rbase = a.row_base[t], rows = a.row_base[t + 1] - rbase;
+    const int bits = a.meta[t].key_bits;
+    const TablePlan p = table_plan(a, n, rows);
+    SortTable st;
+    st.start = start; st.n = n;
+    st.slot_base = (int)s_sum[0]; st.chunk_base = (int)s_sum[1]; st.part = (int)s_sum[2];
+    st.nchunks = p.chunks;
+    st.nb = 0; st.lut = 0;
+    if (tid == 0) {
+        a.tstart[t] = start;
+        a.unit_cnt[t] = 0;
+        a.table_runs[t] = 0;
+        if (t == a.T - 1) {
+            a.tstart[a.T] = (int)o1;
+            a.counters->sort_chunks = st.chunk_base + p.chunks;
+            a.counters->sort_ticket = 0;
+            a.counters->sort_arrived = 0;
+        }
+    }
+    for (int i = tid; i < p.chunks; i += kSortThreads) {
+        SortChunk c;
+        c.t = t;
+        c.first = start + i * kSortTile * a.tiles_per_chunk;
+        c.cnt = min(kSortTile * a.tiles_per_chunk, start + n - c.first);
+        c.pad = 0;
+        a.chunks[st.chunk_base + i] = c;
+    }
+    if (n == 0) {
+        if (tid == 0)
+            a.tables[t] = st;
+        return;
+    }
+
+    // ---- sorted sample: one lookup from each of S equal stretches of the table's positions
+    const int q = min(kSamplesPerBucket, kSortTile / p.want);
+    const int S = p.want * q;
+    uint32_t w[kSortPerThread];
+    const int groups = group_count<kSortGroup>(S), rounds = groups * kSortGroup;
+    const uint64_t stretch = ((uint64_t)n << 32) / (uint32_t)S;      // 32.32
+#pragma unroll
+    for (int r = 0; r < kSortPerThread; ++r) {
+        const int i = min(wave * rounds * kWave + r * kWave + lane, S - 1);
+        // a random place of the stretch: 8 bits of it are enough
+        const int pos = min((int)((stretch * (uint32_t)(i * 256 + (mix_bits((uint32_t)i) & 255u))) >> 40), n - 1);
+        // past the sample: the largest key, sorted behind it
+        w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? min(a.indices[start + pos], rows - 1) : ~0u;
+    }
+    block_sort<uint32_t>(w, groups, 0, bits, s_key, s_cnt, s_wsum);
+    // ---- borders: row 0, every q-th sample once, and the row after one that fills a whole stretch of samples
+    // (a bucket of its own).  Thread j owns candidates 2 j and 2 j + 1.
+    uint32_t cand[2], emit[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int j = 2 * tid + k;
+        emit[k] = 0;
+        cand[k] = 0;
+        if (j < p.want) {
+            const uint32_t c = j == 0 ? 0u : s_key[j * q];
+            const uint32_t before = j <= 1 ? 0u : s_key[(j - 1) * q];
+            const bool fresh = j == 0 || c != before;
+            cand[k] = c;
+            emit[k] = fresh ? (j + 1 < p.want && s_key[(j + 1) * q] == c ? 2u : 1u) : 0u;
+        }
+    }
+    uint32_t total;
+    uint32_t at = block_scan<kSortThreads>(emit[0] + emit[1], s_wsum, total);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (emit[k] > 0)
+            s_list[at] = cand[k];
+        if (emit[k] > 1)
+            s_list[at + 1] = cand[k] + 1;
+        at += emit[k];
+    }
+    __syncthreads();
+    // distinct borders below the number of rows, into s_key
+    const int n_list = (int)total;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int i = 2 * tid + k;
+        emit[k] = i < n_list && s_list[i] < rows && (i == 0 || s_list[i] != s_list[i - 1]) ? 1u : 0u;
+    }
+    at = block_scan<kSortThreads>(emit[0] + emit[1], s_wsum, total);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (emit[k])
+            s_key[at++] = s_list[2 * tid + k];
+    const int na = (int)total;
+    __syncthreads();
+    // multiples of the packed key range that are no border yet (cuts <= kMaxRangeCuts = kSortThreads)
+    uint32_t cut = 0;
+    bool keep = false;
+    if (tid >= 1 && tid < p.cuts) {
+        cut = (uint32_t)tid << a.kb;
+        const int i = lds_lower(s_key, na, cut);
+        keep = i == na || s_key[i] != cut;
+    }
+    at = block_scan<kSortThreads>(keep ? 1u : 0u, s_wsum, total);
+    if (keep)
+        s_cut[at] = cut;
+    const int nc = (int)total;
+    __syncthreads();
+    uint32_t* split = a.split + (int64_t)st.part * kMaxBuckets;
+    if (keep)
+        s_list[at + lds_lower(s_key, na, cut)] = cut;
+    for (int i = tid; i < na; i += kSortThreads)
+        s_list[i + lds_lower(s_cut, nc, s_key[i])] = s_key[i];
+    const int nb = na + nc;
+    __syncthreads();
+    for (int i = tid; i < nb; i += kSortThreads)
+        split[i] = s_list[i];
+    // ---- lookup table: the bucket of every cell's first row
+    const int lut_bits = min(min(kLutBits, bits), ceil_log2((uint32_t)nb) + 3);
+    const int shift = bits - lut_bits;
+    uint16_t* lut = a.lut + (int64_t)st.part * kLutSize;
+    uint32_t span = 0;
+    for (int i = tid; i <= 1 << lut_bits; i += kSortThreads) {
+        const int lo = lds_lower(s_list, nb, ((uint32_t)i << shift) + 1u) - 1;
+        lut[i] = (uint16_t)lo;
+        if (i < 1 << lut_bits)
+            span = max(span, (uint32_t)(lds_lower(s_list, nb, (uint32_t)(i + 1) << shift) - 1 - lo));
+    }
+    span = last_lane(wave_scan_max(span));
+    if (tid == 0)
+        s_sum[0] = 0;
+    __syncthreads();
+    if (lane == 0)
+        atomicMax(&s_sum[0], span);
+    __syncthreads();
+    if (tid == 0) {
+        st.nb = nb;
+        st.lut = shift | (int)s_sum[0] << 8;
+        a.tables[t] = st;
+    }
+}
+
+// ---------------------------------------------------------------- partition
+
+// A table's borders and lookup table in LDS (synchronise before use), and the bucket of a row: the bucket of the
+// first row of its cell, moved on over the borders inside the cell.  Cells of hashed ids hold one border or, for
+// a row with a bucket of its own, two: up to kLinear borders are compared one after the other, all at once; ids
+// that crowd in a few cells are bisected.
+struct Borders {
+    static constexpr int kLinear = 4;
+    uint32_t split[kMaxBuckets + kLinear];
+    uint16_t lut[kLutSize];
+
+    __device__ __forceinline__ void load(const SortArgs& a, const SortTable& st, int bits)
+    {
+        const uint32_t* from = a.split + (int64_t)st.part * kMaxBuckets;
+        for (int i = threadIdx.x; i < st.nb + kLinear; i += kSortThreads)
+            split[i] = i < st.nb ? from[i] : ~0u;
+        const uint32_t* cells = reinterpret_cast<const uint32_t*>(a.lut + (int64_t)st.part * kLutSize);
+        const int n = (1 << (bits - (st.lut & 0xff))) / 2 + 1;
+        for (int i = threadIdx.x; i < n; i += kSortThreads)
+            reinterpret_cast<uint32_t*>(lut)[i] = cells[i];
+    }
+
+    // SPAN: most borders inside a cell; 0: more than kLinear
+    template <int SPAN>
+    __device__ __forceinline__ uint32_t bucket(uint32_t row, int shift, uint32_t last_cell) const
+    {
+        const uint32_t cell = min(row >> shift, last_cell);
+        uint32_t d = lut[cell];
+        if (SPAN > 0) {
+            uint32_t b[SPAN + 1];
+#pragma unroll
+            for (int k = 1; k <= SPAN; ++k)
+                b[k] = split[d + k];
+#pragma unroll
+            for (int k = 1; k <= SPAN; ++k)
+                d += b[k] <= row ? 1u : 0u;
+            return d;
+        }
+        uint32_t hi = lut[cell + 1];
+        while (__ballot(d < hi) != 0ull) {
+            const uint32_t mid = (d + hi + 1) >> 1;
+            const bool up = split[mid] <= row;
+            d = up ? mid : d;
+            hi = up ? hi : max(mid, 1u) - 1u;
+        }
+        return d;
+    }
+
+    // f(the SPAN of the table)
+    template <typename F>
+    __device__ __forceinline__ static void with_span(int span, F f)
+    {
+        switch (span) {
+            case 0:
+            case 1: f(std::integral_constant<int, 1>()); break;
+            case 2: f(std::integral_constant<int, 2>()); break;
+            case 3: f(std::integral_constant<int, 3>()); break;
+            case 4: f(std::integral_constant<int, 4>()); break;
+            default: f(std::integral_constant<int, 0>()); break;
+        }
+    }
+};
+
+__global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortArgs a)
+{
+    __shared__ uint32_t s_hist[kMaxBuckets];
+    __shared__ Borders s_borders;
+    if ((int)blockIdx.x >= a.counters->sort_chunks)
+        return;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const SortChunk c = a.chunks[blockIdx.x];
+    const SortTable st = a.tables[c.t];
+    const int bits = a.meta[c.t].key_bits;
+    const int shift = st.lut & 0xff, span = st.lut >> 8;
+    const uint32_t last_cell = (1u << (bits - shift)) - 1u;
+    const int end = c.first + c.cnt;
+    s_borders.load(a, st, bits);
+    for (int i = threadIdx.x; i < kMaxBuckets; i += kSortThreads)
+        s_hist[i] = 0;
+    // the bag of every tile's first position, one tile per wavefront (the partition starts from it)
+    static_assert(kSortWaves >= 8, "a chunk has at most 8 tiles");
+    if (c.first + wave * kSortTile < end) {
+        const int b = wave_upper(a.offsets + (int64_t)c.t * a.B, a.B, c.first + wave * kSortTile);
+        if (lane == 0)
+            a.tile_bag[(int)blockIdx.x * a.tiles_per_chunk + wave] = b;
+    }
+    __syncthreads();
+    const uint32_t* __restrict__ idx = a.indices + c.first;
+    Borders::with_span(span, [&](auto sp) {
+        constexpr int kSpan = decltype(sp)::value;
+        int first = 0;
+        for (; first + kSortTile <= c.cnt; first += kSortTile) {
+            uint32_t key[kSortPerThread];
+#pragma unroll
+            for (int r = 0; r < kSortPerThread; ++r)
+                key[r] = load_at(idx, (uint32_t)(first + (int)threadIdx.x), r * kSortThreads);
+#pragma unroll
+            for (int r = 0; r < kSortPerThread; ++r)
+                atomicAdd(&s_hist[s_borders.bucket<kSpan>(key[r], shift, last_cell)], 1u);
+        }
+        for (int i = first + (int)threadIdx.x; i - (int)threadIdx.x < c.cnt; i += kSortThreads) {   // whole wavefronts: bucket() may ballot
+            const uint32_t d = s_borders.bucket<kSpan>(idx[min(i, c.cnt - 1)], shift, last_cell);
+            if (i < c.cnt)
+                atomicAdd(&s_hist[d], 1u);
+        }
+    });
+    __syncthreads();
+    for (int i = threadIdx.x; i < st.nb; i += kSortThreads)
+        a.hist[(int64_t)blockIdx.x * kMaxBuckets + i] = s_hist[i];
+}
+
+// One workgroup per table, one thread per bucket: counts of the chunks -> positions of the chunks inside the bucket,
+// bucket starts, work units.  The workgroup that finishes last numbers the units of all tables.
+__global__ __launch_bounds__(kUnitsThreads) void sort_units_kernel(SortArgs a)
+{
+    __shared__ uint32_t s_wsum[2][kUnitsThreads / kWave];
+    __shared__ uint32_t s_last;
+    const int t = blockIdx.x;
+    const int d = threadIdx.x;
+    const SortTable st = a.tables[t];
+    if (st.nb > 0) {
+        uint32_t run = 0;
+        if (d < st.nb) {
+            uint32_t* col = a.hist + (int64_t)st.chunk_base * kMaxBuckets + d;
+            constexpr int kAhead = 8;
+            for (int c = 0; c < st.nchunks; c += kAhead) {
+                uint32_t x[kAhead];
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i)
+                    x[i] = c + i < st.nchunks ? col[(int64_t)(c + i) * kMaxBuckets] : 0u;
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) {
+                    if (c + i < st.nchunks)
+                        col[(int64_t)(c + i) * kMaxBuckets] = run;
+                    run += x[i];
+                }
+            }
+        }
+        uint32_t tot;
+        const uint32_t first = (uint32_t)st.start + block_scan<kUnitsThreads>(run, s_wsum[0], tot);
+        uint32_t lo = 0, range = 1, pieces = 0;
+        if (d < st.nb) {
+            const uint32_t* split = a.split + (int64_t)st.part * kMaxBuckets;
+            a.bstart[(int64_t)st.part * kMaxBuckets + d] = first;
+            lo = split[d];
+            range = (d + 1 < st.nb ? split[d + 1] : a.row_base[t + 1] - a.row_base[t]) - lo;
+            pieces = run == 0 ? 0u : range == 1 ? (run + kSortTile - 1) / kSortTile : 1u;
+        }
+        const uint32_t slot = block_scan<kUnitsThreads>(pieces, s_wsum[1], tot);
+        for (uint32_t i = 0; i < pieces; ++i) {
+            SortUnit u;
+            u.start = (int32_t)(first + i * kSortTile);
+            u.m = (int32_t)(pieces > 1 || range == 1 ? min((uint32_t)kSortTile, run - i * kSortTile) : run);
+            u.key0 = a.row_base[t] + lo;
+            u.bits = ceil_log2(range);
+            u.t = t;
+            u.flags = i > 0 ? kUnitContinued : 0;
+            u.pad[0] = u.pad[1] = 0;
+            a.units[st.slot_base + (int)(slot + i)] = u;
+        }
+        if (d == 0)
+            __hip_atomic_store(&a.unit_cnt[t], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (d == 0) {
+        __threadfence();
+        s_last = atomicAdd(&a.counters->sort_arrived, 1u) == (uint32_t)a.T - 1u;
+    }
+    __syncthreads();
+    if (!s_last)
+        return;
+    __threadfence();
+    uint32_t carry = 0;
+    for (int base = 0; base < a.T; base += kUnitsThreads) {
+        const int i = base + d;
+        const uint32_t c = i < a.T ? __hip_atomic_load(&a.unit_cnt[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        uint32_t tot;
+        const uint32_t ex = block_scan<kUnitsThreads>(c, s_wsum[0], tot);
+        if (i < a.T)
+            a.unit_base[i] = carry + ex;
+        carry += tot;
+        __syncthreads();
+    }
+    if (d == 0)
+        a.unit_base[a.T] = carry;
+}
+
+template <typename W>
+__global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_scatter_kernel(SortArgs a)
+{
+    __shared__ __align__(16) W s_w[kSortTile];
+    // digit counters while ranking, then the digits of the reordered words
+    __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kMaxBuckets];
+    static_assert(kSortWaves * kMaxBuckets == kSortTile, "the digits of a tile replace its counters");
+    __shared__ uint32_t s_next[kMaxBuckets], s_delta[kMaxBuckets];
+    __shared__ Borders s_borders;
+    __shared__ uint32_t s_wsum[kSortWaves];
+    if ((int)blockIdx.x >= a.counters->sort_chunks)
+        return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
+    const SortChunk c = a.chunks[blockIdx.x];
+    const SortTable st = a.tables[c.t];
+    const int bits = a.meta[c.t].key_bits;
+    const int shift = st.lut & 0xff, span = st.lut >> 8;
+    const uint32_t last_cell = (1u << (bits - shift)) - 1u;
+    const int digit_bits = ceil_log2((uint32_t)st.nb + 1u);   // bucket nb: positions past the end
+    const int end = c.first + c.cnt;
+    const int64_t* __restrict__ offsets = a.offsets + (int64_t)c.t * a.B;
+    W* __restrict__ out = static_cast<W*>(a.words[0]);
+    uint16_t* s_dig = &s_cnt[0][0];
+    const uint32_t* s_mark = reinterpret_cast<const uint32_t*>(s_w);
+    uint32_t dg[kSortPerThread];                     // rows of the lookups, then their buckets
+    auto load_rows = [&](int first) {
+        const int m = min(kSortTile, end - first);
+        const int q = opaque(wave * group_count<kPartGroup>(m) * kPartGroup * kWave + lane);
+        const uint32_t* __restrict__ idx = a.indices + first;
+        if (m == kSortTile) {
+#pragma unroll
+            for (int r = 0; r < kSortPerThread; ++r)
+                dg[r] = load_at(idx, (uint32_t)q, r * kWave);
+        } else {
+#pragma unroll
+            for (int r = 0; r < kSortPerThread; ++r)
+                dg[r] = idx[min(q + r * kWave, m - 1)];
+        }
+    };
+    load_rows(c.first);
+    s_borders.load(a, st, bits);
+    for (int i = tid; i < st.nb; i += kSortThreads)
+        s_next[i] = a.bstart[(int64_t)st.part * kMaxBuckets + i] + a.hist[(int64_t)blockIdx.x * kMaxBuckets + i];
+
+    for (int k = 0; c.first + k * kSortTile < end; ++k) {
+        const int first = c.first + k * kSortTile;
+        const int m = min(kSortTile, end - first);
+        const int groups = group_count<kPartGroup>(m), rounds = groups * kPartGroup;
+        const int p0 = wave * rounds * kWave + lane;
+        const int lo = a.tile_bag[(int)blockIdx.x * a.tiles_per_chunk + k];
+        // the next tile's first bag bounds this one's; the last tile of a chunk looks at the next chunk's first tile
+        const bool more = first + m < st.start + st.n;
+        const int hi = more ? a.tile_bag[first + m < end ? (int)blockIdx.x * a.tiles_per_chunk + k + 1
+                                                         : ((int)blockIdx.x + 1) * a.tiles_per_chunk]
+                            : a.B - 1;
+        const uint32_t carry = bags_of_positions(offsets, lo, hi, first, m, rounds, reinterpret_cast<uint32_t*>(s_w), s_wsum);
+        zero_counts(s_cnt);
+        W w[kSortPerThread];
+        uint32_t rank[kSortPerThread];
+        Borders::with_span(span, [&](auto sp) {
+            constexpr int kSpan = decltype(sp)::value;
+            const int q = opaque(p0);
+#pragma unroll
+            for (int r0 = 0; r0 < kSortPerThread; r0 += kPartGroup) {
+                if (r0 < rounds) {
+#pragma unroll
+                    for (int r = r0; r < r0 + kPartGroup; ++r) {
+                        const uint32_t row = dg[r], d = s_borders.bucket<kSpan>(row, shift, last_cell);
+                        w[r] = ((W)(row - s_borders.split[d]) << a.vb) + (W)(max(s_mark[q + r * kWave], carry) - 1u);
+                        dg[r] = d;
+                    }
+                }
+            }
+            if (m < kSortTile) {
+#pragma unroll
+                for (int r = 0; r < kSortPerThread; ++r)
+                    dg[r] = q + r * kWave < m ? dg[r] : (uint32_t)st.nb;
+            }
+        });
+        __syncthreads();
+        rank_rounds<kPartGroup>([&](int r) { return dg[r]; }, groups, digit_bits, s_cnt, rank);
+        __syncthreads();
+        uint32_t counts;
+        const uint32_t starts = digit_starts<kMaxBuckets>(s_cnt, s_wsum, counts);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int d = 2 * tid + i;
+            if (d < st.nb) {
+                const uint32_t nx = s_next[d];
+                s_delta[d] = nx - (i ? starts >> 16 : starts & 0xffffu);
+                s_next[d] = nx + (i ? counts >> 16 : counts & 0xffffu);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r0 = 0; r0 < kSortPerThread; r0 += kPartGroup)
+            if (r0 < rounds) {
+#pragma unroll
+                for (int r = r0; r < r0 + kPartGroup; ++r)
+                    rank[r] += s_cnt[wave][dg[r]];    // slot of the word in the reordered tile
+            }
+        __syncthreads();                              // the counters become the slots' digits
+#pragma unroll
+        for (int r0 = 0; r0 < kSortPerThread; r0 += kPartGroup)
+            if (r0 < rounds) {
+#pragma unroll
+                for (int r = r0; r < r0 + kPartGroup; ++r) {
+                    s_w[rank[r]] = w[r];
+                    s_dig[rank[r]] = (uint16_t)dg[r];
+                }
+            }
+        __syncthreads();
+        if (first + m < end)
+            load_rows(first + m);                     // in flight while this tile is written
+        // the words of a bucket are written together; four at a time so that the LDS reads overlap
+        for (int i0 = 0; i0 < rounds; i0 += 4) {
+            uint32_t to[4];
+            W x[4];
+            const int q = i0 * kSortThreads + tid;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                to[i] = s_dig[q + i * kSortThreads];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                to[i] = s_delta[to[i]] + (uint32_t)(q + i * kSortThreads);
+                x[i] = s_w[q + i * kSortThreads];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (q + i * kSortThreads < m)
+                    out[to[i]] = x[i];
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------- units: sort in LDS, runs
+
+// One workgroup per unit.  A unit of more than kSortTile words -- a bucket the sample undersized, or of a table with
+// more than kMaxBuckets * kSortTile lookups -- takes the same passes tile by tile through global memory.
+template <typename W>
+__global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_local_kernel(SortArgs a)
+{
+    __shared__ __align__(16) W s_w[kSortTile];
+    __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
+    __shared__ uint32_t s_run[kLocalDigits];         // units larger than a tile: next slot of every digit
+    __shared__ uint32_t s_wsum[kSortWaves];
+    __shared__ uint32_t s_heads;
+    __shared__ int s_ticket;
+    __shared__ SortUnit s_unit;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
+    const int total_units = (int)a.unit_base[a.T];
+    const W vmask = ((W)1 << a.vb) - 1;
+
+    // units are handed out one at a time (their sizes differ); the next number is asked for a unit ahead
+    if (tid == 0)
+        s_ticket = (int)atomicAdd(&a.counters->sort_ticket, 1u);
+    for (;;) {
+        __syncthreads();
+        const int u = s_ticket;
+        if (u >= total_units)
+            break;
+        if (wave == 0) {
+            const int t = find_table(a.unit_base, a.T, (uint32_t)u);
+            if (lane < 8)
+                reinterpret_cast<int*>(&s_unit)[lane] = reinterpret_cast<const int*>(&a.units[a.tables[t].slot_base + (u - (int)a.unit_base[t])])[lane];
+        }
+        if (tid == 0)
+            s_heads = 0;
+        __syncthreads();
+        if (tid == 0)
+            s_ticket = (int)atomicAdd(&a.counters->sort_ticket, 1u);
+        const int start = uniform(s_unit.start), m_all = uniform(s_unit.m), bits = uniform(s_unit.bits);
+        const uint32_t key0 = (uint32_t)uniform((int)s_unit.key0);
+        const bool large = m_all > kSortTile;
+        const int passes = (bits + 7) >> 3;
+        W* src = static_cast<W*>(a.words[0]) + start;
+        W* dst = static_cast<W*>(a.words[1]) + start;
+        int sh = a.vb;
+        for (int p = 0; p < passes; ++p) {
+            const int width = pass_width(bits, passes, p);
+            const uint32_t mask = (1u << width) - 1u;
+            if (large) {                             // first slot of every digit in the unit
+                if (tid < kLocalDigits)
+                    s_run[tid] = 0;
+                __syncthreads();
+#pragma unroll 1
+                for (int i = tid; i < m_all; i += kSortThreads)
+                    atomicAdd(&s_run[(uint32_t)(src[i] >> sh) & mask], 1u);
+                __syncthreads();
+                uint32_t tot;
+                const uint32_t ex = block_scan<kSortThreads>(tid < kLocalDigits ? s_run[tid] : 0u, s_wsum, tot);
+                if (tid < kLocalDigits)
+                    s_run[tid] = ex;
+                __syncthreads();
+            }
+#pragma unroll 1
+            for (int first = 0; first < m_all; first += kSortTile) {
+                const int m = min(kSortTile, m_all - first);
+                const int groups = group_count<kSortGroup>(m);
+                const int p0 = wave * groups * kSortGroup * kWave + lane;
+                W w[kSortPerThread];
+                zero_counts(s_cnt);
+                {
+                    const int q = opaque(p0);
+                    const W* from = src + first;
+                    if ((large || p == 0) && (wave + 1) * groups * kSortGroup * kWave <= m) {   // all of the wavefront's words
+#pragma unroll
+                        for (int r = 0; r < kSortPerThread; ++r)
+                            if (r < groups * kSortGroup)
+                                w[r] = load_at(from, (uint32_t)q, r * kWave);
+                    } else if (large || p == 0) {
+#pragma unroll
+                        for (int r = 0; r < kSortPerThread; ++r)
+                            if (r < groups * kSortGroup)
+                                w[r] = q + r * kWave < m ? from[q + r * kWave] : ~(W)0;
+                    } else {
+#pragma unroll
+                        for (int r = 0; r < kSortPerThread; ++r)
+                            if (r < groups * kSortGroup)
+                                w[r] = s_w[q + r * kWave];
+                    }
+                }
+                __syncthreads();
+                block_sort_pass<W>(w, groups, sh, width, s_w, s_cnt, s_wsum);
+                if (large) {
+                    // The tile is in digit order in s_w and the digits' last wavefront row ends where the next digit
+                    // starts: slot in the tile -> slot in the unit
+                    uint32_t counts_lo = 0, counts_hi = 0, first_lo = 0, first_hi = 0;
+                    if (2 * tid < kLocalDigits) {
+                        const uint32_t f = reinterpret_cast<const u32_alias*>(s_cnt[0])[tid];
+                        first_lo = f & 0xffffu;
+                        first_hi = f >> 16;
+                        const uint32_t f2 = 2 * tid + 2 < kLocalDigits ? s_cnt[0][2 * tid + 2] : (uint32_t)(groups * kSortGroup * kSortThreads);
+                        counts_lo = first_hi - first_lo;
+                        counts_hi = f2 - first_hi;
+                    }
+                    __syncthreads();
+                    if (2 * tid < kLocalDigits) {
+                        const uint32_t r_lo = s_run[2 * tid], r_hi = s_run[2 * tid + 1];
+                        reinterpret_cast<u32_alias*>(s_cnt)[2 * tid] = r_lo - first_lo;       // (the counters are done with)
+                        reinterpret_cast<u32_alias*>(s_cnt)[2 * tid + 1] = r_hi - first_hi;
+                        s_run[2 * tid] = r_lo + counts_lo;
+                        s_run[2 * tid + 1] = r_hi + counts_hi;
+                    }
+                    __syncthreads();
+#pragma unroll 1
+                    for (int i = tid; i < m; i += kSortThreads) {
+                        const W x = s_w[i];
+                        dst[reinterpret_cast<const u32_alias*>(s_cnt)[(uint32_t)(x >> sh) & mask] + (uint32_t)i] = x;
+                    }
+                    __syncthreads();
+                }
+            }
+            if (large) {
+                W* x = src; src = dst; dst = x;
+            }
+            sh += width;
+        }
+        // ---- keys and payloads; words that lie in LDS (sorted here) or in memory (large units, and buckets of one
+        // row, which are sorted as they are)
+        uint32_t heads = 0;
+        if (bits > 0 && !large) {
+            const int groups = group_count<kSortGroup>(m_all);
+            const int q = opaque(wave * groups * kSortGroup * kWave + lane);
+            uint32_t* keys = a.keys + start;
+            int32_t* vals = a.vals + start;
+            auto emit = [&](auto all) {
+                constexpr bool kAll = decltype(all)::value;      // the wavefront has words in every round
+#pragma unroll
+                for (int r = 0; r < kSortPerThread; ++r) {
+                    if (r < groups * kSortGroup) {
+                        const int p = q + r * kWave;
+                        const W x = s_w[p], before = s_w[r == 0 ? max(p, 1) - 1 : p - 1];
+                        const bool other = ((x ^ before) >> a.vb) != 0 || (r == 0 && p == 0);
+                        heads += (kAll || p < m_all) && other ? 1u : 0u;
+                        if (kAll || p < m_all) {
+                            store_at(keys, (uint32_t)q, r * kWave, key0 + (uint32_t)(x >> a.vb));
+                            store_at(vals, (uint32_t)q, r * kWave, (int32_t)(x & vmask));
+                        }
+                    }
+                }
+            };
+            if ((wave + 1) * groups * kSortGroup * kWave <= m_all)
+                emit(std::true_type());
+            else
+                emit(std::false_type());
+        } else {
+            if (large) {
+#pragma unroll 1
+                for (int i = tid; i < m_all; i += kSortThreads)
+                    heads += i == 0 || (src[i] >> a.vb) != (src[i - 1] >> a.vb) ? 1u : 0u;
+                __syncthreads();                     // 32-bit words lie where keys or payloads go
+            } else if (tid == 0 && !(s_unit.flags & kUnitContinued)) {
+                heads = 1;
+            }
+#pragma unroll 4
+            for (int i = tid; i < m_all; i += kSortThreads) {
+                const W x = src[i];
+                a.keys[start + i] = key0 + (uint32_t)(x >> a.vb);
+                a.vals[start + i] = (int32_t)(x & vmask);
+            }
+        }
+        heads = last_lane(wave_scan_add(heads));
+        if (lane == 0 && heads > 0)
+            atomicAdd(&s_heads, heads);
+        __syncthreads();
+        if (tid == 0) {
+            a.unit_runs[u] = s_heads;
+            atomicAdd(&a.table_runs[s_unit.t], s_heads);
+        }
+    }
+}
+
+// ---------------------------------------------------------------- small calls: all of it in one workgroup
+//
+// At most kSortTile lookups in at most kSmallBags bags: one workgroup finds every lookup's bag, sorts (linear row id,
+// bag) words in LDS and writes keys, payloads and runs.  A small call is a chain of launches of 2 to 5 us each, most
+// of them with nothing to do: 2048 lookups took 13 launches and 55 us, then three and 20 us with the kernels above.
+constexpr int kSmallBags = 1 << 15;
+
+__global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, int key_bits)
+{
+    __shared__ __align__(16) uint64_t s_w[kSortTile];
+    __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
+    __shared__ uint32_t s_wsum[kSortWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int n = a.n;
+    const int groups = group_count<kSortGroup>(n), rounds = groups * kSortGroup;
+    const int p0 = wave * rounds * kWave + lane;
+    for (int t = tid; t <= a.T; t += kSortThreads)
+        a.tstart[t] = (int)a.offsets[(int64_t)t * a.B];
+    const uint32_t* s_mark = reinterpret_cast<const uint32_t*>(s_w);
+    const uint32_t carry = bags_of_positions(a.offsets, 0, a.T * a.B - 1, 0, n, rounds, reinterpret_cast<uint32_t*>(s_w), s_wsum);
+    uint64_t w[kSortPerThread];
+    {
+        const int q = opaque(p0);
+#pragma unroll
+        for (int r = 0; r < kSortPerThread; ++r) {
+            if (r < rounds) {
+                const int p = q + r * kWave;
+                const uint32_t bag = max(s_mark[p], carry) - 1u;
+                const uint32_t t = a.T == 1 ? 0u : bag / (uint32_t)a.B;
+                w[r] = p < n ? (uint64_t)(a.row_base[t] + a.indices[p]) << 32 | (bag - t * (uint32_t)a.B) : ~0ull;
+            }
+        }
+    }
+    __syncthreads();
+    block_sort<uint64_t>(w, groups, 32, key_bits, s_w, s_cnt, s_wsum);
+    uint32_t mask = 0, mine = 0;
+    const int q = opaque(p0);
+#pragma unroll
+    for (int r = 0; r < kSortPerThread; ++r) {
+        if (r < rounds) {
+            const int p = q + r * kWave;
+            w[r] = s_w[p];
+            const bool head = p < n && (p == 0 || (uint32_t)(s_w[max(p, 1) - 1] >> 32) != (uint32_t)(w[r] >> 32));
+            mask |= (head ? 1u : 0u) << r;
+            mine += (uint32_t)__popcll(__ballot(head));
+        }
+    }
+    __syncthreads();
+    if (lane == 0)
+        s_wsum[wave] = mine;
+    __syncthreads();
+    uint32_t run = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < kSortWaves; ++i) {
+        run += i < wave ? s_wsum[i] : 0u;
+        total += s_wsum[i];
+    }
+#pragma unroll
+    for (int r = 0; r < kSortPerThread; ++r) {
+        if (r < rounds) {
+            const int p = q + r * kWave;
+            const uint64_t hm = __ballot((mask >> r & 1u) != 0u);
+            const uint32_t x = run + __builtin_amdgcn_mbcnt_hi((uint32_t)(hm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hm, 0u));
+            if (p < n) {
+                a.keys[p] = (uint32_t)(w[r] >> 32);
+                a.vals[p] = (int32_t)w[r];
+                if ((p & (kSpanUnit - 1)) == 0)
+                    a.unit_first_run[p / kSpanUnit] = (int32_t)x;
+                if (mask >> r & 1u) {
+                    a.unique_keys[x] = (uint32_t)(w[r] >> 32);
+                    a.seg_offsets[x] = p;
+                }
+            }
+            run += (uint32_t)__popcll(hm);
+        }
+    }
+    if (tid == 0) {
+        a.seg_offsets[total] = n;
+        a.unit_first_run[(n + kSpanUnit - 1) / kSpanUnit] = (int32_t)total;
+        a.counters->num_unique = (int64_t)total;
+    }
+}
+
+// Runs: a run starts where the key changes; a unit's first run is the runs of the tables before its own plus those
+// of the units before it in its table, so a workgroup sums those counts itself.  A thread owns 16 consecutive
+// positions (one count per thread to scan instead of a ballot per 64 positions); the runs are collected in LDS and
+// written together.
+constexpr int kRunThreads = 256;
+constexpr int kRunPer = 16;
+constexpr int kRunTile = kRunThreads * kRunPer;
+__global__ __launch_bounds__(kRunThreads) void sort_runs_kernel(SortArgs a)
+{
+    __shared__ uint32_t s_key[kRunTile];
+    __shared__ int32_t s_pos[kRunTile];
+    __shared__ uint32_t s_wsum[2][kRunThreads / kWave];
+    const int tid = threadIdx.x;
+    const int total_units = (int)a.unit_base[a.T];
+    for (int u = blockIdx.x; u < total_units; u += gridDim.x) {
+        const int t = find_table(a.unit_base, a.T, (uint32_t)u);
+        const int u0 = (int)a.unit_base[t];
+        const SortUnit un = a.units[a.tables[t].slot_base + (u - u0)];
+        const uint32_t unit_runs = a.unit_runs[u];
+        uint32_t part = 0, run;
+        for (int i = tid; i < t; i += kRunThreads)
+            part += a.table_runs[i];
+        for (int i = u0 + tid; i < u; i += kRunThreads)
+            part += a.unit_runs[i];
+        __syncthreads();
+        (void)block_scan<kRunThreads>(part, s_wsum[0], run);
+        if (tid == 0 && u == total_units - 1) {
+            const uint32_t all = run + unit_runs;
+            a.seg_offsets[all] = a.n;
+            a.unit_first_run[(a.n + kSpanUnit - 1) / kSpanUnit] = (int32_t)all;
+            a.counters->num_unique = (int64_t)all;
+        }
+        if (un.bits == 0) {                          // one row: at most one run, and nothing to compare
+            if (tid == 0 && unit_runs > 0) {
+                a.unique_keys[run] = un.key0;
+                a.seg_offsets[run] = un.start;
+            }
+            const int first = (un.start + kSpanUnit - 1) / kSpanUnit, last = (un.start + un.m - 1) / kSpanUnit;
+            for (int i = first + tid; i <= last; i += kRunThreads)
+                a.unit_first_run[i] = (int32_t)(run + (i * kSpanUnit > un.start ? unit_runs : 0u));
+            continue;
+        }
+        for (int first = 0; first < un.m; first += kRunTile) {
+            const int m = min(kRunTile, un.m - first);
+            const int g0 = un.start + first + tid * kRunPer;
+            const int mine = min(max(m - tid * kRunPer, 0), kRunPer);
+            uint32_t key[kRunPer], before = 0, mask = 0;
+            if (mine == kRunPer) {
+#pragma unroll
+                for (int i = 0; i < kRunPer; ++i)    // (combined into 16-byte loads)
+                    key[i] = a.keys[g0 + i];
+            } else {
+#pragma unroll
+                for (int i = 0; i < kRunPer; ++i)
+                    key[i] = i < mine ? a.keys[g0 + i] : 0u;
+            }
+            if (mine > 0 && first + tid > 0)
+                before = a.keys[g0 - 1];
+#pragma unroll
+            for (int i = 0; i < kRunPer; ++i)
+                mask |= (key[i] != (i == 0 ? before : key[i - 1]) ? 1u : 0u) << i;
+            if (first + tid == 0)
+                mask |= 1u;                          // borders of buckets are borders of runs
+            mask &= (1u << mine) - 1u;
+            uint32_t tile_runs;
+            uint32_t at = block_scan<kRunThreads>((uint32_t)__popc(mask), s_wsum[1], tile_runs);
+            // runs before the first position of this thread's that starts a span unit
+            const int k = (0 - g0) & (kSpanUnit - 1);
+            if (k < mine)
+                a.unit_first_run[(g0 + k) / kSpanUnit] = (int32_t)(run + at + (uint32_t)__popc(mask & ((1u << k) - 1u)));
+#pragma unroll
+            for (int i = 0; i < kRunPer; ++i) {
+                if (mask >> i & 1u) {
+                    s_key[at] = key[i];
+                    s_pos[at] = g0 + i;
+                    ++at;
+                }
+            }
+            __syncthreads();
+            for (int i = tid; i < (int)tile_runs; i += kRunThreads) {
+                a.unique_keys[run + i] = s_key[i];
+                a.seg_offsets[run + i] = s_pos[i];
+            }
+            run += tile_runs;
+            __syncthreads();
+        }
+    }
+}
+
+}  // namespace tbe

@@ -1,0 +1,105 @@
+"""GPU test of every path of the backward's sort: the one-workgroup sort of small calls and its size limits, buckets of
+one row, crowded row ids, tables cut by the range of a packed word, 64-bit words, a bucket larger than a tile (the
+sample is made to miss its rows), more tables than lookups, empty tables and empty bags.  Keys, payloads, unique keys
+and segment offsets must equal a stable argsort by (table, row) bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2104_05158_amd import tbe
+
+pytestmark = pytest.mark.gpu
+
+TILE = 8192
+
+
+def _check(dev, rows, batch, lens, idx, what):
+    """lens [T * batch] bag lengths, idx the lookups, table-major"""
+    T = len(rows)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n = int(off[-1])
+    assert idx.size == n
+    bag = np.repeat(np.arange(T * batch), lens)
+    base = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    key = base[bag // batch] + idx
+    order = np.argsort(key, kind="stable")
+    ref_key, ref_val = key[order].astype(np.uint32), (bag % batch)[order].astype(np.int32)
+    head = np.flatnonzero(np.concatenate([[True], ref_key[1:] != ref_key[:-1]]))
+    print(f"{what}: n={n} T={T} batch={batch} runs={head.size}", flush=True)
+    op = tbe.TableBatchedEmbeddingBags(rows, [4] * T, 0, batch, n, device=dev)
+    d_idx, d_off = torch.from_numpy(idx.astype(np.int32)).to(dev), torch.from_numpy(off).to(dev)
+    for _ in range(2):                                   # the second sort starts from the first one's workspace
+        op.backward_sort(d_idx, d_off, batch)
+    art = op.artifacts()
+    assert art["num_unique"] == head.size
+    assert np.array_equal(art["sorted_keys"].cpu().numpy().view(np.uint32), ref_key)
+    assert np.array_equal(art["sorted_vals"].cpu().numpy(), ref_val)
+    assert np.array_equal(art["unique_keys"].cpu().numpy().view(np.uint32), ref_key[head])
+    assert np.array_equal(art["seg_offsets"].cpu().numpy(), np.concatenate([head, [n]]))
+    op.close()
+
+
+def _lens(rng, bags, n):
+    return np.bincount(rng.integers(0, bags, n), minlength=bags)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1024, 1025, TILE - 1, TILE, TILE + 1, 3 * TILE])
+@pytest.mark.parametrize("tables,batch", [(1, 7), (3, 100), (40, 1000)])
+def test_sizes_around_the_one_workgroup_sort(gpu_device, n, tables, batch):
+    rng = np.random.default_rng(n + tables)
+    rows = rng.integers(1, 5000, tables)
+    lens = _lens(rng, tables * batch, n)                 # 40 tables x 1000 bags is beyond the small sort's bags
+    t = np.repeat(np.arange(tables), lens.reshape(tables, batch).sum(1))
+    _check(gpu_device, rows, batch, lens, (rng.random(n) * rows[t]).astype(np.int64), "small")
+
+
+CASES = {
+    # name: (rows, batch, lookups per table, ids)
+    "hot_rows": ([100_000, 3], 300, [200_000, 50_000], "zipf"),
+    "one_row": ([1, 1_000_000], 50, [90_000, 30_000], "first"),
+    "crowded_low_ids": ([10_000_000], 500, [300_000], "crowded"),
+    "tall_tables_large_batch": ([10_000_000, 70_000, 33_000_000], 65536, [70_000, 9_000, 100_000], "uniform"),
+    "words_of_64_bits": ([34_000_000, 500], 65536, [120_000, 40_000], "zipf"),
+    "batch_beyond_16_bits": ([50_000, 20], 70_001, [250_000, 100_000], "zipf"),
+    "empty_tables": ([50, 300_000, 7, 120, 900_000], 4096, [0, 150_000, 0, 1, 20_000], "uniform"),
+    "many_tables": ([900] * 600, 24, [40] * 600, "uniform"),
+}
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_paths_of_the_partition(gpu_device, case):
+    rows, batch, per_table, ids = CASES[case]
+    rng = np.random.default_rng(len(case))
+    lens = np.concatenate([_lens(rng, batch, n) for n in per_table])
+    parts = []
+    for h, n in zip(rows, per_table):
+        if ids == "uniform":
+            parts.append(rng.integers(0, h, n))
+        elif ids == "zipf":
+            parts.append(np.minimum(rng.zipf(1.2, n) * 2_654_435_761 % h, h - 1))
+        elif ids == "crowded":
+            parts.append(rng.integers(0, min(h, 3000), n))
+        else:
+            parts.append(np.zeros(n, np.int64))
+    _check(gpu_device, rows, batch, lens, np.concatenate(parts), case)
+
+
+def _mix(x):
+    x = np.uint32(x)
+    with np.errstate(over="ignore"):
+        x ^= x >> np.uint32(16); x *= np.uint32(0x7feb352d)
+        x ^= x >> np.uint32(15); x *= np.uint32(0x846ca68b)
+    return int(x ^ (x >> np.uint32(16)))
+
+
+@pytest.mark.parametrize("n", [20_000, 90_000])
+def test_bucket_larger_than_a_tile(gpu_device, n):
+    # the sampled lookups hit rows from 1000 on, all others the 1000 rows below: one bucket holds nearly everything
+    rng = np.random.default_rng(n)
+    want = -(-n // 1024)
+    s = want * 16
+    stretch = (n << 32) // s
+    at = [min((stretch * (i * 256 + (_mix(i) & 255))) >> 40, n - 1) for i in range(s)]
+    idx = rng.integers(0, 1000, n)
+    idx[at] = rng.integers(1000, 200_000, s)
+    _check(gpu_device, [200_000], 611, _lens(rng, 611, n), idx, "large bucket")
