@@ -81,6 +81,19 @@ tbe_status_t launch_status()
     return hipGetLastError() == hipSuccess ? TBE_OK : TBE_ERR_HIP;
 }
 
+// offsets[0..n] = exclusive prefix sum of lengths[0..n); the tiles' totals are in block_sums
+tbe_status_t enqueue_apply(const int32_t* lengths, int64_t n, int64_t* offsets, int64_t* block_sums, hipStream_t st)
+{
+    const int nb = (int)ceil_div(n, kScanTile);
+    if (nb <= kScanSums) {
+        hipLaunchKernelGGL(scan64_apply_kernel<kBeforeSums>, dim3(nb), dim3(kThreads), 0, st, lengths, block_sums, offsets, n);
+    } else {
+        hipLaunchKernelGGL(scan64_top_kernel, dim3(1), dim3(kThreads), 0, st, block_sums, nb);
+        hipLaunchKernelGGL(scan64_apply_kernel<kBeforePrefix>, dim3(nb), dim3(kThreads), 0, st, lengths, block_sums, offsets, n);
+    }
+    return launch_status();
+}
+
 // offsets[0..n] = exclusive prefix sum of lengths[0..n)
 tbe_status_t enqueue_scan(const int32_t* lengths, int64_t n, int64_t* offsets, int64_t* block_sums, hipStream_t st)
 {
@@ -89,10 +102,12 @@ tbe_status_t enqueue_scan(const int32_t* lengths, int64_t n, int64_t* offsets, i
         return launch_status();
     }
     const int nb = (int)ceil_div(n, kScanTile);
+    if (nb <= kScanSelf) {
+        hipLaunchKernelGGL(scan64_apply_kernel<kBeforeSelf>, dim3(nb), dim3(kThreads), 0, st, lengths, block_sums, offsets, n);
+        return launch_status();
+    }
     hipLaunchKernelGGL(scan64_reduce_kernel, dim3(nb), dim3(kThreads), 0, st, lengths, block_sums, n);
-    hipLaunchKernelGGL(scan64_top_kernel, dim3(1), dim3(kThreads), 0, st, block_sums, nb);
-    hipLaunchKernelGGL(scan64_apply_kernel, dim3(nb), dim3(kThreads), 0, st, lengths, block_sums, offsets, n);
-    return launch_status();
+    return enqueue_apply(lengths, n, offsets, block_sums, st);
 }
 
 }  // namespace
@@ -154,26 +169,25 @@ tbe_status_t tbe_permute_wtb_to_twb(int32_t W, int32_t T, int32_t B, const int32
     const Scratch s = carve(d_scratch, n);
     if (n == 0)
         return enqueue_scan(d_lengths_out, 0, d_offsets_out, s.block_sums, st);
-    rc = enqueue_scan(d_lengths_in, n, s.offsets_in, s.block_sums, st);
-    if (rc != TBE_OK)
-        return rc;
-    const int vec = B % 4 == 0 ? 4 : 1;
-    const int blocks_per_row = (int)ceil_div(B, kThreads * vec);
-    const int64_t grid = (int64_t)W * T * blocks_per_row;
-    if (grid > kMaxCount)
-        return TBE_ERR_UNSUPPORTED;
-    if (vec == 4)
-        hipLaunchKernelGGL(permute_lengths_kernel<4>, dim3((unsigned)grid), dim3(kThreads), 0, st, d_lengths_in,
-                           d_lengths_out, W, T, B, blocks_per_row);
+    const int nb = (int)ceil_div(n, kScanTile);
+    if (B % 4 == 0)
+        hipLaunchKernelGGL(permute_lengths_kernel<4>, dim3(nb), dim3(kThreads), 0, st, d_lengths_in, d_lengths_out,
+                           s.block_sums, W, T, B, (int32_t)n);
     else
-        hipLaunchKernelGGL(permute_lengths_kernel<1>, dim3((unsigned)grid), dim3(kThreads), 0, st, d_lengths_in,
-                           d_lengths_out, W, T, B, blocks_per_row);
-    rc = enqueue_scan(d_lengths_out, n, d_offsets_out, s.block_sums, st);
+        hipLaunchKernelGGL(permute_lengths_kernel<1>, dim3(nb), dim3(kThreads), 0, st, d_lengths_in, d_lengths_out,
+                           s.block_sums, W, T, B, (int32_t)n);
+    rc = enqueue_apply(d_lengths_out, n, d_offsets_out, s.block_sums, st);
     if (rc != TBE_OK)
         return rc;
     if (num_indices > 0) {
+        // The workgroups of the copy find the starts of their one to three input blocks themselves while there are few
+        // blocks, of half a tile or more on average; otherwise one more launch (3 us) writes all starts.
+        const int64_t rows = (int64_t)W * T;
+        const bool self = rows <= kCopyLdsRows && num_indices / rows >= kCopyTile / 2;
+        if (!self)
+            hipLaunchKernelGGL(permute_starts_kernel, dim3(1), dim3(kThreads), 0, st, d_offsets_out, s.offsets_in, W, T, B);
         hipLaunchKernelGGL(permute_indices_kernel, dim3((unsigned)ceil_div(num_indices, kCopyTile)), dim3(kThreads),
-                           0, st, d_indices_in, s.offsets_in, d_offsets_out, d_indices_out, W, T, B, num_indices);
+                           0, st, d_indices_in, self ? nullptr : s.offsets_in, d_offsets_out, d_indices_out, W, T, B, num_indices);
     }
     return launch_status();
 }

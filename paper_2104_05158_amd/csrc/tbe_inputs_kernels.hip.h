@@ -22,10 +22,13 @@ constexpr int kMaxShards = 1024;
 
 // ---------------------------------------------------------------- lengths -> offsets (Section 7.1)
 //
-// Exclusive prefix sum of int32 lengths into int64 offsets in three launches: per-tile totals, one
-// workgroup scans the totals, every tile rescans itself with its base.  Inside a tile a thread
-// owns one int4 of each of kScanGroups consecutive 1024-length groups, so loads are 16 bytes per
-// lane and contiguous across the wavefront.
+// Exclusive prefix sum of int32 lengths into int64 offsets, a tile of kScanTile lengths per workgroup.  Inside a
+// tile a thread owns one int4 of each of kScanGroups consecutive 1024-length groups, so loads are 16 bytes per lane
+// and contiguous across the wavefront.  How a tile gets the sum of the lengths before it goes by the number of tiles:
+//   up to kScanSelf     it adds them up itself: one launch (256 lengths: 3.0 us instead of 6.8 in three launches)
+//   up to kScanSums     a first launch writes the tiles' totals and every workgroup adds up those before its own
+//   more                a single workgroup scans the totals in between (at 32 KiB of totals per workgroup the
+//                       summing begins to cost more than that launch)
 
 __device__ __forceinline__ int64_t block_exclusive_scan64(int64_t v, int64_t* s_wave /*[4]*/, int64_t& block_total)
 {
@@ -52,6 +55,52 @@ __device__ __forceinline__ int64_t block_exclusive_scan64(int64_t v, int64_t* s_
     block_total = tot;
     __syncthreads();
     return woff + incl - v;
+}
+
+// sum over the workgroup, to all threads (s_wave must not be in use; one barrier)
+__device__ __forceinline__ int64_t block_sum64(int64_t v, int64_t* s_wave)
+{
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1)
+        v += __shfl_xor(v, o);
+    if ((threadIdx.x & (kWave - 1)) == 0)
+        s_wave[threadIdx.x >> 6] = v;
+    __syncthreads();
+    int64_t tot = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / kWave; ++w)
+        tot += s_wave[w];
+    return tot;
+}
+
+// Inclusive sums over the wavefront of kScanGroups values at once, each below 2^25 in every lane if `small`: then a
+// 32-bit scan by data-parallel moves does, otherwise 64-bit shuffles.
+__device__ __forceinline__ void wave_scan_groups(int64_t (&v)[kScanGroups], bool small)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    if (small) {
+#pragma unroll
+        for (int g = 0; g < kScanGroups; ++g) {
+            int x = (int)v[g];
+            x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8
+            x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+            x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+            x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+            x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15, 31
+            x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+            v[g] = (int64_t)x;
+        }
+        return;
+    }
+#pragma unroll
+    for (int g = 0; g < kScanGroups; ++g) {
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int64_t up = __shfl_up(v[g], o);
+            if (lane >= o)
+                v[g] += up;
+        }
+    }
 }
 
 __device__ __forceinline__ int4 load_lengths4(const int32_t* __restrict__ lengths, int64_t i, int64_t n)
@@ -109,21 +158,63 @@ __global__ __launch_bounds__(kThreads) void scan64_top_kernel(int64_t* __restric
     }
 }
 
+constexpr int kScanSelf = 8;
+constexpr int kScanSums = 4096;
+enum { kBeforeSelf = 0, kBeforeSums = 1, kBeforePrefix = 2 };   // where the sum of the lengths before a tile comes from
+
+template <int BEFORE>
 __global__ __launch_bounds__(kThreads) void scan64_apply_kernel(const int32_t* __restrict__ lengths,
                                                                 const int64_t* __restrict__ block_sums,
                                                                 int64_t* __restrict__ offsets, int64_t n)
 {
-    __shared__ int64_t s_wave[kThreads / kWave];
+    constexpr int kWaves = kThreads / kWave;
+    __shared__ int64_t s_wave[kWaves], s_tot[kScanGroups][kWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int64_t tile = (int64_t)blockIdx.x * kScanTile;
-    int64_t carry = block_sums[blockIdx.x];
+    int4 v[kScanGroups];
+    int64_t s[kScanGroups], incl[kScanGroups];
+    int most = 0;
+#pragma unroll
+    for (int g = 0; g < kScanGroups; ++g)
+        v[g] = load_lengths4(lengths, tile + g * (kThreads * 4) + threadIdx.x * 4, n);
+    int64_t before = 0;
+    if (BEFORE == kBeforePrefix) {
+        before = block_sums[blockIdx.x];
+    } else {
+        if (BEFORE == kBeforeSelf) {
+            for (int64_t i = threadIdx.x * 4; i < tile; i += kThreads * 4) {     // whole tiles: no ragged end
+                const int4 x = *reinterpret_cast<const int4*>(lengths + i);
+                before += (int64_t)x.x + x.y + x.z + x.w;
+            }
+        } else {
+            for (int i = threadIdx.x; i < (int)blockIdx.x; i += kThreads)
+                before += block_sums[i];
+        }
+        before = block_sum64(before, s_wave);
+    }
 #pragma unroll
     for (int g = 0; g < kScanGroups; ++g) {
+        s[g] = incl[g] = (int64_t)v[g].x + v[g].y + v[g].z + v[g].w;
+        most = max(max(most, v[g].x), max(v[g].y, max(v[g].z, v[g].w)));
+    }
+    wave_scan_groups(incl, __ballot(most >= (1 << 23)) == 0ull);
+    if (lane == kWave - 1) {
+#pragma unroll
+        for (int g = 0; g < kScanGroups; ++g)
+            s_tot[g][wave] = incl[g];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kScanGroups; ++g) {
+        int64_t o0 = before + incl[g] - s[g];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const int64_t c = s_tot[g][w];
+            o0 += w < wave ? c : 0;
+            before += c;
+        }
         const int64_t i = tile + g * (kThreads * 4) + threadIdx.x * 4;
-        const int4 v = load_lengths4(lengths, i, n);
-        const int64_t s = (int64_t)v.x + v.y + v.z + v.w;
-        int64_t tot;
-        const int64_t o0 = carry + block_exclusive_scan64(s, s_wave, tot);
-        const int64_t o1 = o0 + v.x, o2 = o1 + v.y, o3 = o2 + v.z, o4 = o3 + v.w;
+        const int64_t o1 = o0 + v[g].x, o2 = o1 + v[g].y, o3 = o2 + v[g].z, o4 = o3 + v[g].w;
         if (i + 4 <= n) {
             // offsets + i is 32-byte aligned (i is a multiple of 4)
             *reinterpret_cast<longlong2*>(offsets + i) = make_longlong2(o0, o1);
@@ -136,18 +227,6 @@ __global__ __launch_bounds__(kThreads) void scan64_apply_kernel(const int32_t* _
             if (i + 2 < n) offsets[i + 2] = o2; else if (i + 2 == n) offsets[n] = o2;
             if (i + 3 == n) offsets[n] = o3;
         }
-        carry += tot;
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t value)
-{
-    const int64_t i = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
-    if (i + 4 <= n) {
-        *reinterpret_cast<int4*>(p + i) = make_int4(value, value, value, value);
-    } else {
-        for (int64_t k = i; k < n; ++k)
-            p[k] = value;
     }
 }
 
@@ -156,25 +235,63 @@ __global__ void write_zero_offset_kernel(int64_t* __restrict__ offsets) { offset
 // ---------------------------------------------------------------- (W,T,B) -> (T,W,B) permute (Section 7.1)
 //
 // Bags (w,t,0..B-1) are consecutive on both sides, so the lengths move in rows of B and the indices
-// move as W*T contiguous blocks whose borders are offsets[q*B].
+// move as W*T contiguous blocks whose borders are offsets[q*B].  The blocks of the input have the same sizes, so
+// their starts follow from the output's offsets alone and the input's bags need no prefix sum of their own.
 
-// One workgroup per 256*VEC bags of one output row q = t*W + w; VEC = 4 (16-byte accesses) needs B % 4 == 0.
+// One tile of kScanTile bags of the output per workgroup: moves their lengths and writes the tile's total.
+// VEC = 4 (16-byte accesses) needs B % 4 == 0.
 template <int VEC>
 __global__ __launch_bounds__(kThreads) void permute_lengths_kernel(const int32_t* __restrict__ lengths_in,
-                                                                   int32_t* __restrict__ lengths_out, int32_t W,
-                                                                   int32_t T, int32_t B, int32_t blocks_per_row)
+                                                                   int32_t* __restrict__ lengths_out,
+                                                                   int64_t* __restrict__ block_sums, int32_t W,
+                                                                   int32_t T, int32_t B, int32_t n)
 {
-    const int q = blockIdx.x / blocks_per_row;
-    const int b = ((blockIdx.x - q * blocks_per_row) * kThreads + threadIdx.x) * VEC;
-    if (b >= B)
-        return;
-    const int t = q / W;
-    const int w = q - t * W;
-    const int64_t dst = (int64_t)q * B + b, src = ((int64_t)w * T + t) * B + b;
-    if (VEC == 4)
-        *reinterpret_cast<int4*>(lengths_out + dst) = *reinterpret_cast<const int4*>(lengths_in + src);
-    else
-        lengths_out[dst] = lengths_in[src];
+    __shared__ int64_t s_wave[kThreads / kWave];
+    constexpr int kSteps = kScanTile / (kThreads * VEC);
+    const int64_t tile = (int64_t)blockIdx.x * kScanTile;
+    int64_t sum = 0;
+#pragma unroll
+    for (int k = 0; k < kSteps; ++k) {
+        const int64_t i = tile + (int64_t)(k * kThreads + (int)threadIdx.x) * VEC;
+        if (i >= n)
+            continue;
+        const int q = (int)i / B, b = (int)i - q * B;
+        const int t = q / W, w = q - t * W;
+        const int64_t src = ((int64_t)w * T + t) * B + b;
+        if (VEC == 4) {
+            const int4 v = *reinterpret_cast<const int4*>(lengths_in + src);
+            *reinterpret_cast<int4*>(lengths_out + i) = v;
+            sum += (int64_t)v.x + v.y + v.z + v.w;
+        } else {
+            const int32_t v = lengths_in[src];
+            lengths_out[i] = v;
+            sum += v;
+        }
+    }
+    sum = block_sum64(sum, s_wave);
+    if (threadIdx.x == 0)
+        block_sums[blockIdx.x] = sum;
+}
+
+// one workgroup: first position of every input block (input order (w, t)), from the output's offsets
+__global__ __launch_bounds__(kThreads) void permute_starts_kernel(const int64_t* __restrict__ offsets_out,
+                                                                  int64_t* __restrict__ starts, int32_t W, int32_t T, int32_t B)
+{
+    __shared__ int64_t s_wave[kThreads / kWave];
+    int64_t carry = 0;
+    for (int base = 0; base < W * T; base += kThreads) {
+        const int p = base + threadIdx.x;
+        int64_t size = 0;
+        if (p < W * T) {
+            const int64_t q = (int64_t)(p % T) * W + p / T;
+            size = offsets_out[(q + 1) * B] - offsets_out[q * B];
+        }
+        int64_t tot;
+        const int64_t ex = block_exclusive_scan64(size, s_wave, tot);
+        if (p < W * T)
+            starts[p] = carry + ex;
+        carry += tot;
+    }
 }
 
 // last q in [lo, hi] with offsets[q*B] <= p   (offsets[lo*B] <= p is given)
@@ -190,36 +307,75 @@ __device__ __forceinline__ int find_block(const int64_t* __restrict__ offsets, i
     return lo;
 }
 
+// the same among all `rows` blocks for a whole wavefront: 64 borders per step
+__device__ __forceinline__ int find_block_wave(const int64_t* __restrict__ offsets, int64_t B, int rows, int64_t p)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    int lo = 0, n = rows;
+    while (n > 1) {
+        const int step = (n + kWave - 1) / kWave;
+        const int i = lane * step;
+        const uint64_t le = __ballot(i < n && offsets[(int64_t)(lo + min(i, n - 1)) * B] <= p);
+        const int k = (__popcll(le) - 1) * step;
+        lo += k;
+        n = min(step, n - k);
+    }
+    return lo;
+}
+
 // Every workgroup copies kCopyTile consecutive OUTPUT positions.  The output rows the tile touches
 // are bracketed once per workgroup; when they are few (the usual case: a row holds B bags) their
 // borders and source shifts are staged in LDS, so a position costs a short LDS search, one load and
-// one store, all loads of a thread issued before its stores.
-constexpr int kCopyLdsRows = 64;
+// one store, all loads of a thread issued before its stores.  starts: first position of every input block, or null
+// (at most kCopyLdsRows rows): then the workgroup sums the sizes of the blocks before each of its rows itself.
+constexpr int kCopyLdsRows = 256;
 __global__ __launch_bounds__(kThreads) void permute_indices_kernel(const int32_t* __restrict__ indices_in,
-                                                                   const int64_t* __restrict__ offsets_in,
+                                                                   const int64_t* __restrict__ starts,
                                                                    const int64_t* __restrict__ offsets_out,
                                                                    int32_t* __restrict__ indices_out, int32_t W,
                                                                    int32_t T, int32_t B, int64_t n)
 {
     __shared__ int s_q[2];
+    __shared__ int64_t s_wave[2][kThreads / kWave];
     __shared__ int64_t s_start[kCopyLdsRows];   // first output position of row q_lo + i
     __shared__ int64_t s_shift[kCopyLdsRows];   // source position minus output position inside that row
     const int64_t tile = (int64_t)blockIdx.x * kCopyTile;
     const int64_t tile_end = min(tile + kCopyTile, n);
     const int rows = W * T;
-    if (threadIdx.x < 2)
-        s_q[threadIdx.x] = find_block(offsets_out, B, 0, rows - 1, threadIdx.x == 0 ? tile : tile_end - 1);
+    if (threadIdx.x < 2 * kWave) {
+        const int q = find_block_wave(offsets_out, B, rows, threadIdx.x < kWave ? tile : tile_end - 1);
+        if ((threadIdx.x & (kWave - 1)) == 0)
+            s_q[threadIdx.x >> 6] = q;
+    }
     __syncthreads();
     const int q_lo = s_q[0], q_hi = s_q[1];
     const int nrows = q_hi - q_lo + 1;
     const bool staged = nrows <= kCopyLdsRows;
-    if (staged && (int)threadIdx.x < nrows) {
-        const int q = q_lo + threadIdx.x;
-        const int t = q / W;
-        const int w = q - t * W;
-        const int64_t start = offsets_out[(int64_t)q * B];
-        s_start[threadIdx.x] = start;
-        s_shift[threadIdx.x] = offsets_in[((int64_t)w * T + t) * B] - start;
+    if (starts != nullptr) {
+        if (staged && (int)threadIdx.x < nrows) {
+            const int q = q_lo + threadIdx.x;
+            const int t = q / W;
+            const int w = q - t * W;
+            const int64_t start = offsets_out[(int64_t)q * B];
+            s_start[threadIdx.x] = start;
+            s_shift[threadIdx.x] = starts[(int64_t)w * T + t] - start;
+        }
+    } else {
+        for (int q = q_lo; q <= q_hi; ++q) {
+            const int t = q / W;
+            const int w = q - t * W;
+            int64_t sum = 0;
+            for (int p = threadIdx.x; p < w * T + t; p += kThreads) {
+                const int64_t o = (int64_t)(p % T) * W + p / T;
+                sum += offsets_out[(o + 1) * B] - offsets_out[o * B];
+            }
+            sum = block_sum64(sum, s_wave[q & 1]);
+            if (threadIdx.x == 0) {
+                const int64_t start = offsets_out[(int64_t)q * B];
+                s_start[q - q_lo] = start;
+                s_shift[q - q_lo] = sum - start;
+            }
+        }
     }
     __syncthreads();
     int64_t src[kCopyPerThread];
@@ -240,7 +396,7 @@ __global__ __launch_bounds__(kThreads) void permute_indices_kernel(const int32_t
             const int q = find_block(offsets_out, B, q_lo, q_hi, p);
             const int t = q / W;
             const int w = q - t * W;
-            src[i] = offsets_in[((int64_t)w * T + t) * B] + (p - offsets_out[(int64_t)q * B]);
+            src[i] = starts[(int64_t)w * T + t] + (p - offsets_out[(int64_t)q * B]);
         }
     }
     int32_t v[kCopyPerThread];
