@@ -213,28 +213,45 @@ tbe_status_t tbe_bucketize_rowwise(int32_t T, int32_t B, int32_t W, const int64_
     const Scratch s = carve(d_scratch, n_out);
     if (n_out == 0)
         return enqueue_scan(d_lengths_out, 0, d_offsets_out, s.block_sums, st);
-    int wbits = 0;
-    while ((1 << wbits) < W)
-        ++wbits;
-    // bags per workgroup: the LDS count table holds W * nbags <= 8192 entries; small batches get
-    // fewer bags per workgroup so that the grid still fills the chip
-    int nbags = std::min<int>(kBuckMaxBags, 8192 / W);
-    while (nbags > 8 && n_in / nbags < 2048)
-        nbags >>= 1;
-    const unsigned grid = (unsigned)ceil_div(n_in, nbags);
-    hipLaunchKernelGGL(bucketize_count_kernel, dim3(grid), dim3(kThreads), 0, st, d_rows, d_indices, d_offsets,
-                       d_lengths_out, T, B, W, (int32_t)n_in, nbags);
+    // Bags per workgroup, all of one table, a power of two: the LDS count table holds W * nbags <= 8192 entries; small
+    // batches get fewer bags per workgroup so that the grid still fills the chip
+    int lg = 0;
+    while ((2 << lg) <= std::min(kBuckMaxBags, 8192 / W))
+        ++lg;
+    while (lg > 3 && (n_in >> lg) < 2048)
+        --lg;
+    const int nbags = 1 << lg;
+    const int per_table = (int)ceil_div(B, nbags);
+    const int num_items = T * per_table;                  // at most T * B
+    const unsigned grid = (unsigned)std::min(num_items, 1 << 20);
+    hipLaunchKernelGGL(bucketize_count_kernel, dim3(grid), dim3(kThreads), sizeof(int32_t) * W * nbags, st, d_rows,
+                       d_indices, d_offsets, d_lengths_out, T, B, W, lg, per_table, num_items);
     rc = enqueue_scan(d_lengths_out, n_out, d_offsets_out, s.block_sums, st);
     if (rc != TBE_OK)
         return rc;
     if (num_indices > 0) {
-        if (W <= 32)
-            hipLaunchKernelGGL(bucketize_place_kernel<32>, dim3(grid), dim3(kThreads), 0, st, d_rows, d_indices,
-                               d_offsets, d_offsets_out, d_indices_out, T, B, W, wbits, (int32_t)n_in, nbags);
+        auto place = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, st, d_rows, d_indices, d_offsets, d_offsets_out,
+                               d_indices_out, T, B, W, nbags, per_table, num_items);
+        };
+        if (W <= 2)
+            place(bucketize_place_kernel<1>);
+        else if (W <= 4)
+            place(bucketize_place_kernel<2>);
+        else if (W <= 8)
+            place(bucketize_place_kernel<3>);
+        else if (W <= 16)
+            place(bucketize_place_kernel<4>);
+        else if (W <= 32)
+            place(bucketize_place_kernel<5>);
+        else if (W <= 64)
+            place(bucketize_place_kernel<6>);
+        else if (W <= 128)
+            place(bucketize_place_kernel<7>);
+        else if (W <= 256)
+            place(bucketize_place_kernel<8>);
         else
-            hipLaunchKernelGGL(bucketize_place_kernel<kMaxShards>, dim3(grid), dim3(kThreads), 0, st, d_rows,
-                               d_indices, d_offsets, d_offsets_out, d_indices_out, T, B, W, wbits, (int32_t)n_in,
-                               nbags);
+            place(bucketize_place_kernel<10>);
     }
     return launch_status();
 }

@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace tbe_in {
 
 constexpr int kWave = 64;
@@ -418,58 +420,51 @@ __global__ __launch_bounds__(kThreads) void permute_indices_kernel(const int32_t
 // FILTER of the input stream: the elements of shard w, in input order.  So bucketize is one stable
 // multi-way split of the index stream by shard, plus per-(shard, bag) counts:
 //
-//   pass 1 (count):  a workgroup owns `nbags` consecutive input bags, walks their positions with
-//                    coalesced loads and counts (shard, bag) pairs with integer LDS atomics; the
-//                    counts go out as rows of lengths_out (consecutive b for each shard).
+//   pass 1 (count):  a workgroup owns `nbags` consecutive bags of ONE table, walks their positions and counts
+//                    (shard, bag) pairs with integer LDS atomics; the counts go out as rows of lengths_out
+//                    (consecutive b for each shard).
 //   prefix sum:      lengths_out -> offsets_out (the scan kernels above).
 //   pass 2 (place):  the same bags per workgroup.  offsets_out at the workgroup's first bag is,
 //                    for every shard, exactly where the workgroup's elements of that shard start.
 //                    Positions are handled in sub-tiles: ballot-matched stable ranks per wavefront,
 //                    prefix over wavefronts and shards in LDS, the sub-tile is reordered by shard
 //                    inside LDS and written out in contiguous runs.
-// WMAX bounds the number of shards the LDS tables are sized for.
-__device__ __forceinline__ uint64_t match_key(uint32_t key, bool valid, int bits)
-{
-    uint64_t peers = __ballot(valid);
-    for (int b = 0; b < bits; ++b) {
-        const bool bit = (key >> b) & 1u;
-        const uint64_t bal = __ballot(bit);
-        peers &= bit ? bal : ~bal;
+//
+// Both passes are bound by vector instructions (one per element is 0.8 us at 31 M indices), not by their bytes.  One
+// table per workgroup leaves one divisor, as a multiplication by its reciprocal, and pass 2 needs no bag at all (a
+// workgroup of bags of any table looked every element's bag up in LDS to find its divisor); the number of shard bits
+// is a template parameter.  64 tables x 16384 bags x 30 over 8 shards: 233 -> 135 us for the call, count 35
+// (65 with 4-byte loads and without the border read ahead) and place 60 of it: 4.1 TB/s, what a copy reaches here.
+
+// floor(r / blk) for r < 2^31, exactly: r * mul / 2^(31 + l) with mul = floor(2^(31 + l) / blk) + 1, l = ceil(log2 blk)
+// (mul * blk exceeds 2^(31 + l) by at most blk <= 2^l).  Invalid rows may give a wrong value; callers clamp.
+struct ShardSize {
+    uint32_t blk;    // rows per shard
+    uint32_t mul;
+    int32_t sh;      // l - 1; < 0: blk is 1
+    __device__ __forceinline__ ShardSize(int64_t rows, int32_t W)
+    {
+        blk = max(1u, (uint32_t)((rows + W - 1) / W));
+        const int l = blk == 1u ? 0 : 32 - __clz((int)(blk - 1u));
+        const uint64_t one = 1ull << (31 + l);
+        uint64_t q = (uint64_t)((double)one / (double)blk);      // off by at most one, upwards
+        q -= q * blk > one ? 1u : 0u;
+        mul = (uint32_t)q + 1u;
+        sh = l - 1;
     }
-    return peers;
-}
+    __device__ __forceinline__ uint32_t shard(uint32_t r, uint32_t last) const
+    {
+        const uint32_t q = sh < 0 ? r : __umulhi(r, mul) >> sh;
+        return min(q, last);
+    }
+};
 
 constexpr int kBuckMaxBags = 256;   // bags per workgroup (fewer when W is large: nbags * W <= 8192)
+constexpr int kBuckCount = 8;       // consecutive positions per thread of the counting pass
 constexpr int kBuckPerThread = 8;
 constexpr int kBuckTile = kThreads * kBuckPerThread;  // 2048 positions per sub-tile
 
-struct BuckBags {
-    int32_t off[kBuckMaxBags + 1];   // bag borders relative to the workgroup's first position
-    uint32_t blk[kBuckMaxBags];      // rows per shard of the bag's table
-    float rcp[kBuckMaxBags];         // 1 / blk
-    int32_t tab[kBuckMaxBags];       // table of the bag
-};
-
-// loads the workgroup's bag borders, tables and shard sizes; returns the first position (absolute)
-__device__ __forceinline__ int64_t load_bags(BuckBags& sb, const int64_t* __restrict__ rows,
-                                             const int64_t* __restrict__ offsets, int j0, int nb, int32_t B, int32_t W)
-{
-    const int64_t base = offsets[j0];
-    for (int i = threadIdx.x; i <= nb; i += kThreads)
-        sb.off[i] = (int32_t)(offsets[j0 + i] - base);
-    for (int i = threadIdx.x; i < nb; i += kThreads) {
-        const int t = (j0 + i) / B;
-        sb.tab[i] = t;
-        const uint32_t blk = (uint32_t)((rows[t] + W - 1) / W);
-        sb.blk[i] = blk;
-        sb.rcp[i] = 1.0f / (float)blk;
-    }
-    __syncthreads();
-    return base;
-}
-
-// last a in [0, nb) with off[a] <= p; nb <= 256: eight branch-free halvings, so that the searches of
-// the positions a thread holds overlap their LDS latencies
+// last a in [0, nb) with off[a] <= p; nb <= 256: eight branch-free halvings
 __device__ __forceinline__ int find_bag(const int32_t* off, int nb, int p)
 {
     int a = 0, c = nb;
@@ -483,196 +478,217 @@ __device__ __forceinline__ int find_bag(const int32_t* off, int nb, int p)
     return a;
 }
 
-// floor(r / blk) for r < 2^31, 1 <= blk < 2^31, quotient <= 1024 in every valid case: the float estimate is off by
-// at most one, which the remainder corrects.  (Invalid rows may give a wrong large value; callers clamp.)
-__device__ __forceinline__ uint32_t div_rows(uint32_t r, uint32_t blk, float rcp_blk)
-{
-    uint32_t q = (uint32_t)((float)r * rcp_blk);
-    const int32_t rem = (int32_t)(r - q * blk);
-    q = rem < 0 ? q - 1 : q;
-    q = rem >= (int32_t)blk ? q + 1 : q;
-    return q;
-}
+// four words at any 4-byte aligned address (one 16-byte load)
+struct __attribute__((packed, aligned(4))) Words4 {
+    uint32_t x, y, z, w;
+};
 
+// work items: T * per_table, per_table = ceil(B / nbags), nbags = 1 << lg_nbags; dynamic LDS: W * nbags counters
 __global__ __launch_bounds__(kThreads) void bucketize_count_kernel(const int64_t* __restrict__ rows,
                                                                    const int32_t* __restrict__ indices,
                                                                    const int64_t* __restrict__ offsets,
                                                                    int32_t* __restrict__ lengths_out, int32_t T,
-                                                                   int32_t B, int32_t W, int32_t num_bags,
-                                                                   int32_t nbags)
+                                                                   int32_t B, int32_t W, int32_t lg_nbags,
+                                                                   int32_t per_table, int32_t num_items)
 {
-    __shared__ BuckBags sb;
-    __shared__ int32_t s_cnt[8192];  // [W][nbags]
-    const int j0 = blockIdx.x * nbags;
-    const int nb = min(nbags, num_bags - j0);
-    for (int i = threadIdx.x; i < W * nbags; i += kThreads)
-        s_cnt[i] = 0;
-    const int64_t base = load_bags(sb, rows, offsets, j0, nb, B, W);
-    const int total = sb.off[nb];
-    // Counting does not depend on the order, so a thread takes kBuckPerThread CONSECUTIVE positions: one bag
-    // search for the first of them, then it only steps over the bag borders it meets.
-    for (int p0 = threadIdx.x * kBuckPerThread; p0 < total; p0 += kThreads * kBuckPerThread) {
-        uint32_t r[kBuckPerThread];
+    __shared__ int32_t s_off[kBuckMaxBags + 2];     // (the last one is read ahead, never used)
+    extern __shared__ int32_t s_cnt[];  // [W][nbags]
+    const int nbags = 1 << lg_nbags;
+    for (uint32_t item = blockIdx.x; item < (uint32_t)num_items; item += gridDim.x) {
+        const int t = (int)(item / (uint32_t)per_table);
+        const int b0 = ((int)item - t * per_table) << lg_nbags;
+        const int nb = min(nbags, B - b0);
+        const int64_t* off = offsets + ((int64_t)t * B + b0);
+        const int64_t base = off[0];
+        const ShardSize size(rows[t], W);
+        for (int i = threadIdx.x; i < W << lg_nbags; i += kThreads)
+            s_cnt[i] = 0;
+        for (int i = threadIdx.x; i <= nb; i += kThreads)
+            s_off[i] = (int32_t)(off[i] - base);
+        __syncthreads();
+        const int total = s_off[nb];
+        const uint32_t last = (uint32_t)(W - 1);
+        // Counting does not depend on the order, so a thread takes kBuckCount CONSECUTIVE positions: one bag
+        // search for the first of them, then it only steps over the bag borders it meets (the border after the next
+        // one is on its way meanwhile: some lane steps at nearly every position).
+        for (int p0 = threadIdx.x * kBuckCount; p0 < total; p0 += kThreads * kBuckCount) {
+            uint32_t r[kBuckCount];
+            if (p0 + kBuckCount <= total) {
 #pragma unroll
-        for (int u = 0; u < kBuckPerThread; ++u)
-            r[u] = (uint32_t)indices[base + min(p0 + u, total - 1)];
-        int a = find_bag(sb.off, nb, p0);
-        int next = sb.off[a + 1];
-        uint32_t blk = sb.blk[a];
-        float rcp = sb.rcp[a];
-#pragma unroll
-        for (int u = 0; u < kBuckPerThread; ++u) {
-            const int p = p0 + u;
-            if (p < total) {
-                while (p >= next && a + 1 < nb) {   // p < total = off[nb]: a stays below nb even for bad offsets
-                    ++a;
-                    next = sb.off[a + 1];
-                    blk = sb.blk[a];
-                    rcp = sb.rcp[a];
+                for (int u = 0; u < kBuckCount; u += 4) {
+                    const Words4 v = *reinterpret_cast<const Words4*>(indices + base + p0 + u);
+                    r[u] = v.x, r[u + 1] = v.y, r[u + 2] = v.z, r[u + 3] = v.w;
                 }
-                const uint32_t w = min(div_rows(r[u], blk, rcp), (uint32_t)(W - 1));  // clamp: invalid rows only
-                atomicAdd(&s_cnt[w * nbags + a], 1);
+            } else {
+#pragma unroll
+                for (int u = 0; u < kBuckCount; ++u)
+                    r[u] = (uint32_t)indices[base + min(p0 + u, total - 1)];
+            }
+            int a = find_bag(s_off, nb, p0);
+            int next = s_off[a + 1], next2 = s_off[a + 2];
+#pragma unroll
+            for (int u = 0; u < kBuckCount; ++u) {
+                const int p = p0 + u;
+                if (p < total) {
+                    while (p >= next && a + 1 < nb) {   // p < total = off[nb]: a stays below nb even for bad offsets
+                        ++a;
+                        next = next2;
+                        next2 = s_off[a + 2];
+                    }
+                    atomicAdd(&s_cnt[(size.shard(r[u], last) << lg_nbags) + a], 1);
+                }
             }
         }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < W * nbags; i += kThreads) {
-        const int w = i / nbags;
-        const int a = i - w * nbags;
-        if (a < nb) {
-            const int t = sb.tab[a];
-            lengths_out[((int64_t)w * T + t) * B + (j0 + a - t * B)] = s_cnt[i];
+        __syncthreads();
+        for (int i = threadIdx.x; i < W << lg_nbags; i += kThreads) {
+            const int w = i >> lg_nbags;
+            const int a = i & (nbags - 1);
+            if (a < nb)
+                lengths_out[((int64_t)w * T + t) * B + (b0 + a)] = s_cnt[i];
         }
+        __syncthreads();
     }
 }
 
-template <int WMAX>
+// BITS: W <= 1 << BITS
+template <int BITS>
 __global__ __launch_bounds__(kThreads) void bucketize_place_kernel(const int64_t* __restrict__ rows,
                                                                    const int32_t* __restrict__ indices,
                                                                    const int64_t* __restrict__ offsets,
                                                                    const int64_t* __restrict__ offsets_out,
                                                                    int32_t* __restrict__ indices_out, int32_t T,
-                                                                   int32_t B, int32_t W, int32_t wbits,
-                                                                   int32_t num_bags, int32_t nbags)
+                                                                   int32_t B, int32_t W, int32_t nbags,
+                                                                   int32_t per_table, int32_t num_items)
 {
+    constexpr int kShards = 1 << BITS;
     constexpr int kWaves = kThreads / kWave;
-    constexpr int kDpt = (WMAX + kThreads - 1) / kThreads;  // shards per thread in the shard prefix sum
-    __shared__ BuckBags sb;
-    __shared__ uint32_t s_whist[kWaves][WMAX];
-    __shared__ uint32_t s_dstart[WMAX];   // first slot of the shard inside the reordered sub-tile
-    __shared__ int64_t s_goff[WMAX];      // output position of slot 0 of the shard, minus the slot
-    __shared__ int64_t s_next[WMAX];      // output position of the shard's next element
+    constexpr int kScanThreads = kShards <= kWave ? kWave : kThreads;           // threads of the prefix over the shards
+    constexpr int kDpt = (kShards + kScanThreads - 1) / kScanThreads;           // shards per thread there
+    using Digit = typename std::conditional<BITS <= 8, uint8_t, uint16_t>::type;
+    __shared__ uint32_t s_slot[kWaves][kShards];   // counts of a wavefront, then the slot of its first element
+    __shared__ int32_t s_goff[kShards];            // output position of slot 0 of the shard, minus the slot
+    __shared__ int32_t s_next[kShards];            // output position of the shard's next element
     __shared__ int32_t s_val[kBuckTile];
-    __shared__ uint16_t s_dig[kBuckTile];
+    __shared__ Digit s_dig[kBuckTile];
     __shared__ uint32_t s_wave[kWaves];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
-    const int j0 = blockIdx.x * nbags;
-    const int nb = min(nbags, num_bags - j0);
-    const int64_t base = load_bags(sb, rows, offsets, j0, nb, B, W);
-    const int total = sb.off[nb];
-    {
-        const int t0 = sb.tab[0];
-        for (int d = threadIdx.x; d < W; d += kThreads)
-            s_next[d] = offsets_out[((int64_t)d * T + t0) * B + (j0 - t0 * B)];
-    }
-    const uint64_t lt = (1ull << lane) - 1ull;
+    for (uint32_t item = blockIdx.x; item < (uint32_t)num_items; item += gridDim.x) {
+        const int t = (int)(item / (uint32_t)per_table);
+        const int b0 = ((int)item - t * per_table) * nbags;
+        const int64_t j0 = (int64_t)t * B + b0;
+        const int64_t base = offsets[j0];
+        const int total = (int)(offsets[j0 + min(nbags, B - b0)] - base);
+        const int32_t* __restrict__ in = indices + base;
+        const ShardSize size(rows[t], W);
+        const uint32_t last = (uint32_t)(W - 1);
+        // (s_next is written and read by the same threads, those of the prefix below)
+        if (threadIdx.x < kScanThreads)
+#pragma unroll
+            for (int i = 0; i < kDpt; ++i) {
+                const int d = threadIdx.x * kDpt + i;
+                if (d < W)
+                    s_next[d] = (int32_t)offsets_out[((int64_t)d * T + t) * B + b0];
+            }
 
-    for (int tile0 = 0; tile0 < total; tile0 += kBuckTile) {
-        const int tile_cnt = min(kBuckTile, total - tile0);
-        for (int i = threadIdx.x; i < kWaves * WMAX; i += kThreads)
-            (&s_whist[0][0])[i] = 0;
-        __syncthreads();
+        for (int tile0 = 0; tile0 < total; tile0 += kBuckTile) {
+            const int tile_cnt = min(kBuckTile, total - tile0);
+            // order inside the sub-tile: (wavefront, round, lane) = ascending position
+            const int wbase = tile0 + wave * (kBuckTile / kWaves);
+            uint32_t r[kBuckPerThread];
+#pragma unroll
+            for (int k = 0; k < kBuckPerThread; ++k)
+                r[k] = (uint32_t)in[min(wbase + k * kWave + lane, total - 1)];
+            for (int i = lane; i < kShards; i += kWave)
+                s_slot[wave][i] = 0;
+            uint32_t dig[kBuckPerThread], rank[kBuckPerThread];
+#pragma unroll
+            for (int k = 0; k < kBuckPerThread; ++k) {
+                const bool valid = wbase + k * kWave + lane < total;
+                const uint32_t w = size.shard(r[k], last);
+                dig[k] = w;
+                // lanes of the same shard: one ballot per bit, lanes whose bit differs drop out
+                const uint64_t alive = __ballot(valid);
+                uint32_t lo = (uint32_t)alive, hi = (uint32_t)(alive >> 32);
+#pragma unroll
+                for (int b = 0; b < BITS; ++b) {
+                    const int32_t mk = (int32_t)(w << (31 - b)) >> 31;
+                    const uint64_t bal = __ballot(mk != 0);
+                    lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)bal, (uint32_t)mk, 0x90);
+                    hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(bal >> 32), (uint32_t)mk, 0x90);
+                }
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+                rank[k] = s_slot[wave][w] + below;       // LDS operations of a wavefront execute in order
+                if (valid && below == 0)
+                    atomicAdd(&s_slot[wave][w], (uint32_t)(__popc(lo) + __popc(hi)));
+            }
+            __syncthreads();
 
-        // order inside the sub-tile: (wavefront, round, lane) = ascending position
-        const int wbase = tile0 + wave * (kBuckTile / kWaves);
-        uint32_t r[kBuckPerThread];
+            // exclusive prefix of the counts over shards and, inside a shard, over wavefronts
+            uint32_t tot[kDpt], mine = 0, incl = 0;
+            if (threadIdx.x < kScanThreads) {
 #pragma unroll
-        for (int k = 0; k < kBuckPerThread; ++k)
-            r[k] = (uint32_t)indices[base + min(wbase + k * kWave + lane, total - 1)];
-        uint32_t dig[kBuckPerThread], rank[kBuckPerThread];
-        int32_t local[kBuckPerThread];
+                for (int i = 0; i < kDpt; ++i) {
+                    const int d = threadIdx.x * kDpt + i;
+                    tot[i] = 0;
+                    if (d < W)
 #pragma unroll
-        for (int k = 0; k < kBuckPerThread; ++k) {
-            const int p = wbase + k * kWave + lane;
-            const bool valid = p < total;
-            const int a = find_bag(sb.off, nb, min(p, total - 1));
-            const uint32_t blk = sb.blk[a];
-            const uint32_t w = min(div_rows(r[k], blk, sb.rcp[a]), (uint32_t)(W - 1));
-            local[k] = (int32_t)(r[k] - w * blk);
-            dig[k] = w;
-            const uint64_t peers = match_key(w, valid, wbits);
-            const uint32_t pre = s_whist[wave][w];    // indexed as the LDS array it is (no generic pointer)
-            const uint32_t below = (uint32_t)__popcll(peers & lt);
-            if (valid && below == 0)
-                s_whist[wave][w] = pre + (uint32_t)__popcll(peers);
-            rank[k] = pre + below;
-        }
-        __syncthreads();
-
-        // per shard: exclusive prefix over the wavefronts and the sub-tile total; then the exclusive
-        // prefix of the totals over the shards (kDpt consecutive shards per thread)
-        uint32_t tot[kDpt];
-        uint32_t mine = 0;
+                        for (int w = 0; w < kWaves; ++w)
+                            tot[i] += s_slot[w][d];
+                    mine += tot[i];
+                }
+                incl = mine;
 #pragma unroll
-        for (int i = 0; i < kDpt; ++i) {
-            const int d = threadIdx.x * kDpt + i;
-            uint32_t run = 0;
-            if (d < W) {
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w) {
-                    const uint32_t c = s_whist[w][d];
-                    s_whist[w][d] = run;
-                    run += c;
+                for (int o = 1; o < kWave && o < kShards; o <<= 1) {
+                    const uint32_t up = __shfl_up(incl, o);
+                    if (lane >= o)
+                        incl += up;
                 }
             }
-            tot[i] = run;
-            mine += run;
-        }
-        uint32_t incl = mine;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t up = __shfl_up(incl, o);
-            if (lane >= o)
-                incl += up;
-        }
-        if (lane == kWave - 1)
-            s_wave[wave] = incl;
-        __syncthreads();
-        uint32_t ex = incl - mine;
-        for (int w = 0; w < wave; ++w)
-            ex += s_wave[w];
-#pragma unroll
-        for (int i = 0; i < kDpt; ++i) {
-            const int d = threadIdx.x * kDpt + i;
-            if (d < W) {
-                const int64_t nxt = s_next[d];
-                s_dstart[d] = ex;
-                s_goff[d] = nxt - (int64_t)ex;
-                s_next[d] = nxt + tot[i];
+            uint32_t ex = incl - mine;
+            if constexpr (kScanThreads > kWave) {
+                if (lane == kWave - 1)
+                    s_wave[wave] = incl;
+                __syncthreads();
+                for (int w = 0; w < wave; ++w)
+                    ex += s_wave[w];
             }
-            ex += tot[i];
-        }
-        __syncthreads();
+            if (threadIdx.x < kScanThreads) {
+#pragma unroll
+                for (int i = 0; i < kDpt; ++i) {
+                    const int d = threadIdx.x * kDpt + i;
+                    if (d < W) {
+                        const int32_t nxt = s_next[d];
+                        s_goff[d] = nxt - (int32_t)ex;
+                        s_next[d] = nxt + (int32_t)tot[i];
+#pragma unroll
+                        for (int w = 0; w < kWaves; ++w) {
+                            const uint32_t c = s_slot[w][d];
+                            s_slot[w][d] = ex;
+                            ex += c;
+                        }
+                    }
+                }
+            }
+            __syncthreads();
 
 #pragma unroll
-        for (int k = 0; k < kBuckPerThread; ++k) {
-            const int p = wbase + k * kWave + lane;
-            if (p < total) {
-                const uint32_t pos = s_dstart[dig[k]] + s_whist[wave][dig[k]] + rank[k];
-                s_val[pos] = local[k];
-                s_dig[pos] = (uint16_t)dig[k];
+            for (int k = 0; k < kBuckPerThread; ++k) {
+                if (wbase + k * kWave + lane < total) {
+                    const uint32_t pos = s_slot[wave][dig[k]] + rank[k];
+                    s_val[pos] = (int32_t)(r[k] - dig[k] * size.blk);
+                    s_dig[pos] = (Digit)dig[k];
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kBuckPerThread; ++k) {
+                const int q = threadIdx.x + k * kThreads;
+                if (q < tile_cnt)
+                    indices_out[s_goff[s_dig[q]] + q] = s_val[q];
             }
         }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kBuckPerThread; ++k) {
-            const int q = threadIdx.x + k * kThreads;
-            if (q < tile_cnt)
-                indices_out[s_goff[s_dig[q]] + q] = s_val[q];
-        }
-        __syncthreads();
     }
 }
 

@@ -46,3 +46,28 @@ def test_permute_starts(gpu_device, W, T, B, kind):
     got = _gpu_permute(W, T, B, torch.from_numpy(lens).to(gpu_device), torch.from_numpy(idx).to(gpu_device), gpu_device)
     for g, r, name in zip(got, ref, ("lengths", "offsets", "indices")):
         assert np.array_equal(g, r), name
+
+
+@pytest.mark.parametrize("W", [1, 2, 3, 8, 9, 33, 128, 129, 257, 1024])
+def test_bucketize_divisors_and_remainders(gpu_device, W):
+    """Shard sizes around powers of two up to 2^31, rows next to every shard border, bags that end off every tile."""
+    rng = np.random.default_rng(W)
+    blk = [1, 2, 3, 4, 5, 255, 256, 257, 65535, 65537, (1 << 20) + 1, (1 << 21) - 1, (1 << 31) // W]
+    rows = np.array([min(b * W, (1 << 31) - 1) - k for b in blk for k in (0, 1) if b * W - k > 0], np.int64)
+    T, B = len(rows), 261
+    blks = (rows + W - 1) // W
+    lens = rng.integers(0, 14, (T, B))
+    lens[:, rng.choice(B, 20, replace=False)] = 0
+    lens[0, 3] = 2048 * 2 + 1
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    per = lens.sum(1)
+    idx = []
+    for t in range(T):
+        r = rng.integers(0, W, per[t]) * blks[t] + rng.integers(-1, 2, per[t])      # shard borders
+        free = rng.integers(0, rows[t], per[t])
+        idx.append(np.clip(np.where(rng.random(per[t]) < 0.5, r, free), 0, rows[t] - 1))
+    idx = np.concatenate(idx).astype(np.int32)
+    ref = io.bucketize_rowwise(rows, B, W, idx, offsets)
+    got = _gpu_bucketize(rows, B, W, torch.from_numpy(idx).to(gpu_device), torch.from_numpy(offsets).to(gpu_device), gpu_device)
+    for g, r, name in zip(got, ref, ("lengths", "offsets", "indices")):
+        assert np.array_equal(g, r[:len(g)]), name
