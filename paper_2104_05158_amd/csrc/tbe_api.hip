@@ -107,7 +107,7 @@ struct tbe_s {
     // workspace layout (byte offsets)
     size_t off_meta = 0, off_rowbase = 0, off_counters = 0, off_keys[2] = {0, 0}, off_vals[2] = {0, 0};
     size_t off_tstart = 0, off_stables = 0, off_schunks = 0, off_sunits = 0, off_split = 0, off_lut = 0, off_bstart = 0;
-    size_t off_hist = 0, off_tile_bag = 0, off_unit_cnt = 0, off_unit_base = 0, off_unit_runs = 0, off_table_runs = 0, off_words64[2] = {0, 0};
+    size_t off_hist = 0, off_tile_bag = 0, off_unit_cnt = 0, off_unit_base = 0, off_unit_runs = 0, off_table_runs = 0, off_words64 = 0;
     size_t off_unit_first = 0, off_partials = 0;
     size_t off_long_list = 0, off_zero = 0, workspace_bytes = 0;
     size_t off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
@@ -272,8 +272,7 @@ void plan_workspace(tbe_s* h)
     h->off_unit_base = take(4 * (size_t)(h->T + 1));
     h->off_unit_runs = take(4 * (size_t)slots);
     h->off_table_runs = take(4 * (size_t)h->T);
-    for (int i = 0; i < 2; ++i)
-        h->off_words64[i] = ss.wide ? take(8 * nelem) : 0;
+    h->off_words64 = ss.wide ? take(8 * nelem) : 0;
     const int64_t chunks = std::max<int64_t>(1, ceil_div(nmax, kChunk));
     h->off_unit_first = take(4 * (size_t)(ceil_div(nmax, kSpanUnit) + 1));
     const int dpad = (int)align_up((size_t)h->dmax, 4);
@@ -602,9 +601,10 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.seg_offsets = h->ws<int32_t>(h->off_vals[1]);
     a.unit_first_run = h->ws<int32_t>(h->off_unit_first);
     // a unit reads its words before it writes its keys and payloads to the same positions: 32-bit words share
-    // the memory of the result
-    for (int i = 0; i < 2; ++i)
-        a.words[i] = ss.wide ? h->ws<void>(h->off_words64[i]) : i == 0 ? static_cast<void*>(a.keys) : static_cast<void*>(a.vals);
+    // the memory of the result.  64-bit words have a buffer of their own; their second one is where unique_keys and
+    // seg_offsets go (neighbours in the workspace, 4 bytes an entry each), which a later kernel writes.
+    a.words[0] = ss.wide ? h->ws<void>(h->off_words64) : static_cast<void*>(a.keys);
+    a.words[1] = ss.wide ? static_cast<void*>(a.unique_keys) : static_cast<void*>(a.vals);
     a.n = n;
     a.B = batch;
     a.T = h->T;

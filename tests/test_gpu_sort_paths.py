@@ -92,8 +92,9 @@ def _mix(x):
     return int(x ^ (x >> np.uint32(16)))
 
 
+@pytest.mark.parametrize("rows,batch", [(200_000, 611), (34_000_000, 65536)])     # words of 32 and of 64 bits
 @pytest.mark.parametrize("n", [20_000, 90_000])
-def test_bucket_larger_than_a_tile(gpu_device, n):
+def test_bucket_larger_than_a_tile(gpu_device, n, rows, batch):
     # the sampled lookups hit rows from 1000 on, all others the 1000 rows below: one bucket holds nearly everything
     rng = np.random.default_rng(n)
     want = -(-n // 1024)
@@ -102,4 +103,4 @@ def test_bucket_larger_than_a_tile(gpu_device, n):
     at = [min((stretch * (i * 256 + (_mix(i) & 255))) >> 40, n - 1) for i in range(s)]
     idx = rng.integers(0, 1000, n)
     idx[at] = rng.integers(1000, 200_000, s)
-    _check(gpu_device, [200_000], 611, _lens(rng, 611, n), idx, "large bucket")
+    _check(gpu_device, [rows], batch, _lens(rng, batch, n), idx, "large bucket")
