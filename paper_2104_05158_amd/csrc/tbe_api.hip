@@ -97,6 +97,7 @@ struct tbe_s {
     int dmax = 0;
     int fwd_epl = 4;
     int fwd_kmax = 1;
+    bool fwd_wide = true;    // every table's row takes all lanes of a wavefront
     int key_bits = 1;                   // bits of the tallest table's row index
     int64_t max_rows = 1;
     std::vector<int64_t> woff;      // T+1, elements
@@ -229,8 +230,6 @@ SortShape sort_shape(const tbe_s* h, int64_t batch, int64_t n)
 void plan_workspace(tbe_s* h)
 {
     const int64_t nmax = h->max_indices;
-    const int64_t bags = (int64_t)h->T * h->max_batch;
-    (void)bags;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -322,18 +321,26 @@ tbe_status_t launch_forward(tbe_s* h, const int32_t* idx, const int64_t* off, in
                             OT* out, hipStream_t st)
 {
     const int num_bags = h->T * batch;
+    const bool few = num_bags < kFewBagsShort || (num_bags < kFewBags && n_total >= (int64_t)kFewBagsLookups * num_bags) ||
+                     (h->fwd_wide && n_total >= (int64_t)kWideBagLookups * num_bags);
     // bags per wavefront: enough to amortise the per-block prologue, few enough to keep >= ~16k
     // wavefronts in the grid when the batch is small
     const int bpw = (int)std::min<int64_t>(kFwdMaxBagsPerWave, std::max<int64_t>(1, num_bags / 16384));
-    const int per_block = (kFwdThreads / kWave) * bpw;
+    const int per_block = (kFwdThreads / kWave) * (few ? 1 : bpw);
     const dim3 grid((unsigned)ceil_div(num_bags, per_block)), block(kFwdThreads);
     const TableMeta* meta = h->ws<TableMeta>(h->off_meta);
     const WT* w = static_cast<const WT*>(h->d_weights);
     const int sumD = (int)h->sumD;
     const void* zero = h->ws<void>(h->off_zero);
-#define FWD(EPL, KMAX)                                                                              \
-    hipLaunchKernelGGL((forward_kernel<WT, EPL, KMAX, OT>), grid, block, 0, st, meta, w, idx, off, out, \
-                       zero, batch, num_bags, sumD, n_total, bpw, h->layout)
+#define FWD(EPL, KMAX)                                                                                          \
+    do {                                                                                                        \
+        if (few)                                                                                                \
+            hipLaunchKernelGGL((forward_bag_kernel<WT, EPL, KMAX, OT>), grid, block, 0, st, meta, w, idx, off, out, \
+                               zero, batch, num_bags, sumD, n_total, h->layout);                                \
+        else                                                                                                    \
+            hipLaunchKernelGGL((forward_kernel<WT, EPL, KMAX, OT>), grid, block, 0, st, meta, w, idx, off, out, \
+                               zero, batch, num_bags, sumD, n_total, bpw, h->layout);                           \
+    } while (0)
     if constexpr (sizeof(WT) == 4) {
         if (h->fwd_kmax == 1)
             FWD(4, 1);
@@ -452,6 +459,7 @@ tbe_status_t tbe_create(const tbe_config_t* cfg, tbe_handle_t* out_handle)
         m.dim = h->dims[t];
         m.col = c;
         m.lpr_fwd = std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], h->fwd_epl)));
+        h->fwd_wide = h->fwd_wide && m.lpr_fwd == 6;
         m.lpr_bwd = std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], 8)));
         m.key_bits = table_bits[t];
         w += h->rows[t] * (int64_t)h->dims[t];

@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace tbe {
 
 constexpr int kWave = 64;
@@ -23,6 +25,19 @@ constexpr int kWave = 64;
 constexpr int kFwdThreads = 256;          // 4 wavefronts per workgroup, each with its own block of bags
 constexpr int kFwdUnroll = 4;             // row loads in flight per lane group (8 costs occupancy and is slower)
 constexpr int kFwdMaxBagsPerWave = 8;     // measured best on configs 2-4 (4..32 tried)
+// forward_bag_kernel (one bag per wavefront) takes a call ...
+// ... of fewer than kFewBagsShort bags whatever their length: 2048 bags of 2 lookups, dim 128: 3.5 against 3.2 us;
+// ... of fewer than kFewBags bags that hold kFewBagsLookups lookups on average.  forward_kernel has one bag per
+//     wavefront there too and leaves all lane groups but one idle; from 32,768 bags it packs several (fp32 dim 64, 8
+//     lookups: 24,000 bags 15.0 against 11.6 us, 40,000 bags 15.0 against 17.6).  Bags of 2 lookups have nothing to
+//     spread (fp32 dim 128, 16,384 bags: 8.3 against 8.5);
+// ... of any size if every table's row fills the wavefront and a bag holds kWideBagLookups lookups on average: there
+//     is no lane group to spread over, but up to 8 rows in flight instead of 4.  131,072 bags: fp32 dim 256, 16 lookups
+//     174 against 154 us, dim 512, 24 lookups 463 against 400; fp16 dim 384, 16 lookups 179 against 166.
+constexpr int kFewBagsShort = 8192;
+constexpr int kFewBags = 32768;
+constexpr int kFewBagsLookups = 4;
+constexpr int kWideBagLookups = 16;
 constexpr int kChunk = 128;               // sorted positions per pair of partial-row slots
 constexpr int kSpanUnit = 64;             // a span of the update kernel is a multiple of this many sorted positions
 constexpr int kLongRun = 512;             // runs longer than this are summed in pieces by other kernels (window / dense path)
@@ -345,6 +360,138 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(
             }
         }
         r += nb;
+    }
+}
+
+// Calls of few bags: one bag per wavefront, its lookups spread over all lane groups (group g takes lookups g, g + G,
+// ...), whose sums a butterfly adds at the end.  Such a call cannot fill the chip with bags, so what counts is the
+// length of a bag's chain of dependent loads and that no lane group is idle: forward_kernel would use one of its G
+// groups and four rows a step.  A step takes as many rows per group as the bag still needs, 1, 2, 4 or 8: a short bag
+// issues no loads of the zero row beyond its last step.
+//
+// Per call, forward_kernel -> this kernel (dim 128, 20 lookups a bag): fp32 256 bags 5.6 -> 3.9 us, 2048 8.1 -> 5.8,
+// 24,000 26.8 -> 22.3; fp16 256 bags 5.9 -> 3.7, 24,000 28.2 -> 16.2; fp32 dim 512, 30 lookups, 65,536 bags 321 -> 287.
+constexpr int kBagUnroll = 8;                     // 76 registers for fp32 rows of up to 256 elements, 6 wavefronts a SIMD
+
+template <typename WT, int EPL, int KMAX, typename OT>
+__global__ __launch_bounds__(kFwdThreads) void forward_bag_kernel(
+    const TableMeta* __restrict__ meta, const WT* __restrict__ weights,
+    const int32_t* __restrict__ indices, const int64_t* __restrict__ offsets,
+    OT* __restrict__ out, const void* __restrict__ zero_row, int32_t B, int32_t num_bags,
+    int32_t sumD, int32_t n_total, int32_t table_major)
+{
+    using IO = RowIO<WT, EPL>;
+    using Vec = typename IO::Vec;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int j = uniform(blockIdx.x * (kFwdThreads / kWave) + (threadIdx.x >> 6));
+    if (j >= num_bags)
+        return;
+    const int start = (int)offsets[j];
+    const int len = (int)offsets[j + 1] - start;
+    const uint32_t last = (uint32_t)(n_total - 1);
+    const WT* __restrict__ zrow = static_cast<const WT*>(zero_row);
+    const int t = j / B;
+    const TableMeta m = meta[t];
+    const int D = m.dim;
+    const int lprl = m.lpr_fwd;
+    const int LPR = 1 << lprl;
+    const int G = kWave >> lprl;
+    const int sub = lane & (LPR - 1);
+    const int grp = lane >> lprl;
+    const WT* __restrict__ wbase = weights + m.woff;
+
+    int eoff[KMAX];
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k)
+        eoff[k] = min((sub + k * LPR) * EPL, D - EPL);
+    // as in forward_kernel: four accumulators for fp32 tables, one for fp16
+    constexpr int NACC = sizeof(WT) == 4 ? 4 : 1;
+    float accs[NACC][KMAX][EPL];
+#pragma unroll
+    for (int q = 0; q < NACC; ++q)
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e)
+                accs[q][k][e] = 0.f;
+
+    if (len > 0) {
+        // Up to 8 groups: a step of 8 G lookups lies inside a block of 64, loaded with one instruction a block ahead
+        // and handed out by shuffles.  More groups (rows of up to four lanes): every lane loads its own indices.
+        const bool blocks = G * kBagUnroll <= kWave;
+        int cur = 0, nxt = 0;
+        if (blocks)
+            nxt = indices[min((uint32_t)(start + lane), last)];
+        auto step = [&](auto rows, int it) {
+            constexpr int U = decltype(rows)::value;
+            int idx[U];
+            if (blocks) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    idx[u] = __shfl(cur, (it + u * G + grp) & (kWave - 1));
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    idx[u] = indices[min((uint32_t)(start + it + u * G + grp), last)];
+            }
+            Vec raw[U][KMAX];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const WT* rp = it + u * G + grp < len ? wbase + (int64_t)idx[u] * D : zrow;
+#pragma unroll
+                for (int k = 0; k < KMAX; ++k)
+                    raw[u][k] = IO::ldv(rp + eoff[k]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int k = 0; k < KMAX; ++k)
+                    IO::add(accs[u % NACC][k], raw[u][k]);
+        };
+        for (int it = 0; it < len; it += kBagUnroll * G) {
+            if (blocks && (it & (kWave - 1)) == 0) {
+                cur = nxt;
+                if (len - it > kWave)
+                    nxt = indices[min((uint32_t)(start + it + kWave + lane), last)];
+            }
+            const int left = len - it;
+            if (left > 4 * G)
+                step(std::integral_constant<int, 8>(), it);
+            else if (left > 2 * G)
+                step(std::integral_constant<int, 4>(), it);
+            else if (left > G)
+                step(std::integral_constant<int, 2>(), it);
+            else
+                step(std::integral_constant<int, 1>(), it);
+        }
+    }
+    float acc[KMAX][EPL];
+#pragma unroll
+    for (int k = 0; k < KMAX; ++k)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+            if (NACC == 4)
+                acc[k][e] = (accs[0][k][e] + accs[1 % NACC][k][e]) + (accs[2 % NACC][k][e] + accs[3 % NACC][k][e]);
+            else
+                acc[k][e] = accs[0][k][e];
+        }
+    for (int o = LPR; o < kWave; o <<= 1)
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e)
+                acc[k][e] += __shfl_xor(acc[k][e], o);
+    if (grp == 0) {
+        const int b = j - t * B;
+        OT* op = table_major ? out + (int64_t)B * m.col + (int64_t)b * D : out + (int64_t)b * sumD + m.col;
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            if ((sub + k * LPR) * EPL < D) {
+#pragma unroll
+                for (int q = 0; q < EPL; q += 4)
+                    store_out4(op + eoff[k] + q, acc[k][q], acc[k][q + 1], acc[k][q + 2], acc[k][q + 3]);
+            }
+        }
     }
 }
 
