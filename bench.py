@@ -650,6 +650,12 @@ def run_workload(args, spec, dev, headline):
     comp, logical = kernel_bytes(spec, n_t, u_t, nlong_t, ulong_t, so=out.element_size(), sg=grad.element_size(),
                                  state_per_elem={0: 0, 1: 1, 2: 2}[opt_id], passes_t=sort_passes(spec.rows),
                                  ndense_t=ndense_t, udense_t=udense_t, long_rows_t=long_rows_t)
+    # The library partitions every table once and sorts the buckets in LDS: 4 bytes a lookup in the histogram, 8 in
+    # the partition, 12 in the bucket sort.  Its profile counts the last two as one launch per 8 bits of the row ids.
+    scatter_launches = max(1.0, prof.get("radix_scatter", (0, 0.0))[0] / args.steps)
+    for d in (comp, logical):
+        d["radix_hist"] = float(n_t.sum()) * 4
+        d["radix_scatter"] = float(n_t.sum()) * 20 / scatter_launches
 
     kernels = {}
     for name, (launches, ms) in prof.items():
