@@ -321,25 +321,20 @@ tbe_status_t launch_forward(tbe_s* h, const int32_t* idx, const int64_t* off, in
                             OT* out, hipStream_t st)
 {
     const int num_bags = h->T * batch;
-    const bool few = num_bags < kFewBagsShort || (num_bags < kFewBags && n_total >= (int64_t)kFewBagsLookups * num_bags) ||
-                     (h->fwd_wide && n_total >= (int64_t)kWideBagLookups * num_bags);
-    // bags per wavefront: enough to amortise the per-block prologue, few enough to keep >= ~16k
-    // wavefronts in the grid when the batch is small
-    const int bpw = (int)std::min<int64_t>(kFwdMaxBagsPerWave, std::max<int64_t>(1, num_bags / 16384));
-    const int per_block = (kFwdThreads / kWave) * (few ? 1 : bpw);
-    const dim3 grid((unsigned)ceil_div(num_bags, per_block)), block(kFwdThreads);
+    const ForwardLaunch f = forward_launch(num_bags, n_total, h->fwd_wide);
+    const dim3 grid((unsigned)f.blocks), block(kFwdThreads);
     const TableMeta* meta = h->ws<TableMeta>(h->off_meta);
     const WT* w = static_cast<const WT*>(h->d_weights);
     const int sumD = (int)h->sumD;
     const void* zero = h->ws<void>(h->off_zero);
 #define FWD(EPL, KMAX)                                                                                          \
     do {                                                                                                        \
-        if (few)                                                                                                \
+        if (f.one_bag)                                                                                          \
             hipLaunchKernelGGL((forward_bag_kernel<WT, EPL, KMAX, OT>), grid, block, 0, st, meta, w, idx, off, out, \
                                zero, batch, num_bags, sumD, n_total, h->layout);                                \
         else                                                                                                    \
             hipLaunchKernelGGL((forward_kernel<WT, EPL, KMAX, OT>), grid, block, 0, st, meta, w, idx, off, out, \
-                               zero, batch, num_bags, sumD, n_total, bpw, h->layout);                           \
+                               zero, batch, num_bags, sumD, n_total, f.bags_per_wave, h->layout);               \
     } while (0)
     if constexpr (sizeof(WT) == 4) {
         if (h->fwd_kmax == 1)

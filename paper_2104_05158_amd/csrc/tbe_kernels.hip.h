@@ -17,27 +17,12 @@
 
 #include <type_traits>
 
+#include "tbe_rules.h"
+
 namespace tbe {
 
-constexpr int kWave = 64;
-
-// ---- geometry constants shared by host and device ----
-constexpr int kFwdThreads = 256;          // 4 wavefronts per workgroup, each with its own block of bags
+// ---- geometry constants shared by host and device (those of the launch rules are in tbe_rules.h) ----
 constexpr int kFwdUnroll = 4;             // row loads in flight per lane group (8 costs occupancy and is slower)
-constexpr int kFwdMaxBagsPerWave = 8;     // measured best on configs 2-4 (4..32 tried)
-// forward_bag_kernel (one bag per wavefront) takes a call ...
-// ... of fewer than kFewBagsShort bags whatever their length: 2048 bags of 2 lookups, dim 128: 3.5 against 3.2 us;
-// ... of fewer than kFewBags bags that hold kFewBagsLookups lookups on average.  forward_kernel has one bag per
-//     wavefront there too and leaves all lane groups but one idle; from 32,768 bags it packs several (fp32 dim 64, 8
-//     lookups: 24,000 bags 15.0 against 11.6 us, 40,000 bags 15.0 against 17.6).  Bags of 2 lookups have nothing to
-//     spread (fp32 dim 128, 16,384 bags: 8.3 against 8.5);
-// ... of any size if every table's row fills the wavefront and a bag holds kWideBagLookups lookups on average: there
-//     is no lane group to spread over, but up to 8 rows in flight instead of 4.  131,072 bags: fp32 dim 256, 16 lookups
-//     174 against 154 us, dim 512, 24 lookups 463 against 400; fp16 dim 384, 16 lookups 179 against 166.
-constexpr int kFewBagsShort = 8192;
-constexpr int kFewBags = 32768;
-constexpr int kFewBagsLookups = 4;
-constexpr int kWideBagLookups = 16;
 constexpr int kChunk = 128;               // sorted positions per pair of partial-row slots
 constexpr int kSpanUnit = 64;             // a span of the update kernel is a multiple of this many sorted positions
 constexpr int kLongRun = 512;             // runs longer than this are summed in pieces by other kernels (window / dense path)

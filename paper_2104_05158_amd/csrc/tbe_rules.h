@@ -1,0 +1,57 @@
+// Launch rules and index arithmetic of the embedding library in plain C++: used by the host code and the kernels, and
+// checked on the CPU at sizes and values that a GPU test could not take (tests/test_rules.py).
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace tbe {
+
+constexpr int kWave = 64;
+
+// A launch holds fewer than 2^32 threads.
+constexpr int64_t kMaxLaunchThreads = ((int64_t)1 << 32) - 1;
+
+// ---------------------------------------------------------------- forward
+
+constexpr int kFwdThreads = 256;          // 4 wavefronts per workgroup, each with its own block of bags
+constexpr int kFwdMaxBagsPerWave = 8;     // measured best on configs 2-4 (4..32 tried)
+// forward_bag_kernel (one bag per wavefront) takes a call ...
+// ... of fewer than kFewBagsShort bags whatever their length: 2048 bags of 2 lookups, dim 128: 3.5 against 3.2 us;
+// ... of fewer than kFewBags bags that hold kFewBagsLookups lookups on average.  forward_kernel has one bag per
+//     wavefront there too and leaves all lane groups but one idle; from 32,768 bags it packs several (fp32 dim 64, 8
+//     lookups: 24,000 bags 15.0 against 11.6 us, 40,000 bags 15.0 against 17.6).  Bags of 2 lookups have nothing to
+//     spread (fp32 dim 128, 16,384 bags: 8.3 against 8.5);
+// ... of any size if every table's row fills the wavefront and a bag holds kWideBagLookups lookups on average: there
+//     is no lane group to spread over, but up to 8 rows in flight instead of 4.  131,072 bags: fp32 dim 256, 16 lookups
+//     174 against 154 us, dim 512, 24 lookups 463 against 400; fp16 dim 384, 16 lookups 179 against 166.
+//     Its launch has 64 threads per bag: kMaxLaunchThreads ends that at 2^26 bags.
+constexpr int kFewBagsShort = 8192;
+constexpr int kFewBags = 32768;
+constexpr int kFewBagsLookups = 4;
+constexpr int kWideBagLookups = 16;
+
+struct ForwardLaunch {
+    bool one_bag;          // forward_bag_kernel
+    int bags_per_wave;     // of forward_kernel, which holds a wavefront's borders in its lanes: at most kWave - 1
+    int64_t blocks;
+};
+
+// wide: every table's row takes all lanes of a wavefront
+inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, bool wide)
+{
+    constexpr int64_t kMaxBlocks = kMaxLaunchThreads / kFwdThreads, kWaves = kFwdThreads / kWave;
+    ForwardLaunch f;
+    f.one_bag = (num_bags < kFewBagsShort || (num_bags < kFewBags && lookups >= kFewBagsLookups * num_bags) ||
+                 (wide && lookups >= kWideBagLookups * num_bags)) && num_bags <= kMaxBlocks * kWaves;
+    // enough bags to amortise the per-block prologue, few enough to keep >= ~16k wavefronts in the grid when the batch
+    // is small; beyond 2^29 bags as many as the largest launch needs
+    const int64_t fewest = (num_bags + kMaxBlocks * kWaves - 1) / (kMaxBlocks * kWaves);
+    const int64_t per_wave = std::min<int64_t>(kFwdMaxBagsPerWave, num_bags / 16384);
+    f.bags_per_wave = f.one_bag ? 1 : (int)std::max<int64_t>({1, fewest, per_wave});
+    const int64_t per_block = kWaves * f.bags_per_wave;
+    f.blocks = (num_bags + per_block - 1) / per_block;
+    return f;
+}
+
+}  // namespace tbe

@@ -1,0 +1,14 @@
+// C entry points to the library's launch rules and index arithmetic for tests/test_rules.py.
+#include "tbe_rules.h"
+
+extern "C" {
+
+void forward_launch(int64_t num_bags, int64_t lookups, int wide, int64_t* out /*[3]*/)
+{
+    const tbe::ForwardLaunch f = tbe::forward_launch(num_bags, lookups, wide != 0);
+    out[0] = f.one_bag;
+    out[1] = f.bags_per_wave;
+    out[2] = f.blocks;
+}
+
+}

@@ -63,3 +63,23 @@ def test_many_bags_of_wide_rows(gpu_device, dtype, length):
 
 def test_all_bags_empty(gpu_device):
     _forward_matches(gpu_device, [16, 128], 5, np.zeros((2, 5), np.int64), 0, 0, seed=61)
+
+
+def test_more_bags_of_wide_rows_than_one_bag_per_wavefront_can_launch(gpu_device):
+    # 2^26 bags would be 2^32 threads; 16 lookups a bag, 1.07 G in all, output in 16 bits
+    import torch
+    batch, length, rows, dim = 1 << 26, 16, 1009, 132
+    if torch.cuda.mem_get_info()[0] < 96 << 30:
+        pytest.skip("needs about 60 GB of free device memory")
+    w = wl.make_weights(wl.custom([rows], [dim], 0, 1, 1.0), "cpu", seed=9)
+    op = tbe.TableBatchedEmbeddingBags([rows], [dim], 0, batch, batch * length, device=gpu_device,
+                                       weights=w.to(gpu_device), output_dtype=tbe.TBE_DTYPE_FP16)
+    idx = (torch.arange(batch * length, dtype=torch.int32, device=gpu_device) % rows)
+    off = torch.arange(0, batch * length + 1, length, dtype=torch.int64, device=gpu_device)
+    out = op.forward(idx, off, batch)
+    bags = np.concatenate([np.arange(100), batch // 2 + np.arange(100), batch - 1 - np.arange(100)])
+    got = out[torch.from_numpy(bags).to(gpu_device)].float().cpu().numpy()
+    ref = w.numpy().reshape(rows, dim)[(bags[:, None] * length + np.arange(length)) % rows].astype(np.float64).sum(1)
+    op.close()
+    # fp32 sum of 16 terms, rounded once to fp16 (spacing 2^-24 below its normal range)
+    assert np.all(np.abs(got - ref) <= 2.0 ** -11 * np.abs(ref) + 2.0 ** -24 + 16 * 2.0 ** -24 * 0.16)

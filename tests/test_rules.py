@@ -1,0 +1,43 @@
+"""CPU checks of the launch rules and the index arithmetic that the kernels share with the host (tbe_rules.h), at sizes
+that a GPU test could not take and for inputs that no kernel should be given."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("rules") / "librules.so")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC",
+                           "-I" + os.path.join(ROOT, "paper_2104_05158_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "rules_shim.cpp"), "-o", so])
+    return ctypes.CDLL(so)
+
+
+def _forward(rules, bags, lookups, wide):
+    out = np.zeros(3, np.int64)
+    rules.forward_launch(ctypes.c_int64(bags), ctypes.c_int64(lookups), ctypes.c_int(wide),
+                         out.ctypes.data_as(ctypes.c_void_p))
+    return [int(x) for x in out]
+
+
+@pytest.mark.parametrize("wide", [0, 1])
+@pytest.mark.parametrize("bags", [1, 8191, 8192, 32767, 32768, (1 << 26) - 5, (1 << 26) - 4, (1 << 26) - 3, 1 << 26,
+                                  (1 << 26) + 1, (1 << 29) - 1, 1 << 29, (1 << 31) - 1025])
+def test_forward_launches_hold_every_bag_and_fit_the_grid(rules, bags, wide):
+    # any number of bags a handle can be created for must be launchable: fewer than 2^32 threads
+    for per_bag in (0, 4, 16, 31):
+        lookups = min(bags * per_bag, (1 << 31) - (1 << 24) - 1)
+        one_bag, per_wave, blocks = _forward(rules, bags, lookups, wide)
+        assert 1 <= per_wave <= 63
+        assert blocks * 256 < 1 << 32
+        assert blocks * 4 * per_wave >= bags > (blocks - 1) * 4 * per_wave
+        if one_bag:
+            assert per_wave == 1
+        assert one_bag == int((bags < 8192 or (bags < 32768 and lookups >= 4 * bags) or (wide and lookups >= 16 * bags))
+                              and bags <= (1 << 26) - 4)
