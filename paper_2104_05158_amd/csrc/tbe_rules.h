@@ -5,6 +5,12 @@
 #include <algorithm>
 #include <cstdint>
 
+#ifdef __HIPCC__
+#define TBE_BOTH __host__ __device__ __forceinline__
+#else
+#define TBE_BOTH inline
+#endif
+
 namespace tbe {
 
 constexpr int kWave = 64;
@@ -52,6 +58,24 @@ inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, bool wide
     const int64_t per_block = kWaves * f.bags_per_wave;
     f.blocks = (num_bags + per_block - 1) / per_block;
     return f;
+}
+
+// ---------------------------------------------------------------- sort
+
+// A published integer hash: lowbias32 of Wellons' hash-prospector (public domain).
+TBE_BOTH uint32_t mix_bits(uint32_t x)
+{
+    x ^= x >> 16; x *= 0x7feb352du;
+    x ^= x >> 15; x *= 0x846ca68bu;
+    return x ^ (x >> 16);
+}
+
+// Where sample i of a table of n lookups lies: one from each of the equal stretches of `stretch` positions (32.32),
+// at a random place of it, for which 8 bits are enough.  The product takes up to 40 bits more than n.
+TBE_BOTH int sample_position(uint64_t stretch, uint32_t i, int n)
+{
+    const uint64_t pos = (uint64_t)(((unsigned __int128)stretch * (i * 256u + (mix_bits(i) & 255u))) >> 40);
+    return pos < (uint64_t)n ? (int)pos : n - 1;
 }
 
 }  // namespace tbe

@@ -429,13 +429,6 @@ __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32
     return p;
 }
 
-__device__ __forceinline__ uint32_t mix_bits(uint32_t x)
-{
-    x ^= x >> 16; x *= 0x7feb352du;
-    x ^= x >> 15; x *= 0x846ca68bu;
-    return x ^ (x >> 16);
-}
-
 // first i in [0, n) with p[i] >= v (n if none); p ascending, in LDS
 __device__ __forceinline__ int lds_lower(const uint32_t* p, int n, uint32_t v)
 {
@@ -520,9 +513,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     const uint64_t stretch = ((uint64_t)n << 32) / (uint32_t)S;      // 32.32
 #pragma unroll
     for (int r = 0; r < kSortPerThread; ++r) {
-        const int i = min(wave * rounds * kWave + r * kWave + lane, S - 1);
-        // a random place of the stretch: 8 bits of it are enough
-        const int pos = min((int)((stretch * (uint32_t)(i * 256 + (mix_bits((uint32_t)i) & 255u))) >> 40), n - 1);
+        const int pos = sample_position(stretch, (uint32_t)min(wave * rounds * kWave + r * kWave + lane, S - 1), n);
         // past the sample: the largest key, sorted behind it
         w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? min(a.indices[start + pos], rows - 1) : ~0u;
     }

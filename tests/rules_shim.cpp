@@ -11,4 +11,11 @@ void forward_launch(int64_t num_bags, int64_t lookups, int wide, int64_t* out /*
     out[2] = f.blocks;
 }
 
+void sample_positions(int n, int samples, int32_t* out)
+{
+    const uint64_t stretch = ((uint64_t)n << 32) / (uint32_t)samples;
+    for (int i = 0; i < samples; ++i)
+        out[i] = tbe::sample_position(stretch, (uint32_t)i, n);
+}
+
 }

@@ -41,3 +41,12 @@ def test_forward_launches_hold_every_bag_and_fit_the_grid(rules, bags, wide):
             assert per_wave == 1
         assert one_bag == int((bags < 8192 or (bags < 32768 and lookups >= 4 * bags) or (wide and lookups >= 16 * bags))
                               and bags <= (1 << 26) - 4)
+
+
+@pytest.mark.parametrize("samples", [16, 1024, 8184, 8192])
+@pytest.mark.parametrize("n", [8192, 20_000, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, 100_000_000, (1 << 31) - (1 << 24) - 1])
+def test_samples_come_from_equal_stretches_of_the_whole_table(rules, n, samples):
+    got = np.empty(samples, np.int32)
+    rules.sample_positions(ctypes.c_int(n), ctypes.c_int(samples), got.ctypes.data_as(ctypes.c_void_p))
+    i = np.arange(samples, dtype=np.float64)
+    assert np.all(got >= np.floor(i * n / samples) - 1) and np.all(got <= (i + 1) * n / samples) and np.all(got < n)
