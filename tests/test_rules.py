@@ -13,7 +13,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 @pytest.fixture(scope="module")
 def rules(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("rules") / "librules.so")
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC",
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-Wno-unknown-pragmas", "-shared", "-fPIC",
                            "-I" + os.path.join(ROOT, "paper_2104_05158_amd", "csrc"),
                            os.path.join(ROOT, "tests", "rules_shim.cpp"), "-o", so])
     return ctypes.CDLL(so)
@@ -50,3 +50,32 @@ def test_samples_come_from_equal_stretches_of_the_whole_table(rules, n, samples)
     rules.sample_positions(ctypes.c_int(n), ctypes.c_int(samples), got.ctypes.data_as(ctypes.c_void_p))
     i = np.arange(samples, dtype=np.float64)
     assert np.all(got >= np.floor(i * n / samples) - 1) and np.all(got <= (i + 1) * n / samples) and np.all(got < n)
+
+
+@pytest.mark.parametrize("rows", [1, 2, 5, 255, 256, 257, 70_000, (1 << 20) - 1, 1 << 20, (1 << 31) - 1])
+@pytest.mark.parametrize("buckets", [1, 2, 17, 1023])
+def test_every_index_finds_a_bucket_of_its_table(rules, rows, buckets):
+    # borders and cells as the plan makes them; also indices that are no row of the table, such as a padding value of -1
+    rng = np.random.default_rng(rows % 1000 + buckets)
+    split = np.unique(np.concatenate([[0], rng.integers(0, rows, buckets - 1)])).astype(np.uint32)
+    nb = len(split)
+    bits = max(1, int(rows - 1).bit_length())
+    lut_bits = min(12, bits, int(nb - 1).bit_length() + 3)
+    shift = bits - lut_bits
+    cells = np.arange((1 << lut_bits) + 1, dtype=np.int64) << shift
+    lut = (np.searchsorted(split, cells, side="right") - 1).astype(np.uint16)
+    inside = np.searchsorted(split, cells[1:], side="left") - 1 - lut[:-1].astype(np.int64)
+    span = max(1, int(inside.max()))
+    if span > 4:
+        pytest.skip("bisected on the device")
+    good = np.unique(np.clip(np.concatenate([split.astype(np.int64) + d for d in (-1, 0, 1)] +
+                                            [rng.integers(0, rows, 1000), [rows - 1]]), 0, rows - 1))
+    bad = np.array([rows, rows + 1, 1 << 31, (1 << 32) - 1, (1 << 32) - 7], np.int64)
+    index = np.concatenate([good, bad]).astype(np.uint32)
+    out = np.empty(len(index), np.uint32)
+    padded = np.concatenate([split, np.full(4, 0xffffffff, np.uint32)])
+    ptr = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    rules.partition_buckets(ptr(padded), ptr(lut), ctypes.c_int(shift), ctypes.c_int(span), ctypes.c_uint32(rows), ptr(index),
+                            ctypes.c_int(len(index)), ptr(out))
+    assert np.array_equal(out[:len(good)], np.searchsorted(split, good, side="right") - 1)
+    assert np.all(out[len(good):] == nb - 1)
