@@ -78,23 +78,21 @@ TBE_BOTH int sample_position(uint64_t stretch, uint32_t i, int n)
     return pos < (uint64_t)n ? (int)pos : n - 1;
 }
 
-// The row a lookup is sorted by.  Indices are rows of their table; of any other value the partition makes the last row,
-// so that it finds a bucket, whose counter and positions are the table's own, for every 32-bit word.
-TBE_BOTH uint32_t sort_row(uint32_t index, uint32_t last_row) { return index < last_row ? index : last_row; }
-
 // Bucket of a row: that of the first row of its cell (lut), moved on over the SPAN borders that can lie inside one, all
-// compared at once.  split: first row of every bucket, then SPAN entries of all ones.
+// compared at once.  below: the row before the first row of every bucket (0 - 1 for the first bucket), then SPAN entries of
+// all ones: those are below no 32-bit word, so an index that is no row of the table finds one of its buckets all the same.
 template <int SPAN, typename Cell>
-TBE_BOTH uint32_t linear_bucket(const uint32_t* split, const Cell* lut, uint32_t row, int shift)
+TBE_BOTH uint32_t linear_bucket(const uint32_t* below, const Cell* lut, uint32_t row, int shift, uint32_t last_cell)
 {
-    const uint32_t first = lut[row >> shift];
+    const uint32_t cell = row >> shift;
+    const uint32_t first = lut[cell < last_cell ? cell : last_cell];
     uint32_t border[SPAN + 1], d = first;
 #pragma unroll
     for (int k = 1; k <= SPAN; ++k)
-        border[k] = split[first + k];
+        border[k] = below[first + k];
 #pragma unroll
     for (int k = 1; k <= SPAN; ++k)
-        d += border[k] <= row ? 1u : 0u;
+        d += border[k] < row ? 1u : 0u;
     return d;
 }
 

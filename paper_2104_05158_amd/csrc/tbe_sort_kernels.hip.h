@@ -515,7 +515,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     for (int r = 0; r < kSortPerThread; ++r) {
         const int pos = sample_position(stretch, (uint32_t)min(wave * rounds * kWave + r * kWave + lane, S - 1), n);
         // past the sample: the largest key, sorted behind it
-        w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? sort_row(a.indices[start + pos], rows - 1) : ~0u;
+        w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? min(a.indices[start + pos], rows - 1) : ~0u;
     }
     block_sort<uint32_t>(w, groups, 0, bits, s_key, s_cnt, s_wsum);
     // ---- borders: row 0, every q-th sample once, and the row after one that fills a whole stretch of samples
@@ -614,31 +614,32 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
 // that crowd in a few cells are bisected.
 struct Borders {
     static constexpr int kLinear = 4;
-    uint32_t split[kMaxBuckets + kLinear];
+    uint32_t below[kMaxBuckets + kLinear];     // first row of the bucket, minus 1
     uint16_t lut[kLutSize];
 
     __device__ __forceinline__ void load(const SortArgs& a, const SortTable& st, int bits)
     {
         const uint32_t* from = a.split + (int64_t)st.part * kMaxBuckets;
         for (int i = threadIdx.x; i < st.nb + kLinear; i += kSortThreads)
-            split[i] = i < st.nb ? from[i] : ~0u;
+            below[i] = i < st.nb ? from[i] - 1u : ~0u;
         const uint32_t* cells = reinterpret_cast<const uint32_t*>(a.lut + (int64_t)st.part * kLutSize);
         const int n = (1 << (bits - (st.lut & 0xff))) / 2 + 1;
         for (int i = threadIdx.x; i < n; i += kSortThreads)
             reinterpret_cast<uint32_t*>(lut)[i] = cells[i];
     }
 
-    // SPAN: most borders inside a cell; 0: more than kLinear.  row: as sort_row returns it
+    // SPAN: most borders inside a cell; 0: more than kLinear
     template <int SPAN>
-    __device__ __forceinline__ uint32_t bucket(uint32_t row, int shift) const
+    __device__ __forceinline__ uint32_t bucket(uint32_t row, int shift, uint32_t last_cell) const
     {
         if constexpr (SPAN > 0) {
-            return linear_bucket<SPAN>(split, lut, row, shift);
+            return linear_bucket<SPAN>(below, lut, row, shift, last_cell);
         } else {
-            uint32_t d = lut[row >> shift], hi = lut[(row >> shift) + 1];
+            const uint32_t cell = min(row >> shift, last_cell);
+            uint32_t d = lut[cell], hi = lut[cell + 1];
             while (__ballot(d < hi) != 0ull) {
                 const uint32_t mid = (d + hi + 1) >> 1;
-                const bool up = split[mid] <= row;
+                const bool up = below[mid] < row;
                 d = up ? mid : d;
                 hi = up ? hi : max(mid, 1u) - 1u;
             }
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortArgs a)
     const SortTable st = a.tables[c.t];
     const int bits = a.meta[c.t].key_bits;
     const int shift = st.lut & 0xff, span = st.lut >> 8;
-    const uint32_t last_row = a.row_base[c.t + 1] - a.row_base[c.t] - 1u;
+    const uint32_t last_cell = (1u << (bits - shift)) - 1u;
     const int end = c.first + c.cnt;
     s_borders.load(a, st, bits);
     for (int i = threadIdx.x; i < kMaxBuckets; i += kSortThreads)
@@ -696,10 +697,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortArgs a)
                 key[r] = load_at(idx, (uint32_t)(first + (int)threadIdx.x), r * kSortThreads);
 #pragma unroll
             for (int r = 0; r < kSortPerThread; ++r)
-                atomicAdd(&s_hist[s_borders.bucket<kSpan>(sort_row(key[r], last_row), shift)], 1u);
+                atomicAdd(&s_hist[s_borders.bucket<kSpan>(key[r], shift, last_cell)], 1u);
         }
         for (int i = first + (int)threadIdx.x; i - (int)threadIdx.x < c.cnt; i += kSortThreads) {   // whole wavefronts: bucket() may ballot
-            const uint32_t d = s_borders.bucket<kSpan>(sort_row(idx[min(i, c.cnt - 1)], last_row), shift);
+            const uint32_t d = s_borders.bucket<kSpan>(idx[min(i, c.cnt - 1)], shift, last_cell);
             if (i < c.cnt)
                 atomicAdd(&s_hist[d], 1u);
         }
@@ -802,7 +803,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
     const SortTable st = a.tables[c.t];
     const int bits = a.meta[c.t].key_bits;
     const int shift = st.lut & 0xff, span = st.lut >> 8;
-    const uint32_t last_row = a.row_base[c.t + 1] - a.row_base[c.t] - 1u;
+    const uint32_t last_cell = (1u << (bits - shift)) - 1u;
     const int digit_bits = ceil_log2((uint32_t)st.nb + 1u);   // bucket nb: positions past the end
     const int end = c.first + c.cnt;
     const int64_t* __restrict__ offsets = a.offsets + (int64_t)c.t * a.B;
@@ -852,8 +853,8 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
                 if (r0 < rounds) {
 #pragma unroll
                     for (int r = r0; r < r0 + kPartGroup; ++r) {
-                        const uint32_t row = sort_row(dg[r], last_row), d = s_borders.bucket<kSpan>(row, shift);
-                        w[r] = ((W)(row - s_borders.split[d]) << a.vb) + (W)(max(s_mark[q + r * kWave], carry) - 1u);
+                        const uint32_t row = dg[r], d = s_borders.bucket<kSpan>(row, shift, last_cell);
+                        w[r] = ((W)(row + ~s_borders.below[d]) << a.vb) + (W)(max(s_mark[q + r * kWave], carry) - 1u);
                         dg[r] = d;
                     }
                 }

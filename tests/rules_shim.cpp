@@ -18,14 +18,14 @@ void sample_positions(int n, int samples, int32_t* out)
         out[i] = tbe::sample_position(stretch, (uint32_t)i, n);
 }
 
-// buckets of n indices in a table of `rows` rows, as the partition finds them; lut: first bucket of every cell
-void partition_buckets(const uint32_t* split, const uint16_t* lut, int shift, int span, uint32_t rows, const uint32_t* index, int n, uint32_t* out)
+// buckets of n indices, as the partition finds them; lut: first bucket of every cell
+void partition_buckets(const uint32_t* below, const uint16_t* lut, int shift, uint32_t last_cell, int span, const uint32_t* index, int n, uint32_t* out)
 {
-    for (int i = 0; i < n; ++i) {
-        const uint32_t row = tbe::sort_row(index[i], rows - 1);
-        out[i] = span == 1 ? tbe::linear_bucket<1>(split, lut, row, shift) : span == 2 ? tbe::linear_bucket<2>(split, lut, row, shift)
-               : span == 3 ? tbe::linear_bucket<3>(split, lut, row, shift) : tbe::linear_bucket<4>(split, lut, row, shift);
-    }
+    for (int i = 0; i < n; ++i)
+        out[i] = span == 1 ? tbe::linear_bucket<1>(below, lut, index[i], shift, last_cell)
+               : span == 2 ? tbe::linear_bucket<2>(below, lut, index[i], shift, last_cell)
+               : span == 3 ? tbe::linear_bucket<3>(below, lut, index[i], shift, last_cell)
+                           : tbe::linear_bucket<4>(below, lut, index[i], shift, last_cell);
 }
 
 }
