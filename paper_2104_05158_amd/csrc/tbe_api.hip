@@ -108,7 +108,7 @@ struct tbe_s {
     // workspace layout (byte offsets)
     size_t off_meta = 0, off_rowbase = 0, off_counters = 0, off_keys[2] = {0, 0}, off_vals[2] = {0, 0};
     size_t off_tstart = 0, off_stables = 0, off_schunks = 0, off_sunits = 0, off_split = 0, off_lut = 0, off_bstart = 0;
-    size_t off_hist = 0, off_tile_bag = 0, off_unit_cnt = 0, off_unit_base = 0, off_unit_runs = 0, off_table_runs = 0, off_words64 = 0;
+    size_t off_hist = 0, off_multi = 0, off_tile_bag = 0, off_unit_runs = 0, off_table_runs = 0, off_words64 = 0;
     size_t off_unit_first = 0, off_partials = 0;
     size_t off_long_list = 0, off_zero = 0, workspace_bytes = 0;
     size_t off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
@@ -266,9 +266,8 @@ void plan_workspace(tbe_s* h)
     h->off_lut = take(2 * (size_t)kLutSize * parts);
     h->off_bstart = take(4 * (size_t)kMaxBuckets * parts);
     h->off_hist = take(4 * (size_t)kMaxBuckets * sort_chunks);
+    h->off_multi = take(4 * (size_t)(nmax / ((int64_t)kSortTile * kColAhead) + 1));
     h->off_tile_bag = take(4 * (size_t)(ceil_div(nmax, kSortTile) + (kSortTilesPerChunk + 1) * (int64_t)(h->T + 1)));
-    h->off_unit_cnt = take(4 * (size_t)h->T);
-    h->off_unit_base = take(4 * (size_t)(h->T + 1));
     h->off_unit_runs = take(4 * (size_t)slots);
     h->off_table_runs = take(4 * (size_t)h->T);
     h->off_words64 = ss.wide ? take(8 * nelem) : 0;
@@ -591,9 +590,8 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.lut = h->ws<uint16_t>(h->off_lut);
     a.bstart = h->ws<uint32_t>(h->off_bstart);
     a.hist = h->ws<uint32_t>(h->off_hist);
+    a.multi = h->ws<int32_t>(h->off_multi);
     a.tile_bag = h->ws<int32_t>(h->off_tile_bag);
-    a.unit_cnt = h->ws<uint32_t>(h->off_unit_cnt);
-    a.unit_base = h->ws<uint32_t>(h->off_unit_base);
     a.unit_runs = h->ws<uint32_t>(h->off_unit_runs);
     a.table_runs = h->ws<uint32_t>(h->off_table_runs);
     a.tstart = h->ws<int32_t>(h->off_tstart);
@@ -639,6 +637,9 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     }
     {
         ScopedTimer tm(h, SLOT_RADIX_SCAN, st);
+        const int64_t multi = std::min<int64_t>(h->T, n / ((int64_t)kSortTile * ss.tiles_per_chunk * kColAhead));
+        if (multi > 0)                                   // tables of more than kColAhead chunks, at most
+            hipLaunchKernelGGL(sort_columns_kernel, dim3((unsigned)(multi * (kMaxBuckets / kColBuckets))), dim3(kColThreads), 0, st, a);
         hipLaunchKernelGGL(sort_units_kernel, dim3((unsigned)h->T), dim3(kUnitsThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_units_kernel");
     }

@@ -64,9 +64,10 @@ struct Counters {       // workspace scalars
     uint32_t dense_groups;
     uint32_t win_runs;          // windowed runs / their pieces of this update (written by window_plan_kernel)
     uint32_t win_pieces;
-    int32_t sort_chunks;        // chunks of the partition (written by sort_plan_kernel, which clears the next two)
-    uint32_t sort_arrived;      // workgroups of sort_units_kernel that have finished
-    uint32_t pad1[21];          // (the claim counters below start a 128-byte line of their own)
+    int32_t sort_chunks;        // written by sort_plan_kernel, which clears sort_units and sort_ticket: chunks of the partition,
+    int32_t sort_multi;         // tables of more chunks than sort_units_kernel adds up itself
+    uint32_t sort_units;
+    uint32_t pad1[20];          // (the claim counters below start a 128-byte line of their own)
     uint32_t sort_ticket;       // next unit of sort_local_kernel
     uint32_t pad2[31];
     // window_runs_kernel: next unclaimed piece of each L2 domain, one counter per 128-byte line

@@ -10,7 +10,8 @@
 //                        buckets so that a bucket holds about `target` lookups whatever their distribution.  A row
 //                        that is looked up more often than that gets a bucket of its own, which needs no sorting.
 //   sort_hist_kernel     lookups per bucket and chunk (a chunk is a few tiles of kSortTile positions)
-//   sort_units_kernel    bucket starts, positions of every chunk inside its buckets, and the list of work units
+//   sort_columns_kernel  positions of every chunk inside its buckets, lookups of every bucket
+//   sort_units_kernel    bucket starts and work units
 //   sort_scatter_kernel  stable partition: a lookup becomes one word, (row - first row of the bucket) and bag
 //                        number packed in 32 bits
 //   sort_local_kernel    one workgroup per unit: sorts the words in LDS, writes keys and payloads, counts the runs
@@ -45,15 +46,19 @@ constexpr int kLutSize = (1 << kLutBits) + 8;
 constexpr int kSamplesPerBucket = 16;             // a bucket's size then spreads by 1/4 around the target
 constexpr int kLocalDigits = 256;
 constexpr int kUnitsThreads = 1024;
+constexpr int kColThreads = 1024;                 // 16 wavefronts that share the chunks of a table ...
+constexpr int kColBuckets = kWave;                // ... for 64 of its buckets ...
+constexpr int kColAhead = 16;                     // ... and read this many at a time; a table of no more needs no such workgroup
 
 struct SortTable {       // 32 bytes
     int32_t start, n;    // first position, lookups
-    int32_t slot_base;   // first unit slot
     int32_t chunk_base;  // first chunk
     int32_t nchunks;
     int32_t nb;          // buckets (0: no lookups)
+    int16_t lut_shift;   // of its lookup table
+    int16_t lut_span;    // most borders inside a cell
     int32_t part;        // index of its border / lookup tables
-    int32_t lut;         // lookup-table shift | most borders inside a cell << 8
+    int32_t pad;
 };
 
 struct SortChunk {       // 16 bytes
@@ -66,7 +71,8 @@ struct SortUnit {        // 32 bytes
     int32_t bits;        // bits of the row offsets to sort
     int32_t t;
     int32_t flags;
-    int32_t pad[2];
+    int32_t first;       // the table's first unit (they are numbered one after the other)
+    int32_t pad;
 };
 constexpr int kUnitContinued = 1;     // further part of a one-row bucket: its first lookup starts no run
 
@@ -80,11 +86,10 @@ struct SortArgs {
     SortUnit* units;
     uint32_t* split;         // [parts][kMaxBuckets] first row of every bucket
     uint16_t* lut;           // [parts][kLutSize] bucket of the first row of every cell of rows (and of the row past the last)
-    uint32_t* bstart;        // [parts][kMaxBuckets] first position of every bucket
+    uint32_t* bstart;        // [parts][kMaxBuckets] lookups, then first position of every bucket
     uint32_t* hist;          // [chunks][kMaxBuckets]
+    int32_t* multi;          // tables of more than kColAhead chunks
     int32_t* tile_bag;       // [chunks * tiles_per_chunk] bag of the first position of every tile
-    uint32_t* unit_cnt;      // [T]
-    uint32_t* unit_base;     // [T + 1]
     uint32_t* unit_runs;     // [slots] runs of every unit
     uint32_t* table_runs;    // [T]
     int32_t* tstart;         // [T + 1]
@@ -416,7 +421,7 @@ __device__ __forceinline__ uint32_t bags_of_positions(const int64_t* __restrict_
 
 struct TablePlan {
     int want, cuts;      // buckets asked for, ranges of the packed key
-    int slots, chunks;
+    int chunks;
 };
 
 __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32_t rows)
@@ -424,7 +429,6 @@ __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32
     TablePlan p;
     p.cuts = a.kb >= 31 ? 1 : (int)((rows + (1u << a.kb) - 1) >> a.kb);
     p.want = min(max((n + a.target - 1) / a.target, 1), kMaxBuckets - p.cuts);
-    p.slots = n == 0 ? 0 : p.want + p.cuts + n / kSortTile;
     p.chunks = n == 0 ? 0 : (n + kSortTile * a.tiles_per_chunk - 1) / (kSortTile * a.tiles_per_chunk);
     return p;
 }
@@ -456,17 +460,17 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         s_sum[tid] = 0;
     __syncthreads();
     {   // what the tables before this one take
-        uint32_t slots = 0, chunks = 0, parts = 0;
+        uint32_t multi = 0, chunks = 0, parts = 0;
         for (int i = tid; i < t; i += kSortThreads) {
             const int n = (int)(a.offsets[(int64_t)(i + 1) * a.B] - a.offsets[(int64_t)i * a.B]);
             const TablePlan p = table_plan(a, n, a.row_base[i + 1] - a.row_base[i]);
-            slots += p.slots; chunks += p.chunks; parts += n > 0;
+            multi += p.chunks > kColAhead; chunks += p.chunks; parts += n > 0;
         }
-        slots = last_lane(wave_scan_add(slots));
+        multi = last_lane(wave_scan_add(multi));
         chunks = last_lane(wave_scan_add(chunks));
         parts = last_lane(wave_scan_add(parts));
-        if (lane == 0 && slots > 0) {
-            atomicAdd(&s_sum[0], slots); atomicAdd(&s_sum[1], chunks); atomicAdd(&s_sum[2], parts);
+        if (lane == 0 && parts > 0) {
+            atomicAdd(&s_sum[0], multi); atomicAdd(&s_sum[1], chunks); atomicAdd(&s_sum[2], parts);
         }
     }
     __syncthreads();
@@ -477,18 +481,20 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     const TablePlan p = table_plan(a, n, rows);
     SortTable st;
     st.start = start; st.n = n;
-    st.slot_base = (int)s_sum[0]; st.chunk_base = (int)s_sum[1]; st.part = (int)s_sum[2];
+    st.pad = 0; st.chunk_base = (int)s_sum[1]; st.part = (int)s_sum[2];
     st.nchunks = p.chunks;
-    st.nb = 0; st.lut = 0;
+    st.nb = 0; st.lut_shift = 0; st.lut_span = 0;
     if (tid == 0) {
         a.tstart[t] = start;
-        a.unit_cnt[t] = 0;
         a.table_runs[t] = 0;
+        if (p.chunks > kColAhead)
+            a.multi[s_sum[0]] = t;
         if (t == a.T - 1) {
             a.tstart[a.T] = (int)o1;
             a.counters->sort_chunks = st.chunk_base + p.chunks;
+            a.counters->sort_multi = (int)s_sum[0] + (p.chunks > kColAhead);
+            a.counters->sort_units = 0;
             a.counters->sort_ticket = 0;
-            a.counters->sort_arrived = 0;
         }
     }
     for (int i = tid; i < p.chunks; i += kSortThreads) {
@@ -601,7 +607,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     __syncthreads();
     if (tid == 0) {
         st.nb = nb;
-        st.lut = shift | (int)s_sum[0] << 8;
+        st.lut_shift = (int16_t)shift;
+        st.lut_span = (int16_t)s_sum[0];
         a.tables[t] = st;
     }
 }
@@ -623,7 +630,7 @@ struct Borders {
         for (int i = threadIdx.x; i < st.nb + kLinear; i += kSortThreads)
             below[i] = i < st.nb ? from[i] - 1u : ~0u;
         const uint32_t* cells = reinterpret_cast<const uint32_t*>(a.lut + (int64_t)st.part * kLutSize);
-        const int n = (1 << (bits - (st.lut & 0xff))) / 2 + 1;
+        const int n = (1 << (bits - st.lut_shift)) / 2 + 1;
         for (int i = threadIdx.x; i < n; i += kSortThreads)
             reinterpret_cast<uint32_t*>(lut)[i] = cells[i];
     }
@@ -672,7 +679,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortArgs a)
     const SortChunk c = a.chunks[blockIdx.x];
     const SortTable st = a.tables[c.t];
     const int bits = a.meta[c.t].key_bits;
-    const int shift = st.lut & 0xff, span = st.lut >> 8;
+    const int shift = st.lut_shift, span = st.lut_span;
     const uint32_t last_cell = (1u << (bits - shift)) - 1u;
     const int end = c.first + c.cnt;
     s_borders.load(a, st, bits);
@@ -710,80 +717,117 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortArgs a)
         a.hist[(int64_t)blockIdx.x * kMaxBuckets + i] = s_hist[i];
 }
 
-// One workgroup per table, one thread per bucket: counts of the chunks -> positions of the chunks inside the bucket,
-// bucket starts, work units.  The workgroup that finishes last numbers the units of all tables.
+// Counts of the chunks -> positions of the chunks inside the bucket, and the bucket's lookups, for a table of many chunks.
+// A lane has a bucket and the wavefronts of a workgroup share the chunks out, kColAhead of them at a time: bound by trips
+// to the histogram one after the other.  (sort_units_kernel walked them with one thread per bucket, eight chunks a trip:
+// 49 / 152 / 783 us for one table of 3 M / 10 M / 100 M lookups, now 13 / 24 / 76 in the two.)
+__global__ __launch_bounds__(kColThreads) void sort_columns_kernel(SortArgs a)
+{
+    constexpr int kWaves = kColThreads / kWave;
+    __shared__ uint32_t s_sum[kWaves][kColBuckets];
+    if ((int)(blockIdx.x / (kMaxBuckets / kColBuckets)) >= a.counters->sort_multi)
+        return;
+    const SortTable st = a.tables[a.multi[blockIdx.x / (kMaxBuckets / kColBuckets)]];
+    const int d = (int)(blockIdx.x % (kMaxBuckets / kColBuckets)) * kColBuckets + (int)(threadIdx.x & (kWave - 1));
+    const int wave = uniform(threadIdx.x >> 6);
+    if (d - (int)(threadIdx.x & (kWave - 1)) >= st.nb)
+        return;
+    const bool mine = d < st.nb;
+    const int each = (st.nchunks + kWaves - 1) / kWaves;
+    const int c0 = min(wave * each, st.nchunks), c1 = min(c0 + each, st.nchunks);
+    uint32_t* col = a.hist + (int64_t)st.chunk_base * kMaxBuckets + min(d, st.nb - 1);
+    uint32_t x[kColAhead], sum = 0;
+    for (int c = c0; c < c1; c += kColAhead) {
+#pragma unroll
+        for (int i = 0; i < kColAhead; ++i)
+            x[i] = col[(int64_t)min(c + i, c1 - 1) * kMaxBuckets];
+#pragma unroll
+        for (int i = 0; i < kColAhead; ++i)
+            sum += c + i < c1 ? x[i] : 0u;
+    }
+    s_sum[wave][threadIdx.x & (kWave - 1)] = sum;
+    __syncthreads();
+    uint32_t run = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = s_sum[w][threadIdx.x & (kWave - 1)];
+        run += w < wave ? c : 0u;
+        tot += c;
+    }
+    if (mine && wave == 0)
+        a.bstart[(int64_t)st.part * kMaxBuckets + d] = tot;
+    for (int c = c0; c < c1; c += kColAhead) {
+        if (each > kColAhead) {                      // (otherwise x still holds them)
+#pragma unroll
+            for (int i = 0; i < kColAhead; ++i)
+                x[i] = col[(int64_t)min(c + i, c1 - 1) * kMaxBuckets];
+        }
+#pragma unroll
+        for (int i = 0; i < kColAhead; ++i) {
+            if (mine && c + i < c1)
+                col[(int64_t)(c + i) * kMaxBuckets] = run;
+            run += x[i];
+        }
+    }
+}
+
+// One workgroup per table, one thread per bucket: bucket starts and work units (and, for a table of few chunks, what
+// sort_columns_kernel does for the others).  A table takes the next unit numbers there are: which ones depends on the
+// order of the workgroups, but nothing else does -- units are independent, and runs are counted table by table.  (Numbers
+// in the order of the tables took a last workgroup that waited for all others behind two fences, 13 us of 27.)
 __global__ __launch_bounds__(kUnitsThreads) void sort_units_kernel(SortArgs a)
 {
     __shared__ uint32_t s_wsum[2][kUnitsThreads / kWave];
-    __shared__ uint32_t s_last;
+    __shared__ uint32_t s_first;
     const int t = blockIdx.x;
     const int d = threadIdx.x;
     const SortTable st = a.tables[t];
-    if (st.nb > 0) {
-        uint32_t run = 0;
-        if (d < st.nb) {
-            uint32_t* col = a.hist + (int64_t)st.chunk_base * kMaxBuckets + d;
-            constexpr int kAhead = 8;
-            for (int c = 0; c < st.nchunks; c += kAhead) {
-                uint32_t x[kAhead];
+    if (st.nb == 0)
+        return;
+    uint32_t* bstart = a.bstart + (int64_t)st.part * kMaxBuckets;
+    const uint32_t* split = a.split + (int64_t)st.part * kMaxBuckets;
+    uint32_t run = 0;
+    if (st.nchunks > kColAhead) {
+        run = d < st.nb ? bstart[d] : 0u;
+    } else if (d < st.nb) {
+        uint32_t* col = a.hist + (int64_t)st.chunk_base * kMaxBuckets + d;
+        uint32_t x[kColAhead];
 #pragma unroll
-                for (int i = 0; i < kAhead; ++i)
-                    x[i] = c + i < st.nchunks ? col[(int64_t)(c + i) * kMaxBuckets] : 0u;
+        for (int i = 0; i < kColAhead; ++i)
+            x[i] = col[(int64_t)min(i, st.nchunks - 1) * kMaxBuckets];
 #pragma unroll
-                for (int i = 0; i < kAhead; ++i) {
-                    if (c + i < st.nchunks)
-                        col[(int64_t)(c + i) * kMaxBuckets] = run;
-                    run += x[i];
-                }
+        for (int i = 0; i < kColAhead; ++i) {
+            if (i < st.nchunks) {
+                col[(int64_t)i * kMaxBuckets] = run;
+                run += x[i];
             }
         }
-        uint32_t tot;
-        const uint32_t first = (uint32_t)st.start + block_scan<kUnitsThreads>(run, s_wsum[0], tot);
-        uint32_t lo = 0, range = 1, pieces = 0;
-        if (d < st.nb) {
-            const uint32_t* split = a.split + (int64_t)st.part * kMaxBuckets;
-            a.bstart[(int64_t)st.part * kMaxBuckets + d] = first;
-            lo = split[d];
-            range = (d + 1 < st.nb ? split[d + 1] : a.row_base[t + 1] - a.row_base[t]) - lo;
-            pieces = run == 0 ? 0u : range == 1 ? (run + kSortTile - 1) / kSortTile : 1u;
-        }
-        const uint32_t slot = block_scan<kUnitsThreads>(pieces, s_wsum[1], tot);
-        for (uint32_t i = 0; i < pieces; ++i) {
-            SortUnit u;
-            u.start = (int32_t)(first + i * kSortTile);
-            u.m = (int32_t)(pieces > 1 || range == 1 ? min((uint32_t)kSortTile, run - i * kSortTile) : run);
-            u.key0 = a.row_base[t] + lo;
-            u.bits = ceil_log2(range);
-            u.t = t;
-            u.flags = i > 0 ? kUnitContinued : 0;
-            u.pad[0] = u.pad[1] = 0;
-            a.units[st.slot_base + (int)(slot + i)] = u;
-        }
-        if (d == 0)
-            __hip_atomic_store(&a.unit_cnt[t], tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
-    if (d == 0) {
-        __threadfence();
-        s_last = atomicAdd(&a.counters->sort_arrived, 1u) == (uint32_t)a.T - 1u;
+    uint32_t tot;
+    const uint32_t start = (uint32_t)st.start + block_scan<kUnitsThreads>(run, s_wsum[0], tot);
+    uint32_t lo = 0, range = 1, pieces = 0;
+    if (d < st.nb) {
+        bstart[d] = start;
+        lo = split[d];
+        range = (d + 1 < st.nb ? split[d + 1] : a.row_base[t + 1] - a.row_base[t]) - lo;
+        pieces = run == 0 ? 0u : range == 1 ? (run + kSortTile - 1) / kSortTile : 1u;
     }
-    __syncthreads();
-    if (!s_last)
-        return;
-    __threadfence();
-    uint32_t carry = 0;
-    for (int base = 0; base < a.T; base += kUnitsThreads) {
-        const int i = base + d;
-        const uint32_t c = i < a.T ? __hip_atomic_load(&a.unit_cnt[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-        uint32_t tot;
-        const uint32_t ex = block_scan<kUnitsThreads>(c, s_wsum[0], tot);
-        if (i < a.T)
-            a.unit_base[i] = carry + ex;
-        carry += tot;
-        __syncthreads();
-    }
+    const uint32_t before = block_scan<kUnitsThreads>(pieces, s_wsum[1], tot);
     if (d == 0)
-        a.unit_base[a.T] = carry;
+        s_first = atomicAdd(&a.counters->sort_units, tot);
+    __syncthreads();
+    SortUnit u;
+    u.key0 = a.row_base[t] + lo;
+    u.bits = ceil_log2(range);
+    u.t = t;
+    u.first = (int32_t)s_first;
+    u.pad = 0;
+    for (uint32_t i = 0; i < pieces; ++i) {
+        u.start = (int32_t)(start + i * kSortTile);
+        u.m = (int32_t)(range == 1 ? min((uint32_t)kSortTile, run - i * kSortTile) : run);
+        u.flags = i > 0 ? kUnitContinued : 0;
+        a.units[s_first + before + i] = u;
+    }
 }
 
 template <typename W>
@@ -802,7 +846,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
     const SortChunk c = a.chunks[blockIdx.x];
     const SortTable st = a.tables[c.t];
     const int bits = a.meta[c.t].key_bits;
-    const int shift = st.lut & 0xff, span = st.lut >> 8;
+    const int shift = st.lut_shift, span = st.lut_span;
     const uint32_t last_cell = (1u << (bits - shift)) - 1u;
     const int digit_bits = ceil_log2((uint32_t)st.nb + 1u);   // bucket nb: positions past the end
     const int end = c.first + c.cnt;
@@ -937,7 +981,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
     __shared__ int s_ticket;
     __shared__ SortUnit s_unit;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
-    const int total_units = (int)a.unit_base[a.T];
+    const int total_units = (int)a.counters->sort_units;
     const W vmask = ((W)1 << a.vb) - 1;
 
     // units are handed out one at a time (their sizes differ); the next number is asked for a unit ahead
@@ -948,11 +992,8 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
         const int u = s_ticket;
         if (u >= total_units)
             break;
-        if (wave == 0) {
-            const int t = find_table(a.unit_base, a.T, (uint32_t)u);
-            if (lane < 8)
-                reinterpret_cast<int*>(&s_unit)[lane] = reinterpret_cast<const int*>(&a.units[a.tables[t].slot_base + (u - (int)a.unit_base[t])])[lane];
-        }
+        if (tid < 8)
+            reinterpret_cast<int*>(&s_unit)[tid] = reinterpret_cast<const int*>(&a.units[u])[tid];
         if (tid == 0)
             s_heads = 0;
         __syncthreads();
@@ -1196,20 +1237,18 @@ __global__ __launch_bounds__(kRunThreads) void sort_runs_kernel(SortArgs a)
     __shared__ int32_t s_pos[kRunTile];
     __shared__ uint32_t s_wsum[2][kRunThreads / kWave];
     const int tid = threadIdx.x;
-    const int total_units = (int)a.unit_base[a.T];
+    const int total_units = (int)a.counters->sort_units;
     for (int u = blockIdx.x; u < total_units; u += gridDim.x) {
-        const int t = find_table(a.unit_base, a.T, (uint32_t)u);
-        const int u0 = (int)a.unit_base[t];
-        const SortUnit un = a.units[a.tables[t].slot_base + (u - u0)];
+        const SortUnit un = a.units[u];
         const uint32_t unit_runs = a.unit_runs[u];
         uint32_t part = 0, run;
-        for (int i = tid; i < t; i += kRunThreads)
+        for (int i = tid; i < un.t; i += kRunThreads)
             part += a.table_runs[i];
-        for (int i = u0 + tid; i < u; i += kRunThreads)
+        for (int i = un.first + tid; i < u; i += kRunThreads)
             part += a.unit_runs[i];
         __syncthreads();
         (void)block_scan<kRunThreads>(part, s_wsum[0], run);
-        if (tid == 0 && u == total_units - 1) {
+        if (tid == 0 && un.start + un.m == a.n) {    // the last unit of the last table
             const uint32_t all = run + unit_runs;
             a.seg_offsets[all] = a.n;
             a.unit_first_run[(a.n + kSpanUnit - 1) / kSpanUnit] = (int32_t)all;
