@@ -13,7 +13,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtbe.so")
 SOURCES = [os.path.join(CSRC, "tbe_api.hip"), os.path.join(CSRC, "tbe_inputs_api.hip")]
 HEADERS = [os.path.join(CSRC, "tbe_rules.h"), os.path.join(CSRC, "tbe_kernels.hip.h"),
-           os.path.join(CSRC, "tbe_sort_kernels.hip.h"), os.path.join(CSRC, "tbe_inputs_kernels.hip.h"),
+           os.path.join(CSRC, "tbe_sort_kernels.hip.h"), os.path.join(CSRC, "tbe_radix_kernels.hip.h"),
+           os.path.join(CSRC, "tbe_inputs_kernels.hip.h"),
            os.path.join(ROOT, "include", "tbe.h"), os.path.join(ROOT, "include", "tbe_inputs.h")]
 
 # packed fp32 ALU ops are switched off for all device code of this library

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "tbe_kernels.hip.h"
+#include "tbe_radix_kernels.hip.h"
 #include "tbe_sort_kernels.hip.h"
 
 using namespace tbe;
@@ -43,10 +44,14 @@ const char* const kSlotNames[SLOT_COUNT] = {"forward",       "sort_plan",  "radi
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-// Lookups per bucket: about 512 units in a small call, so that every CU has one or two, and no more than 7/16 of a tile
-// in a large one.  A bucket spreads by 1/4 around that; beyond a tile it takes the slow path through memory, which
+// Lookups per bucket: units come in rounds of the 768 resident workgroups (less some for the last, smaller one of every table
+// and for rows with a unit of their own), in as few rounds as units of at most 7/16 of a tile make, but no unit is worth
+// less than kSortTargetMin.  A bucket spreads by 1/4 around that; beyond a tile it takes the slow path through memory, which
 // one bucket in 1,000 did at half a tile (64 tables, 5.5 M lookups: 76 us for the units, 55 without such a straggler).
+// Sort with 512 units in a smaller call and 7/16 of a tile in a larger one -> this: 1000 rows, 8 tables, 2 M lookups 95 -> 81 us;
+// 60,000 rows 105 -> 87; 64 tables, 4 M 108 -> 105; 4 tables of 1000 rows, 4 M 117 -> 107.
 constexpr int kSortTargetMin = 1024, kSortTargetMax = 3584;
+constexpr int64_t kSortUnitsRound = 704;
 // Tiles per chunk of the partition: a histogram of up to 4 KiB is written and read per chunk, but there should be
 // some 4096 chunks for 512 resident workgroups (98 M lookups: histogram + partition 622 us with up to 4, 660 with 8).
 constexpr int64_t kSortChunksWanted = 4096;
@@ -100,6 +105,7 @@ struct tbe_s {
     bool fwd_wide = true;    // every table's row takes all lanes of a wavefront
     int key_bits = 1;                   // bits of the tallest table's row index
     int64_t max_rows = 1;
+    std::vector<int> pass_digit_bits;   // radix sort, per launch: the widest digit any table sorts in it
     std::vector<int64_t> woff;      // T+1, elements
     std::vector<int64_t> soff;      // T+1, rows
     std::vector<int32_t> coloff;    // T+1
@@ -109,6 +115,7 @@ struct tbe_s {
     size_t off_meta = 0, off_rowbase = 0, off_counters = 0, off_keys[2] = {0, 0}, off_vals[2] = {0, 0};
     size_t off_tstart = 0, off_stables = 0, off_schunks = 0, off_sunits = 0, off_split = 0, off_lut = 0, off_bstart = 0;
     size_t off_hist = 0, off_multi = 0, off_tile_bag = 0, off_unit_runs = 0, off_table_runs = 0, off_words64 = 0;
+    size_t off_tile_base = 0, off_tile_table = 0, off_radix_hist = 0, off_scan_tmp = 0, off_rl_counts = 0;
     size_t off_unit_first = 0, off_partials = 0;
     size_t off_long_list = 0, off_zero = 0, workspace_bytes = 0;
     size_t off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
@@ -222,9 +229,42 @@ SortShape sort_shape(const tbe_s* h, int64_t batch, int64_t n)
     s.wide = ceil_div(h->max_rows, (int64_t)1 << s.kb) > kMaxRangeCuts;
     if (s.wide)
         s.vb = s.kb = 32;
-    s.target = (int)std::min<int64_t>(kSortTargetMax, std::max<int64_t>(kSortTargetMin, n / 512));
+    const int64_t rounds = std::max<int64_t>(1, ceil_div(n, kSortTargetMax * kSortUnitsRound));
+    s.target = (int)std::max<int64_t>(kSortTargetMin, ceil_div(n, rounds * kSortUnitsRound));
     s.tiles_per_chunk = (int)std::min<int64_t>(kSortTilesPerChunk, std::max<int64_t>(1, n / (kSortTile * kSortChunksWanted)));
     return s;
+}
+
+// workspace of the partition, in sizes for the worst call (chunks and buckets never cross a table border; small calls use
+// smaller ones)
+template <typename Take>
+void plan_partition(tbe_s* h, Take take)
+{
+    const int64_t nmax = h->max_indices;
+    const SortShape ss = sort_shape(h, h->max_batch, nmax);
+    int64_t slots = 2 * (int64_t)h->T + 513 + ceil_div(nmax, kSortTargetMax) + nmax / kSortTile;
+    // fewest row-offset bits a call with 32-bit words can have (a smaller batch may use them where the largest does not)
+    int kb = ss.wide ? 0 : ss.kb;
+    while (ceil_div(h->max_rows, (int64_t)1 << kb) > kMaxRangeCuts)
+        ++kb;
+    for (int t = 0; t < h->T; ++t) {
+        const bool tall = h->meta[t].key_bits > kb;
+        slots += tall ? ceil_div(h->rows[t], (int64_t)1 << kb) : 1;
+    }
+    const int64_t parts = std::min<int64_t>(h->T, nmax);
+    const int64_t sort_chunks = std::min<int64_t>(ceil_div(nmax, kSortTile), 2 * kSortChunksWanted + nmax / (kSortTile * kSortTilesPerChunk)) + h->T;
+    h->off_stables = take(sizeof(SortTable) * (size_t)h->T);
+    h->off_schunks = take(sizeof(SortChunk) * (size_t)sort_chunks);
+    h->off_sunits = take(sizeof(SortUnit) * (size_t)slots);
+    h->off_split = take(4 * (size_t)kMaxBuckets * parts);
+    h->off_lut = take(2 * (size_t)kLutSize * parts);
+    h->off_bstart = take(4 * (size_t)kMaxBuckets * parts);
+    h->off_hist = take(4 * (size_t)kMaxBuckets * sort_chunks);
+    h->off_multi = take(4 * (size_t)(nmax / ((int64_t)kSortTile * kColAhead) + 1));
+    h->off_tile_bag = take(4 * (size_t)(ceil_div(nmax, kSortTile) + (kSortTilesPerChunk + 1) * (int64_t)(h->T + 1)));
+    h->off_unit_runs = take(4 * (size_t)slots);
+    h->off_table_runs = take(4 * (size_t)h->T);
+    h->off_words64 = ss.wide ? take(8 * ((size_t)nmax + 64)) : 0;
 }
 
 void plan_workspace(tbe_s* h)
@@ -245,32 +285,24 @@ void plan_workspace(tbe_s* h)
         h->off_keys[i] = take(4 * nelem);
         h->off_vals[i] = take(4 * nelem);
     }
-    // sort: sizes for the worst call (chunks and buckets never cross a table border; small calls use smaller ones)
-    const SortShape ss = sort_shape(h, h->max_batch, nmax);
-    int64_t slots = 2 * (int64_t)h->T + 513 + ceil_div(nmax, kSortTargetMax) + nmax / kSortTile;
-    // fewest row-offset bits a call with 32-bit words can have (a smaller batch may use them where the largest does not)
-    int kb = ss.wide ? 0 : ss.kb;
-    while (ceil_div(h->max_rows, (int64_t)1 << kb) > kMaxRangeCuts)
-        ++kb;
-    for (int t = 0; t < h->T; ++t) {
-        const bool tall = h->meta[t].key_bits > kb;
-        slots += tall ? ceil_div(h->rows[t], (int64_t)1 << kb) : 1;
-    }
-    const int64_t parts = std::min<int64_t>(h->T, nmax);
-    const int64_t sort_chunks = std::min<int64_t>(ceil_div(nmax, kSortTile), 2 * kSortChunksWanted + nmax / (kSortTile * kSortTilesPerChunk)) + h->T;
     h->off_tstart = take(4 * (size_t)(h->T + 1));
-    h->off_stables = take(sizeof(SortTable) * (size_t)h->T);
-    h->off_schunks = take(sizeof(SortChunk) * (size_t)sort_chunks);
-    h->off_sunits = take(sizeof(SortUnit) * (size_t)slots);
-    h->off_split = take(4 * (size_t)kMaxBuckets * parts);
-    h->off_lut = take(2 * (size_t)kLutSize * parts);
-    h->off_bstart = take(4 * (size_t)kMaxBuckets * parts);
-    h->off_hist = take(4 * (size_t)kMaxBuckets * sort_chunks);
-    h->off_multi = take(4 * (size_t)(nmax / ((int64_t)kSortTile * kColAhead) + 1));
-    h->off_tile_bag = take(4 * (size_t)(ceil_div(nmax, kSortTile) + (kSortTilesPerChunk + 1) * (int64_t)(h->T + 1)));
-    h->off_unit_runs = take(4 * (size_t)slots);
-    h->off_table_runs = take(4 * (size_t)h->T);
-    h->off_words64 = ss.wide ? take(8 * nelem) : 0;
+    const size_t off_sort = off;       // a call uses one of the two sorts: their tables share the memory from here on
+    size_t end_sort = off;
+    if (use_radix_sort(h->T, nmax, (int)ceil_div(h->key_bits, 8))) {  // (no smaller call of a handle takes it if the largest does not)
+        // tiles never cross a table border: at most one partly filled tile per table on top of nmax / tile
+        const int64_t max_tiles = ceil_div(nmax, kSortTile) + h->T;
+        const int64_t rl_tiles = std::max<int64_t>(1, ceil_div(nmax, kRlTile));
+        h->off_tile_base = take(4 * (size_t)(h->T + 1));
+        h->off_tile_table = take(sizeof(TileDesc) * (size_t)max_tiles);
+        h->off_radix_hist = take(4 * 256 * (size_t)max_tiles);
+        h->off_scan_tmp = take(4 * (size_t)(std::max(ceil_div(256 * max_tiles, kScanTile), ceil_div(rl_tiles, kScanTile)) + 1));
+        h->off_rl_counts = take(4 * (size_t)(rl_tiles + 16));
+        end_sort = off;
+        off = off_sort;
+    }
+    if (h->T <= kManyTables)
+        plan_partition(h, take);
+    off = std::max(off, end_sort);
     const int64_t chunks = std::max<int64_t>(1, ceil_div(nmax, kChunk));
     h->off_unit_first = take(4 * (size_t)(ceil_div(nmax, kSpanUnit) + 1));
     const int dpad = (int)align_up((size_t)h->dmax, 4);
@@ -436,6 +468,17 @@ tbe_status_t tbe_create(const tbe_config_t* cfg, tbe_handle_t* out_handle)
         h->max_rows = std::max(h->max_rows, cfg->rows[t]);
         h->key_bits = std::max(h->key_bits, table_bits[t]);
     }
+    // radix sort: table t orders its bits in P_t = ceil(bits / 8) passes during the last P_t of the P launches, bits split
+    // as evenly as possible (wider digits first)
+    const int P = (int)ceil_div(h->key_bits, 8);
+    h->pass_digit_bits.assign(P, 1);
+    for (int b : table_bits) {
+        const int pt = (b + 7) / 8, q = b / pt, rem = b - q * pt;
+        for (int lp = 0; lp < pt; ++lp) {
+            int& w = h->pass_digit_bits[P - pt + lp];
+            w = std::max(w, q + (lp < rem ? 1 : 0));
+        }
+    }
 
     h->woff.resize(h->T + 1);
     h->soff.resize(h->T + 1);
@@ -564,6 +607,100 @@ tbe_status_t tbe_forward(tbe_handle_t h, const int32_t* d_indices, const int64_t
     return launch_forward<__half, __half>(h, d_indices, d_offsets, n, batch, out, st);
 }
 
+// exclusive scan of a uint32 device array in place (three launches)
+static tbe_status_t device_scan(tbe_s* h, uint32_t* data, int64_t n, hipStream_t st)
+{
+    const int nb = (int)ceil_div(n, kScanTile);
+    uint32_t* tmp = h->ws<uint32_t>(h->off_scan_tmp);
+    hipLaunchKernelGGL(scan_reduce_kernel, dim3(nb), dim3(kScanThreads), 0, st, data, tmp, n);
+    hipLaunchKernelGGL(scan_top_kernel, dim3(1), dim3(kScanThreads), 0, st, tmp, nb);
+    hipLaunchKernelGGL(scan_apply_kernel, dim3(nb), dim3(kScanThreads), 0, st, data, tmp, n);
+    TBE_LAUNCH_CHECK(h, "device_scan");
+    return TBE_OK;
+}
+
+// the digit-by-digit sort: the same artefacts as the partition
+static tbe_status_t enqueue_radix_sort(tbe_s* h, const int32_t* d_indices, const int64_t* d_offsets, int32_t n,
+                                       int32_t batch, hipStream_t st)
+{
+    Counters* counters = h->ws<Counters>(h->off_counters);
+    const uint32_t* row_base = h->ws<uint32_t>(h->off_rowbase);
+    uint32_t* keys[2] = {h->ws<uint32_t>(h->off_keys[0]), h->ws<uint32_t>(h->off_keys[1])};
+    int32_t* vals[2] = {h->ws<int32_t>(h->off_vals[0]), h->ws<int32_t>(h->off_vals[1])};
+    SortPlan pl;
+    pl.tile_base = h->ws<int32_t>(h->off_tile_base);
+    pl.tstart = h->ws<int32_t>(h->off_tstart);
+    pl.tiles = h->ws<TileDesc>(h->off_tile_table);
+    // upper bound of the number of tiles for THIS call (the exact number is only known on the device)
+    const int max_tiles = (int)(ceil_div(n, kSortTile) + h->T);
+    {   // a2: table borders -> tile plan (keys are the caller's indices; payloads are made in the first pass)
+        ScopedTimer tm(h, SLOT_SORT_PLAN, st);
+        hipLaunchKernelGGL(sort_plan_tables_kernel, dim3(1), dim3(256), 0, st, d_offsets, batch, h->T,
+                           h->ws<int32_t>(h->off_tile_base), h->ws<int32_t>(h->off_tstart), counters);
+        hipLaunchKernelGGL(sort_plan_tiles_kernel, dim3((unsigned)ceil_div(max_tiles, 256)), dim3(256), 0, st,
+                           pl.tile_base, pl.tstart, d_offsets, batch, h->T, h->ws<TileDesc>(h->off_tile_table), max_tiles);
+        TBE_LAUNCH_CHECK(h, "sort_plan kernels");
+    }
+    // a3: stable, segmented by table; every table over the bits of its own row index, in its own number of passes, all
+    // tables finishing in the last launch (tables with fewer passes sit out the first ones)
+    const int passes = (int)ceil_div(h->key_bits, 8);
+    uint32_t* hist = h->ws<uint32_t>(h->off_radix_hist);
+    const TableMeta* meta = h->ws<TableMeta>(h->off_meta);
+    const uint32_t* indices = reinterpret_cast<const uint32_t*>(d_indices);
+    int cur = -1;  // pair that holds the current order (-1 = nothing sorted yet)
+    for (int p = 0; p < passes; ++p) {
+        const int nd_bits = h->pass_digit_bits[p];   // widest digit any table sorts in this launch
+        const int out = cur < 0 ? 0 : cur ^ 1;
+        const uint32_t* keys_cur = cur < 0 ? indices : keys[cur];
+        const int32_t* vals_cur = cur < 0 ? nullptr : vals[cur];
+        {
+            ScopedTimer tm(h, SLOT_RADIX_HIST, st);
+            hipLaunchKernelGGL(radix_hist_kernel, dim3(max_tiles), dim3(kSortThreads), 0, st, pl, meta, keys_cur,
+                               indices, hist, p, passes, nd_bits);
+            TBE_LAUNCH_CHECK(h, "radix_hist_kernel");
+        }
+        {
+            ScopedTimer tm(h, SLOT_RADIX_SCAN, st);
+            const tbe_status_t rc = device_scan(h, hist, (int64_t)max_tiles << nd_bits, st);
+            if (rc != TBE_OK)
+                return rc;
+        }
+        {
+            ScopedTimer tm(h, SLOT_RADIX_SCATTER, st);
+            // a bag number below 2^16 travels as 16 bits between the passes
+            auto launch = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(max_tiles), dim3(kSortThreads), 0, st, pl, meta, keys_cur, vals_cur,
+                                   indices, keys[out], vals[out], hist, d_offsets, row_base, batch, p, passes, nd_bits);
+            };
+            const bool last = p == passes - 1, v16 = batch <= 65536;
+            if (last && v16)
+                launch(radix_scatter_kernel<true, true>);
+            else if (last)
+                launch(radix_scatter_kernel<true, false>);
+            else if (v16)
+                launch(radix_scatter_kernel<false, true>);
+            else
+                launch(radix_scatter_kernel<false, false>);
+            TBE_LAUNCH_CHECK(h, "radix_scatter_kernel");
+        }
+        cur = out;
+    }
+    h->final_buf = cur;
+    {   // a4: run heads -> unique keys, segment offsets (in the free pair of the sort), first run of every span unit
+        ScopedTimer tm(h, SLOT_RUNLENGTH, st);
+        const int rl_tiles = (int)ceil_div(n, kRlTile);
+        uint32_t* rl_counts = h->ws<uint32_t>(h->off_rl_counts);
+        hipLaunchKernelGGL(runlength_count_kernel, dim3(rl_tiles), dim3(kRlThreads), 0, st, keys[cur], rl_counts, n);
+        const tbe_status_t rc = device_scan(h, rl_counts, rl_tiles, st);
+        if (rc != TBE_OK)
+            return rc;
+        hipLaunchKernelGGL(runlength_write_kernel, dim3(rl_tiles), dim3(kRlThreads), 0, st, keys[cur], rl_counts,
+                           keys[cur ^ 1], vals[cur ^ 1], h->ws<int32_t>(h->off_unit_first), counters, n);
+        TBE_LAUNCH_CHECK(h, "runlength kernels");
+    }
+    return TBE_OK;
+}
+
 // a2..a4: needs only the batch's (indices, offsets)
 static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64_t* d_offsets, int32_t n,
                                  int32_t batch, hipStream_t st)
@@ -577,6 +714,9 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         h->final_buf = 0;
         return TBE_OK;
     }
+    const bool small = n <= kSortTile && (int64_t)h->T * batch <= kSmallBags;
+    if (!small && use_radix_sort(h->T, n, (int)ceil_div(h->key_bits, 8)))
+        return enqueue_radix_sort(h, d_indices, d_offsets, n, batch, st);
     const SortShape ss = sort_shape(h, batch, n);
     SortArgs a;
     a.offsets = d_offsets;
@@ -615,7 +755,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.tiles_per_chunk = ss.tiles_per_chunk;
     const int passes = (int)ceil_div(h->key_bits, 8);    // what the profile counts for the sort itself
     h->final_buf = 0;
-    if (n <= kSortTile && (int64_t)h->T * batch <= kSmallBags) {
+    if (small) {
         ScopedTimer tm(h, SLOT_RADIX_SCATTER, st, passes);
         int bits = 1;                                    // of the linear row ids
         while (bits < 32 && ((int64_t)1 << bits) < h->soff[h->T])

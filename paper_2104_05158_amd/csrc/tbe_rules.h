@@ -62,6 +62,29 @@ inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, bool wide
 
 // ---------------------------------------------------------------- sort
 
+// Which sort a call takes: that of tbe_sort_kernels.hip.h, or the digit-by-digit one of tbe_radix_kernels.hip.h.
+// - Tables of at most 256 rows take one pass of the latter; the former's plan is wasted on them (100 rows: 8 tables, 50,000
+//   lookups 52 us by digits, 51 by partition; 200,000 55 / 54; 800,000 56 / 63; 4 M 74 / 105; 16 M 164 / 175).
+// - A table has at most 1024 buckets.  From 3.6 M lookups in it they grow beyond what a workgroup sorts well in LDS, from 8 M
+//   all of them take passes through memory, and the buckets of few tables are too few for 768 resident workgroups.  The
+//   lookups from which that costs more than the passes saved grow with about the third power of the number of tables: 10 M
+//   rows, uniform, 1 table of 10 M lookups 288 us by digits, 328 by partition; 2 of 16 M 745 / 735, of 60 M 2540 / 2730; 3 of
+//   30 M 1920 / 1840, of 60 M 3600 / 3820; 4 of 30 M 2600 / 2380, of 60 M 4650 / 4560; 8 of 30 M 4860 / 4220.  The fewer the
+//   passes the sooner: 1 table, 60,000 rows, 800,000 lookups 88 / 91, 2 M 99 / 110; 1 M rows, 800,000 115 / 98, 2 M 128 / 137;
+//   and with two passes two tables lose by 2 M already (60,000 rows: 2 M 97 / 95, 4 M 116 / 134, 16 M 280 / 320).
+// - The partition takes a plan and 20 KiB of memory per table: 4000 tables of 100 lookups 253 / 249 us, 10,000 557 / 661.
+constexpr int64_t kOnePassMin = 200000;
+constexpr int kManyTables = 4096;
+
+// passes: eight-bit digits of the tallest table's row index
+inline bool use_radix_sort(int64_t tables, int64_t lookups, int passes)
+{
+    constexpr int64_t kTallTable[] = {0, 0, 1000000, 2000000, 3500000};
+    const int64_t power = passes == 2 && tables == 2 ? tables : tables * tables * tables;
+    return tables > kManyTables || (passes <= 1 && lookups >= kOnePassMin) ||
+           (passes > 1 && tables <= 16 && lookups >= kTallTable[std::min(passes, 4)] * power);
+}
+
 // A published integer hash: lowbias32 of Wellons' hash-prospector (public domain).
 TBE_BOTH uint32_t mix_bits(uint32_t x)
 {

@@ -4,7 +4,9 @@
 // The input is table-major, so the lookups of a table already occupy one contiguous range of positions: only the
 // row index has to be sorted, table by table.  Every table is partitioned once into buckets that fit a workgroup's
 // LDS, and every bucket is sorted there -- the lookups cross HBM twice, whatever the number of index bits, where a
-// digit-by-digit radix sort crosses it once per eight bits and once more for the run lengths.
+// digit-by-digit radix sort crosses it once per eight bits and once more for the run lengths.  That holds up to about 6 M
+// lookups in a table; the buckets of a taller one exceed a tile and take the digits through memory one bucket per workgroup.
+// (use_radix_sort in tbe_rules.h names the calls that are better off with the radix sort of tbe_radix_kernels.hip.h.)
 //
 //   sort_plan_kernel     one workgroup per table: sorts a sample of its indices and picks the borders of its
 //                        buckets so that a bucket holds about `target` lookups whatever their distribution.  A row

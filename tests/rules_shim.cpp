@@ -11,6 +11,8 @@ void forward_launch(int64_t num_bags, int64_t lookups, int wide, int64_t* out /*
     out[2] = f.blocks;
 }
 
+int use_radix_sort(int64_t tables, int64_t lookups, int passes) { return tbe::use_radix_sort(tables, lookups, passes); }
+
 void sample_positions(int n, int samples, int32_t* out)
 {
     const uint64_t stretch = ((uint64_t)n << 32) / (uint32_t)samples;

@@ -114,3 +114,32 @@ def test_tables_of_few_and_of_many_chunks(gpu_device, chunks, extra):
     lens = np.concatenate([_lens(rng, 300, n) for n in per_table])
     idx = np.concatenate([np.minimum(rng.zipf(1.3, n) * 2_654_435_761 % h, h - 1) for h, n in zip(rows, per_table)])
     _check(gpu_device, rows, 300, lens, idx, "chunks")
+
+
+@pytest.mark.parametrize("rows,batch,n", [(10_000_000, 65536, 2_000_001), (70_000, 70_001, 2_000_000), (60_000, 300, 1_000_000),
+                                          (200, 65536, 200_003), (256, 70_001, 200_000)])   # payloads of 16 and 32 bits
+def test_one_tall_table_is_sorted_by_digits(gpu_device, rows, batch, n):
+    rng = np.random.default_rng(rows)
+    idx = np.minimum(rng.zipf(1.2, n) * 2_654_435_761 % rows, rows - 1)
+    _check(gpu_device, [rows], batch, _lens(rng, batch, n), idx, "digits")
+
+
+def test_more_tables_than_the_partition_takes(gpu_device):
+    rng = np.random.default_rng(5)
+    T, batch = 4100, 9
+    rows = rng.integers(1, 3000, T)
+    lens = rng.integers(0, 7, T * batch)
+    lens.reshape(T, batch)[rng.choice(T, 500, replace=False)] = 0
+    t = np.repeat(np.arange(T), lens.reshape(T, batch).sum(1))
+    _check(gpu_device, rows, batch, lens, (rng.random(t.size) * rows[t]).astype(np.int64), "many tables")
+
+
+@pytest.mark.parametrize("T,batch,mean", [(4100, 5, 3.0), (1, 2000, 1800.0)])
+def test_a_step_whose_lookups_are_sorted_by_digits(gpu_device, T, batch, mean):
+    import tbe_testlib as tl
+    from paper_2104_05158_amd import workloads as wl
+    rng = np.random.default_rng(T)
+    spec = wl.custom(rng.integers(50, 2000, T), rng.choice([4, 8], T), 0, batch, mean, index_dist="zipf", name="digits")
+    b = wl.make_batch(spec, "cpu", seed=1)
+    tl.full_parity_step(spec, b.indices.numpy(), b.offsets.numpy(), wl.make_weights(spec, "cpu", seed=2).numpy(),
+                        wl.make_grad(spec, "cpu", seed=3).numpy(), gpu_device, what=f"{T} tables")

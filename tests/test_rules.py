@@ -79,3 +79,18 @@ def test_every_index_finds_a_bucket_of_its_table(rules, rows, buckets):
                             ctypes.c_int(span), ptr(index), ctypes.c_int(len(index)), ptr(out))
     assert np.array_equal(out[:len(good)], np.searchsorted(split, good, side="right") - 1)
     assert np.all(out[len(good):] < nb)
+
+
+def test_a_handle_that_never_sorts_by_digits_has_no_smaller_call_that_does(rules):
+    # the workspace holds the tables of the digit-by-digit sort only if the handle's largest call takes it
+    use = lambda t, n, p: bool(rules.use_radix_sort(ctypes.c_int64(t), ctypes.c_int64(n), ctypes.c_int(p)))
+    sizes = [1, 8192, 199_999, 200_000, 999_999, 1_000_000, 2_000_000, 3_500_000, 16_000_000, 100_000_000, 224_000_000,
+             (1 << 31) - (1 << 24) - 1]
+    for passes in (1, 2, 3, 4):
+        for t in (1, 2, 3, 4, 8, 9, 64, 4096, 4097, 1 << 20):
+            chosen = [use(t, n, passes) for n in sizes]
+            assert chosen == sorted(chosen)
+        assert use(4097, 1, passes)
+    assert not use(64, 199_999, 1) and use(64, 200_000, 1)
+    assert not use(1, 999_999, 2) and use(1, 1_000_000, 2) and not use(1, 1_999_999, 3) and use(2, 16_000_000, 3)
+    assert not any(use(t, sizes[-1], 3) for t in (17, 64, 4096))
