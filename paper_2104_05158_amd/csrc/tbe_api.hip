@@ -56,19 +56,15 @@ constexpr int64_t kSortUnitsRound = 704;
 // some 4096 chunks for 512 resident workgroups (98 M lookups: histogram + partition 622 us with up to 4, 660 with 8).
 constexpr int64_t kSortChunksWanted = 4096;
 constexpr int kSortTilesPerChunk = 4;
-constexpr int kDenseGrid = 1024;
+constexpr int kDenseGrid = 1024;  // persistent workgroups of dense_rows_kernel: 4 per CU, a multiple of 8
 // Lookups from which a wavefront of the update kernel owns 128 sorted positions instead of 64.  A small call needs
 // the shorter spans to have wavefronts enough (0.13 M lookups, dims 4..512: 62 us with 64, 112 with 128, 206 with
 // 256; 0.65 M: 156 / 170 / 169); a large one fills the steps of the length classes better with the longer ones
 // (5.5 M lookups, 16-bit rows: 303 us with 128, 319 with 64, 334 with 256; 127 M: 3.84 / 3.87 / 3.88 ms).
 constexpr int64_t kWideSpanMin = 2 << 20;
-// Largest gradient block of a table (bytes) up to which long runs are cut by position.  While the block fits the
-// 4 MiB of an L2 the windows bring no locality, and counts x gradient block has too few slices to fill the chip:
-// batch 611, dims to 512: 28 us for all long runs instead of 245; batch 8191, 128 bf16 columns (2 MiB): 81 instead
-// of 236.  Beyond it gathering loses: batch 16384, 128 fp32 columns (8 MiB): 754 us instead of 410.
-constexpr int64_t kPositionBlock = 4 << 20;
-constexpr int kWindowGrid = 1024;  // persistent workgroups of window_runs_kernel: 8 wavefronts per CU, a multiple of 8
-constexpr int kDenseBagsPerLookup = 8;   // persistent workgroups of dense_rows_kernel: 4 per CU, a multiple of 8
+constexpr int kWindowGrid = 1024;  // persistent workgroups of window_runs_kernel: 4 per CU, a multiple of 8 (by position
+                                   // 1536, 2048 and 8192 are no faster)
+constexpr int kDenseBagsPerLookup = 8;
 
 inline int pow2ceil_log2(int x)
 {
@@ -820,7 +816,7 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
     }
     Counters* counters = h->ws<Counters>(h->off_counters);
     if (a.n > a.long_run) {
-        // the long runs below the dense threshold: plan -> window-border positions -> pieces, window by window
+        // the long runs below the dense threshold: their pieces, after plan -> window-border positions if by bag window
         ScopedTimer tm(h, SLOT_WINDOW_RUNS, st);
         uint32_t* wpre = h->ws<uint32_t>(h->off_wrun);
         uint32_t* ppre = wpre + (h->T + 1);
@@ -921,12 +917,12 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     a.dpad = (int32_t)align_up((size_t)h->dmax, 4);
     a.batch = h->sorted_batch;
     a.table_major = h->layout;
-    // Long runs: by position while every table's gradient block fits an L2, by bag window and as dense rows beyond
-    a.by_position = (int64_t)a.batch * a.dpad * (h->grad_dtype == TBE_DTYPE_FP32 ? 4 : 2) <= kPositionBlock;
-    a.long_run = a.by_position ? kPosPiece : kLongRun;
+    const LongRunRule rule = long_run_rule(n, a.batch, a.dpad, h->grad_dtype == TBE_DTYPE_FP32 ? 4 : 2);
+    a.by_position = rule.by_position;
+    a.long_run = rule.long_run;
     // dense hot rows: only when a run can exceed the threshold and the bounds table of this call fits
     const int thr = dense_threshold(h->sorted_batch);
-    const bool dense_on = !a.by_position && n > thr && dense_bounds_entries(n, h->sorted_batch, h->T) <= h->dbounds_cap &&
+    const bool dense_on = rule.dense && n > thr && dense_bounds_entries(n, h->sorted_batch, h->T) <= h->dbounds_cap &&
                           n / thr + h->T + 2 <= h->max_indices / kDenseMinRun + h->T + 2;
     a.dense_thr = dense_on ? thr : INT32_MAX;
     a.dense_slices = (int32_t)ceil_div(std::max(h->sorted_batch, 1), kDenseSlice);

@@ -13,6 +13,7 @@
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -25,9 +26,6 @@ namespace tbe {
 constexpr int kFwdUnroll = 4;             // row loads in flight per lane group (8 costs occupancy and is slower)
 constexpr int kChunk = 128;               // sorted positions per pair of partial-row slots
 constexpr int kSpanUnit = 64;             // a span of the update kernel is a multiple of this many sorted positions
-constexpr int kLongRun = 512;             // runs longer than this are summed in pieces by other kernels (window / dense path)
-constexpr int kPosPiece = 128;            // shortest piece of a run that is cut by position; also the threshold in that mode
-constexpr int kPosPiecesMax = 256;        // most pieces of such a run (longer runs take longer pieces)
 constexpr int kWinMax = 16;               // most bag windows a long run is cut into
 constexpr int kWinBatch = 8;               // pieces a workgroup of window_runs_kernel claims at a time
 constexpr int kBwdThreads = 256;          // 4 wavefronts = 4 chunks per workgroup
@@ -57,13 +55,13 @@ struct Counters {       // workspace scalars
     // updates, also before a second update after one sort and every replay of a captured graph: the window kernel
     // hands the number of runs over to the fix-up kernel (long_todo) and clears it, the fix-up kernel clears the
     // number of pieces.  Each is cleared by one workgroup of a kernel in which no other reads it.
-    uint32_t long_count;
+    uint32_t long_count;        // (these two are added to together, as one word of 64 bits)
+    uint32_t win_pieces;
     uint32_t long_todo;
     uint32_t check_flags;       // written only by tbe_check_inputs
     uint32_t dense_runs;        // written by the plan kernels: dense runs / groups, windowed runs of this update
     uint32_t dense_groups;
-    uint32_t win_runs;          // windowed runs / their pieces of this update (written by window_plan_kernel)
-    uint32_t win_pieces;
+    uint32_t win_runs;          // windowed runs of this update (window_plan_kernel writes win_pieces, too)
     int32_t sort_chunks;        // written by sort_plan_kernel, which clears sort_units and sort_ticket: chunks of the partition,
     int32_t sort_multi;         // tables of more chunks than sort_units_kernel adds up itself
     uint32_t sort_units;
@@ -528,11 +526,11 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_
 //     members' sums combined with an xor butterfly;
 //   * longer runs use the whole wavefront in several steps (groups take alternate lookups); up to the
 //     call's long_run lookups the owner follows the run past its span and finishes it;
-//   * a longer run is not summed here.  While a table's gradient block fits an L2 (by_position) its
-//     pieces of kPosPiece lookups are listed for window_runs_kernel right away; beyond that the run is
-//     queued, per table, for window_runs_kernel (pieces by bag window) or, past the call's dense
-//     threshold, for dense_rows_kernel (counts x gradient block).  Those write fp32 partial rows to the
-//     workspace, and the fix-up kernel adds a run's partial rows in a fixed order and applies the update.
+//   * a longer run is not summed here.  Past the call's dense threshold it is queued, per table, for
+//     dense_rows_kernel (counts x gradient block).  Below it, while a table's gradient block fits an L2
+//     (by_position), its pieces of kPosPiece lookups are listed for window_runs_kernel right away; beyond that
+//     the run is queued, per table, for window_runs_kernel (pieces by bag window).  Those write fp32 partial
+//     rows to the workspace, and the fix-up kernel adds a run's partial rows in a fixed order and applies the update.
 // The single-lookup rows of the tail of the index distribution move a row, its moment and one gradient row
 // each and run at the rate of the memory system; the steps of the longer runs are bound by how fast gradient
 // rows come out of the caches, so nothing here is arranged around instruction counts.
@@ -595,7 +593,7 @@ struct BwdArgs {
     struct WinPiece* pieces;
     const float* zero_row;  // >= 2 KiB of zeros
     int32_t n;
-    int32_t long_run;      // runs longer than this are long: kLongRun, or kPosPiece when they are cut by position
+    int32_t long_run;      // runs longer than this are long: kLongRun, or kPosPiece in a small call that cuts them by position
     int32_t by_position;   // long runs are cut by position (their pieces are listed by the update kernel), not by bag window
     int32_t T;
     int32_t sumD;
@@ -626,20 +624,12 @@ struct LongRun {         // 32 bytes: what a wavefront of the fix-up kernel need
     uint32_t key;        // linear row id
     int32_t t;           // table
     int32_t s, e;        // sorted positions of the run
-    uint32_t base;       // cut by position: the run's first partial row
-    uint32_t pad[3];
+    uint32_t pad[4];
 };
 
-// Pieces of a run of `len` lookups that is cut by position.
-__device__ __forceinline__ int position_piece(int len)
-{
-    const int per = (len + kPosPiecesMax - 1) / kPosPiecesMax;
-    return max(kPosPiece, (per + kPosPiece - 1) / kPosPiece * kPosPiece);
-}
-
 // Lists the long runs of the lanes in `todo` (one run per lane: length, first position, row id, table) for the
-// fix-up kernel and their pieces for window_runs_kernel.  Partial row = index of the piece in the list: which rows
-// a run gets depends on the order of the atomics, what they hold and the order they are added in does not.
+// fix-up kernel and their pieces for window_runs_kernel.  The order of the lists depends on the order of the atomics,
+// what a piece's partial row holds, where it lies and the order a run's are added in do not.
 __device__ __forceinline__ void list_position_pieces(const BwdArgs& a, uint64_t todo, int len, int first, uint32_t key, int t)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -647,20 +637,22 @@ __device__ __forceinline__ void list_position_pieces(const BwdArgs& a, uint64_t 
         const int src = __ffsll((unsigned long long)todo) - 1;
         todo &= todo - 1;
         const int L = __shfl(len, src), s = __shfl(first, src), k = __shfl((int)key, src);
-        const int piece = position_piece(L);
-        const int np = (L + piece - 1) / piece;
+        const int np = position_pieces(L);
         uint32_t base = 0;
         if (lane == 0) {
-            base = atomicAdd(&a.counters->win_pieces, (uint32_t)np);
-            const uint32_t slot = atomicAdd(&a.counters->long_count, 1u);
-            a.long_list[slot] = LongRun{(uint32_t)k, t, s, s + L, base, {0, 0, 0}};
+            // one atomic for both lists: all runs of a call add to this word, at 6 ns each
+            static_assert(offsetof(Counters, long_count) % 8 == 0 && offsetof(Counters, win_pieces) == offsetof(Counters, long_count) + 4, "");
+            const unsigned long long was = atomicAdd(reinterpret_cast<unsigned long long*>(&a.counters->long_count),
+                                                     (unsigned long long)np << 32 | 1ull);
+            base = (uint32_t)(was >> 32);
+            a.long_list[(uint32_t)was] = LongRun{(uint32_t)k, t, s, s + L, {0, 0, 0, 0}};
         }
         base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
         for (int i = lane; i < np; i += kWave) {
             WinPiece p;
-            p.p0 = s + i * piece;
-            p.p1 = min(s + L, p.p0 + piece);
-            p.slot = (int)base + i;
+            p.p0 = position_of_piece(s, L, np, i);
+            p.p1 = position_of_piece(s, L, np, i + 1);
+            p.slot = p.p0 / kPosSlot;
             p.t = t;
             a.pieces[base + i] = p;
         }
@@ -1120,9 +1112,10 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
                 cl = tl <= lgG ? 3 + tl : 14;
             }
             cls[i] = valid ? cl : -1;
-            if (a.by_position) {
-                list_position_pieces(a, __ballot(valid && cl == 15), len, s_seg[rc], s_key[rc], t);
-            } else if (valid && cl == 15) {
+            const bool cut = a.by_position && len <= a.dense_thr;
+            if (a.by_position)
+                list_position_pieces(a, __ballot(valid && cl == 15 && cut), len, s_seg[rc], s_key[rc], t);
+            if (valid && cl == 15 && !cut) {
                 if (len > a.dense_thr) {
                     const uint32_t dslot = atomicAdd(&a.dense_cnt[t], 1u);
                     a.dense_list[a.tstart[t] / a.dense_thr + t + (int)dslot] = (uint32_t)(ub + run);
@@ -1131,7 +1124,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
                     a.win_list[a.tstart[t] / kLongRun + t + (int)wslot] = (uint32_t)(ub + run);
                 }
                 const uint32_t slot = atomicAdd(&a.counters->long_count, 1u);
-                a.long_list[slot] = LongRun{s_key[rc], t, s_seg[rc], s_seg[rc + 1], 0, {0, 0, 0}};
+                a.long_list[slot] = LongRun{s_key[rc], t, s_seg[rc], s_seg[rc + 1], {0, 0, 0, 0}};
             }
         }
 
@@ -1629,8 +1622,8 @@ __global__ __launch_bounds__(kDenseThreads, 4) void dense_rows_kernel(DenseArgs 
 
 // ---------------------------------------------------------------- long runs in pieces
 //
-// By position (the gradient block fits an L2): pieces of kPosPiece lookups, one wavefront each.  In a call of this
-// size what counts is the length of the chain a wavefront follows -- four rows in flight per lane group, so 128
+// By position (the gradient block fits an L2): pieces of kPosPiece lookups, one wavefront each.  In a small call
+// what counts is the length of the chain a wavefront follows -- four rows in flight per lane group, so 128
 // lookups of a 512-column row are 32 trips to the L2, about 20 us -- and that there are pieces for every CU.
 //
 // By bag window, beyond that:
@@ -1905,10 +1898,10 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
         wvv[1] = IO::ldv(wrow + c.e1);
         OptRow<OPT> st;
         st.load(a.opt, key, wel, c);
-        if (a.by_position) {
-            const int piece = position_piece(e - s);
-            wave_gather_sum<float>([&](int cc) { return pbase + ((int64_t)rec.base + cc) * dpad; }, 0,
-                                   (e - s + piece - 1) / piece, a.zero_row, c, acc);
+        if (a.by_position && !dense) {
+            const int np = position_pieces(e - s);
+            wave_gather_sum<float>([&](int cc) { return pbase + (int64_t)(position_of_piece(s, e - s, np, cc) / kPosSlot) * dpad; },
+                                   0, np, a.zero_row, c, acc);
         } else if (dense && a.dense_dirty[t] != 0u) {
             // the table's gradient block holds Inf / NaN, which the dense sums leave out: this run is
             // summed the plain way, one gathered gradient row per lookup (a rare, slow path)

@@ -60,6 +60,59 @@ inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, bool wide
     return f;
 }
 
+// ---------------------------------------------------------------- update: long runs
+
+constexpr int kLongRun = 512;             // a run of more lookups is long: other kernels than the update kernel sum it, in pieces
+// Largest gradient block of a table (bytes) up to which long runs are cut by position, beyond it by bag window.  While the
+// block fits the 4 MiB of an L2 the windows bring no locality: batch 611, dims to 512: 28 us for all long runs instead of
+// 245; batch 8191, 128 bf16 columns (2 MiB): 81 instead of 236.  Beyond it gathering loses: batch 16384, 128 fp32 columns
+// (8 MiB): 754 us instead of 410.
+constexpr int64_t kPositionBlock = 4 << 20;
+// Gathered gradient (lookups x bytes of an element) from which a call cut by position leaves the runs beyond the dense
+// threshold to counts x gradient block and calls a run long from kLongRun on, as the calls beyond kPositionBlock do.  A
+// smaller call is a matter of latency: it has too few slices of bags to fill the chip, and a wavefront that sums 512
+// lookups by itself is a long chain (1 table of 1000 rows, batch 2048, 128 columns, 0.1 M lookups: the whole update 28 us,
+// 84 with dense rows; 8 tables, batch 16384, 64 columns, 3.9 M: 135 / 152; 64 tables of 1 M rows, batch 8191, 128 bf16 columns,
+// 5.2 M: 430 / 456).  A larger one gathers most of a skewed batch by position and adds every run to one list, 6 ns each:
+// 64 tables of 1000 rows, batch 8191, 128 columns, 26 M lookups 1586 us, 724 with dense rows (790 by window); batch 16384,
+// 32 columns, 52 M 1502 / 513 (615); of 1 M rows, 21 M 1668 / 1464 (1586).  Wide rows take the matrix cores several
+// passes: 512 bf16 columns, 64 tables, 6.6 M 699 / 767; fp32, 128 tables, 13 M 2733 / 2262.
+constexpr int64_t kManyLongBytes = 16000000, kManyLongPerColumn = 65536;
+
+constexpr int kPosPiece = 128;            // a piece by position has at most this many lookups (and fewer than that is never long) ...
+constexpr int kPosPiecesMax = 256;        // ... unless that would make more pieces of a run than this
+// Partial row of a piece: its first position / kPosSlot.  A piece has at least kPosSlot lookups, so no two share one, and a
+// dense run's rows are those of the 128-position chunks that it covers completely, in which no other run has a position.
+constexpr int kPosSlot = 64;
+
+struct LongRunRule {
+    bool by_position, dense;   // dense: runs beyond the dense threshold are summed as dense rows
+    int long_run;              // a run of more lookups is long
+};
+
+// widest: columns of the widest table
+inline LongRunRule long_run_rule(int64_t lookups, int64_t batch, int64_t widest, int grad_bytes)
+{
+    LongRunRule r;
+    r.by_position = batch * widest * grad_bytes <= kPositionBlock;
+    r.dense = !r.by_position || lookups * grad_bytes >= std::max(kManyLongBytes, kManyLongPerColumn * widest);
+    r.long_run = r.dense ? kLongRun : kPosPiece;
+    return r;
+}
+
+TBE_BOTH int position_pieces(int len)
+{
+    const int np = (len + kPosPiece - 1) / kPosPiece;
+    return np < kPosPiecesMax ? np : kPosPiecesMax;
+}
+
+// first position of piece i of the np pieces of a run of `len` lookups from position s (i = np: the end of the run)
+TBE_BOTH int position_of_piece(int s, int len, int np, int i)
+{
+    const int each = len / np, more = len - each * np;    // the first `more` pieces are one longer
+    return s + i * each + (i < more ? i : more);
+}
+
 // ---------------------------------------------------------------- sort
 
 // Which sort a call takes: that of tbe_sort_kernels.hip.h, or the digit-by-digit one of tbe_radix_kernels.hip.h.

@@ -11,6 +11,23 @@ void forward_launch(int64_t num_bags, int64_t lookups, int wide, int64_t* out /*
     out[2] = f.blocks;
 }
 
+void long_run_rule(int64_t lookups, int64_t batch, int64_t widest, int grad_bytes, int32_t* out /*[3]*/)
+{
+    const tbe::LongRunRule r = tbe::long_run_rule(lookups, batch, widest, grad_bytes);
+    out[0] = r.by_position;
+    out[1] = r.dense;
+    out[2] = r.long_run;
+}
+
+// borders of the pieces of a run; returns their number
+int position_pieces(int s, int len, int32_t* out /*[257]*/)
+{
+    const int np = tbe::position_pieces(len);
+    for (int i = 0; i <= np; ++i)
+        out[i] = tbe::position_of_piece(s, len, np, i);
+    return np;
+}
+
 int use_radix_sort(int64_t tables, int64_t lookups, int passes) { return tbe::use_radix_sort(tables, lookups, passes); }
 
 void sample_positions(int n, int samples, int32_t* out)

@@ -24,6 +24,11 @@ CASES = {
     "every_row_dense": ([20], [128], 5000, [10.0], "uniform", 0.0),
     "threshold_follows_batch": ([200, 50], [32, 96], 16384, [8.0, 3.0], "zipf", 1.2),
     "many_dense_runs_small_batch": ([70], [16], 64, [2500.0], "uniform", 0.0),
+    # the gradient block of a table exceeds 4 MiB, or the call holds 4 M lookups: these take the dense kernels (the smaller
+    # ones above are cut by position instead)
+    "five_slices_beyond_4_MiB": ([40, 3000, 100000], [128, 64, 256], 4500, [40.0, 20.0, 10.0], "zipf", 1.3),
+    "narrow_and_widest_beyond_4_MiB": ([30, 25, 60], [512, 4, 260], 2100, [25.0, 25.0, 25.0], "uniform", 0.0),
+    "hundreds_of_copies_4_M_lookups": ([5, 3], [64, 8], 1500, [1800.0, 1000.0], "uniform", 0.0),
 }
 
 
@@ -89,12 +94,13 @@ def test_dense_rows_other_optimizers(gpu_device):
         tgo._run(_spec("two_groups_three_slices", 1), optimizer, tbe.TBE_DTYPE_FP32, gpu_device, steps=2, seed=40)
 
 
-def test_non_finite_gradient_reaches_only_the_rows_its_bag_looks_up(gpu_device):
+@pytest.mark.parametrize("batch", [1500, 9000])      # cut by position, and dense (a block of more than 4 MiB)
+def test_non_finite_gradient_reaches_only_the_rows_its_bag_looks_up(gpu_device, batch):
     """Bag 7 of table 0 carries an Inf and a NaN gradient entry.  Rows (dense or not) that bag 7 does not look
     up must come out exactly as with a finite gradient; rows it does look up must show the same non-finite
     pattern as the oracle."""
     dev = gpu_device
-    spec = wl.custom([24, 500], [128, 64], 0, 1500, [12.0, 6.0], index_dist="zipf", zipf_s=1.2, name="nonfinite")
+    spec = wl.custom([24, 500], [128, 64], 0, batch, [12.0, 6.0], index_dist="zipf", zipf_s=1.2, name="nonfinite")
     b = wl.make_batch(spec, "cpu", seed=31)
     idx, off = b.indices.numpy().copy(), b.offsets.numpy()
     B, N = spec.batch, b.num_indices

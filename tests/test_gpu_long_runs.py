@@ -30,3 +30,27 @@ def test_long_runs_on_both_sides_of_every_border(gpu_device, case, dtype):
     m0 = np.random.default_rng(44).uniform(0, 1, spec.total_rows).astype(np.float32)
     print(f"{case}: N={idx.size} dtype={dtype}", flush=True)
     tl.full_parity_step(spec, idx, off, w, g, gpu_device, lr=0.03, m0=m0, what=case)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("bad", [False, True])
+def test_runs_by_position_beside_dense_ones(gpu_device, layout, bad):
+    """A call of 4 M lookups whose gradient block fits 4 MiB: runs of 513 .. 1024 lookups are cut by position, longer ones
+    summed as dense rows; a bag that holds one row 300 times (more than a count's byte) takes its table's dense runs
+    to the plain sum."""
+    rng = np.random.default_rng(7)
+    batch, dims = 1100, [8, 64]
+    lens = [np.concatenate([rng.integers(500, 1100, 900), rng.integers(1025, 6000, 500), [1, 2, 128, 129, 512, 513, 1024, 1025],
+                            rng.integers(1, 300, 400), [20_000]]) for _ in dims]
+    spec, idx, off = _explicit_case(dims, lens, batch=batch, seed=51, dtype=0)
+    assert idx.size >= 4_000_000 and batch * max(dims) * 4 <= 4 << 20
+    if bad:
+        hot = int(np.argmax(np.bincount(idx[:off[batch]])))
+        at = int(off[5])
+        where = np.flatnonzero(idx[:off[batch]] == hot)[:300]
+        idx[where], idx[at:at + 300] = idx[at:at + 300].copy(), hot
+        assert off[6] - off[5] >= 300
+    w = wl.make_weights(spec, "cpu", seed=52).numpy()
+    g = wl.make_grad(spec, "cpu", seed=53).numpy()
+    print(f"N={idx.size} layout={layout} bad={bad}", flush=True)
+    tl.full_parity_step(spec, idx, off, w, g, gpu_device, lr=0.03, what="position and dense", layout=layout)

@@ -94,3 +94,31 @@ def test_a_handle_that_never_sorts_by_digits_has_no_smaller_call_that_does(rules
     assert not use(64, 199_999, 1) and use(64, 200_000, 1)
     assert not use(1, 999_999, 2) and use(1, 1_000_000, 2) and not use(1, 1_999_999, 3) and use(2, 16_000_000, 3)
     assert not any(use(t, sizes[-1], 3) for t in (17, 64, 4096))
+
+
+@pytest.mark.parametrize("length", [129, 130, 191, 192, 193, 255, 256, 257, 513, 5000, 128 * 256 - 1, 128 * 256, 128 * 256 + 1,
+                                    128 * 255 + 1, 1_000_003, (1 << 31) - (1 << 25)])
+def test_pieces_by_position_cover_a_run_and_own_their_partial_rows(rules, length):
+    # rows are numbered by first position / 64: no piece may be shorter, or the next one (of this run or of the one behind
+    # it) could have the same row
+    for s in (0, 1, 63, 127, 128, 1_000_001):
+        out = np.empty(257, np.int32)
+        np_ = rules.position_pieces(ctypes.c_int(s), ctypes.c_int(length), out.ctypes.data_as(ctypes.c_void_p))
+        borders = out[:np_ + 1].astype(np.int64)
+        sizes = np.diff(borders)
+        assert borders[0] == s and borders[-1] == s + length and np_ <= 256
+        assert sizes.min() >= 64 and sizes.max() - sizes.min() <= 1
+        assert sizes.max() <= 128 or np_ == 256
+        assert len(np.unique(borders // 64)) == np_ + 1
+
+
+def test_which_long_runs_are_cut_how(rules):
+    def rule(n, batch, widest, grad_bytes):
+        out = np.empty(3, np.int32)
+        rules.long_run_rule(ctypes.c_int64(n), ctypes.c_int64(batch), ctypes.c_int64(widest), ctypes.c_int(grad_bytes),
+                            out.ctypes.data_as(ctypes.c_void_p))
+        return out.tolist()
+    assert rule(3_999_999, 8192, 128, 4) == [1, 0, 128] and rule(4_000_000, 8192, 128, 4) == [1, 1, 512]
+    assert rule(4_000_000, 8193, 128, 4) == rule(1, 8193, 128, 4) == [0, 1, 512] and rule(1, 8193, 128, 2) == [1, 0, 128]
+    assert rule(8_388_607, 2048, 512, 4) == [1, 0, 128] and rule(8_388_608, 2048, 512, 4) == [1, 1, 512]
+    assert rule(7_999_999, 8193, 128, 2) == [1, 0, 128] and rule(8_000_000, 8193, 128, 2) == [1, 1, 512]
