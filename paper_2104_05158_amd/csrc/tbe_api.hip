@@ -56,6 +56,9 @@ constexpr int64_t kSortUnitsRound = 704;
 // some 4096 chunks for 512 resident workgroups (98 M lookups: histogram + partition 622 us with up to 4, 660 with 8).
 constexpr int64_t kSortChunksWanted = 4096;
 constexpr int kSortTilesPerChunk = 4;
+// Chunks of a call up to which sort_units_kernel adds all of them up itself: at most six trips, against a launch of 2 us
+// (8 tables, 0.65 M lookups: step of 347 us, 345 without it).
+constexpr int64_t kColumnsMin = 96;
 constexpr int kDenseGrid = 1024;  // persistent workgroups of dense_rows_kernel: 4 per CU, a multiple of 8
 // Lookups from which a wavefront of the update kernel owns 128 sorted positions instead of 64.  A small call needs
 // the shorter spans to have wavefronts enough (0.13 M lookups, dims 4..512: 62 us with 64, 112 with 128, 206 with
@@ -256,7 +259,7 @@ void plan_partition(tbe_s* h, Take take)
     h->off_lut = take(2 * (size_t)kLutSize * parts);
     h->off_bstart = take(4 * (size_t)kMaxBuckets * parts);
     h->off_hist = take(4 * (size_t)kMaxBuckets * sort_chunks);
-    h->off_multi = take(4 * (size_t)(nmax / ((int64_t)kSortTile * kColAhead) + 1));
+    h->off_multi = take(4 * (size_t)(nmax / ((int64_t)kSortTile * kColChunks) + 1));
     h->off_tile_bag = take(4 * (size_t)(ceil_div(nmax, kSortTile) + (kSortTilesPerChunk + 1) * (int64_t)(h->T + 1)));
     h->off_unit_runs = take(4 * (size_t)slots);
     h->off_table_runs = take(4 * (size_t)h->T);
@@ -760,7 +763,10 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         TBE_LAUNCH_CHECK(h, "sort_small_kernel");
         return TBE_OK;
     }
-    const unsigned chunk_grid = (unsigned)(ceil_div(n, (int64_t)kSortTile * ss.tiles_per_chunk) + h->T);
+    const int64_t chunk = (int64_t)kSortTile * ss.tiles_per_chunk;
+    const unsigned chunk_grid = (unsigned)(ceil_div(n, chunk) + h->T);
+    const bool columns = n > kColumnsMin * chunk;
+    a.col_chunks = columns ? kColChunks : INT_MAX;
     {   // a2: samples, bucket borders and chunks
         ScopedTimer tm(h, SLOT_SORT_PLAN, st);
         hipLaunchKernelGGL(sort_plan_kernel, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
@@ -773,9 +779,8 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     }
     {
         ScopedTimer tm(h, SLOT_RADIX_SCAN, st);
-        const int64_t multi = std::min<int64_t>(h->T, n / ((int64_t)kSortTile * ss.tiles_per_chunk * kColAhead));
-        if (multi > 0)                                   // tables of more than kColAhead chunks, at most
-            hipLaunchKernelGGL(sort_columns_kernel, dim3((unsigned)(multi * (kMaxBuckets / kColBuckets))), dim3(kColThreads), 0, st, a);
+        if (columns)
+            hipLaunchKernelGGL(sort_columns_kernel, dim3((unsigned)(std::min<int64_t>(h->T, n / (chunk * kColChunks)) * (kMaxBuckets / kColBuckets))), dim3(kColThreads), 0, st, a);
         hipLaunchKernelGGL(sort_units_kernel, dim3((unsigned)h->T), dim3(kUnitsThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_units_kernel");
     }

@@ -50,7 +50,8 @@ constexpr int kLocalDigits = 256;
 constexpr int kUnitsThreads = 1024;
 constexpr int kColThreads = 1024;                 // 16 wavefronts that share the chunks of a table ...
 constexpr int kColBuckets = kWave;                // ... for 64 of its buckets ...
-constexpr int kColAhead = 16;                     // ... and read this many at a time; a table of no more needs no such workgroup
+constexpr int kColAhead = 16;                     // ... and read this many at a time
+constexpr int kColChunks = 32;                    // a table of no more chunks needs no such workgroups
 
 struct SortTable {       // 32 bytes
     int32_t start, n;    // first position, lookups
@@ -90,7 +91,7 @@ struct SortArgs {
     uint16_t* lut;           // [parts][kLutSize] bucket of the first row of every cell of rows (and of the row past the last)
     uint32_t* bstart;        // [parts][kMaxBuckets] lookups, then first position of every bucket
     uint32_t* hist;          // [chunks][kMaxBuckets]
-    int32_t* multi;          // tables of more than kColAhead chunks
+    int32_t* multi;          // tables of more than col_chunks chunks
     int32_t* tile_bag;       // [chunks * tiles_per_chunk] bag of the first position of every tile
     uint32_t* unit_runs;     // [slots] runs of every unit
     uint32_t* table_runs;    // [T]
@@ -107,6 +108,7 @@ struct SortArgs {
     int32_t kb;              // bits left for the row offset
     int32_t target;          // lookups per bucket
     int32_t tiles_per_chunk;
+    int32_t col_chunks;      // chunks of a table up to which sort_units_kernel adds them up itself
 };
 
 // ---------------------------------------------------------------- wavefront and workgroup primitives
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         for (int i = tid; i < t; i += kSortThreads) {
             const int n = (int)(a.offsets[(int64_t)(i + 1) * a.B] - a.offsets[(int64_t)i * a.B]);
             const TablePlan p = table_plan(a, n, a.row_base[i + 1] - a.row_base[i]);
-            multi += p.chunks > kColAhead; chunks += p.chunks; parts += n > 0;
+            multi += p.chunks > a.col_chunks; chunks += p.chunks; parts += n > 0;
         }
         multi = last_lane(wave_scan_add(multi));
         chunks = last_lane(wave_scan_add(chunks));
@@ -489,12 +491,12 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     if (tid == 0) {
         a.tstart[t] = start;
         a.table_runs[t] = 0;
-        if (p.chunks > kColAhead)
+        if (p.chunks > a.col_chunks)
             a.multi[s_sum[0]] = t;
         if (t == a.T - 1) {
             a.tstart[a.T] = (int)o1;
             a.counters->sort_chunks = st.chunk_base + p.chunks;
-            a.counters->sort_multi = (int)s_sum[0] + (p.chunks > kColAhead);
+            a.counters->sort_multi = (int)s_sum[0] + (p.chunks > a.col_chunks);
             a.counters->sort_units = 0;
             a.counters->sort_ticket = 0;
         }
@@ -789,19 +791,21 @@ __global__ __launch_bounds__(kUnitsThreads) void sort_units_kernel(SortArgs a)
     uint32_t* bstart = a.bstart + (int64_t)st.part * kMaxBuckets;
     const uint32_t* split = a.split + (int64_t)st.part * kMaxBuckets;
     uint32_t run = 0;
-    if (st.nchunks > kColAhead) {
+    if (st.nchunks > a.col_chunks) {
         run = d < st.nb ? bstart[d] : 0u;
     } else if (d < st.nb) {
         uint32_t* col = a.hist + (int64_t)st.chunk_base * kMaxBuckets + d;
-        uint32_t x[kColAhead];
+        for (int c = 0; c < st.nchunks; c += kColAhead) {
+            uint32_t x[kColAhead];
 #pragma unroll
-        for (int i = 0; i < kColAhead; ++i)
-            x[i] = col[(int64_t)min(i, st.nchunks - 1) * kMaxBuckets];
+            for (int i = 0; i < kColAhead; ++i)
+                x[i] = col[(int64_t)min(c + i, st.nchunks - 1) * kMaxBuckets];
 #pragma unroll
-        for (int i = 0; i < kColAhead; ++i) {
-            if (i < st.nchunks) {
-                col[(int64_t)i * kMaxBuckets] = run;
-                run += x[i];
+            for (int i = 0; i < kColAhead; ++i) {
+                if (c + i < st.nchunks) {
+                    col[(int64_t)(c + i) * kMaxBuckets] = run;
+                    run += x[i];
+                }
             }
         }
     }

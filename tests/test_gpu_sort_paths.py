@@ -106,11 +106,11 @@ def test_bucket_larger_than_a_tile(gpu_device, n, rows, batch):
     _check(gpu_device, [rows], batch, _lens(rng, batch, n), idx, "large bucket")
 
 
-@pytest.mark.parametrize("chunks,extra", [(16, 0), (16, 1), (33, 5), (257, -1)])
+@pytest.mark.parametrize("chunks,extra", [(16, 0), (32, 0), (32, 1), (75, 0), (76, 0), (257, -1)])
 def test_tables_of_few_and_of_many_chunks(gpu_device, chunks, extra):
-    # up to 16 chunks of a tile a table's counts are added up where its units are made, beyond by a kernel of its own
+    # up to 32 chunks of a tile, or 96 of all tables, a table's counts are added up where its units are made, beyond by a kernel
     rng = np.random.default_rng(chunks)
-    rows, per_table = [150_000, 9, 700, 2_000_000], [chunks * TILE + extra, 3 * TILE, 0, 17 * TILE + 11]
+    rows, per_table = [150_000, 9, 700, 2_000_000], [chunks * TILE + extra, 3 * TILE, 0, 17 * TILE]
     lens = np.concatenate([_lens(rng, 300, n) for n in per_table])
     idx = np.concatenate([np.minimum(rng.zipf(1.3, n) * 2_654_435_761 % h, h - 1) for h, n in zip(rows, per_table)])
     _check(gpu_device, rows, 300, lens, idx, "chunks")
