@@ -19,6 +19,9 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline bool misaligned(const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; }
 
 constexpr int64_t kMaxCount = ((int64_t)1 << 31) - 1;
+// Input blocks up to which one workgroup of the permute finds the starts of all of them, 256 a trip (1024 blocks: 27 us for
+// the call either way; 2048: 32 with one workgroup, 28 with a prefix sum over the chip; 32,768: 182 / 43; 1 M: 3.2 ms / 0.15).
+constexpr int64_t kOneGroupStarts = 1024;
 
 struct Scratch {
     int64_t* offsets_in;   // int64[num_bags + 1]
@@ -110,6 +113,22 @@ tbe_status_t enqueue_scan(const int32_t* lengths, int64_t n, int64_t* offsets, i
     return enqueue_apply(lengths, n, offsets, block_sums, st);
 }
 
+// s.offsets_in[0..rows): first position of every one of the rows = W * T input blocks
+tbe_status_t enqueue_starts(int64_t rows, const int32_t* lengths_in, const int64_t* offsets_out, const Scratch& s, int32_t W,
+                            int32_t T, int32_t B, hipStream_t st)
+{
+    if (rows <= kOneGroupStarts) {
+        hipLaunchKernelGGL(permute_starts_kernel, dim3(1), dim3(kThreads), 0, st, offsets_out, s.offsets_in, W, T, B);
+        return launch_status();
+    }
+    if (B == 1)                        // a block is a bag
+        return enqueue_scan(lengths_in, rows, s.offsets_in, s.block_sums, st);
+    // the sizes go behind the starts: rows * B + 1 entries of 8 bytes hold rows + 1 of them and rows of 4 bytes
+    int32_t* sizes = reinterpret_cast<int32_t*>(s.offsets_in + (rows + 2) / 2 * 2);
+    hipLaunchKernelGGL(permute_sizes_kernel, dim3((unsigned)ceil_div(rows, kThreads)), dim3(kThreads), 0, st, offsets_out, sizes, W, T, B);
+    return enqueue_scan(sizes, rows, s.offsets_in, s.block_sums, st);
+}
+
 }  // namespace
 
 extern "C" {
@@ -184,8 +203,11 @@ tbe_status_t tbe_permute_wtb_to_twb(int32_t W, int32_t T, int32_t B, const int32
         // blocks, of half a tile or more on average; otherwise one more launch (3 us) writes all starts.
         const int64_t rows = (int64_t)W * T;
         const bool self = rows <= kCopyLdsRows && num_indices / rows >= kCopyTile / 2;
-        if (!self)
-            hipLaunchKernelGGL(permute_starts_kernel, dim3(1), dim3(kThreads), 0, st, d_offsets_out, s.offsets_in, W, T, B);
+        if (!self) {
+            rc = enqueue_starts(rows, d_lengths_in, d_offsets_out, s, W, T, B, st);
+            if (rc != TBE_OK)
+                return rc;
+        }
         hipLaunchKernelGGL(permute_indices_kernel, dim3((unsigned)ceil_div(num_indices, kCopyTile)), dim3(kThreads),
                            0, st, d_indices_in, self ? nullptr : s.offsets_in, d_offsets_out, d_indices_out, W, T, B, num_indices);
     }

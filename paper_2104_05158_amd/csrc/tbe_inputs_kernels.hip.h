@@ -296,6 +296,17 @@ __global__ __launch_bounds__(kThreads) void permute_starts_kernel(const int64_t*
     }
 }
 
+// the same for many blocks: their sizes, in input order, for the prefix sum of lengths
+__global__ __launch_bounds__(kThreads) void permute_sizes_kernel(const int64_t* __restrict__ offsets_out,
+                                                                 int32_t* __restrict__ sizes, int32_t W, int32_t T, int32_t B)
+{
+    const int p = (int)blockIdx.x * kThreads + (int)threadIdx.x;
+    if (p >= W * T)
+        return;
+    const int64_t q = (int64_t)(p % T) * W + p / T;
+    sizes[p] = (int32_t)(offsets_out[(q + 1) * B] - offsets_out[q * B]);
+}
+
 // last q in [lo, hi] with offsets[q*B] <= p   (offsets[lo*B] <= p is given)
 __device__ __forceinline__ int find_block(const int64_t* __restrict__ offsets, int64_t B, int lo, int hi, int64_t p)
 {

@@ -32,7 +32,10 @@ def test_prefix_sums_of_large_lengths(gpu_device, n, top):
 
 
 @pytest.mark.parametrize("W,T,B,kind", [(16, 16, 64, "uneven"), (16, 16, 64, "even"), (16, 17, 64, "even"), (2, 3, 4096, "even"),
-                                        (5, 7, 333, "uneven"), (1, 256, 9, "uneven")])
+                                        (5, 7, 333, "uneven"), (1, 256, 9, "uneven"),
+                                        # one workgroup for the starts, and a prefix sum of sizes (of lengths for one bag a block)
+                                        (32, 32, 5, "even"), (25, 41, 2, "uneven"), (25, 41, 3, "even"), (60, 70, 4, "uneven"),
+                                        (41, 25, 1, "even"), (60, 70, 1, "uneven")])
 def test_permute_starts(gpu_device, W, T, B, kind):
     rng = np.random.default_rng(W * T)
     n = W * T * B
