@@ -102,6 +102,7 @@ struct tbe_s {
     int fwd_epl = 4;
     int fwd_kmax = 1;
     bool fwd_wide = true;    // every table's row takes all lanes of a wavefront
+    int fwd_few = 6;         // lookups a bag from which few bags take one wavefront each
     int key_bits = 1;                   // bits of the tallest table's row index
     int64_t max_rows = 1;
     std::vector<int> pass_digit_bits;   // radix sort, per launch: the widest digit any table sorts in it
@@ -351,7 +352,7 @@ tbe_status_t launch_forward(tbe_s* h, const int32_t* idx, const int64_t* off, in
                             OT* out, hipStream_t st)
 {
     const int num_bags = h->T * batch;
-    const ForwardLaunch f = forward_launch(num_bags, n_total, h->fwd_wide);
+    const ForwardLaunch f = forward_launch(num_bags, n_total, h->fwd_few, h->fwd_wide);
     const dim3 grid((unsigned)f.blocks), block(kFwdThreads);
     const TableMeta* meta = h->ws<TableMeta>(h->off_meta);
     const WT* w = static_cast<const WT*>(h->d_weights);
@@ -502,6 +503,10 @@ tbe_status_t tbe_create(const tbe_config_t* cfg, tbe_handle_t* out_handle)
         s += h->rows[t];
         c += h->dims[t];
     }
+    int narrowest = 6;
+    for (const TableMeta& m : h->meta)
+        narrowest = std::min(narrowest, m.lpr_fwd);
+    h->fwd_few = few_bags_lookups(h->fwd_epl, narrowest);
     h->woff[h->T] = w;
     h->soff[h->T] = s;
     h->coloff[h->T] = c;

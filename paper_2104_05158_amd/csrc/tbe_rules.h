@@ -23,19 +23,21 @@ constexpr int64_t kMaxLaunchThreads = ((int64_t)1 << 32) - 1;
 constexpr int kFwdThreads = 256;          // 4 wavefronts per workgroup, each with its own block of bags
 constexpr int kFwdMaxBagsPerWave = 8;     // measured best on configs 2-4 (4..32 tried)
 // forward_bag_kernel (one bag per wavefront) takes a call ...
-// ... of fewer than kFewBagsShort bags whatever their length: 2048 bags of 2 lookups, dim 128: 3.5 against 3.2 us;
-// ... of fewer than kFewBags bags that hold kFewBagsLookups lookups on average.  forward_kernel has one bag per
-//     wavefront there too and leaves all lane groups but one idle; from 32,768 bags it packs several (fp32 dim 64, 8
-//     lookups: 24,000 bags 15.0 against 11.6 us, 40,000 bags 15.0 against 17.6).  Bags of 2 lookups have nothing to
-//     spread (fp32 dim 128, 16,384 bags: 8.3 against 8.5);
+// ... of fewer than kFewBags bags that hold few_bags_lookups() lookups on average.  forward_kernel has one bag per wavefront
+//     there too and leaves all lane groups but one idle; from 32,768 bags it packs several (fp32 dim 64, 8 lookups:
+//     24,000 bags 15.0 against 11.6 us, 40,000 bags 15.0 against 17.6).  Shorter bags have little to spread and pay for the
+//     sum over the lane groups: a step of it moves 4 or 8 values per lane, and there are the more steps the narrower the
+//     rows.  8000 bags, forward_kernel / this one: fp32 dim 16, 4 lookups 3.5 / 4.1 us, 6 lookups 4.5 / 4.1; dim 128, 4 lookups
+//     4.4 / 4.7; fp16 dim 64, 4 lookups 3.9 / 4.6, 6 lookups 4.9 / 4.6; dim 8, 8 lookups 5.2 / 6.2, 12 lookups 6.6 / 6.2;
 // ... of any size if every table's row fills the wavefront and a bag holds kWideBagLookups lookups on average: there
 //     is no lane group to spread over, but up to 8 rows in flight instead of 4.  131,072 bags: fp32 dim 256, 16 lookups
 //     174 against 154 us, dim 512, 24 lookups 463 against 400; fp16 dim 384, 16 lookups 179 against 166.
 //     Its launch has 64 threads per bag: kMaxLaunchThreads ends that at 2^26 bags.
-constexpr int kFewBagsShort = 8192;
 constexpr int kFewBags = 32768;
-constexpr int kFewBagsLookups = 4;
 constexpr int kWideBagLookups = 16;
+
+// epl: elements per lane; narrowest: log2 of the fewest lanes that a table's row takes
+inline int few_bags_lookups(int epl, int narrowest) { return epl == 8 && narrowest < 2 ? 9 : 6; }
 
 struct ForwardLaunch {
     bool one_bag;          // forward_bag_kernel
@@ -43,13 +45,13 @@ struct ForwardLaunch {
     int64_t blocks;
 };
 
-// wide: every table's row takes all lanes of a wavefront
-inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, bool wide)
+// few: few_bags_lookups(); wide: every table's row takes all lanes of a wavefront
+inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, int few, bool wide)
 {
     constexpr int64_t kMaxBlocks = kMaxLaunchThreads / kFwdThreads, kWaves = kFwdThreads / kWave;
     ForwardLaunch f;
-    f.one_bag = (num_bags < kFewBagsShort || (num_bags < kFewBags && lookups >= kFewBagsLookups * num_bags) ||
-                 (wide && lookups >= kWideBagLookups * num_bags)) && num_bags <= kMaxBlocks * kWaves;
+    f.one_bag = ((num_bags < kFewBags && lookups >= few * num_bags) || (wide && lookups >= kWideBagLookups * num_bags)) &&
+                num_bags <= kMaxBlocks * kWaves;
     // enough bags to amortise the per-block prologue, few enough to keep >= ~16k wavefronts in the grid when the batch
     // is small; beyond 2^29 bags as many as the largest launch needs
     const int64_t fewest = (num_bags + kMaxBlocks * kWaves - 1) / (kMaxBlocks * kWaves);

@@ -3,9 +3,11 @@
 
 extern "C" {
 
-void forward_launch(int64_t num_bags, int64_t lookups, int wide, int64_t* out /*[3]*/)
+int few_bags_lookups(int epl, int narrowest) { return tbe::few_bags_lookups(epl, narrowest); }
+
+void forward_launch(int64_t num_bags, int64_t lookups, int few, int wide, int64_t* out /*[3]*/)
 {
-    const tbe::ForwardLaunch f = tbe::forward_launch(num_bags, lookups, wide != 0);
+    const tbe::ForwardLaunch f = tbe::forward_launch(num_bags, lookups, few, wide != 0);
     out[0] = f.one_bag;
     out[1] = f.bags_per_wave;
     out[2] = f.blocks;

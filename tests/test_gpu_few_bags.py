@@ -48,7 +48,7 @@ def test_lengths_around_every_step(gpu_device, dtype, layout):
 
 @pytest.mark.parametrize("dtype", [0, 1])
 @pytest.mark.parametrize("batch", [1, 8192 // 2 - 1, 8192 // 2, LIMIT // 2 - 1, LIMIT // 2])
-@pytest.mark.parametrize("mean", [2.0, 5.0])
+@pytest.mark.parametrize("mean", [2.0, 5.0, 8.0])
 def test_numbers_of_bags_around_the_limits(gpu_device, batch, dtype, mean):
     lens = np.random.default_rng(batch).poisson(mean, size=(2, batch))
     _forward_matches(gpu_device, [32, 4], batch, lens, dtype, 0, seed=60)

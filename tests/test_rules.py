@@ -21,7 +21,7 @@ def rules(tmp_path_factory):
 
 def _forward(rules, bags, lookups, wide):
     out = np.zeros(3, np.int64)
-    rules.forward_launch(ctypes.c_int64(bags), ctypes.c_int64(lookups), ctypes.c_int(wide),
+    rules.forward_launch(ctypes.c_int64(bags), ctypes.c_int64(lookups), ctypes.c_int(6), ctypes.c_int(wide),
                          out.ctypes.data_as(ctypes.c_void_p))
     return [int(x) for x in out]
 
@@ -31,7 +31,7 @@ def _forward(rules, bags, lookups, wide):
                                   (1 << 26) + 1, (1 << 29) - 1, 1 << 29, (1 << 31) - 1025])
 def test_forward_launches_hold_every_bag_and_fit_the_grid(rules, bags, wide):
     # any number of bags a handle can be created for must be launchable: fewer than 2^32 threads
-    for per_bag in (0, 4, 16, 31):
+    for per_bag in (0, 5, 6, 16, 31):
         lookups = min(bags * per_bag, (1 << 31) - (1 << 24) - 1)
         one_bag, per_wave, blocks = _forward(rules, bags, lookups, wide)
         assert 1 <= per_wave <= 63
@@ -39,8 +39,13 @@ def test_forward_launches_hold_every_bag_and_fit_the_grid(rules, bags, wide):
         assert blocks * 4 * per_wave >= bags > (blocks - 1) * 4 * per_wave
         if one_bag:
             assert per_wave == 1
-        assert one_bag == int((bags < 8192 or (bags < 32768 and lookups >= 4 * bags) or (wide and lookups >= 16 * bags))
+        assert one_bag == int(((bags < 32768 and lookups >= 6 * bags) or (wide and lookups >= 16 * bags))
                               and bags <= (1 << 26) - 4)
+
+
+def test_narrow_16_bit_rows_need_longer_bags_for_a_wavefront_each(rules):
+    few = lambda epl, narrowest: rules.few_bags_lookups(ctypes.c_int(epl), ctypes.c_int(narrowest))
+    assert [few(8, n) for n in range(7)] == [9, 9, 6, 6, 6, 6, 6] and [few(4, n) for n in range(7)] == [6] * 7
 
 
 @pytest.mark.parametrize("samples", [16, 1024, 8184, 8192])
