@@ -2,8 +2,8 @@
 """Benchmark of the table-batched embedding-bag hot path on one MI355X.
 
 A step = one pass of the whole path over one synthetic batch: tbe_forward, then
-tbe_backward_rowwise_adagrad (sort plan, radix sort, run-length, fused reduce + row-wise AdaGrad,
-long runs by bag window, dense hot rows, fix-up) on the same batch.  Inputs, weights and optimizer state are resident in HBM
+tbe_backward_rowwise_adagrad (sort plan, partition, bucket sort, runs, fused reduce + row-wise AdaGrad,
+long runs, dense hot rows, fix-up) on the same batch.  Inputs, weights and optimizer state are resident in HBM
 before the timed region; a rotation of pre-generated batches (different seeds) is used so that no step
 re-reads the previous step's index stream.
 
@@ -104,11 +104,11 @@ def window_count(batch, D, grad_bytes):
     return max(nwin, 1)
 
 
-def sort_passes(rows):
-    """Radix passes (8 bits each at most) the library needs for a table of `rows` rows: the sort is segmented
-    by table and only the bits of the table's own row index are sorted."""
-    bits = np.maximum(1, np.ceil(np.log2(np.maximum(np.asarray(rows, np.float64), 2.0)))).astype(np.int64)
-    return np.ceil(bits / 8.0)
+def sort_word_bytes(rows, batch):
+    """Bytes of the word that the library's sort makes of a lookup: bag number and row offset inside a range of rows
+    share 32 bits while no table takes more than 512 such ranges (sort_shape in the library)."""
+    bag_bits = max(1, int(batch - 1).bit_length())
+    return 4 if -(-int(np.max(rows)) // (1 << (32 - bag_bits))) <= 512 else 8
 
 
 DENSE_SLICE = 1024   # bags per partial row of a dense run (kDenseSlice)
@@ -120,7 +120,7 @@ def dense_threshold(batch):
     return max(1024, batch // 8, 128 * ((nslices + 1) // 2 + 3))
 
 
-def kernel_bytes(spec, n_t, u_t, nlong_t, ulong_t, so=4, sg=4, state_per_elem=0, passes_t=None,
+def kernel_bytes(spec, n_t, u_t, nlong_t, ulong_t, so=4, sg=4, state_per_elem=0, word=4,
                  ndense_t=None, udense_t=None, long_rows_t=None):
     """Bytes one launch of each kernel must move, two ways.
     compulsory: every distinct byte once -- what an ideal cache would leave for HBM; the roofline numerator.
@@ -128,11 +128,10 @@ def kernel_bytes(spec, n_t, u_t, nlong_t, ulong_t, so=4, sg=4, state_per_elem=0,
     n_t / u_t: lookups / distinct rows per table; nlong_t / ulong_t: lookups in / number of runs longer than LONG_RUN
     that window_runs_kernel sums piece by piece (long_rows_t: their partial rows, default one per 128 lookups + 2);
     ndense_t / udense_t: the same for the runs beyond the dense threshold, which dense_rows_kernel sums; so / sg: bytes per output / gradient element; state_per_elem: float32 optimizer
-    states per weight element (0 = one moment per row); passes_t: radix passes per table (default: one pass for
-    every table, the figure per pass).
-    Sort figures are per launch: a table's first scatter pass reads the caller's 4-byte indices and writes key +
-    payload, later passes read and write both; between the passes the payload is 2 bytes while the batch is at most
-    65536 (10 / 12 / 14 bytes per lookup in a first / middle / last pass, 12 in an only pass), else 4 (12 / 16 / 16)."""
+    states per weight element (0 = one moment per row); word: bytes of a lookup between partition and bucket sort
+    (sort_word_bytes).  The sort's bytes are those of the partition, which orders all but a few tall, few-row or very many
+    tables: the histogram reads the indices, the partition reads them and writes words, the bucket sort reads words and
+    writes key and payload."""
     sw = 4 if spec.dtype == 0 else 2
     D = spec.dims.astype(np.float64)
     B = float(spec.batch)
@@ -148,24 +147,14 @@ def kernel_bytes(spec, n_t, u_t, nlong_t, ulong_t, so=4, sg=4, state_per_elem=0,
     partial_rows = nlong_t / 128.0 + 2 * ulong_t if long_rows_t is None else long_rows_t   # fp32 partial rows of long runs
     dense_rows = udense_t * float(-(-spec.batch // DENSE_SLICE))   # one fp32 partial row per 1024-bag slice
     n_upd = n_t - ndense_t - nlong_t                     # lookups the update kernel gathers itself
-    if passes_t is None:
-        scatter = N * 16
-        hist = N * 4
-    else:
-        launches = float(np.max(passes_t))
-        if spec.batch <= 65536:
-            per_lookup = np.where(passes_t <= 1, 12.0, 10.0 + 12.0 * (passes_t - 2) + 14.0)
-        else:
-            per_lookup = 12.0 + 16.0 * (passes_t - 1)
-        scatter = float((n_t * per_lookup).sum()) / launches
-        hist = float((n_t * 4 * passes_t).sum()) / launches
     comp = {
         "forward": float((u_t * D * sw).sum() + io_fwd),
         "sort_plan": 0.0,
-        "radix_hist": hist,
-        "radix_scatter": scatter,
-        "radix_scan": 0.0,
-        "runlength": N * 4 + U * 8,
+        "sort_hist": N * 4,
+        "sort_scan": 0.0,
+        "sort_scatter": N * (4 + word),
+        "sort_local": N * (word + 8),
+        "sort_runs": N * 4 + U * 8,
         # payloads + run descriptors + each gradient row once + the rows it updates itself
         "reduce_update": float(n_upd.sum() * 4 + U * 8 + np.minimum(n_upd * sg * D, slab).sum() +
                                ((u_t - ulong_t - udense_t) * row_rw).sum()),
@@ -648,15 +637,8 @@ def run_workload(args, spec, dev, headline):
         udense_t = torch.bincount(tab[is_dense], minlength=spec.T).cpu().numpy().astype(np.float64)
         del art, uk, tab, lens, is_long, is_dense
     comp, logical = kernel_bytes(spec, n_t, u_t, nlong_t, ulong_t, so=out.element_size(), sg=grad.element_size(),
-                                 state_per_elem={0: 0, 1: 1, 2: 2}[opt_id], passes_t=sort_passes(spec.rows),
+                                 state_per_elem={0: 0, 1: 1, 2: 2}[opt_id], word=sort_word_bytes(spec.rows, spec.batch),
                                  ndense_t=ndense_t, udense_t=udense_t, long_rows_t=long_rows_t)
-    # The library partitions every table once and sorts the buckets in LDS: 4 bytes a lookup in the histogram, 8 in
-    # the partition, 12 in the bucket sort.  Its profile counts the last two as one launch per 8 bits of the row ids.
-    scatter_launches = max(1.0, prof.get("radix_scatter", (0, 0.0))[0] / args.steps)
-    for d in (comp, logical):
-        d["radix_hist"] = float(n_t.sum()) * 4
-        d["radix_scatter"] = float(n_t.sum()) * 20 / scatter_launches
-
     kernels = {}
     for name, (launches, ms) in prof.items():
         if launches:

@@ -239,10 +239,12 @@ TBE_API tbe_status_t tbe_check_inputs(tbe_handle_t h, const int32_t* d_indices, 
 TBE_API tbe_status_t tbe_profile_enable(tbe_handle_t h, int32_t max_calls);
 
 /*
- * Synchronises the recorded events and returns, per kernel slot, the number of timed launches (of the sort itself,
- * slot "radix_scatter": eight-bit digits of the tallest table's row index per call, however few launches order them) and
- * their total duration in milliseconds since the last read; then resets the pool.  names receives
- * pointers to static strings.  capacity = length of the three host arrays; *num_slots = entries filled.
+ * Synchronises the recorded events and returns, per slot, how often it was timed and its total duration in milliseconds
+ * since the last read; then resets the pool.  A slot holds the kernels of one step of a call: "forward"; of the sort
+ * "sort_plan", "sort_hist", "sort_scan", "sort_scatter" (these three once per call, or once per eight bits of the row
+ * indices in the calls that are sorted digit by digit), "sort_local" (not in those; all there is in a small call) and
+ * "sort_runs"; "reduce_update"; of the long runs "window_runs", "dense_rows" and "long_fixup".  names receives pointers to
+ * static strings.  capacity = length of the three host arrays, at least 10; *num_slots = entries filled.
  */
 TBE_API tbe_status_t tbe_profile_read(tbe_handle_t h, int32_t capacity, const char** names,
                               int64_t* launches, double* total_ms, int32_t* num_slots);

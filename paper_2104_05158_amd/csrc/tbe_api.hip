@@ -26,21 +26,24 @@ using namespace tbe;
 
 namespace {
 
+// What the profile times: a slot holds the kernels of one step of a call (the first ten may be all that a caller has room for).
 enum Slot {
     SLOT_FORWARD = 0,
     SLOT_SORT_PLAN,
-    SLOT_RADIX_HIST,
-    SLOT_RADIX_SCAN,
-    SLOT_RADIX_SCATTER,
-    SLOT_RUNLENGTH,
+    SLOT_SORT_HIST,
+    SLOT_SORT_SCAN,
+    SLOT_SORT_SCATTER,
+    SLOT_SORT_RUNS,
     SLOT_REDUCE_UPDATE,
     SLOT_WINDOW_RUNS,
     SLOT_DENSE_ROWS,
     SLOT_LONG_FIXUP,
+    SLOT_SORT_LOCAL,
     SLOT_COUNT
 };
-const char* const kSlotNames[SLOT_COUNT] = {"forward",       "sort_plan",  "radix_hist",    "radix_scan",
-                                            "radix_scatter", "runlength",  "reduce_update", "window_runs", "dense_rows", "long_fixup"};
+const char* const kSlotNames[SLOT_COUNT] = {"forward",       "sort_plan",   "sort_hist",  "sort_scan",  "sort_scatter", "sort_runs",
+                                            "reduce_update", "window_runs", "dense_rows", "long_fixup", "sort_local"};
+constexpr int kSlotsMin = 10;   // fewest a caller of tbe_profile_read makes room for
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -79,7 +82,6 @@ inline int pow2ceil_log2(int x)
 
 struct ProfRec {
     int slot;
-    int count;   // what the record adds to the slot's number of launches
     hipEvent_t start, stop;
 };
 
@@ -153,11 +155,10 @@ struct ScopedTimer {
     hipStream_t st;
     ProfRec rec;
     bool on = false;
-    ScopedTimer(tbe_s* h_, int slot, hipStream_t st_, int count = 1) : h(h_), st(st_)
+    ScopedTimer(tbe_s* h_, int slot, hipStream_t st_) : h(h_), st(st_)
     {
         if (h->profiling && h->ev_used + 2 <= h->ev_pool.size()) {
             rec.slot = slot;
-            rec.count = count;
             rec.start = h->ev_pool[h->ev_used++];
             rec.stop = h->ev_pool[h->ev_used++];
             on = hipEventRecord(rec.start, st) == hipSuccess;
@@ -658,19 +659,19 @@ static tbe_status_t enqueue_radix_sort(tbe_s* h, const int32_t* d_indices, const
         const uint32_t* keys_cur = cur < 0 ? indices : keys[cur];
         const int32_t* vals_cur = cur < 0 ? nullptr : vals[cur];
         {
-            ScopedTimer tm(h, SLOT_RADIX_HIST, st);
+            ScopedTimer tm(h, SLOT_SORT_HIST, st);
             hipLaunchKernelGGL(radix_hist_kernel, dim3(max_tiles), dim3(kSortThreads), 0, st, pl, meta, keys_cur,
                                indices, hist, p, passes, nd_bits);
             TBE_LAUNCH_CHECK(h, "radix_hist_kernel");
         }
         {
-            ScopedTimer tm(h, SLOT_RADIX_SCAN, st);
+            ScopedTimer tm(h, SLOT_SORT_SCAN, st);
             const tbe_status_t rc = device_scan(h, hist, (int64_t)max_tiles << nd_bits, st);
             if (rc != TBE_OK)
                 return rc;
         }
         {
-            ScopedTimer tm(h, SLOT_RADIX_SCATTER, st);
+            ScopedTimer tm(h, SLOT_SORT_SCATTER, st);
             // a bag number below 2^16 travels as 16 bits between the passes
             auto launch = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3(max_tiles), dim3(kSortThreads), 0, st, pl, meta, keys_cur, vals_cur,
@@ -691,7 +692,7 @@ static tbe_status_t enqueue_radix_sort(tbe_s* h, const int32_t* d_indices, const
     }
     h->final_buf = cur;
     {   // a4: run heads -> unique keys, segment offsets (in the free pair of the sort), first run of every span unit
-        ScopedTimer tm(h, SLOT_RUNLENGTH, st);
+        ScopedTimer tm(h, SLOT_SORT_RUNS, st);
         const int rl_tiles = (int)ceil_div(n, kRlTile);
         uint32_t* rl_counts = h->ws<uint32_t>(h->off_rl_counts);
         hipLaunchKernelGGL(runlength_count_kernel, dim3(rl_tiles), dim3(kRlThreads), 0, st, keys[cur], rl_counts, n);
@@ -757,10 +758,9 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.kb = ss.kb;
     a.target = ss.target;
     a.tiles_per_chunk = ss.tiles_per_chunk;
-    const int passes = (int)ceil_div(h->key_bits, 8);    // what the profile counts for the sort itself
     h->final_buf = 0;
     if (small) {
-        ScopedTimer tm(h, SLOT_RADIX_SCATTER, st, passes);
+        ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
         int bits = 1;                                    // of the linear row ids
         while (bits < 32 && ((int64_t)1 << bits) < h->soff[h->T])
             ++bits;
@@ -778,21 +778,24 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         TBE_LAUNCH_CHECK(h, "sort_plan_kernel");
     }
     {
-        ScopedTimer tm(h, SLOT_RADIX_HIST, st);
+        ScopedTimer tm(h, SLOT_SORT_HIST, st);
         hipLaunchKernelGGL(sort_hist_kernel, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_hist_kernel");
     }
     {
-        ScopedTimer tm(h, SLOT_RADIX_SCAN, st);
+        ScopedTimer tm(h, SLOT_SORT_SCAN, st);
         if (columns)
             hipLaunchKernelGGL(sort_columns_kernel, dim3((unsigned)(std::min<int64_t>(h->T, n / (chunk * kColChunks)) * (kMaxBuckets / kColBuckets))), dim3(kColThreads), 0, st, a);
         hipLaunchKernelGGL(sort_units_kernel, dim3((unsigned)h->T), dim3(kUnitsThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_units_kernel");
     }
     {   // a3: the partition and the sort of the buckets in LDS
-        ScopedTimer tm(h, SLOT_RADIX_SCATTER, st, passes);
         auto launch = [&](auto scatter, auto local, int per_cu) {
-            hipLaunchKernelGGL(scatter, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
+            {
+                ScopedTimer tm(h, SLOT_SORT_SCATTER, st);
+                hipLaunchKernelGGL(scatter, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
+            }
+            ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
             hipLaunchKernelGGL(local, dim3(256 * per_cu), dim3(kSortThreads), 0, st, a);
         };
         if (ss.wide)
@@ -802,7 +805,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         TBE_LAUNCH_CHECK(h, "sort_local_kernel");
     }
     {   // a4: run heads -> unique keys, segment offsets, first run of every span unit
-        ScopedTimer tm(h, SLOT_RUNLENGTH, st);
+        ScopedTimer tm(h, SLOT_SORT_RUNS, st);
         hipLaunchKernelGGL(sort_runs_kernel, dim3(1024), dim3(kRunThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_runs_kernel");
     }
@@ -1138,19 +1141,22 @@ tbe_status_t tbe_profile_enable(tbe_handle_t h, int32_t max_calls)
 tbe_status_t tbe_profile_read(tbe_handle_t h, int32_t capacity, const char** names, int64_t* launches,
                               double* total_ms, int32_t* num_slots)
 {
-    if (!h || capacity < SLOT_COUNT || !names || !launches || !total_ms || !num_slots)
+    if (!h || capacity < kSlotsMin || !names || !launches || !total_ms || !num_slots)
         return TBE_ERR_INVALID_ARG;
-    for (int s = 0; s < SLOT_COUNT; ++s) {
+    const int slots = std::min<int>(capacity, SLOT_COUNT);
+    for (int s = 0; s < slots; ++s) {
         names[s] = kSlotNames[s];
         launches[s] = 0;
         total_ms[s] = 0.0;
     }
-    *num_slots = SLOT_COUNT;
+    *num_slots = slots;
     for (const ProfRec& r : h->recs) {
         TBE_HIP_CHECK(h, hipEventSynchronize(r.stop));
         float ms = 0.f;
         TBE_HIP_CHECK(h, hipEventElapsedTime(&ms, r.start, r.stop));
-        launches[r.slot] += r.count;
+        if (r.slot >= slots)
+            continue;
+        launches[r.slot] += 1;
         total_ms[r.slot] += ms;
     }
     h->recs.clear();

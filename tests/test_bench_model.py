@@ -18,8 +18,8 @@ def test_kernel_bytes_on_a_hand_counted_case():
     grad_once = min(10 * 4 * 8, B * 4 * 8) + min(6 * 4 * 16, B * 4 * 16)  # a gradient row at most once per bag
     assert comp["reduce_update"] == N * 4 + U * 8 + grad_once + rmw == 1072
     assert logical["reduce_update"] == N * 4 + U * 8 + (10 * 4 * 8 + 6 * 4 * 16) + rmw == 1392
-    assert comp["radix_hist"] == N * 4 and comp["radix_scatter"] == N * 16
-    assert comp["runlength"] == N * 4 + U * 8
+    assert comp["sort_hist"] == N * 4 and comp["sort_scatter"] == N * 8 and comp["sort_local"] == N * 12
+    assert comp["sort_runs"] == N * 4 + U * 8
     assert comp["long_fixup"] == 0 and comp["dense_rows"] == 0
 
 
@@ -50,23 +50,15 @@ def test_long_runs_add_partial_rows_and_16_bit_types_halve_the_row_bytes():
     assert base["reduce_update"] - half["reduce_update"] == min(5000, 2048) * 2 * 64
 
 
-def test_sort_bytes_per_launch_follow_the_tables_pass_counts():
-    # 300 rows -> 9 bits -> 2 passes; 70000 rows -> 17 bits -> 3 passes
-    assert bench.sort_passes([300, 70000, 256, 2 ** 24, 2 ** 24 + 1]).tolist() == [2, 3, 1, 3, 4]
+def test_sort_bytes_follow_the_width_of_a_word():
+    # batch 65536: 16 bits for the bag, ranges of 65536 rows, at most 512 of them
+    assert bench.sort_word_bytes([300, 1 << 25], 65536) == 4 and bench.sort_word_bytes([300, (1 << 25) + 1], 65536) == 8
+    assert bench.sort_word_bytes([(1 << 25) + 1], 32768) == 4 and bench.sort_word_bytes([(1 << 31) - 1], 1) == 4
     spec = wl.custom([300, 70000], [8, 16], 1, 4, 1.0)
     n_t, u_t = np.array([10.0, 6.0]), np.array([3.0, 6.0])
-    comp, _ = bench.kernel_bytes(spec, n_t, u_t, np.zeros(2), np.zeros(2), passes_t=bench.sort_passes(spec.rows))
-    # three launches; batch <= 65536: the payload is 2 bytes between the passes.  First pass of a table: index in,
-    # key + short payload out (10 bytes per lookup); middle pass 6 in + 6 out; last pass 6 in + 8 out
-    assert comp["radix_scatter"] == (10 * (10 + 14) + 6 * (10 + 12 + 14)) / 3
-    assert comp["radix_hist"] == (10 * 4 * 2 + 6 * 4 * 3) / 3
-    big = wl.custom([300, 70000], [8, 16], 1, 70000, 1.0)
-    comp, _ = bench.kernel_bytes(big, n_t, u_t, np.zeros(2), np.zeros(2), passes_t=bench.sort_passes(big.rows))
-    assert comp["radix_scatter"] == (10 * (12 + 16) + 6 * (12 + 32)) / 3       # 4-byte payloads beyond 65536 bags
-    one = wl.custom([200], [8], 1, 4, 1.0)
-    comp, _ = bench.kernel_bytes(one, np.array([10.0]), np.array([3.0]), np.zeros(1), np.zeros(1),
-                                 passes_t=bench.sort_passes(one.rows))
-    assert comp["radix_scatter"] == 10 * 12                                     # an only pass: index in, key + payload out
+    comp, _ = bench.kernel_bytes(spec, n_t, u_t, np.zeros(2), np.zeros(2), word=8)
+    # index in, word out; word in, key and payload out
+    assert comp["sort_scatter"] == 16 * (4 + 8) and comp["sort_local"] == 16 * (8 + 8) and comp["sort_hist"] == 16 * 4
 
 
 def test_default_invocation_is_config_4_with_3_and_2_alongside():

@@ -340,9 +340,29 @@ def test_profile_slots(gpu_device):
         op.forward(a[0], a[1], spec.batch)
         op.backward_rowwise_adagrad(a[0], a[1], spec.batch, a[2], 0.01, 1e-8)
     prof = op.profile_read()
-    assert prof["forward"][0] == 3 and prof["reduce_update"][0] == 3 and prof["radix_scatter"][0] == 3 * 2
-    assert all(ms >= 0 for _, ms in prof.values())
+    # at most 8192 lookups: one kernel sorts them
+    assert prof["forward"][0] == 3 and prof["reduce_update"][0] == 3 and prof["sort_local"][0] == 3
+    assert all(ms >= 0 for _, ms in prof.values()) and all(prof[s][0] == 0 for s in ("sort_plan", "sort_scatter", "sort_runs"))
     op.profile_enable(0)
+    op.close()
+
+
+@pytest.mark.parametrize("rows,n,expect", [
+    (10_000, 30_000, dict(sort_plan=1, sort_hist=1, sort_scan=1, sort_scatter=1, sort_local=1, sort_runs=1)),       # partition
+    (10_000, 1_000_000, dict(sort_plan=1, sort_hist=2, sort_scan=2, sort_scatter=2, sort_local=0, sort_runs=1)),    # two digits
+])
+def test_profile_counts_every_step_of_the_sort_once(gpu_device, rows, n, expect):
+    batch = 100
+    op = tbe.TableBatchedEmbeddingBags([rows], [4], 0, batch, n, device=gpu_device)
+    idx = torch.from_numpy(np.random.default_rng(1).integers(0, rows, n).astype(np.int32)).to(gpu_device)
+    off = torch.from_numpy((np.arange(batch + 1) * (n // batch)).astype(np.int64)).to(gpu_device)
+    op.profile_enable(4)
+    for _ in range(2):
+        op.backward_sort(idx, off, batch)
+    prof = op.profile_read()
+    assert {k: prof[k][0] for k in expect} == {k: 2 * v for k, v in expect.items()}
+    op.profile_enable(0)
+    op.close()
 
 
 def test_step_captured_in_a_hip_graph_replays_like_eager(gpu_device):
