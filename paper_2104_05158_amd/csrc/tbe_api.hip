@@ -47,14 +47,6 @@ constexpr int kSlotsMin = 10;   // fewest a caller of tbe_profile_read makes roo
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-// Lookups per bucket: units come in rounds of the 768 resident workgroups (less some for the last, smaller one of every table
-// and for rows with a unit of their own), in as few rounds as units of at most 7/16 of a tile make, but no unit is worth
-// less than kSortTargetMin.  A bucket spreads by 1/4 around that; beyond a tile it takes the slow path through memory, which
-// one bucket in 1,000 did at half a tile (64 tables, 5.5 M lookups: 76 us for the units, 55 without such a straggler).
-// Sort with 512 units in a smaller call and 7/16 of a tile in a larger one -> this: 1000 rows, 8 tables, 2 M lookups 95 -> 81 us;
-// 60,000 rows 105 -> 87; 64 tables, 4 M 108 -> 105; 4 tables of 1000 rows, 4 M 117 -> 107.
-constexpr int kSortTargetMin = 1024, kSortTargetMax = 3584;
-constexpr int64_t kSortUnitsRound = 704;
 // Tiles per chunk of the partition: a histogram of up to 4 KiB is written and read per chunk, but there should be
 // some 4096 chunks for 512 resident workgroups (98 M lookups: histogram + partition 622 us with up to 4, 660 with 8).
 constexpr int64_t kSortChunksWanted = 4096;
@@ -230,8 +222,7 @@ SortShape sort_shape(const tbe_s* h, int64_t batch, int64_t n)
     s.wide = ceil_div(h->max_rows, (int64_t)1 << s.kb) > kMaxRangeCuts;
     if (s.wide)
         s.vb = s.kb = 32;
-    const int64_t rounds = std::max<int64_t>(1, ceil_div(n, kSortTargetMax * kSortUnitsRound));
-    s.target = (int)std::max<int64_t>(kSortTargetMin, ceil_div(n, rounds * kSortUnitsRound));
+    s.target = sort_target(n);
     s.tiles_per_chunk = (int)std::min<int64_t>(kSortTilesPerChunk, std::max<int64_t>(1, n / (kSortTile * kSortChunksWanted)));
     return s;
 }
@@ -243,7 +234,8 @@ void plan_partition(tbe_s* h, Take take)
 {
     const int64_t nmax = h->max_indices;
     const SortShape ss = sort_shape(h, h->max_batch, nmax);
-    int64_t slots = 2 * (int64_t)h->T + 513 + ceil_div(nmax, kSortTargetMax) + nmax / kSortTile;
+    // a unit per bucket of every table, and one more per tile of a row that has a bucket of its own
+    int64_t slots = 2 * (int64_t)h->T + sort_buckets_max(nmax) + nmax / kSortTile;
     // fewest row-offset bits a call with 32-bit words can have (a smaller batch may use them where the largest does not)
     int kb = ss.wide ? 0 : ss.kb;
     while (ceil_div(h->max_rows, (int64_t)1 << kb) > kMaxRangeCuts)

@@ -32,6 +32,9 @@ int position_pieces(int s, int len, int32_t* out /*[257]*/)
 
 int use_radix_sort(int64_t tables, int64_t lookups, int passes) { return tbe::use_radix_sort(tables, lookups, passes); }
 
+int sort_target(int64_t lookups) { return tbe::sort_target(lookups); }
+int64_t sort_buckets_max(int64_t lookups) { return tbe::sort_buckets_max(lookups); }
+
 void sample_positions(int n, int samples, int32_t* out)
 {
     const uint64_t stretch = ((uint64_t)n << 32) / (uint32_t)samples;

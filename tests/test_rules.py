@@ -48,6 +48,23 @@ def test_narrow_16_bit_rows_need_longer_bags_for_a_wavefront_each(rules):
     assert [few(8, n) for n in range(7)] == [9, 9, 6, 6, 6, 6, 6] and [few(4, n) for n in range(7)] == [6] * 7
 
 
+def test_a_call_of_any_size_has_room_for_its_buckets(rules):
+    # the memory of a handle is laid out for its largest call: no smaller one may ask for more buckets
+    rules.sort_buckets_max.restype = ctypes.c_int64
+    most = lambda n: rules.sort_buckets_max(ctypes.c_int64(n))
+    target = lambda n: rules.sort_target(ctypes.c_int64(n))
+    round_of = 3584 * 704
+    sizes = {1, 8193, (1 << 31) - (1 << 24) - 1} | {k * round_of for k in (1, 2, 3, 40, 800)}
+    sizes = sorted(s + d for s in sizes for d in (-1, 0, 1) if s + d > 0)
+    before = 0
+    for n in sizes:
+        t = target(n)
+        assert 1024 <= t <= 3584 and before <= most(n)
+        before = most(n)
+        assert -(-n // t) <= most(n)
+    assert target(704 * 1024) == 1024 and target(704 * 1024 + 1) == 1025 and target(round_of + 1) == 1793
+
+
 @pytest.mark.parametrize("samples", [16, 1024, 8184, 8192])
 @pytest.mark.parametrize("n", [8192, 20_000, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, 100_000_000, (1 << 31) - (1 << 24) - 1])
 def test_samples_come_from_equal_stretches_of_the_whole_table(rules, n, samples):
