@@ -140,22 +140,26 @@ inline bool use_radix_sort(int64_t tables, int64_t lookups, int passes)
            (passes > 1 && tables <= 16 && lookups >= kTallTable[std::min(passes, 4)] * power);
 }
 
-// Lookups per bucket: units come in rounds of the 768 resident workgroups (less some for the last, smaller one of every table
-// and for rows with a unit of their own), in as few rounds as units of at most 7/16 of a tile make, but no unit is worth
-// less than kSortTargetMin.  A bucket spreads by 1/4 around that; beyond a tile it takes the slow path through memory, which
-// one bucket in 1,000 did at half a tile (64 tables, 5.5 M lookups: 76 us for the units, 55 without such a straggler).
-// Sort with 512 units in a smaller call and 7/16 of a tile in a larger one -> this: 1000 rows, 8 tables, 2 M lookups 95 -> 81 us;
-// 60,000 rows 105 -> 87; 64 tables, 4 M 108 -> 105; 4 tables of 1000 rows, 4 M 117 -> 107.
-constexpr int kSortTargetMin = 1024, kSortTargetMax = 3584;
-constexpr int64_t kSortUnitsRound = 704;
+// Lookups per bucket: a small call has some 512 units, two a CU, but none is worth less than kSortTargetMin.  From 5/16 of a
+// tile each on, units come in rounds of the 768 resident workgroups (less some for the last, smaller one of every table and
+// for rows with a unit of their own), in as few rounds as units of at most 7/16 of a tile make.  A bucket spreads by 1/4
+// around that; beyond a tile it takes the slow path through memory, which one bucket in 1,000 did at half a tile (64 tables,
+// 5.5 M lookups: 76 us for the units, 55 without such a straggler).  Sort with 512 units in a smaller call and 7/16 of a tile
+// in a larger one -> this: 1000 rows, 8 tables, 2 M lookups 95 -> 81 us; 60,000 rows 105 -> 87; 64 tables, 4 M 108 -> 105; 4
+// tables of 1000 rows, 4 M 117 -> 107.  Whole steps with 512 units / in a round of 704: 0.66 M lookups 320 / 324 us, 0.71 M
+// 330 / 337, 0.84 M 253 / 257, 1.1 to 1.6 M the same, 1.8 M 998 / 977.
+constexpr int kSortTargetMin = 1024, kSortTargetFew = 2560, kSortTargetMax = 3584;
+constexpr int64_t kSortUnitsFew = 512, kSortUnitsRound = 704;
 
-// rounds of units of a call
+// rounds of units of a call that is not small
 inline int64_t sort_rounds(int64_t lookups) { return (lookups + kSortTargetMax * kSortUnitsRound - 1) / (kSortTargetMax * kSortUnitsRound); }
 
 inline int sort_target(int64_t lookups)
 {
-    const int64_t units = std::max<int64_t>(1, sort_rounds(lookups)) * kSortUnitsRound;
-    return (int)std::max<int64_t>(kSortTargetMin, (lookups + units - 1) / units);
+    if (lookups <= kSortTargetFew * kSortUnitsFew)
+        return (int)std::max<int64_t>(kSortTargetMin, lookups / kSortUnitsFew);
+    const int64_t units = sort_rounds(lookups) * kSortUnitsRound;
+    return (int)((lookups + units - 1) / units);
 }
 
 // Most full buckets, rounded up, that calls of at most this many lookups can ask for (a table's last one comes on top)

@@ -54,7 +54,7 @@ def test_a_call_of_any_size_has_room_for_its_buckets(rules):
     most = lambda n: rules.sort_buckets_max(ctypes.c_int64(n))
     target = lambda n: rules.sort_target(ctypes.c_int64(n))
     round_of = 3584 * 704
-    sizes = {1, 8193, (1 << 31) - (1 << 24) - 1} | {k * round_of for k in (1, 2, 3, 40, 800)}
+    sizes = {1, 8193, 512 * 1024, 512 * 2560, (1 << 31) - (1 << 24) - 1} | {k * round_of for k in (1, 2, 3, 40, 800)}
     sizes = sorted(s + d for s in sizes for d in (-1, 0, 1) if s + d > 0)
     before = 0
     for n in sizes:
@@ -62,7 +62,7 @@ def test_a_call_of_any_size_has_room_for_its_buckets(rules):
         assert 1024 <= t <= 3584 and before <= most(n)
         before = most(n)
         assert -(-n // t) <= most(n)
-    assert target(704 * 1024) == 1024 and target(704 * 1024 + 1) == 1025 and target(round_of + 1) == 1793
+    assert target(512 * 2560) == 2560 and target(512 * 2560 + 1) == 1862 and target(round_of + 1) == 1793
 
 
 @pytest.mark.parametrize("samples", [16, 1024, 8184, 8192])
