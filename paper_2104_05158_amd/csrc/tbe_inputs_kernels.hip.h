@@ -29,8 +29,8 @@ constexpr int kMaxShards = 1024;
 // and contiguous across the wavefront.  How a tile gets the sum of the lengths before it goes by the number of tiles:
 //   up to kScanSelf     it adds them up itself: one launch (256 lengths: 3.0 us instead of 6.8 in three launches)
 //   up to kScanSums     a first launch writes the tiles' totals and every workgroup adds up those before its own
-//   more                a single workgroup scans the totals in between (4 M lengths: 16 us either way; 16 M: 55 us when
-//                       every workgroup adds up to 32 KiB of totals, 52 with that launch)
+//   more                a single workgroup scans the totals in between (8 M lengths: 27.4 us with that
+//                       launch, 26 when every workgroup adds up totals; 12 M: 41 either way; 16 M: 52 and 55)
 
 __device__ __forceinline__ int64_t block_exclusive_scan64(int64_t v, int64_t* s_wave /*[4]*/, int64_t& block_total)
 {
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(kThreads) void scan64_top_kernel(int64_t* __restric
 }
 
 constexpr int kScanSelf = 8;
-constexpr int kScanSums = 1024;
+constexpr int kScanSums = 3072;
 enum { kBeforeSelf = 0, kBeforeSums = 1, kBeforePrefix = 2 };   // where the sum of the lengths before a tile comes from
 
 template <int BEFORE>

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 TILE = 4096
 
 
-@pytest.mark.parametrize("n", [8 * TILE - 1, 8 * TILE, 8 * TILE + 1, 9 * TILE + 7, 1024 * TILE, 1024 * TILE + 1, 4096 * TILE, 4096 * TILE + 1])
+@pytest.mark.parametrize("n", [8 * TILE - 1, 8 * TILE, 8 * TILE + 1, 9 * TILE + 7, 3072 * TILE, 3072 * TILE + 1, 4096 * TILE, 4096 * TILE + 1])
 def test_prefix_sums_around_every_launch_border(gpu_device, n):
     lens = np.random.default_rng(n).integers(0, 60, n).astype(np.int32)
     got = _gpu_lengths_to_offsets(lens, gpu_device)
