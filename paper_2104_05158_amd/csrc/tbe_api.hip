@@ -488,9 +488,10 @@ tbe_status_t tbe_create(const tbe_config_t* cfg, tbe_handle_t* out_handle)
         m.rbase = (uint32_t)s;
         m.dim = h->dims[t];
         m.col = c;
-        m.lpr_fwd = std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], h->fwd_epl)));
-        h->fwd_wide = h->fwd_wide && m.lpr_fwd == 6;
-        m.lpr_bwd = std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], 8)));
+        m.rows = (uint32_t)h->rows[t];
+        m.lanes = (uint32_t)std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], h->fwd_epl))) |
+                  (uint32_t)std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], 8))) << 8;
+        h->fwd_wide = h->fwd_wide && m.lpr_fwd() == 6;
         m.key_bits = table_bits[t];
         w += h->rows[t] * (int64_t)h->dims[t];
         s += h->rows[t];
@@ -498,7 +499,7 @@ tbe_status_t tbe_create(const tbe_config_t* cfg, tbe_handle_t* out_handle)
     }
     int narrowest = 6;
     for (const TableMeta& m : h->meta)
-        narrowest = std::min(narrowest, m.lpr_fwd);
+        narrowest = std::min(narrowest, m.lpr_fwd());
     h->fwd_few = few_bags_lookups(h->fwd_epl, narrowest);
     h->woff[h->T] = w;
     h->soff[h->T] = s;

@@ -44,9 +44,12 @@ struct TableMeta {      // 32 bytes, one per table, in the workspace head
     uint32_t rbase;     // linear id of the table's row 0
     int32_t dim;        // D_t
     int32_t col;        // first output column
-    int32_t lpr_fwd;    // log2 lanes per row, forward (EPL elements per lane)
-    int32_t lpr_bwd;    // log2 lanes per row, backward (2 x 4 floats per lane)
+    uint32_t rows;
+    uint32_t lanes;     // log2 lanes per row: forward (EPL elements per lane), 256 x backward (2 x 4 floats per lane)
     int32_t key_bits;   // ceil(log2 rows) (at least 1): the bits of the table's row index that the sort orders
+
+    __host__ __device__ int lpr_fwd() const { return (int)(lanes & 0xffu); }
+    __host__ __device__ int lpr_bwd() const { return (int)(lanes >> 8); }
 };
 
 struct Counters {       // workspace scalars
@@ -77,8 +80,18 @@ struct Counters {       // workspace scalars
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// fp16 -> fp32 accumulate as one mixed-precision FMA: x*1 + a is exactly a + x
-__device__ __forceinline__ float acc_half(float a, __half h) { return __builtin_fmaf(__half2float(h), 1.0f, a); }
+// a + (lower, upper half of v), halves in fp16, as one mixed-precision FMA: x * 1 + a is exactly a + x.  (Written as
+// fmaf(float(h), 1, a) the multiplication is dropped first, and what is left takes a conversion and an addition.)
+__device__ __forceinline__ float acc_lo(float a, uint32_t v)
+{
+    asm("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel_hi:[1,0,0]" : "+v"(a) : "v"(v));
+    return a;
+}
+__device__ __forceinline__ float acc_hi(float a, uint32_t v)
+{
+    asm("v_fma_mix_f32 %0, %1, 1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(a) : "v"(v));
+    return a;
+}
 
 // Row access in the storage type: Vec is the raw vector one lane loads (EPL elements); `add`
 // converts to fp32 and accumulates.  Loads are kept raw until they are consumed so that many can
@@ -116,10 +129,8 @@ struct RowIO<__half, 4> {
     }
     __device__ static __forceinline__ void add(float (&a)[4], Vec v)
     {
-        const __half2 x = *reinterpret_cast<__half2*>(&v.x);
-        const __half2 y = *reinterpret_cast<__half2*>(&v.y);
-        a[0] = acc_half(a[0], __low2half(x)); a[1] = acc_half(a[1], __high2half(x));
-        a[2] = acc_half(a[2], __low2half(y)); a[3] = acc_half(a[3], __high2half(y));
+        a[0] = acc_lo(a[0], v.x); a[1] = acc_hi(a[1], v.x);
+        a[2] = acc_lo(a[2], v.y); a[3] = acc_hi(a[3], v.y);
     }
     __device__ static __forceinline__ void store(__half* p, const float (&f)[4])
     {
@@ -136,16 +147,34 @@ struct RowIO<__half, 8> {
     __device__ static __forceinline__ Vec ldv(const __half* p) { return *reinterpret_cast<const uint4*>(p); }
     __device__ static __forceinline__ void add(float (&a)[8], Vec v)
     {
-        const __half2 x = *reinterpret_cast<__half2*>(&v.x);
-        const __half2 y = *reinterpret_cast<__half2*>(&v.y);
-        const __half2 z = *reinterpret_cast<__half2*>(&v.z);
-        const __half2 w = *reinterpret_cast<__half2*>(&v.w);
-        a[0] = acc_half(a[0], __low2half(x)); a[1] = acc_half(a[1], __high2half(x));
-        a[2] = acc_half(a[2], __low2half(y)); a[3] = acc_half(a[3], __high2half(y));
-        a[4] = acc_half(a[4], __low2half(z)); a[5] = acc_half(a[5], __high2half(z));
-        a[6] = acc_half(a[6], __low2half(w)); a[7] = acc_half(a[7], __high2half(w));
+        a[0] = acc_lo(a[0], v.x); a[1] = acc_hi(a[1], v.x);
+        a[2] = acc_lo(a[2], v.y); a[3] = acc_hi(a[3], v.y);
+        a[4] = acc_lo(a[4], v.z); a[5] = acc_hi(a[5], v.z);
+        a[6] = acc_lo(a[6], v.w); a[7] = acc_hi(a[7], v.w);
     }
 };
+
+// Rows of a table of at most kBufferBytes by 32-bit byte offsets from its first element: a load from kNoRow (or from
+// a column of it) on reads nothing and gives zeros.
+constexpr uint32_t kNoRow = 0xffff0000u;
+constexpr uint64_t kBufferBytes = kNoRow;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const void* table, uint64_t bytes)
+{
+    constexpr int kDataFormat32 = 4 << 15;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(table), 0, (int)(uint32_t)bytes, kDataFormat32);
+}
+
+template <typename Vec>
+__device__ __forceinline__ Vec load_buffer(__amdgpu_buffer_rsrc_t table, uint32_t offset)
+{
+    if constexpr (sizeof(Vec) == 16)
+        return __builtin_bit_cast(Vec, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(table, offset, 0, 0));
+    else
+        return __builtin_bit_cast(Vec, (u32x2)__builtin_amdgcn_raw_buffer_load_b64(table, offset, 0, 0));
+}
 
 // ---------------------------------------------------------------- read-rate probe
 //
@@ -186,9 +215,15 @@ __global__ __launch_bounds__(256) void probe_read_kernel(const uint4* p, size_t 
 // batch always belong to one table, so the lane mapping is uniform inside a batch.
 //
 // The inner loop is branch-free so that all loads of a step are issued back to back: slots past the
-// end of a bag read a row of zeros kept in the workspace (pointer select instead of a predicated
-// load), column offsets past D are clamped (those lanes never store), and the indices of the next
-// step are requested before the rows of the current step are consumed.
+// end of a bag load from kNoRow, in a table too tall for 32-bit offsets a row of zeros kept in the workspace;
+// column offsets past D are clamped (those lanes never store), and the indices of the next step are requested
+// before the rows of the current step are consumed.
+//
+// Bound by L2 trips in flight.  A probe that gathers 256-byte rows, 62 % of them from 2 MiB (what the L2s find of a
+// Zipf batch) and the rest from 1 GiB, reaches 13.7 TB/s whatever the rows in flight; 196 M lookups of 64 and 128
+// fp16 columns take 2.83 ms, 12.9 TB/s.  Offsets formed once a lookup by one lane and mixed FMAs left 9 vector
+// instructions a row of 27, which is 1 % there, 6 % where bags are short (64 tables, 3 lookups: 109 -> 103 us) and
+// 11 % in calls of few bags (24,000 of 20 lookups, 128 fp16 columns: 16.1 -> 14.3 us).
 // 4 pooled values in the output type OT (float, or __half rounded to nearest even)
 __device__ __forceinline__ void store_out4(float* p, float a, float b, float c, float d)
 {
@@ -229,7 +264,7 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(
         const int t = j / B;
         const TableMeta m = meta[t];
         const int D = m.dim;
-        const int lprl = m.lpr_fwd;
+        const int lprl = m.lpr_fwd();
         const int LPR = 1 << lprl;
         const int G = kWave >> lprl;
         const int sub = lane & (LPR - 1);
@@ -270,29 +305,52 @@ __global__ __launch_bounds__(kFwdThreads) void forward_kernel(
             // The address unit spends as long on a 4-byte load as on a 16-byte one, so the indices are not
             // loaded once per row: the LPR lanes of a group load the bag's next LPR indices with ONE
             // instruction (lane `sub` the sub-th of them) a block ahead of their use, and every row load
-            // takes its index from the group's lanes by a shuffle.
+            // takes its index, or its row's offset, from the group's lanes by a shuffle.
             const int gbase = lane & ~(LPR - 1);
-            int cur = 0;
             int nxt = indices[min((uint32_t)(start + sub), last)];
-            for (int it = 0; __ballot(it < len) != 0ull; it += kFwdUnroll) {
-                if ((it & (LPR - 1)) == 0) {
-                    cur = nxt;
-                    nxt = indices[min((uint32_t)(start + it + LPR + sub), last)];
-                }
-                Vec raw[kFwdUnroll][KMAX];
-#pragma unroll
-                for (int u = 0; u < kFwdUnroll; ++u) {
-                    const int idx = __shfl(cur, gbase | ((it + u) & (LPR - 1)));
-                    const WT* rp = (it + u < len) ? wbase + (int64_t)idx * D : zrow;
-#pragma unroll
-                    for (int k = 0; k < KMAX; ++k)
-                        raw[u][k] = IO::ldv(rp + eoff[k]);
-                }
+            const uint64_t table_bytes = (uint64_t)m.rows * (uint32_t)D * sizeof(WT);
+            Vec raw[kFwdUnroll][KMAX];
+            auto add_rows = [&]() {
+                __builtin_amdgcn_sched_barrier(0);       // all rows of a step are requested before the first is added
 #pragma unroll
                 for (int u = 0; u < kFwdUnroll; ++u)
 #pragma unroll
                     for (int k = 0; k < KMAX; ++k)
                         IO::add(accs[u % NACC][k], raw[u][k]);
+            };
+            if (table_bytes <= kBufferBytes) {
+                const __amdgpu_buffer_rsrc_t table = row_buffer(wbase, table_bytes);
+                const uint32_t row_bytes = (uint32_t)D * (uint32_t)sizeof(WT);
+                for (int block = 0; __ballot(block < len) != 0ull; block += LPR) {
+                    const uint32_t cur = block + sub < len ? (uint32_t)nxt * row_bytes : kNoRow;
+                    nxt = indices[min((uint32_t)(start + block + LPR + sub), last)];
+                    for (int i = 0; i < LPR && __ballot(block + i < len) != 0ull; i += kFwdUnroll) {
+#pragma unroll
+                        for (int u = 0; u < kFwdUnroll; ++u) {
+                            const uint32_t row = (uint32_t)__builtin_amdgcn_ds_bpermute((gbase + i + u) * 4, (int)cur);
+#pragma unroll
+                            for (int k = 0; k < KMAX; ++k)
+                                raw[u][k] = load_buffer<Vec>(table, row + (uint32_t)eoff[k] * (uint32_t)sizeof(WT));
+                        }
+                        add_rows();
+                    }
+                }
+            } else {
+                for (int block = 0; __ballot(block < len) != 0ull; block += LPR) {
+                    const int cur = nxt;
+                    nxt = indices[min((uint32_t)(start + block + LPR + sub), last)];
+                    for (int i = 0; i < LPR && __ballot(block + i < len) != 0ull; i += kFwdUnroll) {
+#pragma unroll
+                        for (int u = 0; u < kFwdUnroll; ++u) {
+                            const int idx = __builtin_amdgcn_ds_bpermute((gbase + i + u) * 4, cur);
+                            const WT* rp = block + i + u < len ? wbase + (int64_t)idx * D : zrow;
+#pragma unroll
+                            for (int k = 0; k < KMAX; ++k)
+                                raw[u][k] = IO::ldv(rp + eoff[k]);
+                        }
+                        add_rows();
+                    }
+                }
             }
         } else if (__ballot(len > 0) != 0ull) {
             // rows of one or two lanes: every lane loads its own indices
@@ -377,7 +435,7 @@ __global__ __launch_bounds__(kFwdThreads) void forward_bag_kernel(
     const int t = j / B;
     const TableMeta m = meta[t];
     const int D = m.dim;
-    const int lprl = m.lpr_fwd;
+    const int lprl = m.lpr_fwd();
     const int LPR = 1 << lprl;
     const int G = kWave >> lprl;
     const int sub = lane & (LPR - 1);
@@ -403,29 +461,44 @@ __global__ __launch_bounds__(kFwdThreads) void forward_bag_kernel(
         // Up to 8 groups: a step of 8 G lookups lies inside a block of 64, loaded with one instruction a block ahead
         // and handed out by shuffles.  More groups (rows of up to four lanes): every lane loads its own indices.
         const bool blocks = G * kBagUnroll <= kWave;
+        const uint64_t table_bytes = (uint64_t)m.rows * (uint32_t)D * sizeof(WT);
+        const bool buffer = blocks && table_bytes <= kBufferBytes;   // a lane forms the byte offset of its lookup's row
+        const __amdgpu_buffer_rsrc_t table = row_buffer(wbase, buffer ? table_bytes : 0);
+        const uint32_t row_bytes = (uint32_t)D * (uint32_t)sizeof(WT);
         int cur = 0, nxt = 0;
         if (blocks)
             nxt = indices[min((uint32_t)(start + lane), last)];
         auto step = [&](auto rows, int it) {
             constexpr int U = decltype(rows)::value;
-            int idx[U];
-            if (blocks) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    idx[u] = __shfl(cur, (it + u * G + grp) & (kWave - 1));
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    idx[u] = indices[min((uint32_t)(start + it + u * G + grp), last)];
-            }
             Vec raw[U][KMAX];
+            if (buffer) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const WT* rp = it + u * G + grp < len ? wbase + (int64_t)idx[u] * D : zrow;
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t row = (uint32_t)__builtin_amdgcn_ds_bpermute(((it & (kWave - 1)) + u * G + grp) * 4, cur);
 #pragma unroll
-                for (int k = 0; k < KMAX; ++k)
-                    raw[u][k] = IO::ldv(rp + eoff[k]);
+                    for (int k = 0; k < KMAX; ++k)
+                        raw[u][k] = load_buffer<Vec>(table, row + (uint32_t)eoff[k] * (uint32_t)sizeof(WT));
+                }
+            } else {
+                int idx[U];
+                if (blocks) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        idx[u] = __shfl(cur, (it + u * G + grp) & (kWave - 1));
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        idx[u] = indices[min((uint32_t)(start + it + u * G + grp), last)];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const WT* rp = it + u * G + grp < len ? wbase + (int64_t)idx[u] * D : zrow;
+#pragma unroll
+                    for (int k = 0; k < KMAX; ++k)
+                        raw[u][k] = IO::ldv(rp + eoff[k]);
+                }
             }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -434,7 +507,7 @@ __global__ __launch_bounds__(kFwdThreads) void forward_bag_kernel(
         };
         for (int it = 0; it < len; it += kBagUnroll * G) {
             if (blocks && (it & (kWave - 1)) == 0) {
-                cur = nxt;
+                cur = !buffer ? nxt : it + lane < len ? (int)((uint32_t)nxt * row_bytes) : (int)kNoRow;
                 if (len - it > kWave)
                     nxt = indices[min((uint32_t)(start + it + kWave + lane), last)];
             }
@@ -1075,7 +1148,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
         m.rbase = (uint32_t)uniform((int)m.rbase);
         m.dim = uniform(m.dim);
         m.col = uniform(m.col);
-        m.lpr_bwd = uniform(m.lpr_bwd);
+        m.lanes = (uint32_t)uniform((int)m.lanes);
         const uint32_t t_hi = (uint32_t)uniform((int)a.row_base[t + 1]);
         int rb = 0;
 #pragma unroll
@@ -1084,7 +1157,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
             rb += __popcll(__ballot(run < nruns && s_key[min(run, nruns - 1)] < t_hi));
         }
         const int D = m.dim;
-        const int lprl = m.lpr_bwd;
+        const int lprl = m.lpr_bwd();
         const int lgG = 6 - lprl;
         const int G = 1 << lgG;
         const GT* gb = a.table_major ? grad_out + (int64_t)a.batch * m.col : grad_out + m.col;
@@ -1771,7 +1844,7 @@ __device__ __forceinline__ void sum_piece(const BwdArgs& a, const int4 rec /* p0
     const TableMeta m = a.meta[rec.w];
     const int64_t stride = a.table_major ? m.dim : a.sumD;
     const GT* gb = a.table_major ? grad_out + (int64_t)a.batch * m.col : grad_out + m.col;
-    const Cols c(m.dim, m.lpr_bwd, lane);
+    const Cols c(m.dim, m.lpr_bwd(), lane);
     const int G = kWave >> c.lprl;
     float acc[2][4];
 #pragma unroll
@@ -1887,7 +1960,7 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
         const uint32_t key = rec.key;
         const bool dense = e - s > a.dense_thr;
         const TableMeta m = a.meta[t];
-        const Cols c(m.dim, m.lpr_bwd, lane);
+        const Cols c(m.dim, m.lpr_bwd(), lane);
         const int k0 = s / kChunk;
         const float* pbase = a.partials;
         const int64_t dpad = a.dpad;
