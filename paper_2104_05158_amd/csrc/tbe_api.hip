@@ -55,11 +55,6 @@ constexpr int kSortTilesPerChunk = 4;
 // (8 tables, 0.65 M lookups: step of 347 us, 345 without it).
 constexpr int64_t kColumnsMin = 96;
 constexpr int kDenseGrid = 1024;  // persistent workgroups of dense_rows_kernel: 4 per CU, a multiple of 8
-// Lookups from which a wavefront of the update kernel owns 128 sorted positions instead of 64.  A small call needs
-// the shorter spans to have wavefronts enough (0.13 M lookups, dims 4..512: 62 us with 64, 112 with 128, 206 with
-// 256; 0.65 M: 156 / 170 / 169); a large one fills the steps of the length classes better with the longer ones
-// (5.5 M lookups, 16-bit rows: 303 us with 128, 319 with 64, 334 with 256; 127 M: 3.84 / 3.87 / 3.88 ms).
-constexpr int64_t kWideSpanMin = 2 << 20;
 constexpr int kWindowGrid = 1024;  // persistent workgroups of window_runs_kernel: 4 per CU, a multiple of 8 (by position
                                    // 1536, 2048 and 8192 are no faster)
 constexpr int kDenseBagsPerLookup = 8;
@@ -97,6 +92,7 @@ struct tbe_s {
     int fwd_kmax = 1;
     bool fwd_wide = true;    // every table's row takes all lanes of a wavefront
     int fwd_few = 6;         // lookups a bag from which few bags take one wavefront each
+    int64_t lanes_bwd = 0;   // lanes that a row takes in the update kernel, all tables together
     int key_bits = 1;                   // bits of the tallest table's row index
     int64_t max_rows = 1;
     std::vector<int> pass_digit_bits;   // radix sort, per launch: the widest digit any table sorts in it
@@ -492,6 +488,7 @@ tbe_status_t tbe_create(const tbe_config_t* cfg, tbe_handle_t* out_handle)
         m.lanes = (uint32_t)std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], h->fwd_epl))) |
                   (uint32_t)std::min(6, pow2ceil_log2((int)ceil_div(h->dims[t], 8))) << 8;
         h->fwd_wide = h->fwd_wide && m.lpr_fwd() == 6;
+        h->lanes_bwd += (int64_t)1 << m.lpr_bwd();
         m.key_bits = table_bits[t];
         w += h->rows[t] * (int64_t)h->dims[t];
         s += h->rows[t];
@@ -813,12 +810,15 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
     {
         ScopedTimer tm(h, SLOT_REDUCE_UPDATE, st);
         const int per_block = kBwdThreads / kWave;
-        if (a.n >= kWideSpanMin)
-            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, 128>), dim3((unsigned)ceil_div(ceil_div(a.n, 128), per_block)),
-                               dim3(kBwdThreads), 0, st, a);
-        else
-            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, 64>), dim3((unsigned)ceil_div(ceil_div(a.n, 64), per_block)),
-                               dim3(kBwdThreads), 0, st, a);
+        auto launch = [&](auto kernel, int span) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(ceil_div(a.n, span), per_block)), dim3(kBwdThreads), 0, st, a);
+        };
+        switch (update_span(a.n, h->lanes_bwd, h->T)) {
+            case 16: launch(reduce_update_kernel<WT, GT, OPT, 16>, 16); break;
+            case 32: launch(reduce_update_kernel<WT, GT, OPT, 32>, 32); break;
+            case 64: launch(reduce_update_kernel<WT, GT, OPT, 64>, 64); break;
+            default: launch(reduce_update_kernel<WT, GT, OPT, 128>, 128); break;
+        }
     }
     Counters* counters = h->ws<Counters>(h->off_counters);
     if (a.n > a.long_run) {

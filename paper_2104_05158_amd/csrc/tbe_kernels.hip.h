@@ -25,7 +25,7 @@ namespace tbe {
 // ---- geometry constants shared by host and device (those of the launch rules are in tbe_rules.h) ----
 constexpr int kFwdUnroll = 4;             // row loads in flight per lane group (8 costs occupancy and is slower)
 constexpr int kChunk = 128;               // sorted positions per pair of partial-row slots
-constexpr int kSpanUnit = 64;             // a span of the update kernel is a multiple of this many sorted positions
+constexpr int kSpanUnit = 16;             // a span of the update kernel is a multiple of this many sorted positions
 constexpr int kWinMax = 16;               // most bag windows a long run is cut into
 constexpr int kWinBatch = 8;               // pieces a workgroup of window_runs_kernel claims at a time
 constexpr int kBwdThreads = 256;          // 4 wavefronts = 4 chunks per workgroup
@@ -1048,9 +1048,10 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     using IO = RowIO<WT, 4>;
     const GT* __restrict__ grad_out = static_cast<const GT*>(a.grad_out);
     constexpr int kWaves = kBwdThreads / kWave;
-    constexpr int kRounds = SPAN / kWave;         // staging rounds of one entry per lane
+    constexpr int kRounds = SPAN < kWave ? 1 : SPAN / kWave;   // staging rounds of one entry per lane
+    constexpr int kStaged = kRounds * kWave;      // positions whose payloads are staged: the span's, and those after a short one
     constexpr int kSegCap = (kRounds + 1) * kWave; // >= SPAN + 1
-    constexpr int kValCap = SPAN + kLongRun;      // a run owned by the span ends within this window
+    constexpr int kValCap = kStaged + kLongRun;   // a run owned by the span ends within this window
     // row-wise AdaGrad keeps one moment per row, so several runs per lane group fit in registers; the
     // element-wise optimizers carry whole state rows and take one run per group
     constexpr int kNB1 = OPT != kOptRowwiseAdagrad ? 1 : sizeof(WT) == 2 ? 4 : 2;   // runs of one lookup per group
@@ -1058,9 +1059,9 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     static_assert(SPAN <= 256, "run indices of a span are kept in bytes");
     static_assert(kShortRun == 4, "run_batch is instantiated for 1..4 lookups");
     __shared__ int32_t s_seg_all[kWaves][kSegCap];
-    __shared__ uint32_t s_key_all[kWaves][SPAN];
+    __shared__ uint32_t s_key_all[kWaves][kStaged];
     __shared__ int32_t s_val_all[kWaves][kValCap];
-    __shared__ uint8_t s_list_all[kWaves][SPAN];
+    __shared__ uint8_t s_list_all[kWaves][kStaged];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x >> 6;
@@ -1112,8 +1113,8 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     {
         const int e_last = uniform(s_seg[nruns]);
         const int s_last = uniform(s_seg[nruns - 1]);
-        if (e_last > q1 && e_last - s_last <= a.long_run) {
-            for (int p = q1 + lane; p < e_last; p += kWave)
+        if (e_last > q0 + kStaged && e_last - s_last <= a.long_run) {
+            for (int p = q0 + kStaged + lane; p < e_last; p += kWave)
                 s_val[p - q0] = vals[p];
             __threadfence_block();
             __builtin_amdgcn_wave_barrier();

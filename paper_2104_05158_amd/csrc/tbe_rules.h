@@ -62,6 +62,27 @@ inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, int few, 
     return f;
 }
 
+// ---------------------------------------------------------------- update: spans
+
+// Sorted positions that a wavefront of the update kernel owns.  What a span costs is a chain: its descriptors, then steps of
+// 64 / lanes rows or a few times that (lanes: of a row, 8 columns each), so a call that leaves the chip room for more
+// wavefronts takes shorter spans, the shorter the wider its rows.  Short spans of narrow rows only fill their steps worse
+// and stage more often.  kSpanWaves wavefronts per lane of a row (mean of the tables) is where the two meet; update
+// kernel, us, spans of 16 / 32 / 64 / 128: dims 4..512, 0.17 M lookups 34 / 37 / 61 / 112; 384 columns, 3444
+// lookups 20 / 32 / 56 / 100; 128 columns, 0.65 M 142 / 144 / 151 / 157, 2 M in fp16 114 / 100 / 108 / 121, 6.2 M in 16 bits
+// 423 / 355 / 320 / 305; 256 columns, 1 M 157 / 165 / 178 / 200; 512, 4 M 625 / 631 / 641 / 644; 64, 1.2 M 65 / 52 / 48 / 53;
+// 16, 1 M 64 / 40 / 33 / 33; 8, 0.16 M 15 / 13 / 13 / 14.
+constexpr int64_t kSpanWaves = 4096;
+
+// lanes: of a row, added up over the tables
+inline int update_span(int64_t lookups, int64_t lanes, int64_t tables)
+{
+    for (int span = 16; span < 128; span *= 2)
+        if (lookups <= span * kSpanWaves * lanes / tables)
+            return span;
+    return 128;
+}
+
 // ---------------------------------------------------------------- update: long runs
 
 constexpr int kLongRun = 512;             // a run of more lookups is long: other kernels than the update kernel sum it, in pieces

@@ -30,6 +30,8 @@ int position_pieces(int s, int len, int32_t* out /*[257]*/)
     return np;
 }
 
+int update_span(int64_t lookups, int64_t lanes, int64_t tables) { return tbe::update_span(lookups, lanes, tables); }
+
 int use_radix_sort(int64_t tables, int64_t lookups, int passes) { return tbe::use_radix_sort(tables, lookups, passes); }
 
 int sort_target(int64_t lookups) { return tbe::sort_target(lookups); }

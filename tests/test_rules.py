@@ -144,3 +144,10 @@ def test_which_long_runs_are_cut_how(rules):
     assert rule(4_000_000, 8193, 128, 4) == rule(1, 8193, 128, 4) == [0, 1, 512] and rule(1, 8193, 128, 2) == [1, 0, 128]
     assert rule(8_388_607, 2048, 512, 4) == [1, 0, 128] and rule(8_388_608, 2048, 512, 4) == [1, 1, 512]
     assert rule(7_999_999, 8193, 128, 2) == [1, 0, 128] and rule(8_000_000, 8193, 128, 2) == [1, 1, 512]
+
+
+def test_spans_shorten_while_the_chip_has_room_for_more_wavefronts(rules):
+    span = lambda n, lanes, tables: rules.update_span(ctypes.c_int64(n), ctypes.c_int64(lanes), ctypes.c_int64(tables))
+    assert [span(n, 1, 1) for n in (1, 65_536, 65_537, 131_072, 131_073, 262_144, 262_145)] == [16, 16, 32, 32, 64, 64, 128]
+    assert span(1_048_576, 16 * 7, 7) == 16 and span(1_048_577, 16 * 7, 7) == 32
+    assert span((1 << 31) - (1 << 24), 64 << 20, 1 << 20) == 128
