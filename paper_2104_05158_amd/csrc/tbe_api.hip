@@ -748,6 +748,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.kb = ss.kb;
     a.target = ss.target;
     a.tiles_per_chunk = ss.tiles_per_chunk;
+    a.select = 0;
     h->final_buf = 0;
     if (small) {
         ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
@@ -762,24 +763,34 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     const unsigned chunk_grid = (unsigned)(ceil_div(n, chunk) + h->T);
     const bool columns = n > kColumnsMin * chunk;
     a.col_chunks = columns ? kColChunks : INT_MAX;
+    a.select = use_select_sort(h->T, n);
     {   // a2: samples, bucket borders and chunks
         ScopedTimer tm(h, SLOT_SORT_PLAN, st);
         hipLaunchKernelGGL(sort_plan_kernel, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_plan_kernel");
     }
-    {
-        ScopedTimer tm(h, SLOT_SORT_HIST, st);
-        hipLaunchKernelGGL(sort_hist_kernel, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
-        TBE_LAUNCH_CHECK(h, "sort_hist_kernel");
-    }
-    {
-        ScopedTimer tm(h, SLOT_SORT_SCAN, st);
-        if (columns)
-            hipLaunchKernelGGL(sort_columns_kernel, dim3((unsigned)(std::min<int64_t>(h->T, n / (chunk * kColChunks)) * (kMaxBuckets / kColBuckets))), dim3(kColThreads), 0, st, a);
-        hipLaunchKernelGGL(sort_units_kernel, dim3((unsigned)h->T), dim3(kUnitsThreads), 0, st, a);
-        TBE_LAUNCH_CHECK(h, "sort_units_kernel");
-    }
-    {   // a3: the partition and the sort of the buckets in LDS
+    if (a.select) {   // a3: units that find their lookups themselves
+        ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
+        const dim3 grid((unsigned)std::min<int64_t>(n / ss.target + 2 * (int64_t)h->T, 1024));
+        if (ss.wide)
+            hipLaunchKernelGGL(sort_select_kernel<uint64_t>, grid, dim3(kSortThreads), 0, st, a);
+        else
+            hipLaunchKernelGGL(sort_select_kernel<uint32_t>, grid, dim3(kSortThreads), 0, st, a);
+        TBE_LAUNCH_CHECK(h, "sort_select_kernel");
+    } else {
+        {
+            ScopedTimer tm(h, SLOT_SORT_HIST, st);
+            hipLaunchKernelGGL(sort_hist_kernel, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
+            TBE_LAUNCH_CHECK(h, "sort_hist_kernel");
+        }
+        {
+            ScopedTimer tm(h, SLOT_SORT_SCAN, st);
+            if (columns)
+                hipLaunchKernelGGL(sort_columns_kernel, dim3((unsigned)(std::min<int64_t>(h->T, n / (chunk * kColChunks)) * (kMaxBuckets / kColBuckets))), dim3(kColThreads), 0, st, a);
+            hipLaunchKernelGGL(sort_units_kernel, dim3((unsigned)h->T), dim3(kUnitsThreads), 0, st, a);
+            TBE_LAUNCH_CHECK(h, "sort_units_kernel");
+        }
+        // a3: the partition and the sort of the buckets in LDS
         auto launch = [&](auto scatter, auto local, int per_cu) {
             {
                 ScopedTimer tm(h, SLOT_SORT_SCATTER, st);

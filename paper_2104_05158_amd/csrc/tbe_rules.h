@@ -186,6 +186,17 @@ inline int sort_target(int64_t lookups)
 // Most full buckets, rounded up, that calls of at most this many lookups can ask for (a table's last one comes on top)
 inline int64_t sort_buckets_max(int64_t lookups) { return std::max<int64_t>(1, sort_rounds(lookups)) * kSortUnitsRound; }
 
+// Middle calls: the units find their lookups themselves, each among all of its table's (sort_select_kernel), instead of
+// having them brought by histogram, units and scatter.  That reads a table's indices once per unit: while tables have
+// kSelectMean lookups on average the three launches cost more.  Sort, us, with them / without: 40 tables of 4400 lookups 71 /
+// 36, 64 of 570 62 / 26, 1 of 22,000 67 / 40, 8 of 20,000 71 / 44, 30 of 9800 77 / 46; beyond it 8 of 29,000 72 / 68, 20 of
+// 33,000 86 / 78, and 1 of 122,000 87 / 124.  The host does not know how the lookups spread over the tables, and a workgroup
+// takes 1.3 us per 4096 of its table's: kSelectLookups ends what a call can lose if one table has nearly all of them.
+constexpr int kSelectCap = 6144;           // words of a unit that is sorted in LDS
+constexpr int64_t kSelectMean = 4 * kSelectCap, kSelectLookups = 1 << 18;
+
+inline bool use_select_sort(int64_t tables, int64_t lookups) { return lookups <= kSelectLookups && lookups <= kSelectMean * tables; }
+
 // A published integer hash: lowbias32 of Wellons' hash-prospector (public domain).
 TBE_BOTH uint32_t mix_bits(uint32_t x)
 {

@@ -19,7 +19,9 @@
 //   sort_local_kernel    one workgroup per unit: sorts the words in LDS, writes keys and payloads, counts the runs
 //   sort_runs_kernel     bucket borders are run borders, so a unit's runs start at a known index: unique_keys,
 //                        seg_offsets, and the first run of every span unit
-// A call of at most kSortTile lookups is sorted by (table, row) at once, by one workgroup (sort_small_kernel).
+// A call of some 100,000 lookups leaves out histogram, units and partition: sort_select_kernel sorts units that it finds
+// itself (use_select_sort).  One of at most kSortTile lookups is sorted by (table, row) at once, by one workgroup
+// (sort_small_kernel).
 //
 // (The runs' first index could also come from a look-back over the units' counts inside sort_local_kernel; at
 // 38,000 units its polling took 6 ms where the extra kernel takes 0.2.)
@@ -75,9 +77,10 @@ struct SortUnit {        // 32 bytes
     int32_t t;
     int32_t flags;
     int32_t first;       // the table's first unit (they are numbered one after the other)
-    int32_t pad;
+    uint32_t last;       // sort_select_kernel: offset of the unit's last row from key0 (of the last unit: of any index)
 };
 constexpr int kUnitContinued = 1;     // further part of a one-row bucket: its first lookup starts no run
+constexpr int kUnitNone = 2;          // no bucket (sort_select_kernel; until then start, m of its units are those of the table)
 
 struct SortArgs {
     const int64_t* offsets;
@@ -109,6 +112,7 @@ struct SortArgs {
     int32_t target;          // lookups per bucket
     int32_t tiles_per_chunk;
     int32_t col_chunks;      // chunks of a table up to which sort_units_kernel adds them up itself
+    int32_t select;          // the units are filled by sort_select_kernel
 };
 
 // ---------------------------------------------------------------- wavefront and workgroup primitives
@@ -331,26 +335,26 @@ __device__ __forceinline__ int group_count(int m) { return (m + kSortThreads * G
 
 // One pass of a stable sort of the words w, in registers at positions wavefront * rounds * 64 + r * 64 + lane: by
 // `width` bits from `sh` on; the result is in s_w, barrier included.  s_cnt: cleared, and synchronised since.
-template <typename W>
-__device__ __forceinline__ void block_sort_pass(W (&w)[kSortPerThread], int groups, int sh, int width, W* s_w,
+template <typename W, int PER>
+__device__ __forceinline__ void block_sort_pass(W (&w)[PER], int groups, int sh, int width, W* s_w,
                                                 uint16_t (&s_cnt)[kSortWaves][kLocalDigits], uint32_t* s_wsum)
 {
     const int wave = uniform(threadIdx.x >> 6);
-    uint32_t rank[kSortPerThread];
+    uint32_t rank[PER];
     rank_rounds<kSortGroup>([&](int r) { return digit_of(w[r], sh, width); }, groups, width, s_cnt, rank);
     __syncthreads();
     uint32_t counts;
     (void)digit_starts<kLocalDigits>(s_cnt, s_wsum, counts);
     __syncthreads();
 #pragma unroll
-    for (int r0 = 0; r0 < kSortPerThread; r0 += kSortGroup)
+    for (int r0 = 0; r0 < PER; r0 += kSortGroup)
         if (r0 < groups * kSortGroup) {
 #pragma unroll
             for (int r = r0; r < r0 + kSortGroup; ++r)
                 rank[r] += s_cnt[wave][digit_of(w[r], sh, width)];
         }
 #pragma unroll
-    for (int r = 0; r < kSortPerThread; ++r)
+    for (int r = 0; r < PER; ++r)
         if (r < groups * kSortGroup)
             s_w[rank[r]] = w[r];
     __syncthreads();
@@ -359,8 +363,8 @@ __device__ __forceinline__ void block_sort_pass(W (&w)[kSortPerThread], int grou
 // the digits of pass p of P over `bits` bits
 __device__ __forceinline__ int pass_width(int bits, int P, int p) { return bits / P + (p < bits % P ? 1 : 0); }
 
-template <typename W>
-__device__ __forceinline__ void block_sort(W (&w)[kSortPerThread], int groups, int shift, int bits, W* s_w,
+template <typename W, int PER>
+__device__ __forceinline__ void block_sort(W (&w)[PER], int groups, int shift, int bits, W* s_w,
                                            uint16_t (&s_cnt)[kSortWaves][kLocalDigits], uint32_t* s_wsum)
 {
     const int p0 = (int)(threadIdx.x >> 6) * groups * kSortGroup * kWave + (int)(threadIdx.x & (kWave - 1));
@@ -371,12 +375,12 @@ __device__ __forceinline__ void block_sort(W (&w)[kSortPerThread], int groups, i
         if (p > 0) {
             const int q = opaque(p0);
 #pragma unroll
-            for (int r = 0; r < kSortPerThread; ++r)
+            for (int r = 0; r < PER; ++r)
                 if (r < groups * kSortGroup)
                     w[r] = s_w[q + r * kWave];
         }
         __syncthreads();
-        block_sort_pass<W>(w, groups, shift, width, s_w, s_cnt, s_wsum);
+        block_sort_pass(w, groups, shift, width, s_w, s_cnt, s_wsum);
         shift += width;
     }
 }
@@ -426,6 +430,7 @@ __device__ __forceinline__ uint32_t bags_of_positions(const int64_t* __restrict_
 struct TablePlan {
     int want, cuts;      // buckets asked for, ranges of the packed key
     int chunks;
+    int units;           // select: most buckets there can be
 };
 
 __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32_t rows)
@@ -433,7 +438,8 @@ __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32
     TablePlan p;
     p.cuts = a.kb >= 31 ? 1 : (int)((rows + (1u << a.kb) - 1) >> a.kb);
     p.want = min(max((n + a.target - 1) / a.target, 1), kMaxBuckets - p.cuts);
-    p.chunks = n == 0 ? 0 : (n + kSortTile * a.tiles_per_chunk - 1) / (kSortTile * a.tiles_per_chunk);
+    p.chunks = n == 0 || a.select ? 0 : (n + kSortTile * a.tiles_per_chunk - 1) / (kSortTile * a.tiles_per_chunk);
+    p.units = n == 0 || !a.select ? 0 : p.want + p.cuts - 1;
     return p;
 }
 
@@ -464,17 +470,18 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         s_sum[tid] = 0;
     __syncthreads();
     {   // what the tables before this one take
-        uint32_t multi = 0, chunks = 0, parts = 0;
+        uint32_t multi = 0, chunks = 0, parts = 0, units = 0;
         for (int i = tid; i < t; i += kSortThreads) {
             const int n = (int)(a.offsets[(int64_t)(i + 1) * a.B] - a.offsets[(int64_t)i * a.B]);
             const TablePlan p = table_plan(a, n, a.row_base[i + 1] - a.row_base[i]);
-            multi += p.chunks > a.col_chunks; chunks += p.chunks; parts += n > 0;
+            multi += p.chunks > a.col_chunks; chunks += p.chunks; parts += n > 0; units += p.units;
         }
         multi = last_lane(wave_scan_add(multi));
         chunks = last_lane(wave_scan_add(chunks));
         parts = last_lane(wave_scan_add(parts));
+        units = last_lane(wave_scan_add(units));
         if (lane == 0 && parts > 0) {
-            atomicAdd(&s_sum[0], multi); atomicAdd(&s_sum[1], chunks); atomicAdd(&s_sum[2], parts);
+            atomicAdd(&s_sum[0], multi); atomicAdd(&s_sum[1], chunks); atomicAdd(&s_sum[2], parts); atomicAdd(&s_sum[3], units);
         }
     }
     __syncthreads();
@@ -497,7 +504,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             a.tstart[a.T] = (int)o1;
             a.counters->sort_chunks = st.chunk_base + p.chunks;
             a.counters->sort_multi = (int)s_sum[0] + (p.chunks > a.col_chunks);
-            a.counters->sort_units = 0;
+            a.counters->sort_units = s_sum[3] + (uint32_t)p.units;
             a.counters->sort_ticket = 0;
         }
     }
@@ -514,6 +521,11 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             a.tables[t] = st;
         return;
     }
+    if (p.units == 1) {                              // (select) one bucket
+        if (tid == 0)
+            a.units[s_sum[3]] = SortUnit{start, n, rbase, ceil_log2(rows), t, 0, (int32_t)s_sum[3], ~0u};
+        return;
+    }
 
     // ---- sorted sample: one lookup from each of S equal stretches of the table's positions
     const int q = min(kSamplesPerBucket, kSortTile / p.want);
@@ -527,7 +539,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         // past the sample: the largest key, sorted behind it
         w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? min(a.indices[start + pos], rows - 1) : ~0u;
     }
-    block_sort<uint32_t>(w, groups, 0, bits, s_key, s_cnt, s_wsum);
+    block_sort(w, groups, 0, bits, s_key, s_cnt, s_wsum);
     // ---- borders: row 0, every q-th sample once, and the row after one that fills a whole stretch of samples
     // (a bucket of its own).  Thread j owns candidates 2 j and 2 j + 1.
     uint32_t cand[2], emit[2];
@@ -589,6 +601,20 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         s_list[i + lds_lower(s_cut, nc, s_key[i])] = s_key[i];
     const int nb = na + nc;
     __syncthreads();
+    if (a.select) {
+        for (int i = tid; i < p.units; i += kSortThreads) {
+            SortUnit u{start, n, 0, 0, t, kUnitNone, (int32_t)s_sum[3], 0};
+            if (i < nb) {                            // (an index that is no row of the table is the last bucket's)
+                u.flags = 0;
+                const uint32_t lo = s_list[i], hi = i + 1 < nb ? s_list[i + 1] : rows;
+                u.key0 = rbase + lo;
+                u.bits = ceil_log2(hi - lo);
+                u.last = i + 1 < nb ? hi - lo - 1u : ~0u - lo;
+            }
+            a.units[s_sum[3] + i] = u;
+        }
+        return;
+    }
     for (int i = tid; i < nb; i += kSortThreads)
         split[i] = s_list[i];
     // ---- lookup table: the bucket of every cell's first row
@@ -827,7 +853,7 @@ __global__ __launch_bounds__(kUnitsThreads) void sort_units_kernel(SortArgs a)
     u.bits = ceil_log2(range);
     u.t = t;
     u.first = (int32_t)s_first;
-    u.pad = 0;
+    u.last = 0;
     for (uint32_t i = 0; i < pieces; ++i) {
         u.start = (int32_t)(start + i * kSortTile);
         u.m = (int32_t)(range == 1 ? min((uint32_t)kSortTile, run - i * kSortTile) : run);
@@ -1057,7 +1083,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
                     }
                 }
                 __syncthreads();
-                block_sort_pass<W>(w, groups, sh, width, s_w, s_cnt, s_wsum);
+                block_sort_pass(w, groups, sh, width, s_w, s_cnt, s_wsum);
                 if (large) {
                     // The tile is in digit order in s_w and the digits' last wavefront row ends where the next digit
                     // starts: slot in the tile -> slot in the unit
@@ -1147,6 +1173,214 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
     }
 }
 
+// ---------------------------------------------------------------- middle calls: every unit finds its lookups itself
+//
+// In a call of some 100,000 lookups the launches of the partition (histogram, units, scatter) each cost their latency and
+// little else.  Here the workgroup of a unit reads all indices of the unit's table instead, out of L2, and keeps those
+// of its own rows: table lookups x units index reads in all, but nothing to wait for between the plan and the sort.
+// The lookups of earlier rows are counted on the way: that is where the unit's own start.  Bound by latency and, from some
+// 20,000 lookups of a table on, by the scan (1.3 us a step).  40 tables, 0.17 M lookups: 18 us, where histogram, units, scatter
+// and bucket sort took 51; 64 tables, 37,000 lookups 13 us, 43.
+constexpr int kSelectWords = kSelectCap / kSortThreads;
+constexpr int kSelectPer = 8;                     // positions per thread and step of the scan (16, in 16-byte loads: no faster)
+constexpr int kSelectStep = kSortThreads * kSelectPer;
+constexpr int kSelectCoarse = kSortThreads;       // bag borders in LDS: every (B / 512)-th
+
+template <typename W>
+__global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_select_kernel(SortArgs a)
+{
+    static_assert(kSelectCap % (kSortGroup * kSortThreads) == 0 && kSelectCap >= kSelectStep && kSelectCap <= kSortTile, "");
+    __shared__ __align__(16) W s_w[kSelectCap];   // row offsets of the unit's lookups, then the words
+    __shared__ uint32_t s_pos[kSelectCap];        // their positions in the table
+    __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
+    __shared__ int32_t s_coarse[kSelectCoarse];
+    __shared__ uint32_t s_hits[2][kSortWaves], s_wsum[kSortWaves];
+    __shared__ uint32_t s_below, s_heads;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
+    const int total_units = (int)a.counters->sort_units;
+    const W vmask = ((W)1 << a.vb) - 1;
+    for (int u = blockIdx.x; u < total_units; u += gridDim.x) {
+        const SortUnit un = a.units[u];
+        if (un.flags & kUnitNone) {                  // fewer buckets than there could be
+            if (tid == 0) {
+                a.units[u].m = 0;
+                a.unit_runs[u] = 0;
+            }
+            continue;
+        }
+        const int n = un.m, t = un.t;
+        const uint32_t* __restrict__ idx = a.indices + un.start;
+        const int64_t* __restrict__ offsets = a.offsets + (int64_t)t * a.B;
+        const int lg_each = max(0, ceil_log2((uint32_t)a.B) - 9);      // bags per coarse border
+        static_assert(kSelectCoarse == 1 << 9, "");
+        __syncthreads();
+        s_coarse[tid] = (int64_t)tid << lg_each < a.B ? (int)offsets[tid << lg_each] - un.start : INT32_MAX;
+        if (tid == 0)
+            s_heads = 0;
+        // bag of a position: the last one that starts at or before it
+        auto bag_of = [&](int pos) {
+            int c = 0;
+#pragma unroll
+            for (int s = kSelectCoarse / 2; s > 0; s >>= 1)
+                c += s_coarse[c + s] <= pos ? s : 0;
+            int b = c << lg_each;
+            for (int s = (1 << lg_each) >> 1; s > 0; s >>= 1)
+                b += b + s < a.B && (int)offsets[b + s] - un.start <= pos ? s : 0;
+            return (uint32_t)b;
+        };
+        // Finds the lookups of the rows [row0, row0 + last]: put(slot, row offset, position) for each, in position order;
+        // full(found, step) before the lookups of a step, the last `step` of the `found` so far, are put.  Returns their number;
+        // below: the thread's lookups of earlier rows.
+        auto scan = [&](uint32_t row0, uint32_t last, auto put, auto full, uint32_t& below) {
+            uint32_t found = 0;
+            uint32_t key[kSelectPer];
+            const int q = wave * kSelectPer * kWave + lane;
+#pragma unroll
+            for (int r = 0; r < kSelectPer; ++r)
+                key[r] = idx[min(q + r * kWave, n - 1)];
+            int buf = 0;
+            for (int first = 0; first < n; first += kSelectStep, buf ^= 1) {
+                uint32_t next[kSelectPer], rank[kSelectPer], hits = 0;
+#pragma unroll
+                for (int r = 0; r < kSelectPer; ++r)
+                    next[r] = idx[min(first + kSelectStep + q + r * kWave, n - 1)];
+#pragma unroll
+                for (int r = 0; r < kSelectPer; ++r) {
+                    const bool valid = first + q + r * kWave < n;
+                    const bool mine = valid && key[r] - row0 <= last;
+                    below += valid && key[r] < row0 ? 1u : 0u;
+                    const uint64_t bal = __ballot(mine);
+                    rank[r] = mine ? __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, hits)) : ~0u;
+                    hits += (uint32_t)__popcll(bal);
+                }
+                if (lane == 0)
+                    s_hits[buf][wave] = hits;
+                __syncthreads();
+                uint32_t base = found, step = 0;
+#pragma unroll
+                for (int w = 0; w < kSortWaves; ++w) {
+                    const uint32_t c = s_hits[buf][w];
+                    base += w < wave ? c : 0u;
+                    step += c;
+                }
+                found += step;
+                full(found, step);
+#pragma unroll
+                for (int r = 0; r < kSelectPer; ++r)
+                    if (rank[r] != ~0u)
+                        put(base + rank[r], key[r] - row0, (uint32_t)(first + q + r * kWave));
+#pragma unroll
+                for (int r = 0; r < kSelectPer; ++r)
+                    key[r] = next[r];
+            }
+            return found;
+        };
+        // keys and payloads of a single row's first m lookups in LDS
+        auto emit_row = [&](uint32_t key, int at, int m) {
+            for (int i = tid; i < m; i += kSortThreads) {
+                a.keys[at + i] = key;
+                a.vals[at + i] = (int32_t)bag_of((int)(i < kSelectCap ? s_pos[i] : (uint32_t)s_w[i - kSelectCap]));
+            }
+        };
+        // One pass for all rows of the unit as a rule.  If they have more lookups than fit the LDS (the sample undersized the
+        // bucket) they are halved; the lookups of a single row need no sorting and leave in as many parts as it takes.
+        const uint32_t table_rows = a.row_base[t + 1] - a.row_base[t];
+        const uint32_t first_row = un.key0 - a.row_base[t];
+        const uint32_t unit_rows = min(un.last, table_rows - first_row - 1u) + 1u;
+        uint32_t lo = 0, rows = unit_rows, heads = 0;             // the rows [lo, lo + rows) of the unit
+        int unit_start = 0, unit_m = 0;
+        while (lo < unit_rows) {
+            const uint32_t row0 = first_row + lo, key0 = un.key0 + lo;
+            const uint32_t last = lo + rows == unit_rows ? un.last - lo : rows - 1u;
+            __syncthreads();
+            if (tid == 0)
+                s_below = 0;
+            const bool single = rows == 1;
+            const uint32_t cap = single ? 2 * kSelectCap : kSelectCap;
+            uint32_t below = 0, done = 0;
+            // a single row's positions take both arrays
+            auto put = [&](uint32_t slot, uint32_t row, uint32_t pos) {
+                slot -= done;
+                if (slot < (uint32_t)kSelectCap) {
+                    s_pos[slot] = pos;
+                    if (!single)
+                        s_w[slot] = (W)row;
+                } else if (slot < cap) {
+                    s_w[slot - kSelectCap] = (W)pos;
+                }
+            };
+            const int m = (int)scan(row0, last, put, [](uint32_t, uint32_t) {}, below);
+            below = last_lane(wave_scan_add(below));
+            if (lane == 0)
+                atomicAdd(&s_below, below);
+            __syncthreads();
+            const int start = un.start + (int)s_below;
+            if (m > (int)cap && !single) {
+                rows = (rows + 1) / 2;
+                continue;
+            }
+            if (single) {
+                if (m > (int)cap) {
+                    (void)scan(row0, last, put, [&](uint32_t found, uint32_t step) {
+                        if (found - done > cap) {
+                            emit_row(key0, start + (int)done, (int)(found - step - done));
+                            done = found - step;
+                            __syncthreads();
+                        }
+                    }, below);
+                    __syncthreads();
+                }
+                emit_row(key0, start + (int)done, m - (int)done);
+            } else if (m > 0) {
+#pragma unroll 4
+                for (int i = tid; i < m; i += kSortThreads)
+                    s_pos[i] = bag_of((int)s_pos[i]);
+                __syncthreads();
+                uint32_t* keys = a.keys + start;
+                int32_t* vals = a.vals + start;
+                const int groups = group_count<kSortGroup>(m);
+                const int p0 = opaque(wave * groups * kSortGroup * kWave + lane);
+                W w[kSelectWords];
+#pragma unroll
+                for (int r = 0; r < kSelectWords; ++r) {
+                    if (r < groups * kSortGroup) {
+                        const int p = p0 + r * kWave;
+                        w[r] = p < m ? (s_w[p] << a.vb) | (W)s_pos[p] : ~(W)0;
+                    }
+                }
+                __syncthreads();
+                block_sort(w, groups, a.vb, ceil_log2(rows), s_w, s_cnt, s_wsum);
+#pragma unroll
+                for (int r = 0; r < kSelectWords; ++r) {
+                    const int p = p0 + r * kWave;
+                    if (r < groups * kSortGroup && p < m) {
+                        const W x = s_w[p], before = s_w[max(p, 1) - 1];
+                        heads += p == 0 || ((x ^ before) >> a.vb) != 0 ? 1u : 0u;
+                        keys[p] = key0 + (uint32_t)(x >> a.vb);
+                        vals[p] = (int32_t)(x & vmask);
+                    }
+                }
+            }
+            heads += single && tid == 0 && m > 0 ? 1u : 0u;
+            if (lo == 0)
+                unit_start = start;
+            unit_m += m;
+            lo += rows;
+            rows = unit_rows - lo;
+        }
+        heads = last_lane(wave_scan_add(heads));
+        if (lane == 0 && heads > 0)
+            atomicAdd(&s_heads, heads);
+        __syncthreads();
+        if (tid == 0) {
+            a.units[u].start = unit_m > 0 ? unit_start : 0;
+            a.units[u].m = unit_m;
+            a.unit_runs[u] = s_heads;
+            atomicAdd(&a.table_runs[t], s_heads);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- small calls: all of it in one workgroup
 //
 // At most kSortTile lookups in at most kSmallBags bags: one workgroup finds every lookup's bag, sorts (linear row id,
@@ -1181,7 +1415,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, in
         }
     }
     __syncthreads();
-    block_sort<uint64_t>(w, groups, 32, key_bits, s_w, s_cnt, s_wsum);
+    block_sort(w, groups, 32, key_bits, s_w, s_cnt, s_wsum);
     uint32_t mask = 0, mine = 0;
     const int q = opaque(p0);
 #pragma unroll
@@ -1247,6 +1481,8 @@ __global__ __launch_bounds__(kRunThreads) void sort_runs_kernel(SortArgs a)
     for (int u = blockIdx.x; u < total_units; u += gridDim.x) {
         const SortUnit un = a.units[u];
         const uint32_t unit_runs = a.unit_runs[u];
+        if (un.m == 0)
+            continue;
         uint32_t part = 0, run;
         for (int i = tid; i < un.t; i += kRunThreads)
             part += a.table_runs[i];

@@ -1,0 +1,53 @@
+"""GPU parity of the sort whose units find their lookups themselves (calls of at most 2^18 lookups, 24,576 a table on average):
+sizes on both sides of its borders, tables of one bucket and of many, rows with more lookups than a workgroup's LDS holds
+positions (12,288), buckets that have to be halved, empty tables, and bags by the thousand.  Bit-exact."""
+import numpy as np
+import pytest
+
+from test_gpu_sort_paths import _check, _lens
+
+pytestmark = pytest.mark.gpu
+MEAN, MOST = 24_576, 1 << 18
+
+CASES = {
+    # name: (rows, batch, lookups per table, share of the hottest row)
+    "one_table_at_the_border": ([1_000_000], 700, [MEAN], 0.0),
+    "one_table_beyond_it": ([1_000_000], 700, [MEAN + 1], 0.0),
+    "most_lookups": ([30_000, 9, 500_000] * 5, 300, [MOST // 15] * 14 + [MOST - MOST // 15 * 14], 0.01),
+    "more_than_that": ([30_000, 9, 500_000] * 5, 300, [MOST // 15] * 14 + [MOST + 1 - MOST // 15 * 14], 0.01),
+    "steps_of_the_scan": ([5000] * 8, 40, [4095, 4096, 4097, 8191, 8192, 8193, 1, 12_289], 0.05),
+    "one_bucket_each": ([700, 70_000, 3] * 9, 1000, [1023, 1024, 1025, 1, 0, 640, 511, 512, 513] * 3, 0.0),
+    "one_table_has_nearly_all": ([100_000] * 9, 800, [200_000, 3, 0, 17, 0, 0, 1, 1000, 0], 0.1),
+    "row_that_fills_the_lds": ([1_000_000, 40], 900, [40_000, 100], 12_288 / 40_000),
+    "row_beyond_the_lds": ([1_000_000, 40], 900, [40_000, 100], 0.9),
+    "tables_of_one_row": ([1, 1, 2], 65536, [30_000, 13_000, 9_000], 0.0),
+    "words_of_64_bits": ([40_000_000, 500], 70_001, [45_000, 4_000], 0.3),
+    "bags_by_the_thousand": ([50_000] * 3, 65536, [24_000, 100, 30_000], 0.02),
+    "one_bag_a_table": ([50_000] * 5, 1, [24_000, 100, 0, 30_000, 2], 0.02),
+}
+
+
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_units_that_find_their_lookups_themselves(gpu_device, case):
+    rows, batch, per_table, hot = CASES[case]
+    rng = np.random.default_rng(len(case))
+    lens = np.concatenate([_lens(rng, batch, n) for n in per_table])
+    parts = []
+    for h, n in zip(rows, per_table):
+        x = rng.integers(0, h, n)
+        x[rng.permutation(n)[:round(hot * n)]] = h * 2 // 3
+        parts.append(x)
+    print(f"{case}: N={sum(per_table)}", flush=True)
+    _check(gpu_device, rows, batch, lens, np.concatenate(parts), case)
+
+
+@pytest.mark.parametrize("rows,batch", [(300_000, 500), (40_000_000, 70_001)])     # words of 32 and of 64 bits
+def test_buckets_that_have_to_be_halved(gpu_device, rows, batch):
+    # lookups in stretches of 1024 of which the sample takes 16: every 64th is a row from 2000 on, and so may be all of the
+    # sample; the 2000 rows below share a bucket or two
+    rng = np.random.default_rng(3)
+    n = 24_000
+    idx = rng.integers(0, 2000, n)
+    idx[::3] = rng.integers(2000, rows, len(idx[::3]))
+    idx[n // 2:] = 7                                                               # one row: beyond the LDS by itself
+    _check(gpu_device, [rows], batch, _lens(rng, batch, n), idx, "halved")

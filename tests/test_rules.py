@@ -151,3 +151,9 @@ def test_spans_shorten_while_the_chip_has_room_for_more_wavefronts(rules):
     assert [span(n, 1, 1) for n in (1, 65_536, 65_537, 131_072, 131_073, 262_144, 262_145)] == [16, 16, 32, 32, 64, 64, 128]
     assert span(1_048_576, 16 * 7, 7) == 16 and span(1_048_577, 16 * 7, 7) == 32
     assert span((1 << 31) - (1 << 24), 64 << 20, 1 << 20) == 128
+
+
+def test_which_calls_have_units_that_find_their_lookups_themselves(rules):
+    use = lambda t, n: bool(rules.use_select_sort(ctypes.c_int64(t), ctypes.c_int64(n)))
+    assert use(1, 24_576) and not use(1, 24_577) and use(10, 245_760) and not use(10, 245_761)
+    assert use(11, 1 << 18) and use(4096, 1 << 18) and not use(4096, (1 << 18) + 1)
