@@ -51,6 +51,10 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // some 4096 chunks for 512 resident workgroups (98 M lookups: histogram + partition 622 us with up to 4, 660 with 8).
 constexpr int64_t kSortChunksWanted = 4096;
 constexpr int kSortTilesPerChunk = 4;
+// Lookups up to which a chunk is a quarter or half of a tile: the call has not tiles enough for the chip, and the workgroup of a
+// short one is done sooner.  Histogram, units, scatter with chunks of 8192 / 4096 / 2048: 1 table, 41,000 lookups 29 / 25 / 24 us,
+// 0.49 M 37 / 40 / 47; 3 tables, 0.37 M 35 / 30 / 30; 8 tables, 0.65 M 37 / 32 / 31; 1.0 M 38 / 37 / 36; 64 tables, 2 M 37 / 35 / 39.
+constexpr int64_t kSortQuarterTiles = 1 << 17, kSortHalfTiles = 3 << 18;
 // Chunks of a call up to which sort_units_kernel adds all of them up itself: at most six trips, against a launch of 2 us
 // (8 tables, 0.65 M lookups: step of 347 us, 345 without it).
 constexpr int64_t kColumnsMin = 96;
@@ -205,7 +209,7 @@ int64_t dense_bounds_entries(int64_t n, int64_t batch, int T)
 struct SortShape {
     int vb, kb;
     bool wide;
-    int target, tiles_per_chunk;
+    int target, tiles_per_chunk, chunk;
 };
 
 SortShape sort_shape(const tbe_s* h, int64_t batch, int64_t n)
@@ -220,7 +224,14 @@ SortShape sort_shape(const tbe_s* h, int64_t batch, int64_t n)
         s.vb = s.kb = 32;
     s.target = sort_target(n);
     s.tiles_per_chunk = (int)std::min<int64_t>(kSortTilesPerChunk, std::max<int64_t>(1, n / (kSortTile * kSortChunksWanted)));
+    s.chunk = n <= kSortQuarterTiles ? kSortTile / 4 : n <= kSortHalfTiles ? kSortTile / 2 : kSortTile * s.tiles_per_chunk;
     return s;
+}
+
+// most chunks, all tables but for one partly filled chunk each, of the calls that have chunks of less than a tile
+int64_t short_chunks(int64_t nmax)
+{
+    return std::max(ceil_div(std::min(nmax, kSortQuarterTiles), kSortTile / 4), ceil_div(std::min(nmax, kSortHalfTiles), kSortTile / 2));
 }
 
 // workspace of the partition, in sizes for the worst call (chunks and buckets never cross a table border; small calls use
@@ -241,7 +252,8 @@ void plan_partition(tbe_s* h, Take take)
         slots += tall ? ceil_div(h->rows[t], (int64_t)1 << kb) : 1;
     }
     const int64_t parts = std::min<int64_t>(h->T, nmax);
-    const int64_t sort_chunks = std::min<int64_t>(ceil_div(nmax, kSortTile), 2 * kSortChunksWanted + nmax / (kSortTile * kSortTilesPerChunk)) + h->T;
+    const int64_t sort_chunks = std::max(std::min<int64_t>(ceil_div(nmax, kSortTile), 2 * kSortChunksWanted + nmax / (kSortTile * kSortTilesPerChunk)),
+                                         short_chunks(nmax)) + h->T;
     h->off_stables = take(sizeof(SortTable) * (size_t)h->T);
     h->off_schunks = take(sizeof(SortChunk) * (size_t)sort_chunks);
     h->off_sunits = take(sizeof(SortUnit) * (size_t)slots);
@@ -249,8 +261,8 @@ void plan_partition(tbe_s* h, Take take)
     h->off_lut = take(2 * (size_t)kLutSize * parts);
     h->off_bstart = take(4 * (size_t)kMaxBuckets * parts);
     h->off_hist = take(4 * (size_t)kMaxBuckets * sort_chunks);
-    h->off_multi = take(4 * (size_t)(nmax / ((int64_t)kSortTile * kColChunks) + 1));
-    h->off_tile_bag = take(4 * (size_t)(ceil_div(nmax, kSortTile) + (kSortTilesPerChunk + 1) * (int64_t)(h->T + 1)));
+    h->off_multi = take(4 * (size_t)(std::max(nmax / kSortTile, short_chunks(nmax)) / kColChunks + 1));
+    h->off_tile_bag = take(4 * (size_t)(std::max(ceil_div(nmax, kSortTile), short_chunks(nmax)) + (kSortTilesPerChunk + 1) * (int64_t)(h->T + 1)));
     h->off_unit_runs = take(4 * (size_t)slots);
     h->off_table_runs = take(4 * (size_t)h->T);
     h->off_words64 = ss.wide ? take(8 * ((size_t)nmax + 64)) : 0;
@@ -748,6 +760,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.kb = ss.kb;
     a.target = ss.target;
     a.tiles_per_chunk = ss.tiles_per_chunk;
+    a.chunk = ss.chunk;
     a.select = 0;
     h->final_buf = 0;
     if (small) {
@@ -759,9 +772,9 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         TBE_LAUNCH_CHECK(h, "sort_small_kernel");
         return TBE_OK;
     }
-    const int64_t chunk = (int64_t)kSortTile * ss.tiles_per_chunk;
+    const int64_t chunk = ss.chunk;
     const unsigned chunk_grid = (unsigned)(ceil_div(n, chunk) + h->T);
-    const bool columns = n > kColumnsMin * chunk;
+    const bool columns = n > kColumnsMin * std::max<int64_t>(chunk, kSortTile);
     a.col_chunks = columns ? kColChunks : INT_MAX;
     a.select = use_select_sort(h->T, n);
     {   // a2: samples, bucket borders and chunks

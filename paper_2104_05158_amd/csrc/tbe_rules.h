@@ -186,6 +186,16 @@ inline int sort_target(int64_t lookups)
 // Most full buckets, rounded up, that calls of at most this many lookups can ask for (a table's last one comes on top)
 inline int64_t sort_buckets_max(int64_t lookups) { return std::max<int64_t>(1, sort_rounds(lookups)) * kSortUnitsRound; }
 
+// Samples per bucket of a table's plan.  A bucket's size spreads by 1/4 around the target with 16 of them; with 8, by 1/3, which
+// a target of at most 5/16 of a tile leaves room for where a workgroup would sort thousands of samples (1 table, 0.49 M lookups,
+// 480 buckets: plan of 31 us, 39 with 16).
+TBE_BOTH int samples_per_bucket(int buckets, int target)
+{
+    const int room = 8192 / buckets;
+    const int want = target <= kSortTargetFew && buckets > 128 ? 8 : 16;
+    return room < want ? room : want;
+}
+
 // Middle calls: the units find their lookups themselves, each among all of its table's (sort_select_kernel), instead of
 // having them brought by histogram, units and scatter.  That reads a table's indices once per unit: while tables have
 // kSelectMean lookups on average the three launches cost more.  Sort, us, with them / without: 40 tables of 4400 lookups 71 /

@@ -47,7 +47,6 @@ constexpr int kMaxBuckets = 1024;                 // per table
 constexpr int kMaxRangeCuts = 512;                // of those, bucket borders at multiples of the packed key range
 constexpr int kLutBits = 12;
 constexpr int kLutSize = (1 << kLutBits) + 8;
-constexpr int kSamplesPerBucket = 16;             // a bucket's size then spreads by 1/4 around the target
 constexpr int kLocalDigits = 256;
 constexpr int kUnitsThreads = 1024;
 constexpr int kColThreads = 1024;                 // 16 wavefronts that share the chunks of a table ...
@@ -110,6 +109,7 @@ struct SortArgs {
     int32_t vb;              // bits of the bag number in a word
     int32_t kb;              // bits left for the row offset
     int32_t target;          // lookups per bucket
+    int32_t chunk;           // positions of a chunk: tiles_per_chunk tiles, or in a small call less than one
     int32_t tiles_per_chunk;
     int32_t col_chunks;      // chunks of a table up to which sort_units_kernel adds them up itself
     int32_t select;          // the units are filled by sort_select_kernel
@@ -335,16 +335,16 @@ __device__ __forceinline__ int group_count(int m) { return (m + kSortThreads * G
 
 // One pass of a stable sort of the words w, in registers at positions wavefront * rounds * 64 + r * 64 + lane: by
 // `width` bits from `sh` on; the result is in s_w, barrier included.  s_cnt: cleared, and synchronised since.
-template <typename W, int PER>
+template <typename W, int PER, int ND>
 __device__ __forceinline__ void block_sort_pass(W (&w)[PER], int groups, int sh, int width, W* s_w,
-                                                uint16_t (&s_cnt)[kSortWaves][kLocalDigits], uint32_t* s_wsum)
+                                                uint16_t (&s_cnt)[kSortWaves][ND], uint32_t* s_wsum)
 {
     const int wave = uniform(threadIdx.x >> 6);
     uint32_t rank[PER];
     rank_rounds<kSortGroup>([&](int r) { return digit_of(w[r], sh, width); }, groups, width, s_cnt, rank);
     __syncthreads();
     uint32_t counts;
-    (void)digit_starts<kLocalDigits>(s_cnt, s_wsum, counts);
+    (void)digit_starts<ND>(s_cnt, s_wsum, counts);
     __syncthreads();
 #pragma unroll
     for (int r0 = 0; r0 < PER; r0 += kSortGroup)
@@ -363,12 +363,13 @@ __device__ __forceinline__ void block_sort_pass(W (&w)[PER], int groups, int sh,
 // the digits of pass p of P over `bits` bits
 __device__ __forceinline__ int pass_width(int bits, int P, int p) { return bits / P + (p < bits % P ? 1 : 0); }
 
-template <typename W, int PER>
+template <typename W, int PER, int ND>
 __device__ __forceinline__ void block_sort(W (&w)[PER], int groups, int shift, int bits, W* s_w,
-                                           uint16_t (&s_cnt)[kSortWaves][kLocalDigits], uint32_t* s_wsum)
+                                           uint16_t (&s_cnt)[kSortWaves][ND], uint32_t* s_wsum)
 {
     const int p0 = (int)(threadIdx.x >> 6) * groups * kSortGroup * kWave + (int)(threadIdx.x & (kWave - 1));
-    const int passes = (bits + 7) >> 3;
+    constexpr int kBits = ND == 256 ? 8 : 10;
+    const int passes = (bits + kBits - 1) / kBits;
     for (int p = 0; p < passes; ++p) {
         const int width = pass_width(bits, passes, p);
         zero_counts(s_cnt);
@@ -438,7 +439,7 @@ __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32
     TablePlan p;
     p.cuts = a.kb >= 31 ? 1 : (int)((rows + (1u << a.kb) - 1) >> a.kb);
     p.want = min(max((n + a.target - 1) / a.target, 1), kMaxBuckets - p.cuts);
-    p.chunks = n == 0 || a.select ? 0 : (n + kSortTile * a.tiles_per_chunk - 1) / (kSortTile * a.tiles_per_chunk);
+    p.chunks = n == 0 || a.select ? 0 : (n + a.chunk - 1) / a.chunk;
     p.units = n == 0 || !a.select ? 0 : p.want + p.cuts - 1;
     return p;
 }
@@ -460,12 +461,16 @@ __device__ __forceinline__ int lds_lower(const uint32_t* p, int n, uint32_t v)
 __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
 {
     __shared__ __align__(16) uint32_t s_key[kSortTile];
-    __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
+    __shared__ __align__(16) uint16_t s_cnt[kSortWaves][1024];     // (samples are few: two passes of ten bits)
     __shared__ uint32_t s_list[kMaxBuckets + 2], s_cut[kMaxRangeCuts];
     __shared__ uint32_t s_wsum[kSortWaves];
     __shared__ uint32_t s_sum[4];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int t = blockIdx.x;
+    const int64_t o0 = a.offsets[(int64_t)t * a.B], o1 = a.offsets[(int64_t)(t + 1) * a.B];
+    const int start = (int)o0, n = (int)(o1 - o0);
+    const uint32_t rbase = a.row_base[t], rows = a.row_base[t + 1] - rbase;
+    const int bits = a.meta[t].key_bits;
     if (tid < 4)
         s_sum[tid] = 0;
     __syncthreads();
@@ -485,10 +490,6 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         }
     }
     __syncthreads();
-    const int64_t o0 = a.offsets[(int64_t)t * a.B], o1 = a.offsets[(int64_t)(t + 1) * a.B];
-    const int start = (int)o0, n = (int)(o1 - o0);
-    const uint32_t rbase = a.row_base[t], rows = a.row_base[t + 1] - rbase;
-    const int bits = a.meta[t].key_bits;
     const TablePlan p = table_plan(a, n, rows);
     SortTable st;
     st.start = start; st.n = n;
@@ -511,8 +512,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     for (int i = tid; i < p.chunks; i += kSortThreads) {
         SortChunk c;
         c.t = t;
-        c.first = start + i * kSortTile * a.tiles_per_chunk;
-        c.cnt = min(kSortTile * a.tiles_per_chunk, start + n - c.first);
+        c.first = start + i * a.chunk;
+        c.cnt = min(a.chunk, start + n - c.first);
         c.pad = 0;
         a.chunks[st.chunk_base + i] = c;
     }
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     }
 
     // ---- sorted sample: one lookup from each of S equal stretches of the table's positions
-    const int q = min(kSamplesPerBucket, kSortTile / p.want);
+    const int q = samples_per_bucket(p.want, a.target);
     const int S = p.want * q;
     uint32_t w[kSortPerThread];
     const int groups = group_count<kSortGroup>(S), rounds = groups * kSortGroup;
@@ -703,10 +704,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_hist_kernel(SortArgs a)
 {
     __shared__ uint32_t s_hist[kMaxBuckets];
     __shared__ Borders s_borders;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const SortChunk c = a.chunks[blockIdx.x];        // (requested together with the number of chunks; there is room for the grid)
     if ((int)blockIdx.x >= a.counters->sort_chunks)
         return;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const SortChunk c = a.chunks[blockIdx.x];
     const SortTable st = a.tables[c.t];
     const int bits = a.meta[c.t].key_bits;
     const int shift = st.lut_shift, span = st.lut_span;
@@ -872,10 +873,10 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
     __shared__ uint32_t s_next[kMaxBuckets], s_delta[kMaxBuckets];
     __shared__ Borders s_borders;
     __shared__ uint32_t s_wsum[kSortWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
+    const SortChunk c = a.chunks[blockIdx.x];        // (requested together with the number of chunks; there is room for the grid)
     if ((int)blockIdx.x >= a.counters->sort_chunks)
         return;
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
-    const SortChunk c = a.chunks[blockIdx.x];
     const SortTable st = a.tables[c.t];
     const int bits = a.meta[c.t].key_bits;
     const int shift = st.lut_shift, span = st.lut_span;
@@ -1016,21 +1017,18 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
     const int total_units = (int)a.counters->sort_units;
     const W vmask = ((W)1 << a.vb) - 1;
 
-    // units are handed out one at a time (their sizes differ); the next number is asked for a unit ahead
-    if (tid == 0)
-        s_ticket = (int)atomicAdd(&a.counters->sort_ticket, 1u);
-    for (;;) {
+    // Units beyond the grid are handed out one at a time (their sizes differ); the next number is asked for a unit ahead.
+    // (All workgroups add to one word, at 6 ns each: no unit that has a workgroup of its own waits for that.)
+    const bool tickets = total_units > (int)gridDim.x;
+    for (int u = blockIdx.x; u < total_units;) {
         __syncthreads();
-        const int u = s_ticket;
-        if (u >= total_units)
-            break;
         if (tid < 8)
             reinterpret_cast<int*>(&s_unit)[tid] = reinterpret_cast<const int*>(&a.units[u])[tid];
         if (tid == 0)
             s_heads = 0;
         __syncthreads();
         if (tid == 0)
-            s_ticket = (int)atomicAdd(&a.counters->sort_ticket, 1u);
+            s_ticket = tickets ? (int)(gridDim.x + atomicAdd(&a.counters->sort_ticket, 1u)) : total_units;
         const int start = uniform(s_unit.start), m_all = uniform(s_unit.m), bits = uniform(s_unit.bits);
         const uint32_t key0 = (uint32_t)uniform((int)s_unit.key0);
         const bool large = m_all > kSortTile;
@@ -1170,6 +1168,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
             a.unit_runs[u] = s_heads;
             atomicAdd(&a.table_runs[s_unit.t], s_heads);
         }
+        u = s_ticket;                                // (written two barriers ago)
     }
 }
 

@@ -51,3 +51,14 @@ def test_buckets_that_have_to_be_halved(gpu_device, rows, batch):
     idx[::3] = rng.integers(2000, rows, len(idx[::3]))
     idx[n // 2:] = 7                                                               # one row: beyond the LDS by itself
     _check(gpu_device, [rows], batch, _lens(rng, batch, n), idx, "halved")
+
+
+@pytest.mark.parametrize("n", [1 << 17, (1 << 17) + 1, 3 << 18, (3 << 18) + 1])
+@pytest.mark.parametrize("tables", [1, 3])
+def test_chunks_of_less_than_a_tile(gpu_device, tables, n):
+    # a quarter of a tile up to 2^17 lookups, half of one up to 3 x 2^18; one table of more than 128 buckets has 8 samples each
+    rng = np.random.default_rng(n + tables)
+    per_table = [n] if tables == 1 else [n - 2047 - n // 3, 2047, n // 3]
+    lens = np.concatenate([_lens(rng, 5000, m) for m in per_table])
+    idx = np.concatenate([np.minimum(rng.zipf(1.3, m) * 2_654_435_761 % 2_000_000, 1_999_999) for m in per_table])
+    _check(gpu_device, [2_000_000] * tables, 5000, lens, idx, "short chunks")
