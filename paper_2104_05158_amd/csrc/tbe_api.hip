@@ -110,7 +110,7 @@ struct tbe_s {
     size_t off_tstart = 0, off_stables = 0, off_schunks = 0, off_sunits = 0, off_split = 0, off_lut = 0, off_bstart = 0;
     size_t off_hist = 0, off_multi = 0, off_tile_bag = 0, off_unit_runs = 0, off_table_runs = 0, off_words64 = 0;
     size_t off_tile_base = 0, off_tile_table = 0, off_radix_hist = 0, off_scan_tmp = 0, off_rl_counts = 0;
-    size_t off_unit_first = 0, off_partials = 0;
+    size_t off_unit_first = 0, off_partials = 0, off_small_long = 0;
     size_t off_long_list = 0, off_zero = 0, workspace_bytes = 0;
     size_t off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
     size_t off_dense_dirty = 0, off_dense_cnt = 0, off_dense_list = 0, off_drun = 0, off_dgroup = 0, off_dbounds = 0;
@@ -124,6 +124,7 @@ struct tbe_s {
     bool bound = false;
     int final_buf = -1;  // which (keys, vals) pair holds the sorted result of the last backward
     int32_t sorted_n = -1, sorted_batch = 0;  // size of the batch that was sorted last
+    bool sorted_small = false;                // and whether by one workgroup
 
     // profiling
     std::vector<hipEvent_t> ev_pool;
@@ -306,6 +307,7 @@ void plan_workspace(tbe_s* h)
     off = std::max(off, end_sort);
     const int64_t chunks = std::max<int64_t>(1, ceil_div(nmax, kChunk));
     h->off_unit_first = take(4 * (size_t)(ceil_div(nmax, kSpanUnit) + 1));
+    h->off_small_long = take(4 * (size_t)(std::min<int64_t>(nmax, kSortTile) / kPosPiece + 2));
     const int dpad = (int)align_up((size_t)h->dmax, 4);
     h->off_partials = take(4 * (size_t)chunks * 2 * (size_t)dpad);
     h->off_long_list = take(sizeof(LongRun) * (size_t)(nmax / kPosPiece + 2));
@@ -722,6 +724,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         return TBE_OK;
     }
     const bool small = n <= kSortTile && (int64_t)h->T * batch <= kSmallBags;
+    h->sorted_small = small;
     if (!small && use_radix_sort(h->T, n, (int)ceil_div(h->key_bits, 8)))
         return enqueue_radix_sort(h, d_indices, d_offsets, n, batch, st);
     const SortShape ss = sort_shape(h, batch, n);
@@ -748,6 +751,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.unique_keys = h->ws<uint32_t>(h->off_keys[1]);
     a.seg_offsets = h->ws<int32_t>(h->off_vals[1]);
     a.unit_first_run = h->ws<int32_t>(h->off_unit_first);
+    a.small_long = h->ws<uint32_t>(h->off_small_long);
     // a unit reads its words before it writes its keys and payloads to the same positions: 32-bit words share
     // the memory of the result.  64-bit words have a buffer of their own; their second one is where unique_keys and
     // seg_offsets go (neighbours in the workspace, 4 bytes an entry each), which a later kernel writes.
@@ -837,6 +841,10 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
         auto launch = [&](auto kernel, int span) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(ceil_div(a.n, span), per_block)), dim3(kBwdThreads), 0, st, a);
         };
+        if (a.small) {
+            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit>), dim3((unsigned)(a.span_blocks + a.n / (kPosPiece + 1))), dim3(kBwdThreads), 0, st, a);
+            return;
+        }
         switch (update_span(a.n, h->lanes_bwd, h->T)) {
             case 16: launch(reduce_update_kernel<WT, GT, OPT, 16>, 16); break;
             case 32: launch(reduce_update_kernel<WT, GT, OPT, 32>, 32); break;
@@ -948,8 +956,12 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     a.batch = h->sorted_batch;
     a.table_major = h->layout;
     const LongRunRule rule = long_run_rule(n, a.batch, a.dpad, h->grad_dtype == TBE_DTYPE_FP32 ? 4 : 2);
+    const int widest = pow2ceil_log2((int)ceil_div(h->dmax, 8));
+    a.small = h->sorted_small && small_long_runs(n, 1 << std::min(6, widest));
+    a.span_blocks = (int32_t)ceil_div(ceil_div(n, kSpanUnit), kBwdThreads / kWave);
+    a.small_long = h->ws<uint32_t>(h->off_small_long);
     a.by_position = rule.by_position;
-    a.long_run = rule.long_run;
+    a.long_run = a.small ? kPosPiece : rule.long_run;
     // dense hot rows: only when a run can exceed the threshold and the bounds table of this call fits
     const int thr = dense_threshold(h->sorted_batch);
     const bool dense_on = rule.dense && n > thr && dense_bounds_entries(n, h->sorted_batch, h->T) <= h->dbounds_cap &&

@@ -123,6 +123,14 @@ inline LongRunRule long_run_rule(int64_t lookups, int64_t batch, int64_t widest,
     return r;
 }
 
+// Whether the workgroups of the update kernel sum the long runs of a call of at most a tile of lookups themselves: one of four
+// wavefronts takes 16 rows of the widest table per lane group and trip, and the longest run there can be, all lookups of the call,
+// should take no more than 32 trips.
+constexpr int kSmallLongTrips = 32;
+
+// lanes: of a row of the widest table
+inline bool small_long_runs(int64_t lookups, int lanes) { return lookups <= (int64_t)kSmallLongTrips * 16 * (kWave / lanes); }
+
 TBE_BOTH int position_pieces(int len)
 {
     const int np = (len + kPosPiece - 1) / kPosPiece;

@@ -105,6 +105,7 @@ struct SortArgs {
     uint32_t* unique_keys;
     int32_t* seg_offsets;
     int32_t* unit_first_run;
+    uint32_t* small_long;    // indices of a small call's runs of more than kPosPiece lookups, their number in front
     int32_t n, B, T;
     int32_t vb;              // bits of the bag number in a word
     int32_t kb;              // bits left for the row offset
@@ -1391,7 +1392,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, in
 {
     __shared__ __align__(16) uint64_t s_w[kSortTile];
     __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
-    __shared__ uint32_t s_wsum[kSortWaves];
+    __shared__ uint32_t s_wsum[kSortWaves], s_long;
+    __shared__ uint16_t s_starts[kSortTile + 1];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int n = a.n;
     const int groups = group_count<kSortGroup>(n), rounds = groups * kSortGroup;
@@ -1451,12 +1453,24 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, in
                 if (mask >> r & 1u) {
                     a.unique_keys[x] = (uint32_t)(w[r] >> 32);
                     a.seg_offsets[x] = p;
+                    s_starts[x] = (uint16_t)p;
                 }
             }
             run += (uint32_t)__popcll(hm);
         }
     }
+    // the long runs, for the update
     if (tid == 0) {
+        s_starts[total] = (uint16_t)n;
+        s_long = 0;
+    }
+    __syncthreads();
+    for (uint32_t x = tid; x < total; x += kSortThreads)
+        if (s_starts[x + 1] - s_starts[x] > kPosPiece)
+            a.small_long[1 + atomicAdd(&s_long, 1u)] = x;
+    __syncthreads();
+    if (tid == 0) {
+        a.small_long[0] = s_long;
         a.seg_offsets[total] = n;
         a.unit_first_run[(n + kSpanUnit - 1) / kSpanUnit] = (int32_t)total;
         a.counters->num_unique = (int64_t)total;

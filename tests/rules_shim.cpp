@@ -34,6 +34,8 @@ int update_span(int64_t lookups, int64_t lanes, int64_t tables) { return tbe::up
 
 int use_radix_sort(int64_t tables, int64_t lookups, int passes) { return tbe::use_radix_sort(tables, lookups, passes); }
 
+int small_long_runs(int64_t lookups, int lanes) { return tbe::small_long_runs(lookups, lanes); }
+
 int use_select_sort(int64_t tables, int64_t lookups) { return tbe::use_select_sort(tables, lookups); }
 
 int sort_target(int64_t lookups) { return tbe::sort_target(lookups); }

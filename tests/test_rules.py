@@ -157,3 +157,8 @@ def test_which_calls_have_units_that_find_their_lookups_themselves(rules):
     use = lambda t, n: bool(rules.use_select_sort(ctypes.c_int64(t), ctypes.c_int64(n)))
     assert use(1, 24_576) and not use(1, 24_577) and use(10, 245_760) and not use(10, 245_761)
     assert use(11, 1 << 18) and use(4096, 1 << 18) and not use(4096, (1 << 18) + 1)
+
+
+def test_small_calls_sum_their_long_runs_in_at_most_32_trips(rules):
+    small = lambda n, lanes: bool(rules.small_long_runs(ctypes.c_int64(n), ctypes.c_int(lanes)))
+    assert small(512, 64) and not small(513, 64) and small(4096, 8) and not small(4097, 8) and small(8192, 4) and small(8192, 1)
