@@ -841,19 +841,22 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
         auto launch = [&](auto kernel, int span) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(ceil_div(a.n, span), per_block)), dim3(kBwdThreads), 0, st, a);
         };
-        if (a.small) {
-            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit>), dim3((unsigned)(a.span_blocks + a.n / (kPosPiece + 1))), dim3(kBwdThreads), 0, st, a);
-            return;
-        }
-        switch (update_span(a.n, h->lanes_bwd, h->T)) {
-            case 16: launch(reduce_update_kernel<WT, GT, OPT, 16>, 16); break;
-            case 32: launch(reduce_update_kernel<WT, GT, OPT, 32>, 32); break;
-            case 64: launch(reduce_update_kernel<WT, GT, OPT, 64>, 64); break;
-            default: launch(reduce_update_kernel<WT, GT, OPT, 128>, 128); break;
+        if (a.small || a.piece_blocks > 0) {
+            const int64_t long_blocks = a.small ? a.n / (kPosPiece + 1) : a.piece_blocks;
+            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, true>), dim3((unsigned)(a.span_blocks + long_blocks)), dim3(kBwdThreads), 0, st, a);
+            if (a.small)
+                return;
+        } else {
+            switch (update_span(a.n, h->lanes_bwd, h->T)) {
+                case 16: launch(reduce_update_kernel<WT, GT, OPT, 16, false>, 16); break;
+                case 32: launch(reduce_update_kernel<WT, GT, OPT, 32, false>, 32); break;
+                case 64: launch(reduce_update_kernel<WT, GT, OPT, 64, false>, 64); break;
+                default: launch(reduce_update_kernel<WT, GT, OPT, 128, false>, 128); break;
+            }
         }
     }
     Counters* counters = h->ws<Counters>(h->off_counters);
-    if (a.n > a.long_run) {
+    if (a.n > a.long_run && a.piece_blocks == 0) {
         // the long runs below the dense threshold: their pieces, after plan -> window-border positions if by bag window
         ScopedTimer tm(h, SLOT_WINDOW_RUNS, st);
         uint32_t* wpre = h->ws<uint32_t>(h->off_wrun);
@@ -962,6 +965,7 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     a.small_long = h->ws<uint32_t>(h->off_small_long);
     a.by_position = rule.by_position;
     a.long_run = a.small ? kPosPiece : rule.long_run;
+    a.piece_blocks = rule.found && !a.small && n > a.long_run && update_span(n, h->lanes_bwd, h->T) == kSpanUnit ? (int32_t)ceil_div(ceil_div(n, kPosSlot), kBwdThreads / kWave) : 0;
     // dense hot rows: only when a run can exceed the threshold and the bounds table of this call fits
     const int thr = dense_threshold(h->sorted_batch);
     const bool dense_on = rule.dense && n > thr && dense_bounds_entries(n, h->sorted_batch, h->T) <= h->dbounds_cap &&
@@ -990,7 +994,7 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     }
     const int per_block = kBwdThreads / kWave;
     const int64_t max_long = n / a.long_run + 1;
-    const dim3 grid_fix((unsigned)std::min<int64_t>(2048, ceil_div(max_long, per_block)));
+    const dim3 grid_fix((unsigned)(a.piece_blocks > 0 ? a.piece_blocks : std::min<int64_t>(2048, ceil_div(max_long, per_block))));
     if (h->dtype == TBE_DTYPE_FP32)
         launch_update_grad<float>(a, grid_fix, st, h);
     else

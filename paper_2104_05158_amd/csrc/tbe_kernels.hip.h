@@ -669,6 +669,8 @@ struct BwdArgs {
     int32_t long_run;      // runs longer than this are long: kLongRun, or kPosPiece in a small call that cuts them by position
     int32_t small;         // long runs are those that sort_small_kernel listed, each summed by a workgroup of this kernel
     int32_t span_blocks;   // small: workgroups of spans; those of long runs follow
+    int32_t piece_blocks;  // > 0: long runs are found by position, a wavefront per partial row; this many workgroups of the update
+                           // kernel, in front of those of the spans, sum their pieces, as many of the fix-up add them up
     const uint32_t* small_long;   // small: indices of the long runs, their number in front
     int32_t by_position;   // long runs are cut by position (their pieces are listed by the update kernel), not by bag window
     int32_t T;
@@ -1003,6 +1005,50 @@ __device__ __forceinline__ void sum_lookups(const BwdArgs& a, const TableMeta& m
     }
 }
 
+// One wavefront sums the gradient rows of one piece and writes its partial row.
+template <typename GT>
+__device__ __forceinline__ void sum_piece(const BwdArgs& a, const int4 rec /* p0, p1, slot, t */)
+{
+    const TableMeta m = a.meta[rec.w];
+    const Cols c(m.dim, m.lpr_bwd(), threadIdx.x & (kWave - 1));
+    float acc[2][4];
+    sum_lookups<GT>(a, m, c, rec.x, rec.y, acc);
+    store_partial(a.partials + (int64_t)rec.z * a.dpad, acc, c);
+}
+
+// Long runs by position need no list: partial rows are numbered by position, kPosSlot positions each, and at most one piece
+// starts in those of a number (at most one long run does), always of the last run that starts before their end.
+// The positions [s, e) of that run if it is long; its index, or -1.
+__device__ __forceinline__ int long_run_by_position(const BwdArgs& a, int slot, int& s, int& e)
+{
+    static_assert(kPosSlot % kSpanUnit == 0, "");
+    if (slot >= (a.n + kPosSlot - 1) / kPosSlot)
+        return -1;
+    const int end = min(a.n, (slot + 1) * kPosSlot);
+    const int run = uniform(a.unit_first_run[(end + kSpanUnit - 1) / kSpanUnit]) - 1;
+    s = uniform(a.seg_offsets[run]), e = uniform(a.seg_offsets[run + 1]);
+    return e - s > a.long_run ? run : -1;
+}
+
+// A piece by one wavefront beside the spans, in their launch.  In one of its own after them it added a chain of up to 128 rows
+// to calls that are little more than such chains, and 5 us to those without long runs: 40 tables of 4..512 columns, 0.17 M
+// lookups: step of 105 -> 86 us; Adam, 0.44 M 190 -> 184; 512 columns, 0.2 M 171 -> 154 (pieces of 64 lookups: 87 and 165).
+template <typename GT>
+__device__ __forceinline__ void sum_piece_by_position(const BwdArgs& a, int slot)
+{
+    int s, e;
+    const int run = long_run_by_position(a, slot, s, e);
+    if (run < 0)
+        return;
+    const int np = position_pieces(e - s);
+    const int i = first_piece_from(e - s, np, slot * kPosSlot - s);
+    const int p0 = position_of_piece(s, e - s, np, i);
+    if (i >= np || p0 >= (slot + 1) * kPosSlot)
+        return;
+    const int t = uniform(find_table(a.row_base, a.T, (uint32_t)uniform((int)a.unique_keys[run])));
+    sum_piece<GT>(a, make_int4(p0, position_of_piece(s, e - s, np, i + 1), slot, t));
+}
+
 // A long run of a small call, by one workgroup: its wavefronts sum a share each, the first adds the shares in their order
 // and applies the update.  One launch less for the pieces and one for the fix-up, which are empty as a rule and cost 4 us
 // each all the same (2048 lookups, 64 columns: step of 20.6 -> 17.3 us).
@@ -1136,8 +1182,9 @@ __device__ __forceinline__ void run_batch(const BwdArgs& a, WT* __restrict__ wta
     }
 }
 
-// SPAN: sorted positions owned by one wavefront
-template <typename WT, typename GT, int OPT, int SPAN>
+// SPAN: sorted positions owned by one wavefront.  OWN: workgroups of this launch sum the long runs (small) or their pieces
+// (piece_blocks); otherwise the spans list them.  (In one kernel the scalar registers did not do: 0.3 % of 0.65 M lookups.)
+template <typename WT, typename GT, int OPT, int SPAN, bool OWN>
 __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
 {
     using IO = RowIO<WT, 4>;
@@ -1158,16 +1205,22 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     __shared__ __align__(16) int32_t s_val_all[kWaves][kValCap];
     __shared__ uint8_t s_list_all[kWaves][kStaged];
 
-    if constexpr (SPAN == kSpanUnit) {                // (small calls have the shortest spans)
-        if (a.small && (int)blockIdx.x >= a.span_blocks) {
-            static_assert(sizeof(s_val_all) >= sizeof(float) * kWaves * kMaxDim && kValCap % 4 == 0, "");
-            small_long_run<WT, GT, OPT>(a, (int)blockIdx.x - a.span_blocks, reinterpret_cast<float(*)[kMaxDim]>(&s_val_all[0][0]));
-            return;
-        }
-    }
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x >> 6;
-    const int k = uniform(blockIdx.x * kWaves + wv);
+    int block = (int)blockIdx.x;
+    if constexpr (OWN) {
+        if (a.small && block >= a.span_blocks) {
+            static_assert(sizeof(s_val_all) >= sizeof(float) * kWaves * kMaxDim && kValCap % 4 == 0, "");
+            small_long_run<WT, GT, OPT>(a, block - a.span_blocks, reinterpret_cast<float(*)[kMaxDim]>(&s_val_all[0][0]));
+            return;
+        }
+        if (block < a.piece_blocks) {
+            sum_piece_by_position<GT>(a, uniform(block * kWaves + wv));
+            return;
+        }
+        block -= a.piece_blocks;
+    }
+    const int k = uniform(block * kWaves + wv);
     const int q0 = k * SPAN;
     if (q0 >= a.n)
         return;
@@ -1288,7 +1341,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
                 cl = tl <= lgG ? 3 + tl : 14;
             }
             cls[i] = valid ? cl : -1;
-            if (a.small)
+            if constexpr (OWN)
                 continue;
             const bool cut = a.by_position && len <= a.dense_thr;
             if (a.by_position)
@@ -1936,17 +1989,6 @@ __global__ __launch_bounds__(256) void window_pieces_kernel(BwdArgs a, const uin
     }
 }
 
-// One wavefront sums the gradient rows of one piece and writes its partial row.
-template <typename GT>
-__device__ __forceinline__ void sum_piece(const BwdArgs& a, const int4 rec /* p0, p1, slot, t */)
-{
-    const TableMeta m = a.meta[rec.w];
-    const Cols c(m.dim, m.lpr_bwd(), threadIdx.x & (kWave - 1));
-    float acc[2][4];
-    sum_lookups<GT>(a, m, c, rec.x, rec.y, acc);
-    store_partial(a.partials + (int64_t)rec.z * a.dpad, acc, c);
-}
-
 template <typename GT>
 __global__ __launch_bounds__(kBwdThreads) void window_runs_kernel(BwdArgs a)
 {
@@ -2010,15 +2052,9 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
     const int lane = threadIdx.x & (kWave - 1);
     const int wave_global = uniform(blockIdx.x * (kBwdThreads / kWave) + (threadIdx.x >> 6));
     const int wave_total = gridDim.x * (kBwdThreads / kWave);
-    const int cnt = (int)a.counters->long_todo;
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        a.counters->win_pieces = 0;
     WT* __restrict__ weights = static_cast<WT*>(a.weights);
     float acc[2][4];
-    for (int i = wave_global; i < cnt; i += wave_total) {
-        const LongRun rec = a.long_list[i];
-        const int s = rec.s, e = rec.e, t = rec.t;
-        const uint32_t key = rec.key;
+    auto fix = [&](uint32_t key, int t, int s, int e) {
         const bool dense = e - s > a.dense_thr;
         const TableMeta m = a.meta[t];
         const Cols c(m.dim, m.lpr_bwd(), lane);
@@ -2055,6 +2091,22 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
                                    (nwin + step - 1) / step, a.zero_row, c, acc);
         }
         optimizer_epilogue<WT, OPT>(wrow, wvv, acc, m.dim, c, c.grp == 0, a.opt, key, wel, st);
+    };
+    if (a.piece_blocks > 0) {
+        int s, e;
+        const int run = long_run_by_position(a, wave_global, s, e);
+        if (run >= 0 && s >= wave_global * kPosSlot) {
+            const uint32_t key = (uint32_t)uniform((int)a.unique_keys[run]);
+            fix(key, uniform(find_table(a.row_base, a.T, key)), s, e);
+        }
+        return;
+    }
+    const int cnt = (int)a.counters->long_todo;
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        a.counters->win_pieces = 0;
+    for (int i = wave_global; i < cnt; i += wave_total) {
+        const LongRun rec = a.long_list[i];
+        fix(rec.key, rec.t, rec.s, rec.e);
     }
 }
 

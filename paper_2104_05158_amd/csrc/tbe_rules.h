@@ -102,6 +102,12 @@ constexpr int64_t kPositionBlock = 4 << 20;
 // passes: 512 bf16 columns, 64 tables, 6.6 M 699 / 767; fp32, 128 tables, 13 M 2733 / 2262.
 constexpr int64_t kManyLongBytes = 16000000, kManyLongPerColumn = 65536;
 
+// Lookups up to which the long runs of a call without dense ones are found by position instead of listed: every partial row
+// there could be takes a wavefront that looks for it, twice, which a larger call does not get back (step, us, listed / found: 40
+// tables of 4..512 columns, 0.17 M 103 / 85; 512 columns, 0.2 M 171 / 154; 128, 0.33 M 94 / 92; uniform, 0.65 M 295 / 298;
+// 16-bit, 2 M 358 / 361, 6.2 M 688 / 694; 256 fp32 columns, 3.6 M 544 / 548).  Narrow rows (longer spans) have short chains and stay listed.
+constexpr int64_t kFoundLookups = 1 << 19;
+
 constexpr int kPosPiece = 128;            // a piece by position has at most this many lookups (and fewer than that is never long) ...
 constexpr int kPosPiecesMax = 256;        // ... unless that would make more pieces of a run than this
 // Partial row of a piece: its first position / kPosSlot.  A piece has at least kPosSlot lookups, so no two share one, and a
@@ -110,6 +116,7 @@ constexpr int kPosSlot = 64;
 
 struct LongRunRule {
     bool by_position, dense;   // dense: runs beyond the dense threshold are summed as dense rows
+    bool found;                // by position, and by wavefronts that look for them
     int long_run;              // a run of more lookups is long
 };
 
@@ -119,6 +126,7 @@ inline LongRunRule long_run_rule(int64_t lookups, int64_t batch, int64_t widest,
     LongRunRule r;
     r.by_position = batch * widest * grad_bytes <= kPositionBlock;
     r.dense = !r.by_position || lookups * grad_bytes >= std::max(kManyLongBytes, kManyLongPerColumn * widest);
+    r.found = !r.dense && lookups <= kFoundLookups;
     r.long_run = r.dense ? kLongRun : kPosPiece;
     return r;
 }
@@ -142,6 +150,14 @@ TBE_BOTH int position_of_piece(int s, int len, int np, int i)
 {
     const int each = len / np, more = len - each * np;    // the first `more` pieces are one longer
     return s + i * each + (i < more ? i : more);
+}
+
+// first of the np pieces of a run of `len` lookups that starts `from` positions behind the run's start, or later (np: none)
+TBE_BOTH int first_piece_from(int len, int np, int from)
+{
+    const int each = len / np, more = len - each * np;
+    const int longer = more * (each + 1);
+    return from <= 0 ? 0 : from <= longer ? (from + each) / (each + 1) : more + (from - longer + each - 1) / each;
 }
 
 // ---------------------------------------------------------------- sort

@@ -13,12 +13,13 @@ void forward_launch(int64_t num_bags, int64_t lookups, int few, int wide, int64_
     out[2] = f.blocks;
 }
 
-void long_run_rule(int64_t lookups, int64_t batch, int64_t widest, int grad_bytes, int32_t* out /*[3]*/)
+void long_run_rule(int64_t lookups, int64_t batch, int64_t widest, int grad_bytes, int32_t* out /*[4]*/)
 {
     const tbe::LongRunRule r = tbe::long_run_rule(lookups, batch, widest, grad_bytes);
     out[0] = r.by_position;
     out[1] = r.dense;
     out[2] = r.long_run;
+    out[3] = r.found;
 }
 
 // borders of the pieces of a run; returns their number
@@ -29,6 +30,8 @@ int position_pieces(int s, int len, int32_t* out /*[257]*/)
         out[i] = tbe::position_of_piece(s, len, np, i);
     return np;
 }
+
+int first_piece_from(int len, int np, int from) { return tbe::first_piece_from(len, np, from); }
 
 int update_span(int64_t lookups, int64_t lanes, int64_t tables) { return tbe::update_span(lookups, lanes, tables); }
 

@@ -54,3 +54,21 @@ def test_runs_by_position_beside_dense_ones(gpu_device, layout, bad):
     g = wl.make_grad(spec, "cpu", seed=53).numpy()
     print(f"N={idx.size} layout={layout} bad={bad}", flush=True)
     tl.full_parity_step(spec, idx, off, w, g, gpu_device, lr=0.03, what="position and dense", layout=layout)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n", [(1 << 19) - 37, 1 << 19, (1 << 19) + 1])
+def test_long_runs_found_by_position_and_listed(gpu_device, n, dtype):
+    """Calls on both sides of the size from which long runs are listed instead of found by position: runs that start at every
+    place of the positions of a partial row, one behind the other and with short ones between, some of more than 256 pieces."""
+    rng = np.random.default_rng(n)
+    lens = [np.concatenate([rng.integers(120, 400, 500), [33_000, 40_000, 1, 64, 63, 129, 192, 193], rng.integers(1, 200, 300)]) for _ in range(2)]
+    lens[0] = np.concatenate([lens[0], [1] * 3])
+    rest = n - sum(int(x.sum()) for x in lens)
+    lens[1] = np.concatenate([lens[1], [rest // 2, rest - rest // 2]])
+    spec, idx, off = _explicit_case([128, 36], lens, batch=900, seed=55 + dtype, dtype=dtype)
+    assert idx.size == n
+    w = wl.make_weights(spec, "cpu", seed=56).numpy()
+    g = wl.make_grad(spec, "cpu", seed=57).numpy()
+    print(f"N={n} dtype={dtype}", flush=True)
+    tl.full_parity_step(spec, idx, off, w, g, gpu_device, lr=0.03, what="found and listed")

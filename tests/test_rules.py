@@ -134,12 +134,32 @@ def test_pieces_by_position_cover_a_run_and_own_their_partial_rows(rules, length
         assert len(np.unique(borders // 64)) == np_ + 1
 
 
+def test_every_piece_starts_at_one_row_of_partial_sums(rules):
+    # what a wavefront finds that looks at the 64 positions of a partial row: the piece that starts there, if any
+    for s, length in [(0, 129), (63, 129), (64, 129), (1, 256), (77, 257), (130, 1000), (5, 32768), (5, 32769), (9, 32767 + 256), (127, 100_003)]:
+        out = np.empty(257, np.int32)
+        np_ = rules.position_pieces(ctypes.c_int(s), ctypes.c_int(length), out.ctypes.data_as(ctypes.c_void_p))
+        starts = out[:np_].tolist()
+        found = {}
+        for slot in range(s // 64, (s + length - 1) // 64 + 1):
+            i = rules.first_piece_from(ctypes.c_int(length), ctypes.c_int(np_), ctypes.c_int(slot * 64 - s))
+            assert i == next((j for j, p in enumerate(starts) if p >= slot * 64), np_)
+            if i < np_ and starts[i] < slot * 64 + 64:
+                found[i] = slot
+        assert found == {i: p // 64 for i, p in enumerate(starts)}
+
+
 def test_which_long_runs_are_cut_how(rules):
     def rule(n, batch, widest, grad_bytes):
-        out = np.empty(3, np.int32)
+        out = np.empty(4, np.int32)
         rules.long_run_rule(ctypes.c_int64(n), ctypes.c_int64(batch), ctypes.c_int64(widest), ctypes.c_int(grad_bytes),
                             out.ctypes.data_as(ctypes.c_void_p))
-        return out.tolist()
+        return out[:3].tolist()
+    def found(n, batch):
+        out = np.empty(4, np.int32)
+        rules.long_run_rule(ctypes.c_int64(n), ctypes.c_int64(batch), ctypes.c_int64(128), ctypes.c_int(4), out.ctypes.data_as(ctypes.c_void_p))
+        return bool(out[3])
+    assert found(1 << 19, 8192) and not found((1 << 19) + 1, 8192) and not found(1000, 8193)
     assert rule(3_999_999, 8192, 128, 4) == [1, 0, 128] and rule(4_000_000, 8192, 128, 4) == [1, 1, 512]
     assert rule(4_000_000, 8193, 128, 4) == rule(1, 8193, 128, 4) == [0, 1, 512] and rule(1, 8193, 128, 2) == [1, 0, 128]
     assert rule(8_388_607, 2048, 512, 4) == [1, 0, 128] and rule(8_388_608, 2048, 512, 4) == [1, 1, 512]
