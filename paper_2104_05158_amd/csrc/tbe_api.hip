@@ -783,12 +783,16 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.select = use_select_sort(h->T, n);
     {   // a2: samples, bucket borders and chunks
         ScopedTimer tm(h, SLOT_SORT_PLAN, st);
-        hipLaunchKernelGGL(sort_plan_kernel, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
+        if (a.select)
+            hipLaunchKernelGGL(sort_plan_kernel<true>, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
+        else
+            hipLaunchKernelGGL(sort_plan_kernel<false>, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_plan_kernel");
     }
     if (a.select) {   // a3: units that find their lookups themselves
         ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
-        const dim3 grid((unsigned)std::min<int64_t>(n / ss.target + 2 * (int64_t)h->T, 1024));
+        static_assert(kSelectLookups / kSortTargetMin + kSelectLookups / kSelectPart <= kSortUnitsRound, "the workspace has room for the units");
+        const dim3 grid((unsigned)std::min<int64_t>(n / ss.target + n / kSelectPart + 2 * (int64_t)h->T, 1024));
         if (ss.wide)
             hipLaunchKernelGGL(sort_select_kernel<uint64_t>, grid, dim3(kSortThreads), 0, st, a);
         else

@@ -221,13 +221,25 @@ TBE_BOTH int samples_per_bucket(int buckets, int target)
 }
 
 // Middle calls: the units find their lookups themselves, each among all of its table's (sort_select_kernel), instead of
-// having them brought by histogram, units and scatter.  That reads a table's indices once per unit: while tables have
-// kSelectMean lookups on average the three launches cost more.  Sort, us, with them / without: 40 tables of 4400 lookups 71 /
-// 36, 64 of 570 62 / 26, 1 of 22,000 67 / 40, 8 of 20,000 71 / 44, 30 of 9800 77 / 46; beyond it 8 of 29,000 72 / 68, 20 of
-// 33,000 86 / 78, and 1 of 122,000 87 / 124.  The host does not know how the lookups spread over the tables, and a workgroup
-// takes 1.3 us per 4096 of its table's: kSelectLookups ends what a call can lose if one table has nearly all of them.
+// having them brought by histogram, units and scatter.  That reads a table's indices twice per unit: while tables have
+// kSelectMean lookups on average the three launches cost more.  Sort, us, with them / without: 40 tables of 4300 lookups 41 /
+// 26, 60 of 4300 43 / 28, 1 of 20,000 39 / 29, 11 of 23,800 43 / 35.  The host does not know how the lookups spread over the
+// tables.  One table with 60,000 of 3 tables' 42 / 36 (Zipf 42 / 37), 100,000 of 40 47 / 43 (47 / 45), 120,000 of 16 48 / 46
+// (48 / 49), 200,000 of 11 53 / 57 (52 / 63), 251,000 of 11 52 / 64 (53 / 73; in 16,384 bags 57 / 83): kSelectLookups ends what a
+// call can lose.
 constexpr int kSelectCap = 6144;           // words of a unit that is sorted in LDS
 constexpr int64_t kSelectMean = 4 * kSelectCap, kSelectLookups = 1 << 18;
+
+// Units of a row of which `sampled` of a table's `samples` samples are.  One workgroup would place all lookups of a hot row, and
+// walk the table once more for every 12,288 of them (11 tables, one of 200,000 Zipf lookups: sort of 100 us, 62 with parts).
+// Together the rows of a table have at most lookups / kSelectPart units more than one each.
+constexpr int kSelectPart = 4096;
+constexpr int kSelectHot = (int)(kSelectLookups / kSelectPart);    // most rows with more than one
+
+TBE_BOTH int select_parts(uint32_t sampled, int lookups, int samples)
+{
+    return 1 + (int)(sampled * (uint32_t)lookups / (uint32_t)samples / (uint32_t)kSelectPart);
+}
 
 inline bool use_select_sort(int64_t tables, int64_t lookups) { return lookups <= kSelectLookups && lookups <= kSelectMean * tables; }
 

@@ -79,6 +79,7 @@ struct SortUnit {        // 32 bytes
     uint32_t last;       // sort_select_kernel: offset of the unit's last row from key0 (of the last unit: of any index)
 };
 constexpr int kUnitContinued = 1;     // further part of a one-row bucket: its first lookup starts no run
+constexpr int kUnitMore = 4;          // sort_select_kernel: further parts follow; the part's number is in the bits from 8 on
 constexpr int kUnitNone = 2;          // no bucket (sort_select_kernel; until then start, m of its units are those of the table)
 
 struct SortArgs {
@@ -132,6 +133,16 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t v)   // inclusive
     v += dpp0<0x118, 0xf>(v);
     v += dpp0<0x142, 0xa>(v);
     v += dpp0<0x143, 0xc>(v);
+    return v;
+}
+
+template <int N>
+__device__ __forceinline__ uint32_t first_lanes_scan_add(uint32_t v)   // inclusive, over the first N lanes
+{
+    static_assert(N == 8, "");
+    v += dpp0<0x111, 0xf>(v);
+    v += dpp0<0x112, 0xf>(v);
+    v += dpp0<0x114, 0xf>(v);
     return v;
 }
 
@@ -432,7 +443,7 @@ __device__ __forceinline__ uint32_t bags_of_positions(const int64_t* __restrict_
 struct TablePlan {
     int want, cuts;      // buckets asked for, ranges of the packed key
     int chunks;
-    int units;           // select: most buckets there can be
+    int units;           // select: most there can be, of all buckets and rows of several units
 };
 
 __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32_t rows)
@@ -441,7 +452,7 @@ __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32
     p.cuts = a.kb >= 31 ? 1 : (int)((rows + (1u << a.kb) - 1) >> a.kb);
     p.want = min(max((n + a.target - 1) / a.target, 1), kMaxBuckets - p.cuts);
     p.chunks = n == 0 || a.select ? 0 : (n + a.chunk - 1) / a.chunk;
-    p.units = n == 0 || !a.select ? 0 : p.want + p.cuts - 1;
+    p.units = n == 0 || !a.select ? 0 : p.want + p.cuts - 1 + n / kSelectPart;
     return p;
 }
 
@@ -459,11 +470,14 @@ __device__ __forceinline__ int lds_lower(const uint32_t* p, int n, uint32_t v)
     return lo;
 }
 
+// SELECT: a.select (in one kernel the partition's plan took 0.3 us longer)
+template <bool SELECT>
 __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
 {
     __shared__ __align__(16) uint32_t s_key[kSortTile];
     __shared__ __align__(16) uint16_t s_cnt[kSortWaves][1024];     // (samples are few: two passes of ten bits)
     __shared__ uint32_t s_list[kMaxBuckets + 2], s_cut[kMaxRangeCuts];
+    __shared__ uint32_t s_hot[kSelectHot], s_more[kSelectHot], s_hots;    // (select) rows of several units, and how many more each has
     __shared__ uint32_t s_wsum[kSortWaves];
     __shared__ uint32_t s_sum[4];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
@@ -474,6 +488,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     const int bits = a.meta[t].key_bits;
     if (tid < 4)
         s_sum[tid] = 0;
+    if (SELECT && tid == 0)
+        s_hots = 0;
     __syncthreads();
     {   // what the tables before this one take
         uint32_t multi = 0, chunks = 0, parts = 0, units = 0;
@@ -523,7 +539,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             a.tables[t] = st;
         return;
     }
-    if (p.units == 1) {                              // (select) one bucket
+    if (SELECT && p.units == 1) {                              // (select) one bucket
         if (tid == 0)
             a.units[s_sum[3]] = SortUnit{start, n, rbase, ceil_log2(rows), t, 0, (int32_t)s_sum[3], ~0u};
         return;
@@ -545,6 +561,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     // ---- borders: row 0, every q-th sample once, and the row after one that fills a whole stretch of samples
     // (a bucket of its own).  Thread j owns candidates 2 j and 2 j + 1.
     uint32_t cand[2], emit[2];
+    const int part_samples = (int)((int64_t)kSelectPart * S / n);      // (that many hold lookups for a unit more)
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int j = 2 * tid + k;
@@ -556,6 +573,15 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             const bool fresh = j == 0 || c != before;
             cand[k] = c;
             emit[k] = fresh ? (j + 1 < p.want && s_key[(j + 1) * q] == c ? 2u : 1u) : 0u;
+            if (SELECT && emit[k] > 1 && s_key[min(j * q + part_samples, S) - 1] == c) {
+                const uint32_t sampled = (uint32_t)lds_lower(s_key + j * q, S - j * q, c + 1u);
+                const uint32_t more = (uint32_t)select_parts(sampled, n, S) - 1u;
+                if (more > 0) {
+                    const uint32_t i = atomicAdd(&s_hots, 1u);
+                    s_hot[i] = c;
+                    s_more[i] = more;
+                }
+            }
         }
     }
     uint32_t total;
@@ -603,18 +629,26 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         s_list[i + lds_lower(s_cut, nc, s_key[i])] = s_key[i];
     const int nb = na + nc;
     __syncthreads();
-    if (a.select) {
-        for (int i = tid; i < p.units; i += kSortThreads) {
-            SortUnit u{start, n, 0, 0, t, kUnitNone, (int32_t)s_sum[3], 0};
-            if (i < nb) {                            // (an index that is no row of the table is the last bucket's)
-                u.flags = 0;
-                const uint32_t lo = s_list[i], hi = i + 1 < nb ? s_list[i + 1] : rows;
-                u.key0 = rbase + lo;
-                u.bits = ceil_log2(hi - lo);
-                u.last = i + 1 < nb ? hi - lo - 1u : ~0u - lo;
+    if (SELECT) {
+        const int hots = (int)s_hots;
+        for (int i = tid; i < nb; i += kSortThreads) {                     // (an index that is no row of the table is the last bucket's)
+            const uint32_t lo = s_list[i], hi = i + 1 < nb ? s_list[i + 1] : rows;
+            uint32_t more = 0, at = s_sum[3] + (uint32_t)i;
+            for (int k = 0; k < hots; ++k) {
+                at += s_hot[k] < lo ? s_more[k] : 0u;
+                more += s_hot[k] == lo ? s_more[k] : 0u;
             }
-            a.units[s_sum[3] + i] = u;
+            SortUnit u{start, n, rbase + lo, ceil_log2(hi - lo), t, 0, (int32_t)s_sum[3], i + 1 < nb ? hi - lo - 1u : ~0u - lo};
+            for (uint32_t k = 0; k <= more; ++k) {
+                u.flags = (int32_t)(k << 8) | (k < more ? kUnitMore : 0);
+                a.units[at + k] = u;
+            }
         }
+        int used = nb;
+        for (int k = 0; k < hots; ++k)
+            used += (int)s_more[k];
+        for (int i = used + tid; i < p.units; i += kSortThreads)
+            a.units[s_sum[3] + i] = SortUnit{start, n, 0, 0, t, kUnitNone, (int32_t)s_sum[3], 0};
         return;
     }
     for (int i = tid; i < nb; i += kSortThreads)
@@ -1178,24 +1212,28 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
 // In a call of some 100,000 lookups the launches of the partition (histogram, units, scatter) each cost their latency and
 // little else.  Here the workgroup of a unit reads all indices of the unit's table instead, out of L2, and keeps those
 // of its own rows: table lookups x units index reads in all, but nothing to wait for between the plan and the sort.
-// The lookups of earlier rows are counted on the way: that is where the unit's own start.  Bound by latency and, from some
-// 20,000 lookups of a table on, by the scan (1.3 us a step).  40 tables, 0.17 M lookups: 18 us, where histogram, units, scatter
-// and bucket sort took 51; 64 tables, 37,000 lookups 13 us, 43.
+// It reads them twice.  The first time every wavefront counts the lookups of its own rows and of earlier ones in a stretch of
+// the table, which says where the unit starts and where the stretch's go; the second time they are put there, in order.
+// Neither waits for the other wavefronts.  Read once, in steps whose counts all wavefronts exchange, 4096 positions took 1.3 us;
+// now 0.6.  Bound by latency and, from some 20,000 lookups of a table on, by that walk.  40 tables, 0.17 M lookups: 15 us, where
+// histogram, units, scatter and bucket sort took 47; 11 tables, one with 200,000 lookups: 45 us, 53 (in steps 75).
 constexpr int kSelectWords = kSelectCap / kSortThreads;
-constexpr int kSelectPer = 8;                     // positions per thread and step of the scan (16, in 16-byte loads: no faster)
-constexpr int kSelectStep = kSortThreads * kSelectPer;
-constexpr int kSelectCoarse = kSortThreads;       // bag borders in LDS: every (B / 512)-th
+constexpr int kSelectPer = 12;                    // positions per thread and block (200,000 lookups of a table: 16 are 4 us slower, 8 the same)
+constexpr int kSelectCoarse = kSortThreads;       // bag borders in LDS: every (B / 512)-th (every (B / 4096)-th: no faster)
 
 template <typename W>
 __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_select_kernel(SortArgs a)
 {
-    static_assert(kSelectCap % (kSortGroup * kSortThreads) == 0 && kSelectCap >= kSelectStep && kSelectCap <= kSortTile, "");
-    __shared__ __align__(16) W s_w[kSelectCap];   // row offsets of the unit's lookups, then the words
-    __shared__ uint32_t s_pos[kSelectCap];        // their positions in the table
+    static_assert(kSelectCap % (kSortGroup * kSortThreads) == 0 && kSelectCap <= kSortTile, "");
+    // positions of the unit's lookups in the table, then their row offsets and later their words; the positions of a single
+    // row's take all of it, kSelectRow at a time
+    __shared__ __align__(16) uint32_t s_pos[kSelectCap * (1 + sizeof(W) / 4)];
+    W* s_w = reinterpret_cast<W*>(s_pos + kSelectCap);
+    constexpr int kSelectRow = kSelectCap * (1 + sizeof(W) / 4);
     __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
     __shared__ int32_t s_coarse[kSelectCoarse];
-    __shared__ uint32_t s_hits[2][kSortWaves], s_wsum[kSortWaves];
-    __shared__ uint32_t s_below, s_heads;
+    __shared__ uint32_t s_below[kSortWaves], s_hits[kSortWaves], s_wsum[kSortWaves];
+    __shared__ uint32_t s_heads;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
     const int total_units = (int)a.counters->sort_units;
     const W vmask = ((W)1 << a.vb) - 1;
@@ -1208,13 +1246,14 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sel
             }
             continue;
         }
-        const int n = un.m, t = un.t;
-        const uint32_t* __restrict__ idx = a.indices + un.start;
+        const int n = uniform(un.m), t = uniform(un.t), table_start = uniform(un.start);
+        const uint32_t unit_key = (uint32_t)uniform((int)un.key0), unit_last = (uint32_t)uniform((int)un.last);
+        const __amdgpu_buffer_rsrc_t idx = row_buffer(a.indices + table_start, 4ull * (uint32_t)n);
         const int64_t* __restrict__ offsets = a.offsets + (int64_t)t * a.B;
         const int lg_each = max(0, ceil_log2((uint32_t)a.B) - 9);      // bags per coarse border
         static_assert(kSelectCoarse == 1 << 9, "");
         __syncthreads();
-        s_coarse[tid] = (int64_t)tid << lg_each < a.B ? (int)offsets[tid << lg_each] - un.start : INT32_MAX;
+        s_coarse[tid] = (int64_t)tid << lg_each < a.B ? (int)offsets[tid << lg_each] - table_start : INT32_MAX;
         if (tid == 0)
             s_heads = 0;
         // bag of a position: the last one that starts at or before it
@@ -1223,115 +1262,141 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sel
 #pragma unroll
             for (int s = kSelectCoarse / 2; s > 0; s >>= 1)
                 c += s_coarse[c + s] <= pos ? s : 0;
-            int b = c << lg_each;
-            for (int s = (1 << lg_each) >> 1; s > 0; s >>= 1)
-                b += b + s < a.B && (int)offsets[b + s] - un.start <= pos ? s : 0;
+            int b = c << lg_each, lg = lg_each;
+            auto starts = [&](int bag) { return (int)offsets[min(bag, a.B)] - table_start <= pos ? 1 : 0; };
+            for (; lg > 1; lg -= 2) {
+                const int quarter = 1 << (lg - 2);
+                b += (starts(b + quarter) + starts(b + 2 * quarter) + starts(b + 3 * quarter)) * quarter;
+            }
+            if (lg > 0)
+                b += starts(b + 1);
             return (uint32_t)b;
         };
-        // Finds the lookups of the rows [row0, row0 + last]: put(slot, row offset, position) for each, in position order;
-        // full(found, step) before the lookups of a step, the last `step` of the `found` so far, are put.  Returns their number;
-        // below: the thread's lookups of earlier rows.
-        auto scan = [&](uint32_t row0, uint32_t last, auto put, auto full, uint32_t& below) {
-            uint32_t found = 0;
-            uint32_t key[kSelectPer];
-            const int q = wave * kSelectPer * kWave + lane;
+        // Every wavefront reads a stretch of the table's positions, block by block, the first out of registers: use(key, at, full)
+        // with its positions from `at` on, all of them or (full false) those before `end`.
+        constexpr int kBlock = kSelectPer * kWave;
+        const int each = (n + kSortWaves * kWave - 1) / (kSortWaves * kWave) * kWave;
+        const int begin = min(wave * each, n), end = min(begin + each, n);
+        uint32_t first_block[kSelectPer];
+        auto load = [&](uint32_t (&key)[kSelectPer], int at) {     // behind the table: 0
+            const int from = opaque((at + lane) * 4) & 0x7fffff;        // (seen not to be negative, the rest goes into the instruction)
+            static_assert(kSelectLookups + 2 * kBlock <= 0x7fffff / 4, "");
 #pragma unroll
             for (int r = 0; r < kSelectPer; ++r)
-                key[r] = idx[min(q + r * kWave, n - 1)];
-            int buf = 0;
-            for (int first = 0; first < n; first += kSelectStep, buf ^= 1) {
-                uint32_t next[kSelectPer], rank[kSelectPer], hits = 0;
-#pragma unroll
-                for (int r = 0; r < kSelectPer; ++r)
-                    next[r] = idx[min(first + kSelectStep + q + r * kWave, n - 1)];
-#pragma unroll
-                for (int r = 0; r < kSelectPer; ++r) {
-                    const bool valid = first + q + r * kWave < n;
-                    const bool mine = valid && key[r] - row0 <= last;
-                    below += valid && key[r] < row0 ? 1u : 0u;
-                    const uint64_t bal = __ballot(mine);
-                    rank[r] = mine ? __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, hits)) : ~0u;
-                    hits += (uint32_t)__popcll(bal);
-                }
-                if (lane == 0)
-                    s_hits[buf][wave] = hits;
-                __syncthreads();
-                uint32_t base = found, step = 0;
-#pragma unroll
-                for (int w = 0; w < kSortWaves; ++w) {
-                    const uint32_t c = s_hits[buf][w];
-                    base += w < wave ? c : 0u;
-                    step += c;
-                }
-                found += step;
-                full(found, step);
-#pragma unroll
-                for (int r = 0; r < kSelectPer; ++r)
-                    if (rank[r] != ~0u)
-                        put(base + rank[r], key[r] - row0, (uint32_t)(first + q + r * kWave));
-#pragma unroll
-                for (int r = 0; r < kSelectPer; ++r)
-                    key[r] = next[r];
-            }
-            return found;
+                key[r] = __builtin_amdgcn_raw_buffer_load_b32(idx, from + r * kWave * 4, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);                     // (not behind the block before it)
         };
-        // keys and payloads of a single row's first m lookups in LDS
+        auto walk = [&](auto use) {
+            uint32_t even[kSelectPer], odd[kSelectPer];
+#pragma unroll
+            for (int r = 0; r < kSelectPer; ++r)
+                even[r] = first_block[r];
+            int at = begin;
+            for (; at + 2 * kBlock <= end; at += 2 * kBlock) {
+                load(odd, at + kBlock);
+                use(even, at, std::true_type());
+                load(even, at + 2 * kBlock);
+                use(odd, at + kBlock, std::true_type());
+            }
+            if (at + kBlock <= end) {
+                load(odd, at + kBlock);
+                use(even, at, std::true_type());
+                at += kBlock;
+#pragma unroll
+                for (int r = 0; r < kSelectPer; ++r)
+                    even[r] = odd[r];
+            }
+            use(even, at, std::false_type());
+        };
+        // keys and payloads of a single row's m lookups in LDS
         auto emit_row = [&](uint32_t key, int at, int m) {
+#pragma unroll 4
             for (int i = tid; i < m; i += kSortThreads) {
                 a.keys[at + i] = key;
-                a.vals[at + i] = (int32_t)bag_of((int)(i < kSelectCap ? s_pos[i] : (uint32_t)s_w[i - kSelectCap]));
+                a.vals[at + i] = (int32_t)bag_of((int)s_pos[i]);
             }
         };
         // One pass for all rows of the unit as a rule.  If they have more lookups than fit the LDS (the sample undersized the
-        // bucket) they are halved; the lookups of a single row need no sorting and leave in as many parts as it takes.
-        const uint32_t table_rows = a.row_base[t + 1] - a.row_base[t];
-        const uint32_t first_row = un.key0 - a.row_base[t];
-        const uint32_t unit_rows = min(un.last, table_rows - first_row - 1u) + 1u;
+        // bucket) they are halved; the lookups of a single row need no sorting and leave in as many turns as it takes.
+        const uint32_t table_key = (uint32_t)uniform((int)a.row_base[t]);
+        const uint32_t table_rows = (uint32_t)uniform((int)a.row_base[t + 1]) - table_key;
+        const uint32_t first_row = unit_key - table_key;
+        const uint32_t unit_rows = min(unit_last, table_rows - first_row - 1u) + 1u;
         uint32_t lo = 0, rows = unit_rows, heads = 0;             // the rows [lo, lo + rows) of the unit
         int unit_start = 0, unit_m = 0;
         while (lo < unit_rows) {
-            const uint32_t row0 = first_row + lo, key0 = un.key0 + lo;
-            const uint32_t last = lo + rows == unit_rows ? un.last - lo : rows - 1u;
-            __syncthreads();
-            if (tid == 0)
-                s_below = 0;
+            const uint32_t row0 = first_row + lo, key0 = unit_key + lo;
+            const uint32_t last = lo + rows == unit_rows ? unit_last - lo : rows - 1u;
+            const uint32_t top = row0 + last;
             const bool single = rows == 1;
-            const uint32_t cap = single ? 2 * kSelectCap : kSelectCap;
-            uint32_t below = 0, done = 0;
-            // a single row's positions take both arrays
-            auto put = [&](uint32_t slot, uint32_t row, uint32_t pos) {
-                slot -= done;
-                if (slot < (uint32_t)kSelectCap) {
-                    s_pos[slot] = pos;
-                    if (!single)
-                        s_w[slot] = (W)row;
-                } else if (slot < cap) {
-                    s_w[slot - kSelectCap] = (W)pos;
+            load(first_block, begin);
+            uint32_t below = 0, upto = 0;
+            walk([&](const uint32_t (&key)[kSelectPer], int at, auto full) {
+#pragma unroll
+                for (int r = 0; r < kSelectPer; ++r) {
+                    const bool valid = full || at + r * kWave + lane < end;
+                    below += valid && key[r] < row0 ? 1u : 0u;
+                    upto += valid && key[r] <= top ? 1u : 0u;
                 }
-            };
-            const int m = (int)scan(row0, last, put, [](uint32_t, uint32_t) {}, below);
+            });
             below = last_lane(wave_scan_add(below));
-            if (lane == 0)
-                atomicAdd(&s_below, below);
+            upto = last_lane(wave_scan_add(upto));
             __syncthreads();
-            const int start = un.start + (int)s_below;
-            if (m > (int)cap && !single) {
+            if (lane == 0) {
+                s_below[wave] = below;
+                s_hits[wave] = upto - below;
+            }
+            __syncthreads();
+            below = first_lanes_scan_add<kSortWaves>(lane < kSortWaves ? s_below[lane] : 0u);
+            const uint32_t hits = first_lanes_scan_add<kSortWaves>(lane < kSortWaves ? s_hits[lane] : 0u);
+            const int start = table_start + __builtin_amdgcn_readlane((int)below, kSortWaves - 1);
+            const int m = __builtin_amdgcn_readlane((int)hits, kSortWaves - 1);
+            const int next_slot = __builtin_amdgcn_readlane((int)hits, wave);
+            const int first_slot = wave == 0 ? 0 : __builtin_amdgcn_readlane((int)hits, max(wave, 1) - 1);
+            if (m > kSelectCap && !single) {
                 rows = (rows + 1) / 2;
                 continue;
             }
-            if (single) {
-                if (m > (int)cap) {
-                    (void)scan(row0, last, put, [&](uint32_t found, uint32_t step) {
-                        if (found - done > cap) {
-                            emit_row(key0, start + (int)done, (int)(found - step - done));
-                            done = found - step;
-                            __syncthreads();
+            // put(slot, row offset, position) for each of them, in position order
+            auto select = [&](auto put) {
+                uint32_t slot = (uint32_t)first_slot;
+                // (compared again: no masks are kept of the first block)
+                const uint32_t from = (uint32_t)uniform(opaque((int)row0)), to = (uint32_t)uniform(opaque((int)top));
+                walk([&](const uint32_t (&key)[kSelectPer], int at, auto full) {
+                    const int from_pos = opaque(at + lane);
+#pragma unroll
+                    for (int r = 0; r < kSelectPer; ++r) {
+                        const int pos = from_pos + r * kWave;
+                        const uint64_t mine = __ballot(key[r] <= to) & ~__ballot(key[r] < from) & (full ? ~0ull : __ballot(pos < end));
+                        if (mine != 0) {
+                            if (__builtin_amdgcn_inverse_ballot_w64(mine))
+                                put(__builtin_amdgcn_mbcnt_hi((uint32_t)(mine >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mine, slot)),
+                                    key[r] - row0, (uint32_t)pos);
+                            slot += (uint32_t)__popcll(mine);
                         }
-                    }, below);
+                    }
+                });
+            };
+            // (of a row with several units this one's part, the last takes the rest)
+            const int part = un.flags >> 8;
+            const int from_slot = min(part * kSelectPart, m), to_slot = un.flags & kUnitMore ? min((part + 1) * kSelectPart, m) : m;
+            if (single) {
+                for (int done = from_slot; done < to_slot; done += kSelectRow) {
+                    if (first_slot < min(done + kSelectRow, to_slot) && next_slot > done)
+                        select([&](uint32_t slot, uint32_t, uint32_t pos) {
+                            if (slot - (uint32_t)done < (uint32_t)kSelectRow)
+                                s_pos[slot - done] = pos;
+                        });
+                    __syncthreads();
+                    emit_row(key0, start + done, min(kSelectRow, to_slot - done));
                     __syncthreads();
                 }
-                emit_row(key0, start + (int)done, m - (int)done);
             } else if (m > 0) {
+                select([&](uint32_t slot, uint32_t row, uint32_t pos) {
+                    s_pos[slot] = pos;
+                    s_w[slot] = (W)row;
+                });
+                __syncthreads();
 #pragma unroll 4
                 for (int i = tid; i < m; i += kSortThreads)
                     s_pos[i] = bag_of((int)s_pos[i]);
@@ -1361,10 +1426,10 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sel
                     }
                 }
             }
-            heads += single && tid == 0 && m > 0 ? 1u : 0u;
+            heads += single && tid == 0 && part == 0 && m > 0 ? 1u : 0u;
             if (lo == 0)
-                unit_start = start;
-            unit_m += m;
+                unit_start = start + from_slot;
+            unit_m += to_slot - from_slot;
             lo += rows;
             rows = unit_rows - lo;
         }

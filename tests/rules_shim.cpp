@@ -41,6 +41,8 @@ int small_long_runs(int64_t lookups, int lanes) { return tbe::small_long_runs(lo
 
 int use_select_sort(int64_t tables, int64_t lookups) { return tbe::use_select_sort(tables, lookups); }
 
+int select_parts(int sampled, int lookups, int samples) { return tbe::select_parts((uint32_t)sampled, lookups, samples); }
+
 int sort_target(int64_t lookups) { return tbe::sort_target(lookups); }
 int64_t sort_buckets_max(int64_t lookups) { return tbe::sort_buckets_max(lookups); }
 

@@ -41,6 +41,36 @@ def test_units_that_find_their_lookups_themselves(gpu_device, case):
     _check(gpu_device, rows, batch, lens, np.concatenate(parts), case)
 
 
+PARTS = {
+    # name: (rows, batch, lookups per table, per table the rows that are looked up oftenest and their shares)
+    "two_units": ([1_000_000, 300], 900, [24_000, 500], [{500_000: 0.2}, {}]),
+    "five_rows_beside_each_other": ([1_000_000] * 8, 1024, [150_000] + [100] * 7, [{70 + i: 0.19 for i in range(5)}] + [{}] * 7),
+    "first_and_last_row": ([77_777] * 6, 300, [60_000, 0, 40_000, 1, 2, 3], [{0: 0.4, 77_776: 0.4}, {}, {77_776: 0.5, 0: 0.3}, {}, {}, {}]),
+    "one_row_of_a_large_call": ([1_000_000] * 11, 16_384, [261_000] + [10] * 10, [{999_999: 0.98}] + [{}] * 10),
+    "words_of_64_bits": ([40_000_000, 500], 70_001, [45_000, 4_000], [{39_999_999: 0.3, 5: 0.5}, {}]),
+}
+
+
+@pytest.mark.parametrize("order", ["spread", "first"])
+@pytest.mark.parametrize("case", sorted(PARTS))
+def test_rows_of_several_units(gpu_device, case, order):
+    """A row that the sample holds often enough is placed by several workgroups, 4096 of its lookups each; where all of them lie
+    in the first positions of the table a wavefront has more of them than it would of an even spread."""
+    rows, batch, per_table, hot = PARTS[case]
+    rng = np.random.default_rng(len(case))
+    lens = np.concatenate([_lens(rng, batch, n) for n in per_table])
+    parts = []
+    for h, n, most in zip(rows, per_table, hot):
+        x = rng.integers(0, h, n)
+        at = rng.permutation(n) if order == "spread" else np.arange(n)
+        for row, share in most.items():
+            x[at[:int(share * n)]] = row
+            at = at[int(share * n):]
+        parts.append(x)
+    print(f"{case} {order}: N={sum(per_table)}", flush=True)
+    _check(gpu_device, rows, batch, lens, np.concatenate(parts), case)
+
+
 @pytest.mark.parametrize("rows,batch", [(300_000, 500), (40_000_000, 70_001)])     # words of 32 and of 64 bits
 def test_buckets_that_have_to_be_halved(gpu_device, rows, batch):
     # lookups in stretches of 1024 of which the sample takes 16: every 64th is a row from 2000 on, and so may be all of the

@@ -179,6 +179,19 @@ def test_which_calls_have_units_that_find_their_lookups_themselves(rules):
     assert use(11, 1 << 18) and use(4096, 1 << 18) and not use(4096, (1 << 18) + 1)
 
 
+def test_hot_rows_take_no_more_units_than_there_is_room_for(rules):
+    # whatever rows a table's samples are of: the units beyond one each are at most one per 4096 lookups
+    rng = np.random.default_rng(11)
+    parts = lambda sampled, n, samples: rules.select_parts(ctypes.c_int(sampled), ctypes.c_int(n), ctypes.c_int(samples))
+    for n in (1025, 4095, 4096, 8191, 8192, 100_003, (1 << 18) - 1, 1 << 18):
+        want = (n + 1023) // 1024
+        samples = want * min(16, 8192 // want)
+        assert parts(samples, n, samples) == 1 + n // 4096
+        cuts = np.sort(rng.integers(0, samples + 1, 40))
+        of_rows = np.diff(np.concatenate([[0], cuts, [samples]]))
+        assert sum(parts(int(k), n, samples) - 1 for k in of_rows) <= n // 4096
+
+
 def test_small_calls_sum_their_long_runs_in_at_most_32_trips(rules):
     small = lambda n, lanes: bool(rules.small_long_runs(ctypes.c_int64(n), ctypes.c_int(lanes)))
     assert small(512, 64) and not small(513, 64) and small(4096, 8) and not small(4097, 8) and small(8192, 4) and small(8192, 1)
