@@ -1316,14 +1316,14 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sel
                 a.vals[at + i] = (int32_t)bag_of((int)s_pos[i]);
             }
         };
-        // One pass for all rows of the unit as a rule.  If they have more lookups than fit the LDS (the sample undersized the
-        // bucket) they are halved; the lookups of a single row need no sorting and leave in as many turns as it takes.
+        // One part for all rows of the unit as a rule.  If they have more lookups than fit the LDS (the sample undersized the
+        // bucket) they are cut; the lookups of a single row need no sorting and leave in as many turns as it takes.
         const uint32_t table_key = (uint32_t)uniform((int)a.row_base[t]);
         const uint32_t table_rows = (uint32_t)uniform((int)a.row_base[t + 1]) - table_key;
         const uint32_t first_row = unit_key - table_key;
         const uint32_t unit_rows = min(unit_last, table_rows - first_row - 1u) + 1u;
         uint32_t lo = 0, rows = unit_rows, heads = 0;             // the rows [lo, lo + rows) of the unit
-        int unit_start = 0, unit_m = 0;
+        int unit_start = 0, unit_m = 0, all = -1;
         while (lo < unit_rows) {
             const uint32_t row0 = first_row + lo, key0 = unit_key + lo;
             const uint32_t last = lo + rows == unit_rows ? unit_last - lo : rows - 1u;
@@ -1353,8 +1353,10 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sel
             const int m = __builtin_amdgcn_readlane((int)hits, kSortWaves - 1);
             const int next_slot = __builtin_amdgcn_readlane((int)hits, wave);
             const int first_slot = wave == 0 ? 0 : __builtin_amdgcn_readlane((int)hits, max(wave, 1) - 1);
+            if (all < 0)
+                all = m;
             if (m > kSelectCap && !single) {
-                rows = (rows + 1) / 2;
+                rows = select_fewer_rows(rows, m);
                 continue;
             }
             // put(slot, row offset, position) for each of them, in position order
@@ -1431,7 +1433,9 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sel
                 unit_start = start + from_slot;
             unit_m += to_slot - from_slot;
             lo += rows;
-            rows = unit_rows - lo;
+            if (unit_m == all)
+                break;
+            rows = select_next_rows(rows, m, unit_rows - lo, all - unit_m);
         }
         heads = last_lane(wave_scan_add(heads));
         if (lane == 0 && heads > 0)

@@ -43,6 +43,9 @@ int use_select_sort(int64_t tables, int64_t lookups) { return tbe::use_select_so
 
 int select_parts(int sampled, int lookups, int samples) { return tbe::select_parts((uint32_t)sampled, lookups, samples); }
 
+uint32_t select_fewer_rows(uint32_t rows, int found) { return tbe::select_fewer_rows(rows, found); }
+uint32_t select_next_rows(uint32_t rows, int found, uint32_t rest_rows, int rest) { return tbe::select_next_rows(rows, found, rest_rows, rest); }
+
 int sort_target(int64_t lookups) { return tbe::sort_target(lookups); }
 int64_t sort_buckets_max(int64_t lookups) { return tbe::sort_buckets_max(lookups); }
 

@@ -1,10 +1,10 @@
 """GPU parity of the sort whose units find their lookups themselves (calls of at most 2^18 lookups, 24,576 a table on average):
 sizes on both sides of its borders, tables of one bucket and of many, rows with more lookups than a workgroup's LDS holds
-positions (12,288), buckets that have to be halved, empty tables, and bags by the thousand.  Bit-exact."""
+positions (12,288), units that have to be cut because the sample missed their rows, empty tables, and bags by the thousand.  Bit-exact."""
 import numpy as np
 import pytest
 
-from test_gpu_sort_paths import _check, _lens
+from test_gpu_sort_paths import _check, _lens, _mix
 
 pytestmark = pytest.mark.gpu
 MEAN, MOST = 24_576, 1 << 18
@@ -71,16 +71,42 @@ def test_rows_of_several_units(gpu_device, case, order):
     _check(gpu_device, rows, batch, lens, np.concatenate(parts), case)
 
 
+CUT = {
+    # name: lookups that the sample misses: (first row, rows, lookups) each
+    "many_parts": [(0, 2000, 38_000)],
+    "last_part_is_a_row_beyond_the_lds": [(0, 1999, 20_000), (1999, 1, 18_000)],
+    "first_part_is_a_row_beyond_the_lds": [(0, 1, 18_000), (1, 1999, 20_000)],
+    "rows_beyond_the_lds_beside_each_other": [(0, 700, 5000), (700, 1, 12_289), (701, 1, 12_288), (702, 1298, 8000)],
+    "a_few_rows_of_a_wide_unit": [(1990, 10, 38_000)],
+    "just_fits": [(0, 2000, 6144)],
+    "just_too_many": [(0, 2000, 6145)],
+}
+
+
+@pytest.mark.parametrize("second", [False, True])                                  # the table's unit starts behind another table
 @pytest.mark.parametrize("rows,batch", [(300_000, 500), (40_000_000, 70_001)])     # words of 32 and of 64 bits
-def test_buckets_that_have_to_be_halved(gpu_device, rows, batch):
-    # lookups in stretches of 1024 of which the sample takes 16: every 64th is a row from 2000 on, and so may be all of the
-    # sample; the 2000 rows below share a bucket or two
+@pytest.mark.parametrize("case", sorted(CUT))
+def test_units_that_have_to_be_cut(gpu_device, case, rows, batch, second):
     rng = np.random.default_rng(3)
-    n = 24_000
-    idx = rng.integers(0, 2000, n)
-    idx[::3] = rng.integers(2000, rows, len(idx[::3]))
-    idx[n // 2:] = 7                                                               # one row: beyond the LDS by itself
-    _check(gpu_device, [rows], batch, _lens(rng, batch, n), idx, "halved")
+    n = 40_000
+    want = -(-n // 1024)
+    samples = 16 * want
+    stretch = (n << 32) // samples
+    at = np.array([min((stretch * (i * 256 + (_mix(i) & 255))) >> 40, n - 1) for i in range(samples)])
+    assert len(np.unique(at)) == samples
+    # the sample holds row 2000 often enough for it to be a border, and rows behind it
+    idx = rng.integers(2001, rows, n)
+    idx[at[:48]] = 2000
+    missed = np.concatenate([rng.integers(first, first + count, m) for first, count, m in CUT[case]])
+    idx[rng.permutation(np.setdiff1d(np.arange(n), at))[:missed.size]] = missed
+    # the plan's borders: row 0, every 16th sample, and the row behind one that fills a stretch of samples
+    sampled = np.sort(idx[at])[::16]
+    borders = np.unique(np.concatenate([[0], sampled[1:], sampled[:-1][sampled[:-1] == sampled[1:]] + 1]))
+    assert borders[1] == 2000 and np.count_nonzero(idx < 2000) == missed.size and (missed.size > 6144) == (case != "just_fits")
+    tables = [(rows, _lens(rng, batch, n), idx), (900, _lens(rng, batch, 5000), rng.integers(0, 900, 5000))]
+    heights, lens, parts = zip(*(tables[::-1] if second else tables))
+    print(f"{case} rows={rows} second={second}", flush=True)
+    _check(gpu_device, list(heights), batch, np.concatenate(lens), np.concatenate(parts), case)
 
 
 @pytest.mark.parametrize("n", [1 << 17, (1 << 17) + 1, 3 << 18, (3 << 18) + 1])

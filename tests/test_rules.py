@@ -192,6 +192,43 @@ def test_hot_rows_take_no_more_units_than_there_is_room_for(rules):
         assert sum(parts(int(k), n, samples) - 1 for k in of_rows) <= n // 4096
 
 
+def _parts_of_a_unit(rules, looked_up, rows):
+    """What sort_select_kernel does with a unit of `rows` rows: its parts as (first row, rows, lookups), and the walks."""
+    rules.select_fewer_rows.restype = rules.select_next_rows.restype = ctypes.c_uint32
+    at = np.sort(looked_up)
+    lo, size, walks, done, parts, total = 0, rows, 0, 0, [], None
+    while lo < rows:
+        m = int(np.searchsorted(at, lo + size) - np.searchsorted(at, lo))
+        walks += 1
+        total = m if total is None else total
+        if m > 6144 and size > 1:
+            size = rules.select_fewer_rows(ctypes.c_uint32(size), ctypes.c_int(m))
+            continue
+        parts.append((lo, size, m))
+        done += m
+        lo += size
+        if done == total:
+            break
+        size = rules.select_next_rows(ctypes.c_uint32(size), ctypes.c_int(m), ctypes.c_uint32(rows - lo), ctypes.c_int(total - done))
+    return parts, walks
+
+
+@pytest.mark.parametrize("rows", [2, 3, 7000, 1_000_000, (1 << 32) - 1])
+def test_a_unit_that_does_not_fit_is_cut_into_few_parts(rules, rows):
+    rng = np.random.default_rng(rows % 977)
+    n, few = 200_000, min(rows, 1000)
+    for looked_up in (rng.integers(0, few, n), rng.integers(rows - few, rows, n), rng.integers(0, rows, n), rng.integers(0, rows, 6145),
+                      rng.choice(min(rows, 1 << 20), few, replace=False)[rng.integers(0, few, n)],
+                      (rows * 2.0 ** -rng.integers(0, 33, n) * rng.random(n)).astype(np.int64),
+                      np.concatenate([np.full(7000, rows // 3), rng.integers(0, rows, 5000)])):
+        looked_up = np.minimum(looked_up, rows - 1)
+        parts, walks = _parts_of_a_unit(rules, looked_up, rows)
+        assert all(m <= 6144 or size == 1 for _, size, m in parts) and sum(m for *_, m in parts) == looked_up.size
+        assert all(a + size == b for (a, size, _), (b, *_) in zip(parts, parts[1:])) and parts[0][0] == 0
+        # down and up the rows once, and two walks a part
+        assert walks <= 2 * np.log2(rows) + 2 * (looked_up.size / 6144 + 1)
+
+
 def test_small_calls_sum_their_long_runs_in_at_most_32_trips(rules):
     small = lambda n, lanes: bool(rules.small_long_runs(ctypes.c_int64(n), ctypes.c_int(lanes)))
     assert small(512, 64) and not small(513, 64) and small(4096, 8) and not small(4097, 8) and small(8192, 4) and small(8192, 1)
