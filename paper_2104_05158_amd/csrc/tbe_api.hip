@@ -52,11 +52,13 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 constexpr int64_t kSortChunksWanted = 4096;
 constexpr int kSortTilesPerChunk = 4;
 // Lookups up to which a chunk is a quarter or half of a tile: the call has not tiles enough for the chip, and the workgroup of a
-// short one is done sooner.  Histogram, units, scatter with chunks of 8192 / 4096 / 2048: 1 table, 41,000 lookups 29 / 25 / 24 us,
+// short one is done sooner.  (One table of more than 2^18 would do as well with whole ones; the host does not know how many of a
+// call's lookups a table has.)  Histogram, units, scatter with chunks of 8192 / 4096 / 2048: 1 table, 41,000 lookups 29 / 25 / 24 us,
 // 0.49 M 37 / 40 / 47; 3 tables, 0.37 M 35 / 30 / 30; 8 tables, 0.65 M 37 / 32 / 31; 1.0 M 38 / 37 / 36; 64 tables, 2 M 37 / 35 / 39.
 constexpr int64_t kSortQuarterTiles = 1 << 17, kSortHalfTiles = 3 << 18;
-// Chunks of a call up to which sort_units_kernel adds all of them up itself: at most six trips, against a launch of 2 us
-// (8 tables, 0.65 M lookups: step of 347 us, 345 without it).
+// Tiles of a call up to which sort_units_kernel adds up all chunks itself, 16 a trip: at most six trips with chunks of a tile and
+// twelve with chunks of half of one (all lookups in one table), against a launch of 2 us (8 tables, 0.65 M lookups: step of
+// 347 us, 345 without it).
 constexpr int64_t kColumnsMin = 96;
 constexpr int kDenseGrid = 1024;  // persistent workgroups of dense_rows_kernel: 4 per CU, a multiple of 8
 constexpr int kWindowGrid = 1024;  // persistent workgroups of window_runs_kernel: 4 per CU, a multiple of 8 (by position

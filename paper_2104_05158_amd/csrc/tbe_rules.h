@@ -131,9 +131,9 @@ inline LongRunRule long_run_rule(int64_t lookups, int64_t batch, int64_t widest,
     return r;
 }
 
-// Whether the workgroups of the update kernel sum the long runs of a call of at most a tile of lookups themselves: one of four
-// wavefronts takes 16 rows of the widest table per lane group and trip, and the longest run there can be, all lookups of the call,
-// should take no more than 32 trips.
+// Whether the workgroups of the update kernel sum the long runs of a call of at most a tile of lookups themselves: the four
+// wavefronts of one take 16 rows of the widest table per lane group and trip together, four each, and the longest run there can be,
+// all lookups of the call, should take no more than 32 trips.
 constexpr int kSmallLongTrips = 32;
 
 // lanes: of a row of the widest table
@@ -213,9 +213,11 @@ inline int64_t sort_buckets_max(int64_t lookups) { return std::max<int64_t>(1, s
 // Samples per bucket of a table's plan.  A bucket's size spreads by 1/4 around the target with 16 of them; with 8, by 1/3, which
 // a target of at most 5/16 of a tile leaves room for where a workgroup would sort thousands of samples (1 table, 0.49 M lookups,
 // 480 buckets: plan of 31 us, 39 with 16).
+constexpr int kSamplesMax = 8192;
+
 TBE_BOTH int samples_per_bucket(int buckets, int target)
 {
-    const int room = 8192 / buckets;
+    const int room = kSamplesMax / buckets;
     const int want = target <= kSortTargetFew && buckets > 128 ? 8 : 16;
     return room < want ? room : want;
 }

@@ -43,6 +43,7 @@ constexpr int kSortThreads = 512;                 // 8 wavefronts
 constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kSortPerThread = 16;
 constexpr int kSortTile = kSortThreads * kSortPerThread;   // 8192 words: what a workgroup sorts in LDS
+static_assert(kSamplesMax <= kSortTile, "one workgroup sorts a table's samples");
 constexpr int kMaxBuckets = 1024;                 // per table
 constexpr int kMaxRangeCuts = 512;                // of those, bucket borders at multiples of the packed key range
 constexpr int kLutBits = 12;
@@ -1203,7 +1204,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
             a.unit_runs[u] = s_heads;
             atomicAdd(&a.table_runs[s_unit.t], s_heads);
         }
-        u = s_ticket;                                // (written two barriers ago)
+        u = s_ticket;                                // (written before the barrier above, at the latest)
     }
 }
 
@@ -1553,6 +1554,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, in
 constexpr int kRunThreads = 256;
 constexpr int kRunPer = 16;
 constexpr int kRunTile = kRunThreads * kRunPer;
+static_assert(kRunPer <= kSpanUnit, "a thread writes the first run of one span unit at most");
 __global__ __launch_bounds__(kRunThreads) void sort_runs_kernel(SortArgs a)
 {
     __shared__ uint32_t s_key[kRunTile];
