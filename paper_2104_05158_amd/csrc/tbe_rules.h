@@ -72,6 +72,8 @@ inline ForwardLaunch forward_launch(int64_t num_bags, int64_t lookups, int few, 
 // lookups 20 / 32 / 56 / 100; 128 columns, 0.65 M 142 / 144 / 151 / 157, 2 M in fp16 114 / 100 / 108 / 121, 6.2 M in 16 bits
 // 423 / 355 / 320 / 305; 256 columns, 1 M 157 / 165 / 178 / 200; 512, 4 M 625 / 631 / 641 / 644; 64, 1.2 M 65 / 52 / 48 / 53;
 // 16, 1 M 64 / 40 / 33 / 33; 8, 0.16 M 15 / 13 / 13 / 14.
+// The mean is over tables whatever their share of the lookups: seven tables of 8 columns with 25,000 each beside one of 512 with
+// 1000 take spans of 16, 22 us (64 with spans of 64 and long runs in launches of their own).
 constexpr int64_t kSpanWaves = 4096;
 
 // lanes: of a row, added up over the tables
