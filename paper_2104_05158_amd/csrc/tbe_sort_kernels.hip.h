@@ -491,12 +491,44 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         s_sum[tid] = 0;
     if (SELECT && tid == 0)
         s_hots = 0;
+    const TablePlan p = table_plan(a, n, rows);
+    // ---- a sample: one lookup from each of S equal stretches of the table's positions.  Requested before the tables before this
+    // one are counted: bound by the misses a CU has in flight (1000 samples 2 us, 7700 samples, of 2 M lookups, 23 of 45).
+    const int q = samples_per_bucket(p.want, a.target);
+    const int S = p.want * q;
+    const int groups = group_count<kSortGroup>(S), rounds = groups * kSortGroup;
+    uint32_t w[kSortPerThread];
+    const int prior = min(tid, t - 1);               // (of up to kSortThreads tables, requested before the sample)
+    int64_t prior_end = 0, prior_start = 0;
+    uint32_t prior_rows = 0;
+    if (t > 0) {
+        prior_end = a.offsets[(int64_t)(prior + 1) * a.B];
+        prior_start = a.offsets[(int64_t)prior * a.B];
+        prior_rows = a.row_base[prior + 1] - a.row_base[prior];
+    }
+    if (n > 0) {
+        const uint64_t stretch = ((uint64_t)n << 32) / (uint32_t)S;      // 32.32
+        const uint32_t* __restrict__ idx = a.indices + start;
+        const int first = wave * rounds * kWave + lane;
+#pragma unroll
+        for (int r = 0; r < kSortPerThread; r += kSortGroup)
+            if (r < rounds) {
+#pragma unroll
+                for (int x = 0; x < kSortGroup; ++x)
+                    w[r + x] = idx[sample_position(stretch, (uint32_t)min(first + (r + x) * kWave, S - 1), n)];
+            }
+    }
     __syncthreads();
     {   // what the tables before this one take
         uint32_t multi = 0, chunks = 0, parts = 0, units = 0;
         for (int i = tid; i < t; i += kSortThreads) {
-            const int n = (int)(a.offsets[(int64_t)(i + 1) * a.B] - a.offsets[(int64_t)i * a.B]);
-            const TablePlan p = table_plan(a, n, a.row_base[i + 1] - a.row_base[i]);
+            if (i >= kSortThreads) {
+                prior_end = a.offsets[(int64_t)(i + 1) * a.B];
+                prior_start = a.offsets[(int64_t)i * a.B];
+                prior_rows = a.row_base[i + 1] - a.row_base[i];
+            }
+            const int n = (int)(prior_end - prior_start);
+            const TablePlan p = table_plan(a, n, prior_rows);
             multi += p.chunks > a.col_chunks; chunks += p.chunks; parts += n > 0; units += p.units;
         }
         multi = last_lane(wave_scan_add(multi));
@@ -508,7 +540,6 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         }
     }
     __syncthreads();
-    const TablePlan p = table_plan(a, n, rows);
     SortTable st;
     st.start = start; st.n = n;
     st.pad = 0; st.chunk_base = (int)s_sum[1]; st.part = (int)s_sum[2];
@@ -546,18 +577,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         return;
     }
 
-    // ---- sorted sample: one lookup from each of S equal stretches of the table's positions
-    const int q = samples_per_bucket(p.want, a.target);
-    const int S = p.want * q;
-    uint32_t w[kSortPerThread];
-    const int groups = group_count<kSortGroup>(S), rounds = groups * kSortGroup;
-    const uint64_t stretch = ((uint64_t)n << 32) / (uint32_t)S;      // 32.32
+    // ---- sorted: past the sample the largest key, behind it
 #pragma unroll
-    for (int r = 0; r < kSortPerThread; ++r) {
-        const int pos = sample_position(stretch, (uint32_t)min(wave * rounds * kWave + r * kWave + lane, S - 1), n);
-        // past the sample: the largest key, sorted behind it
-        w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? min(a.indices[start + pos], rows - 1) : ~0u;
-    }
+    for (int r = 0; r < kSortPerThread; ++r)
+        w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? min(w[r], rows - 1) : ~0u;
     block_sort(w, groups, 0, bits, s_key, s_cnt, s_wsum);
     // ---- borders: row 0, every q-th sample once, and the row after one that fills a whole stretch of samples
     // (a bucket of its own).  Thread j owns candidates 2 j and 2 j + 1.
@@ -654,21 +677,39 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     }
     for (int i = tid; i < nb; i += kSortThreads)
         split[i] = s_list[i];
-    // ---- lookup table: the bucket of every cell's first row
+    // ---- lookup table: the bucket of every cell's first row, the last border at or before it.  A border counts in the
+    // first cell that starts at or behind it; the low halves add up to the buckets, the high ones count the borders that
+    // do not start their cell, which lie inside the one before.  (A bisection of the borders per cell took 2 to 9 us.)
     const int lut_bits = min(min(kLutBits, bits), ceil_log2((uint32_t)nb) + 3);
-    const int shift = bits - lut_bits;
-    uint16_t* lut = a.lut + (int64_t)st.part * kLutSize;
-    uint32_t span = 0;
-    for (int i = tid; i <= 1 << lut_bits; i += kSortThreads) {
-        const int lo = lds_lower(s_list, nb, ((uint32_t)i << shift) + 1u) - 1;
-        lut[i] = (uint16_t)lo;
-        if (i < 1 << lut_bits)
-            span = max(span, (uint32_t)(lds_lower(s_list, nb, (uint32_t)(i + 1) << shift) - 1 - lo));
-    }
-    span = last_lane(wave_scan_max(span));
+    const int shift = bits - lut_bits, cells = 1 << lut_bits;
+    uint32_t* s_cell = s_key;
+    static_assert((1 << kLutBits) < kSortTile && (1 << kLutBits) % kSortThreads == 0, "");
+    for (int i = tid; i <= cells; i += kSortThreads)
+        s_cell[i] = 0;
     if (tid == 0)
         s_sum[0] = 0;
     __syncthreads();
+    for (int i = tid; i < nb; i += kSortThreads) {
+        const uint32_t row = s_list[i], cell = (row >> shift) + ((row & ((1u << shift) - 1u)) != 0 ? 1u : 0u);
+        atomicAdd(&s_cell[cell], cell << shift == row ? 1u : 0x10001u);
+    }
+    __syncthreads();
+    uint16_t* lut = a.lut + (int64_t)st.part * kLutSize;
+    const int each = max(cells / kSortThreads, 1), c0 = tid * each;
+    uint32_t borders = 0;
+    if (c0 < cells)
+        for (int i = 0; i < each; ++i)
+            borders += s_cell[c0 + i] & 0xffffu;
+    uint32_t bucket = block_scan<kSortThreads>(borders, s_wsum, total) - 1u, span = 0;
+    if (c0 < cells)
+        for (int i = 0; i < each; ++i) {
+            bucket += s_cell[c0 + i] & 0xffffu;
+            lut[c0 + i] = (uint16_t)bucket;
+            span = max(span, s_cell[c0 + i + 1] >> 16);
+        }
+    if (tid == 0)
+        lut[cells] = (uint16_t)(nb - 1);
+    span = last_lane(wave_scan_max(span));
     if (lane == 0)
         atomicMax(&s_sum[0], span);
     __syncthreads();
