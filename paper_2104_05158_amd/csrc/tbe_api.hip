@@ -742,6 +742,7 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.lut = h->ws<uint16_t>(h->off_lut);
     a.bstart = h->ws<uint32_t>(h->off_bstart);
     a.hist = h->ws<uint32_t>(h->off_hist);
+    a.starts = reinterpret_cast<uint16_t*>(a.hist);
     a.multi = h->ws<int32_t>(h->off_multi);
     a.tile_bag = h->ws<int32_t>(h->off_tile_bag);
     a.unit_runs = h->ws<uint32_t>(h->off_unit_runs);
@@ -767,7 +768,8 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.target = ss.target;
     a.tiles_per_chunk = ss.tiles_per_chunk;
     a.chunk = ss.chunk;
-    a.select = 0;
+    a.lg_chunk = pow2ceil_log2(ss.chunk);
+    a.mode = use_select_sort(h->T, n) ? kSortSelect : use_pieces_sort(!ss.wide, n, ss.chunk) ? kSortPieces : kSortPartition;
     h->final_buf = 0;
     if (small) {
         ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
@@ -780,18 +782,29 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     }
     const int64_t chunk = ss.chunk;
     const unsigned chunk_grid = (unsigned)(ceil_div(n, chunk) + h->T);
-    const bool columns = n > kColumnsMin * std::max<int64_t>(chunk, kSortTile);
+    const bool columns = a.mode == kSortPartition && n > kColumnsMin * std::max<int64_t>(chunk, kSortTile);
     a.col_chunks = columns ? kColChunks : INT_MAX;
-    a.select = use_select_sort(h->T, n);
     {   // a2: samples, bucket borders and chunks
         ScopedTimer tm(h, SLOT_SORT_PLAN, st);
-        if (a.select)
-            hipLaunchKernelGGL(sort_plan_kernel<true>, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
+        auto plan = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a); };
+        if (a.mode == kSortSelect)
+            plan(sort_plan_kernel<kSortSelect>);
+        else if (a.mode == kSortPieces)
+            plan(sort_plan_kernel<kSortPieces>);
         else
-            hipLaunchKernelGGL(sort_plan_kernel<false>, dim3((unsigned)h->T), dim3(kSortThreads), 0, st, a);
+            plan(sort_plan_kernel<kSortPartition>);
         TBE_LAUNCH_CHECK(h, "sort_plan_kernel");
     }
-    if (a.select) {   // a3: units that find their lookups themselves
+    // a3: the partition and the sort of the buckets in LDS
+    auto partition = [&](auto scatter, auto local, int64_t resident) {
+        {
+            ScopedTimer tm(h, SLOT_SORT_SCATTER, st);
+            hipLaunchKernelGGL(scatter, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
+        }
+        ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
+        hipLaunchKernelGGL(local, dim3((unsigned)sort_local_blocks(n, h->T, ss.target, kSortTile, resident)), dim3(kSortThreads), 0, st, a);
+    };
+    if (a.mode == kSortSelect) {   // a3: units that find their lookups themselves
         ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
         static_assert(kSelectLookups / kSortTargetMin + kSelectLookups / kSelectPart <= kSortUnitsRound, "the workspace has room for the units");
         const dim3 grid((unsigned)std::min<int64_t>(n / ss.target + n / kSelectPart + 2 * (int64_t)h->T, 1024));
@@ -800,6 +813,10 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
         else
             hipLaunchKernelGGL(sort_select_kernel<uint32_t>, grid, dim3(kSortThreads), 0, st, a);
         TBE_LAUNCH_CHECK(h, "sort_select_kernel");
+    } else if (a.mode == kSortPieces) {   // (the words lie where the runs will be written)
+        a.words[0] = a.unique_keys;
+        partition(sort_scatter_kernel<uint32_t, true>, sort_local_kernel<uint32_t, true>, 256 * 3);
+        TBE_LAUNCH_CHECK(h, "sort_local_kernel");
     } else {
         {
             ScopedTimer tm(h, SLOT_SORT_HIST, st);
@@ -813,19 +830,10 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
             hipLaunchKernelGGL(sort_units_kernel, dim3((unsigned)h->T), dim3(kUnitsThreads), 0, st, a);
             TBE_LAUNCH_CHECK(h, "sort_units_kernel");
         }
-        // a3: the partition and the sort of the buckets in LDS
-        auto launch = [&](auto scatter, auto local, int per_cu) {
-            {
-                ScopedTimer tm(h, SLOT_SORT_SCATTER, st);
-                hipLaunchKernelGGL(scatter, dim3(chunk_grid), dim3(kSortThreads), 0, st, a);
-            }
-            ScopedTimer tm(h, SLOT_SORT_LOCAL, st);
-            hipLaunchKernelGGL(local, dim3(256 * per_cu), dim3(kSortThreads), 0, st, a);
-        };
         if (ss.wide)
-            launch(sort_scatter_kernel<uint64_t>, sort_local_kernel<uint64_t>, 2);
+            partition(sort_scatter_kernel<uint64_t, false>, sort_local_kernel<uint64_t, false>, 256 * 2);
         else
-            launch(sort_scatter_kernel<uint32_t>, sort_local_kernel<uint32_t>, 3);
+            partition(sort_scatter_kernel<uint32_t, false>, sort_local_kernel<uint32_t, false>, 256 * 3);
         TBE_LAUNCH_CHECK(h, "sort_local_kernel");
     }
     {   // a4: run heads -> unique keys, segment offsets, first run of every span unit

@@ -240,10 +240,12 @@ constexpr int64_t kSelectMean = 4 * kSelectCap, kSelectLookups = 1 << 18;
 constexpr int kSelectPart = 4096;
 constexpr int kSelectHot = (int)(kSelectLookups / kSelectPart);    // most rows with more than one
 
-TBE_BOTH int select_parts(uint32_t sampled, int lookups, int samples)
+TBE_BOTH int unit_parts(uint32_t sampled, int lookups, int samples, int part)
 {
-    return 1 + (int)(sampled * (uint32_t)lookups / (uint32_t)samples / (uint32_t)kSelectPart);
+    return 1 + (int)((uint64_t)sampled * (uint32_t)lookups / (uint32_t)samples / (uint32_t)part);
 }
+
+TBE_BOTH int select_parts(uint32_t sampled, int lookups, int samples) { return unit_parts(sampled, lookups, samples, kSelectPart); }
 
 // A unit whose lookups do not fit the LDS (its rows have more of them than the sample said) is taken in parts.  Rows to try
 // after `rows` turned out to have `found` lookups, too many, ...
@@ -263,6 +265,29 @@ TBE_BOTH uint32_t select_next_rows(uint32_t rows, int found, uint32_t rest_rows,
 }
 
 inline bool use_select_sort(int64_t tables, int64_t lookups) { return lookups <= kSelectLookups && lookups <= kSelectMean * tables; }
+
+// Other calls of 32-bit words, up to kPiecesMax chunks: every chunk's words are put in order of their buckets where they lie and a
+// unit collects its piece of each chunk of its table, where the partition of larger ones counts first (histogram, starts, units).
+// Sort, us, uniform / Zipf 1.05 indices, counted -> collected: 1 table, 40,000 lookups 39 / 39 -> 32 / 32, 0.6 M 70 / 65 -> 54 / 61; 8
+// tables, 0.66 M 48 / 47 -> 42 / 42; 16, 2.6 M 95 / 93 -> 77 / 78; 64, 2 M 73 / 69 -> 64 / 61, 6.2 M 124 / 118 -> 113 / 109, 8 M 140 /
+// 137 -> 133 / 129; 600, 2 M 105 / 103 -> 81 / 78; 16, of which one has 4 M, 140 / 145 -> 133 / 146; 64, one 8 M 234 / 252 -> 209 /
+// 231.  Beyond, a table's units read the starts of hundreds of chunks for pieces of a few words (64 tables, 19 M lookups: the
+// units 208 us, 119 and 55 for the count).  kPiecesMax is also what a workgroup holds of them in LDS.
+constexpr int kPiecesMax = 1024;
+
+inline bool use_pieces_sort(bool words32, int64_t lookups, int chunk) { return words32 && lookups <= (int64_t)kPiecesMax * chunk; }
+
+// Workgroups of the bucket sort: one per unit there can be (and no fewer than are resident: tables cut by the packed range have
+// more units) while those are at most kUnitsDispatched, otherwise as many as are resident, which take the units one by one.  An atomic on one word and a descriptor wait in front of every unit (with 768 workgroups, us, ->
+// one each: 64 tables, 2 M lookups 74 -> 64, 8 M 139 -> 133, 20 M 286 -> 283), but a workgroup's start costs more once there
+// are tens of thousands (128 tables, 100 M lookups 1285 -> 1319).
+constexpr int64_t kUnitsDispatched = 8192;
+
+inline int64_t sort_local_blocks(int64_t lookups, int64_t tables, int target, int tile, int64_t resident)
+{
+    const int64_t units = lookups / target + lookups / tile + 2 * tables;
+    return units <= kUnitsDispatched ? std::max(units, resident) : resident;
+}
 
 // A published integer hash: lowbias32 of Wellons' hash-prospector (public domain).
 TBE_BOTH uint32_t mix_bits(uint32_t x)

@@ -19,8 +19,9 @@
 //   sort_local_kernel    one workgroup per unit: sorts the words in LDS, writes keys and payloads, counts the runs
 //   sort_runs_kernel     bucket borders are run borders, so a unit's runs start at a known index: unique_keys,
 //                        seg_offsets, and the first run of every span unit
-// A call of some 100,000 lookups leaves out histogram, units and partition: sort_select_kernel sorts units that it finds
-// itself (use_select_sort).  One of at most kSortTile lookups is sorted by (table, row) at once, by one workgroup
+// A call of up to 8 M lookups leaves out histogram, columns and units: its chunks are put in order of their buckets where they
+// lie, and a unit collects its piece of each (use_pieces_sort).  One of some 100,000 leaves out the partition, too:
+// sort_select_kernel sorts units that it finds itself (use_select_sort).  One of at most kSortTile lookups is sorted by (table, row) at once, by one workgroup
 // (sort_small_kernel).
 //
 // (The runs' first index could also come from a look-back over the units' counts inside sort_local_kernel; at
@@ -74,14 +75,21 @@ struct SortUnit {        // 32 bytes
     int32_t start, m;    // positions
     uint32_t key0;       // linear row id that row offset 0 stands for
     int32_t bits;        // bits of the row offsets to sort
-    int32_t t;
-    int32_t flags;
+    uint16_t t, bucket;  // (bucket: pieces)
+    int32_t flags;       // kUnit...; the part's number in the bits from 8 on
     int32_t first;       // the table's first unit (they are numbered one after the other)
-    uint32_t last;       // sort_select_kernel: offset of the unit's last row from key0 (of the last unit: of any index)
+    uint32_t last;       // select: offset of the unit's last row from key0 (of the last unit: of any index); pieces: the table's first chunk
 };
+static_assert(sizeof(SortUnit) == 32 && kManyTables <= 65536, "");
 constexpr int kUnitContinued = 1;     // further part of a one-row bucket: its first lookup starts no run
-constexpr int kUnitMore = 4;          // sort_select_kernel: further parts follow; the part's number is in the bits from 8 on
-constexpr int kUnitNone = 2;          // no bucket (sort_select_kernel; until then start, m of its units are those of the table)
+constexpr int kUnitNone = 2;          // (select, pieces) no bucket; until the unit is sorted its start and m are those of the table
+constexpr int kUnitMore = 4;          // (select, pieces) further parts follow
+
+// How the lookups come to their units: by a partition with known places (histogram, units, scatter), every unit finding its
+// own among all of the table's (use_select_sort), or every chunk sorted by bucket where it lies and the units collecting
+// their piece of each (use_pieces_sort).
+enum SortMode { kSortPartition, kSortSelect, kSortPieces };
+constexpr int kPieceStarts = kMaxBuckets + 8;     // first positions of the buckets in a chunk, as many words of 16 bits
 
 struct SortArgs {
     const int64_t* offsets;
@@ -95,6 +103,7 @@ struct SortArgs {
     uint16_t* lut;           // [parts][kLutSize] bucket of the first row of every cell of rows (and of the row past the last)
     uint32_t* bstart;        // [parts][kMaxBuckets] lookups, then first position of every bucket
     uint32_t* hist;          // [chunks][kMaxBuckets]
+    uint16_t* starts;        // [chunks][kPieceStarts] (pieces; in the memory of hist)
     int32_t* multi;          // tables of more than col_chunks chunks
     int32_t* tile_bag;       // [chunks * tiles_per_chunk] bag of the first position of every tile
     uint32_t* unit_runs;     // [slots] runs of every unit
@@ -112,10 +121,11 @@ struct SortArgs {
     int32_t vb;              // bits of the bag number in a word
     int32_t kb;              // bits left for the row offset
     int32_t target;          // lookups per bucket
+    int32_t lg_chunk;        // (pieces: a chunk is a power of two)
     int32_t chunk;           // positions of a chunk: tiles_per_chunk tiles, or in a small call less than one
     int32_t tiles_per_chunk;
     int32_t col_chunks;      // chunks of a table up to which sort_units_kernel adds them up itself
-    int32_t select;          // the units are filled by sort_select_kernel
+    int32_t mode;            // SortMode
 };
 
 // ---------------------------------------------------------------- wavefront and workgroup primitives
@@ -399,27 +409,13 @@ __device__ __forceinline__ void block_sort(W (&w)[PER], int groups, int shift, i
     }
 }
 
-// Bags of the positions [first, first + m) of a table (offsets: its B + 1 bag borders; bags lo..hi are the ones
-// that can hold them): every bag that is not empty marks its first position, and a position's bag is the largest
-// mark at or before it, for position p = wavefront * rounds * 64 + r * 64 + lane
-//     max(s_mark[p], returned carry of the wavefront) - 1.
-// s_mark: rounds * kSortThreads words of LDS, rounds a multiple of 2.  Barriers inside, the last one before the
-// caller may read.
-__device__ __forceinline__ uint32_t bags_of_positions(const int64_t* __restrict__ offsets, int lo, int hi, int first, int m,
-                                                      int rounds, uint32_t* s_mark, uint32_t* s_wsum)
+// Makes every mark the largest at or before it in its wavefront's stretch, position p = wavefront * rounds * 64 + r * 64 +
+// lane, and returns the largest before the stretch.  Two barriers, the last one before the caller may read.
+__device__ __forceinline__ uint32_t carry_marks(int rounds, uint32_t* s_mark, uint32_t* s_wsum)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x >> 6;
     const int p0 = wave * rounds * kWave + lane;
-    for (int i = threadIdx.x; i < rounds * (kSortThreads / 4); i += kSortThreads)
-        reinterpret_cast<uint4*>(s_mark)[i] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-    for (int i = lo + (int)threadIdx.x; i <= hi; i += kSortThreads) {
-        const int o = (int)offsets[i], e = (int)offsets[i + 1];
-        const int p = max(o - first, 0);
-        if (e > o && e > first && p < m)
-            s_mark[p] = (uint32_t)i + 1u;
-    }
     __syncthreads();
     uint32_t top = 0;
     for (int r = 0; r < rounds; r += 2) {
@@ -439,21 +435,45 @@ __device__ __forceinline__ uint32_t bags_of_positions(const int64_t* __restrict_
     return carry;
 }
 
+// Bags of the positions [first, first + m) of a table (offsets: its B + 1 bag borders; bags lo..hi are the ones
+// that can hold them): every bag that is not empty marks its first position, and a position's bag is the largest
+// mark at or before it, for position p = wavefront * rounds * 64 + r * 64 + lane
+//     max(s_mark[p], returned carry of the wavefront) - 1.
+// s_mark: rounds * kSortThreads words of LDS, rounds a multiple of 2.  Barriers inside, the last one before the
+// caller may read.
+__device__ __forceinline__ uint32_t bags_of_positions(const int64_t* __restrict__ offsets, int lo, int hi, int first, int m,
+                                                      int rounds, uint32_t* s_mark, uint32_t* s_wsum)
+{
+    for (int i = threadIdx.x; i < rounds * (kSortThreads / 4); i += kSortThreads)
+        reinterpret_cast<uint4*>(s_mark)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    for (int i = lo + (int)threadIdx.x; i <= hi; i += kSortThreads) {
+        const int o = (int)offsets[i], e = (int)offsets[i + 1];
+        const int p = max(o - first, 0);
+        if (e > o && e > first && p < m)
+            s_mark[p] = (uint32_t)i + 1u;
+    }
+    return carry_marks(rounds, s_mark, s_wsum);
+}
+
 // ---------------------------------------------------------------- plan
 
 struct TablePlan {
     int want, cuts;      // buckets asked for, ranges of the packed key
     int chunks;
-    int units;           // select: most there can be, of all buckets and rows of several units
+    int units;           // select, pieces: most there can be, of all buckets and rows of several units
 };
+
+// lookups of a unit of a row that has several
+__device__ __forceinline__ int unit_part(int mode) { return mode == kSortSelect ? kSelectPart : kSortTile; }
 
 __device__ __forceinline__ TablePlan table_plan(const SortArgs& a, int n, uint32_t rows)
 {
     TablePlan p;
     p.cuts = a.kb >= 31 ? 1 : (int)((rows + (1u << a.kb) - 1) >> a.kb);
     p.want = min(max((n + a.target - 1) / a.target, 1), kMaxBuckets - p.cuts);
-    p.chunks = n == 0 || a.select ? 0 : (n + a.chunk - 1) / a.chunk;
-    p.units = n == 0 || !a.select ? 0 : p.want + p.cuts - 1 + n / kSelectPart;
+    p.chunks = n == 0 || a.mode == kSortSelect ? 0 : (n + a.chunk - 1) / a.chunk;
+    p.units = n == 0 || a.mode == kSortPartition ? 0 : p.want + p.cuts - 1 + n / unit_part(a.mode);
     return p;
 }
 
@@ -471,16 +491,15 @@ __device__ __forceinline__ int lds_lower(const uint32_t* p, int n, uint32_t v)
     return lo;
 }
 
-// SELECT: a.select (in one kernel the partition's plan took 0.3 us longer)
-template <bool SELECT>
+// MODE: a.mode (in one kernel the partition's plan took 0.3 us longer)
+template <int MODE>
 __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
 {
     __shared__ __align__(16) uint32_t s_key[kSortTile];
     __shared__ __align__(16) uint16_t s_cnt[kSortWaves][1024];     // (samples are few: two passes of ten bits)
     __shared__ uint32_t s_list[kMaxBuckets + 2], s_cut[kMaxRangeCuts];
-    __shared__ uint32_t s_hot[kSelectHot], s_more[kSelectHot], s_hots;    // (select) rows of several units, and how many more each has
     __shared__ uint32_t s_wsum[kSortWaves];
-    __shared__ uint32_t s_sum[4];
+    __shared__ uint32_t s_sum[4], s_hot;             // (s_hot: a row may have several units)
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int t = blockIdx.x;
     const int64_t o0 = a.offsets[(int64_t)t * a.B], o1 = a.offsets[(int64_t)(t + 1) * a.B];
@@ -489,8 +508,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     const int bits = a.meta[t].key_bits;
     if (tid < 4)
         s_sum[tid] = 0;
-    if (SELECT && tid == 0)
-        s_hots = 0;
+    if (tid == 0)
+        s_hot = 0;
     const TablePlan p = table_plan(a, n, rows);
     // ---- a sample: one lookup from each of S equal stretches of the table's positions.  Requested before the tables before this
     // one are counted: bound by the misses a CU has in flight (1000 samples 2 us, 7700 samples, of 2 M lookups, 23 of 45).
@@ -571,9 +590,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             a.tables[t] = st;
         return;
     }
-    if (SELECT && p.units == 1) {                              // (select) one bucket
+    if (MODE == kSortSelect && p.units == 1) {                 // one bucket
         if (tid == 0)
-            a.units[s_sum[3]] = SortUnit{start, n, rbase, ceil_log2(rows), t, 0, (int32_t)s_sum[3], ~0u};
+            a.units[s_sum[3]] = SortUnit{start, n, rbase, ceil_log2(rows), (uint16_t)t, 0, 0, (int32_t)s_sum[3], ~0u};
         return;
     }
 
@@ -585,7 +604,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     // ---- borders: row 0, every q-th sample once, and the row after one that fills a whole stretch of samples
     // (a bucket of its own).  Thread j owns candidates 2 j and 2 j + 1.
     uint32_t cand[2], emit[2];
-    const int part_samples = (int)((int64_t)kSelectPart * S / n);      // (that many hold lookups for a unit more)
+    const int part = unit_part(MODE);
+    const int part_samples = (int)((uint32_t)part * (uint32_t)S / (uint32_t)n);      // so many hold lookups for a unit more
+    static_assert((int64_t)kSortTile * kSamplesMax < (int64_t)1 << 32, "");
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int j = 2 * tid + k;
@@ -597,15 +618,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             const bool fresh = j == 0 || c != before;
             cand[k] = c;
             emit[k] = fresh ? (j + 1 < p.want && s_key[(j + 1) * q] == c ? 2u : 1u) : 0u;
-            if (SELECT && emit[k] > 1 && s_key[min(j * q + part_samples, S) - 1] == c) {
-                const uint32_t sampled = (uint32_t)lds_lower(s_key + j * q, S - j * q, c + 1u);
-                const uint32_t more = (uint32_t)select_parts(sampled, n, S) - 1u;
-                if (more > 0) {
-                    const uint32_t i = atomicAdd(&s_hots, 1u);
-                    s_hot[i] = c;
-                    s_more[i] = more;
-                }
-            }
+            if (MODE != kSortPartition && emit[k] > 1 && s_key[min(j * q + part_samples, S) - 1] == c)
+                s_hot = 1;
         }
     }
     uint32_t total;
@@ -619,7 +633,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         at += emit[k];
     }
     __syncthreads();
-    // distinct borders below the number of rows, into s_key
+    // distinct borders below the number of rows
+    uint32_t* s_uniq = reinterpret_cast<uint32_t*>(&s_cnt[0][0]);      // (the counters are done with)
     const int n_list = (int)total;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
@@ -630,7 +645,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
 #pragma unroll
     for (int k = 0; k < 2; ++k)
         if (emit[k])
-            s_key[at++] = s_list[2 * tid + k];
+            s_uniq[at++] = s_list[2 * tid + k];
     const int na = (int)total;
     __syncthreads();
     // multiples of the packed key range that are no border yet (cuts <= kMaxRangeCuts = kSortThreads)
@@ -638,8 +653,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     bool keep = false;
     if (tid >= 1 && tid < p.cuts) {
         cut = (uint32_t)tid << a.kb;
-        const int i = lds_lower(s_key, na, cut);
-        keep = i == na || s_key[i] != cut;
+        const int i = lds_lower(s_uniq, na, cut);
+        keep = i == na || s_uniq[i] != cut;
     }
     at = block_scan<kSortThreads>(keep ? 1u : 0u, s_wsum, total);
     if (keep)
@@ -648,32 +663,46 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
     __syncthreads();
     uint32_t* split = a.split + (int64_t)st.part * kMaxBuckets;
     if (keep)
-        s_list[at + lds_lower(s_key, na, cut)] = cut;
+        s_list[at + lds_lower(s_uniq, na, cut)] = cut;
     for (int i = tid; i < na; i += kSortThreads)
-        s_list[i + lds_lower(s_cut, nc, s_key[i])] = s_key[i];
+        s_list[i + lds_lower(s_cut, nc, s_uniq[i])] = s_uniq[i];
     const int nb = na + nc;
     __syncthreads();
-    if (SELECT) {
-        const int hots = (int)s_hots;
-        for (int i = tid; i < nb; i += kSortThreads) {                     // (an index that is no row of the table is the last bucket's)
-            const uint32_t lo = s_list[i], hi = i + 1 < nb ? s_list[i + 1] : rows;
-            uint32_t more = 0, at = s_sum[3] + (uint32_t)i;
-            for (int k = 0; k < hots; ++k) {
-                at += s_hot[k] < lo ? s_more[k] : 0u;
-                more += s_hot[k] == lo ? s_more[k] : 0u;
-            }
-            SortUnit u{start, n, rbase + lo, ceil_log2(hi - lo), t, 0, (int32_t)s_sum[3], i + 1 < nb ? hi - lo - 1u : ~0u - lo};
-            for (uint32_t k = 0; k <= more; ++k) {
-                u.flags = (int32_t)(k << 8) | (k < more ? kUnitMore : 0);
-                a.units[at + k] = u;
+    if (MODE != kSortPartition) {
+        // ---- units: one per bucket, and for a bucket of one row as many as its samples say it has lookups for
+        uint32_t lo[2], hi[2], parts[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int i = 2 * tid + k;
+            lo[k] = hi[k] = 0;
+            parts[k] = 0;
+            if (i < nb) {
+                lo[k] = s_list[i];
+                hi[k] = i + 1 < nb ? s_list[i + 1] : rows;
+                parts[k] = 1;
+                if (s_hot && hi[k] - lo[k] == 1) {
+                    const int before = lds_lower(s_key, S, lo[k]);
+                    parts[k] = (uint32_t)unit_parts((uint32_t)lds_lower(s_key + before, S - before, hi[k]), n, S, part);
+                }
             }
         }
-        int used = nb;
-        for (int k = 0; k < hots; ++k)
-            used += (int)s_more[k];
-        for (int i = used + tid; i < p.units; i += kSortThreads)
-            a.units[s_sum[3] + i] = SortUnit{start, n, 0, 0, t, kUnitNone, (int32_t)s_sum[3], 0};
-        return;
+        at = s_sum[3] + block_scan<kSortThreads>(parts[0] + parts[1], s_wsum, total);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int i = 2 * tid + k;
+            SortUnit u{start, n, rbase + lo[k], ceil_log2(hi[k] - lo[k]), (uint16_t)t, (uint16_t)i, 0, (int32_t)s_sum[3], 0};
+            // (an index that is no row of the table is the last bucket's)
+            u.last = MODE == kSortPieces ? (uint32_t)st.chunk_base : i + 1 < nb ? hi[k] - lo[k] - 1u : ~0u - lo[k];
+            for (uint32_t j = 0; j < parts[k]; ++j) {
+                u.flags = (int32_t)(j << 8) | (j + 1 < parts[k] ? kUnitMore : 0);
+                a.units[at++] = u;
+            }
+        }
+        for (int i = (int)total + tid; i < p.units; i += kSortThreads)
+            a.units[s_sum[3] + i] = SortUnit{start, n, 0, 0, (uint16_t)t, 0, kUnitNone, (int32_t)s_sum[3], (uint32_t)st.chunk_base};
+        if (MODE == kSortSelect)
+            return;
+        __syncthreads();                             // (the samples make room for the cells)
     }
     for (int i = tid; i < nb; i += kSortThreads)
         split[i] = s_list[i];
@@ -929,7 +958,8 @@ __global__ __launch_bounds__(kUnitsThreads) void sort_units_kernel(SortArgs a)
     SortUnit u;
     u.key0 = a.row_base[t] + lo;
     u.bits = ceil_log2(range);
-    u.t = t;
+    u.t = (uint16_t)t;
+    u.bucket = (uint16_t)d;
     u.first = (int32_t)s_first;
     u.last = 0;
     for (uint32_t i = 0; i < pieces; ++i) {
@@ -940,14 +970,18 @@ __global__ __launch_bounds__(kUnitsThreads) void sort_units_kernel(SortArgs a)
     }
 }
 
-template <typename W>
+// PIECES (a.mode is kSortPieces): the words stay where the chunk's lookups lie, in order of their buckets, and the buckets' first
+// positions in it are written down.  A chunk is a chain of trips and barriers (4096 lookups 9.4 us: descriptors 1.3, borders and
+// lookups 1.3, the bags of its ends 1.0, of all positions 1.3, buckets 1.4, ranks 2.2, order and writing 1.1).
+template <typename W, bool PIECES>
 __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_scatter_kernel(SortArgs a)
 {
     __shared__ __align__(16) W s_w[kSortTile];
     // digit counters while ranking, then the digits of the reordered words
     __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kMaxBuckets];
     static_assert(kSortWaves * kMaxBuckets == kSortTile, "the digits of a tile replace its counters");
-    __shared__ uint32_t s_next[kMaxBuckets], s_delta[kMaxBuckets];
+    __shared__ uint32_t s_next[PIECES ? 1 : kMaxBuckets], s_delta[PIECES ? 1 : kMaxBuckets];
+    __shared__ int s_bag[2];
     __shared__ Borders s_borders;
     __shared__ uint32_t s_wsum[kSortWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = uniform(tid >> 6);
@@ -981,20 +1015,35 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
     };
     load_rows(c.first);
     s_borders.load(a, st, bits);
-    for (int i = tid; i < st.nb; i += kSortThreads)
-        s_next[i] = a.bstart[(int64_t)st.part * kMaxBuckets + i] + a.hist[(int64_t)blockIdx.x * kMaxBuckets + i];
+    if constexpr (PIECES) {                          // bags of the chunk's first and last position
+        if (wave < 2) {
+            const int b = wave_upper(offsets, a.B, wave == 0 ? c.first : end - 1);
+            if (lane == 0)
+                s_bag[wave] = b;
+        }
+        __syncthreads();
+    } else {
+        for (int i = tid; i < st.nb; i += kSortThreads)
+            s_next[i] = a.bstart[(int64_t)st.part * kMaxBuckets + i] + a.hist[(int64_t)blockIdx.x * kMaxBuckets + i];
+    }
 
     for (int k = 0; c.first + k * kSortTile < end; ++k) {
         const int first = c.first + k * kSortTile;
         const int m = min(kSortTile, end - first);
         const int groups = group_count<kPartGroup>(m), rounds = groups * kPartGroup;
         const int p0 = wave * rounds * kWave + lane;
-        const int lo = a.tile_bag[(int)blockIdx.x * a.tiles_per_chunk + k];
-        // the next tile's first bag bounds this one's; the last tile of a chunk looks at the next chunk's first tile
-        const bool more = first + m < st.start + st.n;
-        const int hi = more ? a.tile_bag[first + m < end ? (int)blockIdx.x * a.tiles_per_chunk + k + 1
-                                                         : ((int)blockIdx.x + 1) * a.tiles_per_chunk]
-                            : a.B - 1;
+        int lo, hi;
+        if constexpr (PIECES) {
+            lo = s_bag[0];
+            hi = s_bag[1];
+        } else {
+            lo = a.tile_bag[(int)blockIdx.x * a.tiles_per_chunk + k];
+            // the next tile's first bag bounds this one's; the last tile of a chunk looks at the next chunk's first tile
+            const bool more = first + m < st.start + st.n;
+            hi = more ? a.tile_bag[first + m < end ? (int)blockIdx.x * a.tiles_per_chunk + k + 1
+                                                   : ((int)blockIdx.x + 1) * a.tiles_per_chunk]
+                      : a.B - 1;
+        }
         const uint32_t carry = bags_of_positions(offsets, lo, hi, first, m, rounds, reinterpret_cast<uint32_t*>(s_w), s_wsum);
         zero_counts(s_cnt);
         W w[kSortPerThread];
@@ -1024,13 +1073,18 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
         __syncthreads();
         uint32_t counts;
         const uint32_t starts = digit_starts<kMaxBuckets>(s_cnt, s_wsum, counts);
+        if constexpr (PIECES) {
+            if (2 * tid <= st.nb)                     // (bucket nb starts behind the last word)
+                reinterpret_cast<uint32_t*>(a.starts + (int64_t)blockIdx.x * kPieceStarts)[tid] = starts;
+        } else {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int d = 2 * tid + i;
-            if (d < st.nb) {
-                const uint32_t nx = s_next[d];
-                s_delta[d] = nx - (i ? starts >> 16 : starts & 0xffffu);
-                s_next[d] = nx + (i ? counts >> 16 : counts & 0xffffu);
+            for (int i = 0; i < 2; ++i) {
+                const int d = 2 * tid + i;
+                if (d < st.nb) {
+                    const uint32_t nx = s_next[d];
+                    s_delta[d] = nx - (i ? starts >> 16 : starts & 0xffffu);
+                    s_next[d] = nx + (i ? counts >> 16 : counts & 0xffffu);
+                }
             }
         }
         __syncthreads();
@@ -1041,17 +1095,26 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
                 for (int r = r0; r < r0 + kPartGroup; ++r)
                     rank[r] += s_cnt[wave][dg[r]];    // slot of the word in the reordered tile
             }
-        __syncthreads();                              // the counters become the slots' digits
+        if constexpr (!PIECES)
+            __syncthreads();                          // the counters become the slots' digits
 #pragma unroll
         for (int r0 = 0; r0 < kSortPerThread; r0 += kPartGroup)
             if (r0 < rounds) {
 #pragma unroll
                 for (int r = r0; r < r0 + kPartGroup; ++r) {
                     s_w[rank[r]] = w[r];
-                    s_dig[rank[r]] = (uint16_t)dg[r];
+                    if constexpr (!PIECES)
+                        s_dig[rank[r]] = (uint16_t)dg[r];
                 }
             }
         __syncthreads();
+        if constexpr (PIECES) {
+#pragma unroll
+            for (int i = 0; i < kSortPerThread; ++i)
+                if (i * kSortThreads + tid < m)
+                    out[first + i * kSortThreads + tid] = s_w[i * kSortThreads + tid];
+            return;                                   // a chunk is one tile
+        }
         if (first + m < end)
             load_rows(first + m);                     // in flight while this tile is written
         // the words of a bucket are written together; four at a time so that the LDS reads overlap
@@ -1080,9 +1143,20 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
 
 // One workgroup per unit.  A unit of more than kSortTile words -- a bucket the sample undersized, or of a table with
 // more than kMaxBuckets * kSortTile lookups -- takes the same passes tile by tile through global memory.
-template <typename W>
+//
+// PIECES (a.mode is kSortPieces): the unit's words are collected first, its piece of every chunk of the table in turn.  Where the
+// pieces start says how many lookups of the table go before the unit: no histogram, no second walk over the indices.  A unit
+// that does not fit is collected in memory, where its keys will be.  8 tables, 0.66 M lookups: 16.7 us instead of 14.7, for 9.1
+// of the histogram and 6.0 of the units; 64 tables, 6.2 M: 62 instead of 49, for 27 (the words of a unit are collected four a
+// thread at a time: with eight, registers spill and every reload is a trip to memory, 22 us instead of 16.7).
+constexpr int kCollect = 4;
+
+template <typename W, bool PIECES>
 __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_local_kernel(SortArgs a)
 {
+    static_assert(!PIECES || sizeof(W) == 4, "a unit is collected where its keys go");
+    __shared__ uint32_t s_slot[PIECES ? kPiecesMax : 1];           // first slot of every chunk's piece in the unit ...
+    __shared__ uint32_t s_from[PIECES ? kPiecesMax : 1];           // ... and where slot 0 would lie if all of the unit lay there
     __shared__ __align__(16) W s_w[kSortTile];
     __shared__ __align__(16) uint16_t s_cnt[kSortWaves][kLocalDigits];
     __shared__ uint32_t s_run[kLocalDigits];         // units larger than a tile: next slot of every digit
@@ -1099,19 +1173,119 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
     const bool tickets = total_units > (int)gridDim.x;
     for (int u = blockIdx.x; u < total_units;) {
         __syncthreads();
-        if (tid < 8)
-            reinterpret_cast<int*>(&s_unit)[tid] = reinterpret_cast<const int*>(&a.units[u])[tid];
+        if (tid < 8) {
+            const int i = opaque(tid);
+            reinterpret_cast<int*>(&s_unit)[i] = reinterpret_cast<const int*>(&a.units[u])[i];
+        }
         if (tid == 0)
             s_heads = 0;
         __syncthreads();
         if (tid == 0)
             s_ticket = tickets ? (int)(gridDim.x + atomicAdd(&a.counters->sort_ticket, 1u)) : total_units;
-        const int start = uniform(s_unit.start), m_all = uniform(s_unit.m), bits = uniform(s_unit.bits);
+        int start = uniform(s_unit.start), m_all = uniform(s_unit.m);
+        const int bits = uniform(s_unit.bits);
         const uint32_t key0 = (uint32_t)uniform((int)s_unit.key0);
-        const bool large = m_all > kSortTile;
+        bool large = m_all > kSortTile;
+        int from_slot = 0;                           // (PIECES) first of the unit's slots, not 0 for a further part of a row
+        const W* pieces = static_cast<const W*>(a.words[0]);
+        if constexpr (PIECES) {
+            const int table_start = start, flags = uniform(s_unit.flags);
+            const int nchunks = flags & kUnitNone ? 0 : (m_all + a.chunk - 1) >> a.lg_chunk;
+            const uint16_t* starts = a.starts + (int64_t)uniform((int)s_unit.last) * kPieceStarts + uniform((int)s_unit.bucket);
+            uint32_t before = 0, slots = 0;
+            for (int c0 = 0; c0 < nchunks; c0 += kSortThreads) {
+                // (up to 64 chunks: every wavefront for itself)
+                const bool few = nchunks <= kWave;
+                const int c = few ? lane : c0 + tid;
+                uint32_t s = 0, e = 0, sum;
+                if (c < nchunks) {
+                    s = starts[(int64_t)c * kPieceStarts];
+                    e = starts[(int64_t)c * kPieceStarts + 1];
+                }
+                uint32_t slot = slots;
+                if (few) {
+                    const uint32_t incl = wave_scan_add(e - s);
+                    slot = incl - (e - s);
+                    sum = last_lane(incl);
+                    before = last_lane(wave_scan_add(s));
+                } else {
+                    uint32_t ahead;
+                    slot += block_scan<kSortThreads>(e - s, s_wsum, sum);
+                    __syncthreads();
+                    (void)block_scan<kSortThreads>(s, s_wsum, ahead);
+                    __syncthreads();
+                    before += ahead;
+                }
+                slots += sum;
+                if (c < nchunks && (!few || wave == 0)) {
+                    s_slot[c] = slot;
+                    s_from[c] = (uint32_t)(table_start + c * a.chunk) + s - slot;
+                }
+            }
+            __syncthreads();
+            start = table_start + uniform((int)before);
+            m_all = uniform((int)slots);
+            if (bits == 0) {                         // of a row with several units this one's part, the last takes the rest
+                const int part = flags >> 8;
+                from_slot = min(part * kSortTile, m_all);
+                m_all = (flags & kUnitMore ? min((part + 1) * kSortTile, m_all) : m_all) - from_slot;
+                start += from_slot;
+            }
+            large = m_all > kSortTile;
+            // The words go to LDS, those of a unit that does not fit where its keys will be.  A wavefront has a stretch of the
+            // slots and walks the chunks that have them, the next 64 in its lanes.
+#pragma unroll 1
+            for (int first = 0; first < m_all; first += kSortTile) {
+                const int m = min(kSortTile, m_all - first), rounds = group_count<kSortGroup>(m) * kSortGroup;
+                const int q = wave * rounds * kWave, end = from_slot + first + m - 1;
+                const int p0 = min(from_slot + first + q, end);
+                int c = -1;                          // chunk of slot p0, the last one whose piece starts at or before it
+                for (int i = 0; i < nchunks; i += kWave)
+                    c += __popcll(__ballot(i + lane < nchunks && (int)s_slot[min(i + lane, nchunks - 1)] <= p0));
+                int ahead = c;                       // lane i: chunk ahead + i
+                uint32_t slot = s_slot[min(c + lane, nchunks - 1)], from = s_from[min(c + lane, nchunks - 1)];
+                uint32_t here = (uint32_t)__builtin_amdgcn_readfirstlane((int)from);
+#pragma unroll 1
+                for (int r0 = 0; r0 < rounds; r0 += kCollect) {
+                    W w[kCollect];
+#pragma unroll
+                    for (int r = 0; r < kCollect; ++r) {
+                        if (r0 + r < rounds) {
+                            const int p1 = p0 + (r0 + r) * kWave, p = min(p1 + lane, end);
+                            uint32_t at = here;
+                            while (c + 1 < nchunks) {
+                                if (c + 1 - ahead == kWave) {
+                                    ahead = c + 1;
+                                    slot = s_slot[min(ahead + lane, nchunks - 1)];
+                                    from = s_from[min(ahead + lane, nchunks - 1)];
+                                }
+                                const int next = __builtin_amdgcn_readlane((int)slot, c + 1 - ahead);
+                                if (next >= p1 + kWave)
+                                    break;
+                                ++c;
+                                here = (uint32_t)__builtin_amdgcn_readlane((int)from, c - ahead);
+                                at = p >= next ? here : at;
+                            }
+                            w[r] = pieces[at + (uint32_t)p];
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < kCollect; ++r) {
+                        const int i = q + (r0 + r) * kWave + lane;
+                        if (r0 + r < rounds) {
+                            if (!large)
+                                s_w[i] = i < m ? w[r] : ~(W)0;
+                            else if (i < m)
+                                reinterpret_cast<W*>(a.keys)[start + first + i] = w[r];
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+        }
         const int passes = (bits + 7) >> 3;
-        W* src = static_cast<W*>(a.words[0]) + start;
-        W* dst = static_cast<W*>(a.words[1]) + start;
+        W* src = (PIECES ? reinterpret_cast<W*>(a.keys) : static_cast<W*>(a.words[0])) + start;
+        W* dst = (PIECES ? reinterpret_cast<W*>(a.vals) : static_cast<W*>(a.words[1])) + start;
         int sh = a.vb;
         for (int p = 0; p < passes; ++p) {
             const int width = pass_width(bits, passes, p);
@@ -1140,12 +1314,12 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
                 {
                     const int q = opaque(p0);
                     const W* from = src + first;
-                    if ((large || p == 0) && (wave + 1) * groups * kSortGroup * kWave <= m) {   // all of the wavefront's words
+                    if ((large || (!PIECES && p == 0)) && (wave + 1) * groups * kSortGroup * kWave <= m) {   // all of the wavefront's words
 #pragma unroll
                         for (int r = 0; r < kSortPerThread; ++r)
                             if (r < groups * kSortGroup)
                                 w[r] = load_at(from, (uint32_t)q, r * kWave);
-                    } else if (large || p == 0) {
+                    } else if (large || (!PIECES && p == 0)) {
 #pragma unroll
                         for (int r = 0; r < kSortPerThread; ++r)
                             if (r < groups * kSortGroup)
@@ -1196,7 +1370,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
         // ---- keys and payloads; words that lie in LDS (sorted here) or in memory (large units, and buckets of one
         // row, which are sorted as they are)
         uint32_t heads = 0;
-        if (bits > 0 && !large) {
+        if ((PIECES || bits > 0) && !large) {
             const int groups = group_count<kSortGroup>(m_all);
             const int q = opaque(wave * groups * kSortGroup * kWave + lane);
             uint32_t* keys = a.keys + start;
@@ -1222,27 +1396,33 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
             else
                 emit(std::false_type());
         } else {
-            if (large) {
+            if (large && bits > 0) {
 #pragma unroll 1
-                for (int i = tid; i < m_all; i += kSortThreads)
+                for (int i = opaque(tid); i < m_all; i += kSortThreads)
                     heads += i == 0 || (src[i] >> a.vb) != (src[i - 1] >> a.vb) ? 1u : 0u;
                 __syncthreads();                     // 32-bit words lie where keys or payloads go
-            } else if (tid == 0 && !(s_unit.flags & kUnitContinued)) {
+            } else if (!PIECES && tid == 0 && !(s_unit.flags & kUnitContinued)) {
                 heads = 1;
             }
 #pragma unroll 4
-            for (int i = tid; i < m_all; i += kSortThreads) {
+            for (int i = opaque(tid); i < m_all; i += kSortThreads) {
                 const W x = src[i];
                 a.keys[start + i] = key0 + (uint32_t)(x >> a.vb);
                 a.vals[start + i] = (int32_t)(x & vmask);
             }
         }
+        if (PIECES && bits == 0)                     // one run, of the row's first unit
+            heads = tid == 0 && m_all > 0 && from_slot == 0 ? 1u : 0u;
         heads = last_lane(wave_scan_add(heads));
         if (lane == 0 && heads > 0)
             atomicAdd(&s_heads, heads);
         __syncthreads();
         if (tid == 0) {
             a.unit_runs[u] = s_heads;
+            if (PIECES) {
+                a.units[u].start = start;
+                a.units[u].m = m_all;
+            }
             atomicAdd(&a.table_runs[s_unit.t], s_heads);
         }
         u = s_ticket;                                // (written before the barrier above, at the latest)
