@@ -114,7 +114,7 @@ struct tbe_s {
     size_t off_tile_base = 0, off_tile_table = 0, off_radix_hist = 0, off_scan_tmp = 0, off_rl_counts = 0;
     size_t off_unit_first = 0, off_partials = 0, off_small_long = 0;
     size_t off_long_list = 0, off_zero = 0, workspace_bytes = 0;
-    size_t off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
+    size_t off_piece_done = 0, end_zero = 0, off_win_cnt = 0, off_win_list = 0, off_wrun = 0, off_wbounds = 0;
     size_t off_dense_dirty = 0, off_dense_cnt = 0, off_dense_list = 0, off_drun = 0, off_dgroup = 0, off_dbounds = 0;
     int64_t dbounds_cap = 0;   // entries
     size_t weight_bytes = 0, state_bytes = 0;
@@ -271,6 +271,9 @@ void plan_partition(tbe_s* h, Take take)
     h->off_words64 = ss.wide ? take(8 * ((size_t)nmax + 64)) : 0;
 }
 
+// most partial rows by position of a call that finds its long runs
+int64_t piece_slots_max(const tbe_s* h) { return ceil_div(std::min(h->max_indices, kFoundLookups), kPosSlot); }
+
 void plan_workspace(tbe_s* h)
 {
     const int64_t nmax = h->max_indices;
@@ -316,8 +319,11 @@ void plan_workspace(tbe_s* h)
     // dense hot rows: per-table queues, compact run list, groups, and the runs' positions at every
     // kDenseSlice-th bag.  The threshold is never below kDenseMinRun, which bounds the number of dense runs.
     const int64_t dense_runs_max = nmax / kDenseMinRun + h->T + 2;
-    h->off_dense_cnt = take(4 * (size_t)h->T);
+    h->off_dense_cnt = take(4 * (size_t)h->T);       // (the first of those that are zero between updates ...
     h->off_dense_dirty = take(4 * (size_t)h->T);
+    h->off_win_cnt = take(4 * (size_t)h->T);
+    h->off_piece_done = take(4 * (size_t)piece_slots_max(h));
+    h->end_zero = off;                               // ... and where they end)
     h->off_dense_list = take(4 * (size_t)dense_runs_max);
     h->off_drun = take(4 * (size_t)dense_runs_max);
     h->off_dgroup = take(sizeof(DenseGroup) * (size_t)(dense_runs_max / kDenseRows + h->T + 1));
@@ -332,7 +338,6 @@ void plan_workspace(tbe_s* h)
     h->off_dbounds = take(4 * (size_t)h->dbounds_cap);
     // long runs below the dense threshold: per-table queues, the prefix of their lengths, and the runs' piece records
     const int64_t win_runs_max = nmax / kLongRun + h->T + 2;
-    h->off_win_cnt = take(4 * (size_t)h->T);
     h->off_win_list = take(4 * (size_t)win_runs_max);
     h->off_wrun = take(4 * 2 * (size_t)(h->T + 1));   // prefixes of the per-table queue lengths and piece counts
     h->off_wbounds = take(sizeof(WinPiece) * (size_t)win_runs_max * kWinMax);   // the runs' piece records
@@ -583,9 +588,7 @@ tbe_status_t tbe_bind(tbe_handle_t h, void* d_weights, float* d_state, void* d_w
                                hipMemcpyHostToDevice));
     TBE_HIP_CHECK(h, hipMemcpy(h->d_ws + h->off_counters, &zero, sizeof(zero), hipMemcpyHostToDevice));
     TBE_HIP_CHECK(h, hipMemset(h->d_ws + h->off_zero, 0, kZeroRowBytes));
-    TBE_HIP_CHECK(h, hipMemset(h->d_ws + h->off_dense_cnt, 0, 4 * (size_t)h->T));
-    TBE_HIP_CHECK(h, hipMemset(h->d_ws + h->off_dense_dirty, 0, 4 * (size_t)h->T));
-    TBE_HIP_CHECK(h, hipMemset(h->d_ws + h->off_win_cnt, 0, 4 * (size_t)h->T));
+    TBE_HIP_CHECK(h, hipMemset(h->d_ws + h->off_dense_cnt, 0, h->end_zero - h->off_dense_cnt));
     TBE_HIP_CHECK(h, hipDeviceSynchronize());
     h->bound = true;
     h->final_buf = -1;
@@ -858,8 +861,7 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
         if (a.small || a.piece_blocks > 0) {
             const int64_t long_blocks = a.small ? a.n / (kPosPiece + 1) : a.piece_blocks;
             hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, true>), dim3((unsigned)(a.span_blocks + long_blocks)), dim3(kBwdThreads), 0, st, a);
-            if (a.small)
-                return;
+            return;                  // (long runs and all)
         } else {
             switch (update_span(a.n, h->lanes_bwd, h->T)) {
                 case 16: launch(reduce_update_kernel<WT, GT, OPT, 16, false>, 16); break;
@@ -870,7 +872,7 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
         }
     }
     Counters* counters = h->ws<Counters>(h->off_counters);
-    if (a.n > a.long_run && a.piece_blocks == 0) {
+    if (a.n > a.long_run) {
         // the long runs below the dense threshold: their pieces, after plan -> window-border positions if by bag window
         ScopedTimer tm(h, SLOT_WINDOW_RUNS, st);
         uint32_t* wpre = h->ws<uint32_t>(h->off_wrun);
@@ -980,6 +982,7 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     a.by_position = rule.by_position;
     a.long_run = a.small ? kPosPiece : rule.long_run;
     a.piece_blocks = rule.found && !a.small && n > a.long_run && update_span(n, h->lanes_bwd, h->T) == kSpanUnit ? (int32_t)ceil_div(ceil_div(n, kPosSlot), kBwdThreads / kWave) : 0;
+    a.piece_done = h->ws<uint32_t>(h->off_piece_done);
     // dense hot rows: only when a run can exceed the threshold and the bounds table of this call fits
     const int thr = dense_threshold(h->sorted_batch);
     const bool dense_on = rule.dense && n > thr && dense_bounds_entries(n, h->sorted_batch, h->T) <= h->dbounds_cap &&
@@ -1008,7 +1011,7 @@ static tbe_status_t enqueue_update(tbe_s* h, const void* d_grad_out, const OptCa
     }
     const int per_block = kBwdThreads / kWave;
     const int64_t max_long = n / a.long_run + 1;
-    const dim3 grid_fix((unsigned)(a.piece_blocks > 0 ? a.piece_blocks : std::min<int64_t>(2048, ceil_div(max_long, per_block))));
+    const dim3 grid_fix((unsigned)std::min<int64_t>(2048, ceil_div(max_long, per_block)));
     if (h->dtype == TBE_DTYPE_FP32)
         launch_update_grad<float>(a, grid_fix, st, h);
     else

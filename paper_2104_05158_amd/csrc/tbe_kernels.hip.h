@@ -669,8 +669,9 @@ struct BwdArgs {
     int32_t long_run;      // runs longer than this are long: kLongRun, or kPosPiece in a small call that cuts them by position
     int32_t small;         // long runs are those that sort_small_kernel listed, each summed by a workgroup of this kernel
     int32_t span_blocks;   // small: workgroups of spans; those of long runs follow
-    int32_t piece_blocks;  // > 0: long runs are found by position, a wavefront per partial row; this many workgroups of the update
-                           // kernel, in front of those of the spans, sum their pieces, as many of the fix-up add them up
+    int32_t piece_blocks;  // > 0: long runs are found by position, not listed; this many workgroups of the update kernel, in front of
+                           // those of the spans, sum their pieces, a wavefront per partial row there could be
+    uint32_t* piece_done;  // [n / kPosSlot] (piece_blocks) pieces summed so far of the long run that starts there (zero between updates)
     const uint32_t* small_long;   // small: indices of the long runs, their number in front
     int32_t by_position;   // long runs are cut by position (their pieces are listed by the update kernel), not by bag window
     int32_t T;
@@ -778,6 +779,26 @@ struct GradIO<__hip_bfloat16> {
         a[0] += __uint_as_float(v.x << 16); a[1] += __uint_as_float(v.x & 0xffff0000u);
         a[2] += __uint_as_float(v.y << 16); a[3] += __uint_as_float(v.y & 0xffff0000u);
     }
+};
+
+// An element of a partial row that a wavefront of another L2 adds up in the same launch: goes around the L2s both ways.
+struct SharedFloat {
+    float x;
+};
+
+template <>
+struct GradIO<SharedFloat> {
+    using Vec = float4;
+    __device__ static __forceinline__ Vec ldv(const SharedFloat* p)
+    {
+        const uint64_t* q = reinterpret_cast<const uint64_t*>(p);
+        const uint64_t a = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t b = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return make_float4(__uint_as_float((uint32_t)a), __uint_as_float((uint32_t)(a >> 32)), __uint_as_float((uint32_t)b),
+                           __uint_as_float((uint32_t)(b >> 32)));
+    }
+    __device__ static __forceinline__ void requested() {}
+    __device__ static __forceinline__ void add(float (&a)[4], const Vec v) { acc4(a, v); }
 };
 
 // Per-lane column geometry of a D-element row covered by LPR lanes with two 4-element blocks each.
@@ -963,6 +984,21 @@ __device__ __forceinline__ void store_partial(float* __restrict__ dst, const flo
     }
 }
 
+__device__ __forceinline__ void store_shared(float* __restrict__ dst, const float (&acc)[2][4], const Cols& c)
+{
+    auto st = [](float* p, const float (&v)[4]) {
+        uint64_t* q = reinterpret_cast<uint64_t*>(p);
+        __hip_atomic_store(q, (uint64_t)__float_as_uint(v[1]) << 32 | __float_as_uint(v[0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(q + 1, (uint64_t)__float_as_uint(v[3]) << 32 | __float_as_uint(v[2]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (c.grp == 0) {
+        if (c.c0)
+            st(dst + c.e0, acc[0]);
+        if (c.c1)
+            st(dst + c.e1, acc[1]);
+    }
+}
+
 // Sum of the gradient rows of the sorted positions [p0, p1) of one table, by one wavefront; every lane group has it.
 template <typename GT>
 __device__ __forceinline__ void sum_lookups(const BwdArgs& a, const TableMeta& m, const Cols& c, int p0, int p1, float (&acc)[2][4])
@@ -1027,35 +1063,66 @@ __device__ __forceinline__ void sum_piece(const BwdArgs& a, const int4 rec /* p0
 
 // Long runs by position need no list: partial rows are numbered by position, kPosSlot positions each, and at most one piece
 // starts in those of a number (at most one long run does), always of the last run that starts before their end.
-// The positions [s, e) of that run if it is long; its index, or -1.
-__device__ __forceinline__ int long_run_by_position(const BwdArgs& a, int slot, int& s, int& e)
+struct FoundPiece {
+    int run, s, e;           // index and positions of the run
+    int p0, p1;              // positions of the piece
+    bool found;              // a piece of a long run starts there
+};
+
+__device__ __forceinline__ FoundPiece find_piece(const BwdArgs& a, int slot)
 {
     static_assert(kPosSlot % kSpanUnit == 0, "");
-    if (slot >= (a.n + kPosSlot - 1) / kPosSlot)
-        return -1;
-    const int end = min(a.n, (slot + 1) * kPosSlot);
-    const int run = uniform(a.unit_first_run[(end + kSpanUnit - 1) / kSpanUnit]) - 1;
-    s = uniform(a.seg_offsets[run]), e = uniform(a.seg_offsets[run + 1]);
-    return e - s > a.long_run ? run : -1;
+    FoundPiece f;
+    const bool valid = slot < (a.n + kPosSlot - 1) / kPosSlot;
+    const int end = min(a.n, (valid ? slot + 1 : 1) * kPosSlot);
+    f.run = a.unit_first_run[(end + kSpanUnit - 1) / kSpanUnit] - 1;
+    f.s = a.seg_offsets[f.run];
+    f.e = a.seg_offsets[f.run + 1];
+    const int len = f.e - f.s, np = position_pieces(len);
+    const int i = first_piece_from(len, np, slot * kPosSlot - f.s);
+    f.p0 = position_of_piece(f.s, len, np, i);
+    f.p1 = position_of_piece(f.s, len, np, i + 1);
+    f.found = valid && len > a.long_run && i < np && f.p0 < (slot + 1) * kPosSlot;
+    return f;
 }
 
-// A piece by one wavefront beside the spans, in their launch.  In one of its own after them it added a chain of up to 128 rows
-// to calls that are little more than such chains, and 5 us to those without long runs: 40 tables of 4..512 columns, 0.17 M
-// lookups: step of 105 -> 86 us; Adam, 0.44 M 190 -> 184; 512 columns, 0.2 M 171 -> 154 (pieces of 64 lookups: 87 and 165).
-template <typename GT>
-__device__ __forceinline__ void sum_piece_by_position(const BwdArgs& a, int slot)
+// One wavefront sums the gradient rows of a piece and writes its partial row.  The one that is the last of its run's to do so
+// adds the partial rows up in their order and applies the update: whichever wavefront that is, the sum is the same.  The rows
+// are stored and loaded past the L2s; a wavefront counts its piece when its stores have arrived, and loads the others' when
+// all are counted.  (A launch of its own for the last part took 5 to 11 us, most of it its latency.)
+template <typename WT, typename GT, int OPT>
+__device__ __forceinline__ void piece_of_found_run(const BwdArgs& a, int slot, int run, int s, int e, int p0, int p1)
 {
-    int s, e;
-    const int run = long_run_by_position(a, slot, s, e);
-    if (run < 0)
-        return;
+    using IO = RowIO<WT, 4>;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t key = (uint32_t)uniform((int)a.unique_keys[run]);
+    const TableMeta m = a.meta[uniform(find_table(a.row_base, a.T, key))];
+    const Cols c(m.dim, m.lpr_bwd(), lane);
     const int np = position_pieces(e - s);
-    const int i = first_piece_from(e - s, np, slot * kPosSlot - s);
-    const int p0 = position_of_piece(s, e - s, np, i);
-    if (i >= np || p0 >= (slot + 1) * kPosSlot)
+    float acc[2][4];
+    sum_lookups<GT>(a, m, c, p0, p1, acc);
+    store_shared(a.partials + (int64_t)slot * a.dpad, acc, c);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    uint32_t* done = a.piece_done + s / kPosSlot;
+    uint32_t before = 0;
+    if (lane == 0)
+        before = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (uniform((int)before) != np - 1)
         return;
-    const int t = uniform(find_table(a.row_base, a.T, (uint32_t)uniform((int)a.unique_keys[run])));
-    sum_piece<GT>(a, make_int4(p0, position_of_piece(s, e - s, np, i + 1), slot, t));
+    asm volatile("" ::: "memory");
+    if (lane == 0)
+        __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int64_t wel = m.woff + (int64_t)(key - m.rbase) * m.dim;
+    WT* wrow = static_cast<WT*>(a.weights) + wel;
+    typename IO::Vec wvv[2];
+    wvv[0] = IO::ldv(wrow + c.e0);
+    wvv[1] = IO::ldv(wrow + c.e1);
+    OptRow<OPT> st;
+    st.load(a.opt, key, wel, c);
+    const SharedFloat* rows = reinterpret_cast<const SharedFloat*>(a.partials);
+    wave_gather_sum<SharedFloat>([&](int i) { return rows + (int64_t)(position_of_piece(s, e - s, np, i) / kPosSlot) * a.dpad; }, 0, np,
+                                 a.zero_row, c, acc);
+    optimizer_epilogue<WT, OPT>(wrow, wvv, acc, m.dim, c, c.grp == 0, a.opt, key, wel, st);
 }
 
 // A long run of a small call, by one workgroup: its wavefronts sum a share each, the first adds the shares in their order
@@ -1225,7 +1292,13 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
             return;
         }
         if (block < a.piece_blocks) {
-            sum_piece_by_position<GT>(a, uniform(block * kWaves + wv));
+            // beside the spans: in a launch of its own after them a piece added a chain of up to 128 rows to calls that are little
+            // more than such chains, and 5 us to those without long runs (40 tables of 4..512 columns, 0.17 M lookups: step of
+            // 105 -> 86 us; Adam, 0.44 M 190 -> 184; 512 columns, 0.2 M 171 -> 154; pieces of 64 lookups: 87 and 165)
+            const int slot = uniform(block * kWaves + wv);
+            const FoundPiece f = find_piece(a, slot);
+            if (uniform(f.found))
+                piece_of_found_run<WT, GT, OPT>(a, slot, uniform(f.run), uniform(f.s), uniform(f.e), uniform(f.p0), uniform(f.p1));
             return;
         }
         block -= a.piece_blocks;
@@ -2102,15 +2175,6 @@ __global__ __launch_bounds__(kBwdThreads) void long_run_fixup_kernel(BwdArgs a)
         }
         optimizer_epilogue<WT, OPT>(wrow, wvv, acc, m.dim, c, c.grp == 0, a.opt, key, wel, st);
     };
-    if (a.piece_blocks > 0) {
-        int s, e;
-        const int run = long_run_by_position(a, wave_global, s, e);
-        if (run >= 0 && s >= wave_global * kPosSlot) {
-            const uint32_t key = (uint32_t)uniform((int)a.unique_keys[run]);
-            fix(key, uniform(find_table(a.row_base, a.T, key)), s, e);
-        }
-        return;
-    }
     const int cnt = (int)a.counters->long_todo;
     if (blockIdx.x == 0 && threadIdx.x == 0)
         a.counters->win_pieces = 0;

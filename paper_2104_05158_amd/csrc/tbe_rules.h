@@ -105,9 +105,9 @@ constexpr int64_t kPositionBlock = 4 << 20;
 constexpr int64_t kManyLongBytes = 16000000, kManyLongPerColumn = 65536;
 
 // Lookups up to which the long runs of a call without dense ones are found by position instead of listed: every partial row
-// there could be takes a wavefront that looks for it, twice, which a larger call does not get back (step, us, listed / found: 40
+// there could be takes a wavefront that looks for it, which a larger call does not get back (with the sums added up in a launch of their own, step, us, listed / found: 40
 // tables of 4..512 columns, 0.17 M 103 / 85; 512 columns, 0.2 M 171 / 154; 128, 0.33 M 94 / 92; uniform, 0.65 M 295 / 298;
-// 16-bit, 2 M 358 / 361, 6.2 M 688 / 694; 256 fp32 columns, 3.6 M 544 / 548).  Narrow rows (longer spans) have short chains and stay listed.
+// 16-bit, 2 M 358 / 361, 6.2 M 688 / 694; 256 fp32 columns, 3.6 M 544 / 548; added up beside the spans, in a launch of 4096 wavefronts, 6.2 M 670 / 729).  Narrow rows (longer spans) have short chains and stay listed.
 constexpr int64_t kFoundLookups = 1 << 19;
 
 constexpr int kPosPiece = 128;            // a piece by position has at most this many lookups (and fewer than that is never long) ...
