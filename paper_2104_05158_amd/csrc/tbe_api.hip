@@ -858,16 +858,20 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
         auto launch = [&](auto kernel, int span) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)ceil_div(ceil_div(a.n, span), per_block)), dim3(kBwdThreads), 0, st, a);
         };
-        if (a.small || a.piece_blocks > 0) {
+        if (a.small || a.piece_blocks > 0) {         // (long runs and all)
             const int64_t long_blocks = a.small ? a.n / (kPosPiece + 1) : a.piece_blocks;
-            hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, true>), dim3((unsigned)(a.span_blocks + long_blocks)), dim3(kBwdThreads), 0, st, a);
-            return;                  // (long runs and all)
+            const dim3 grid((unsigned)(a.span_blocks + long_blocks));
+            if (a.small)
+                hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, kLongSmall>), grid, dim3(kBwdThreads), 0, st, a);
+            else
+                hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, kLongPieces>), grid, dim3(kBwdThreads), 0, st, a);
+            return;
         } else {
             switch (update_span(a.n, h->lanes_bwd, h->T)) {
-                case 16: launch(reduce_update_kernel<WT, GT, OPT, 16, false>, 16); break;
-                case 32: launch(reduce_update_kernel<WT, GT, OPT, 32, false>, 32); break;
-                case 64: launch(reduce_update_kernel<WT, GT, OPT, 64, false>, 64); break;
-                default: launch(reduce_update_kernel<WT, GT, OPT, 128, false>, 128); break;
+                case 16: launch(reduce_update_kernel<WT, GT, OPT, 16, kLongListed>, 16); break;
+                case 32: launch(reduce_update_kernel<WT, GT, OPT, 32, kLongListed>, 32); break;
+                case 64: launch(reduce_update_kernel<WT, GT, OPT, 64, kLongListed>, 64); break;
+                default: launch(reduce_update_kernel<WT, GT, OPT, 128, kLongListed>, 128); break;
             }
         }
     }

@@ -1259,9 +1259,15 @@ __device__ __forceinline__ void run_batch(const BwdArgs& a, WT* __restrict__ wta
     }
 }
 
-// SPAN: sorted positions owned by one wavefront.  OWN: workgroups of this launch sum the long runs (small) or their pieces
-// (piece_blocks); otherwise the spans list them.  (In one kernel the scalar registers did not do: 0.3 % of 0.65 M lookups.)
-template <typename WT, typename GT, int OPT, int SPAN, bool OWN>
+// SPAN: sorted positions owned by one wavefront.  LONG: who sums the long runs.  (In one kernel the scalar registers did not do:
+// 0.3 % of 0.65 M lookups; with kLongSmall and kLongPieces in one 2048 lookups took 0.2 us more.)
+enum LongRuns {
+    kLongListed,       // the spans list them for other kernels
+    kLongSmall,        // workgroups of this launch (a.small)
+    kLongPieces,       // workgroups of this launch sum their pieces (a.piece_blocks)
+};
+
+template <typename WT, typename GT, int OPT, int SPAN, int LONG>
 __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
 {
     using IO = RowIO<WT, 4>;
@@ -1285,12 +1291,14 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x >> 6;
     int block = (int)blockIdx.x;
-    if constexpr (OWN) {
-        if (a.small && block >= a.span_blocks) {
+    if constexpr (LONG == kLongSmall) {
+        if (block >= a.span_blocks) {
             static_assert(sizeof(s_val_all) >= sizeof(float) * kWaves * kMaxDim && kValCap % 4 == 0, "");
             small_long_run<WT, GT, OPT>(a, block - a.span_blocks, reinterpret_cast<float(*)[kMaxDim]>(&s_val_all[0][0]));
             return;
         }
+    }
+    if constexpr (LONG == kLongPieces) {
         if (block < a.piece_blocks) {
             // beside the spans: in a launch of its own after them a piece added a chain of up to 128 rows to calls that are little
             // more than such chains, and 5 us to those without long runs (40 tables of 4..512 columns, 0.17 M lookups: step of
@@ -1424,7 +1432,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
                 cl = tl <= lgG ? 3 + tl : 14;
             }
             cls[i] = valid ? cl : -1;
-            if constexpr (OWN)
+            if constexpr (LONG != kLongListed)
                 continue;
             const bool cut = a.by_position && len <= a.dense_thr;
             if (a.by_position)

@@ -386,6 +386,7 @@ __device__ __forceinline__ void block_sort_pass(W (&w)[PER], int groups, int sh,
 // the digits of pass p of P over `bits` bits
 __device__ __forceinline__ int pass_width(int bits, int P, int p) { return bits / P + (p < bits % P ? 1 : 0); }
 
+// s_cnt: cleared, and synchronised since (between other work of the caller's: clearing and a barrier take 0.3 to 0.5 us).
 template <typename W, int PER, int ND>
 __device__ __forceinline__ void block_sort(W (&w)[PER], int groups, int shift, int bits, W* s_w,
                                            uint16_t (&s_cnt)[kSortWaves][ND], uint32_t* s_wsum)
@@ -395,15 +396,15 @@ __device__ __forceinline__ void block_sort(W (&w)[PER], int groups, int shift, i
     const int passes = (bits + kBits - 1) / kBits;
     for (int p = 0; p < passes; ++p) {
         const int width = pass_width(bits, passes, p);
-        zero_counts(s_cnt);
         if (p > 0) {
+            zero_counts(s_cnt);
             const int q = opaque(p0);
 #pragma unroll
             for (int r = 0; r < PER; ++r)
                 if (r < groups * kSortGroup)
                     w[r] = s_w[q + r * kWave];
+            __syncthreads();
         }
-        __syncthreads();
         block_sort_pass(w, groups, shift, width, s_w, s_cnt, s_wsum);
         shift += width;
     }
@@ -510,6 +511,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
         s_sum[tid] = 0;
     if (tid == 0)
         s_hot = 0;
+    zero_counts(s_cnt);
     const TablePlan p = table_plan(a, n, rows);
     // ---- a sample: one lookup from each of S equal stretches of the table's positions.  Requested before the tables before this
     // one are counted: bound by the misses a CU has in flight (1000 samples 2 us, 7700 samples, of 2 M lookups, 23 of 45).
@@ -1616,6 +1618,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sel
                     __syncthreads();
                 }
             } else if (m > 0) {
+                zero_counts(s_cnt);
                 select([&](uint32_t slot, uint32_t row, uint32_t pos) {
                     s_pos[slot] = pos;
                     s_w[slot] = (W)row;
@@ -1689,8 +1692,16 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, in
     const int n = a.n;
     const int groups = group_count<kSortGroup>(n), rounds = groups * kSortGroup;
     const int p0 = wave * rounds * kWave + lane;
-    for (int t = tid; t <= a.T; t += kSortThreads)
-        a.tstart[t] = (int)a.offsets[(int64_t)t * a.B];
+    const int table_start = tid <= a.T ? (int)a.offsets[(int64_t)tid * a.B] : 0;
+    uint32_t index[kSortPerThread];                  // on their way while the bags are found
+#pragma unroll
+    for (int r = 0; r < kSortPerThread; r += kSortGroup)
+        if (r < rounds) {
+#pragma unroll
+            for (int x = 0; x < kSortGroup; ++x)
+                index[r + x] = a.indices[min(p0 + (r + x) * kWave, n - 1)];
+        }
+    zero_counts(s_cnt);
     const uint32_t* s_mark = reinterpret_cast<const uint32_t*>(s_w);
     const uint32_t carry = bags_of_positions(a.offsets, 0, a.T * a.B - 1, 0, n, rounds, reinterpret_cast<uint32_t*>(s_w), s_wsum);
     uint64_t w[kSortPerThread];
@@ -1702,7 +1713,7 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, in
                 const int p = q + r * kWave;
                 const uint32_t bag = max(s_mark[p], carry) - 1u;
                 const uint32_t t = a.T == 1 ? 0u : bag / (uint32_t)a.B;
-                w[r] = p < n ? (uint64_t)(a.row_base[t] + a.indices[p]) << 32 | (bag - t * (uint32_t)a.B) : ~0ull;
+                w[r] = p < n ? (uint64_t)((a.T == 1 ? 0u : a.row_base[t]) + index[r]) << 32 | (bag - t * (uint32_t)a.B) : ~0ull;
             }
         }
     }
@@ -1760,6 +1771,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_small_kernel(SortArgs a, in
         if (s_starts[x + 1] - s_starts[x] > kPosPiece)
             a.small_long[1 + atomicAdd(&s_long, 1u)] = x;
     __syncthreads();
+    for (int t = tid; t <= a.T; t += kSortThreads)
+        a.tstart[t] = t < kSortThreads ? table_start : (int)a.offsets[(int64_t)t * a.B];
     if (tid == 0) {
         a.small_long[0] = s_long;
         a.seg_offsets[total] = n;
