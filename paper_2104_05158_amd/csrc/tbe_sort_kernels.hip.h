@@ -492,6 +492,42 @@ __device__ __forceinline__ int lds_lower(const uint32_t* p, int n, uint32_t v)
     return lo;
 }
 
+// Up to kRankSamples samples are sorted by counting for each how many go before it, every thread a stretch of them: two passes of the
+// sort in LDS cost 3.8 us however few there are, this 0.5 for 64 and 1.3 for 256.
+constexpr int kRankBits = 8;
+constexpr int kRankSamples = 1 << kRankBits;
+
+// w: the thread's words, at positions p0 + r * 64 (behind n: any), of at most 32 - kRankBits bits; the result is in s_out, barrier
+// included.  s_tmp: 2 * kRankSamples words, cleared, and synchronised since.
+template <int PER>
+__device__ __forceinline__ void rank_sort(const uint32_t (&w)[PER], int n, int p0, uint32_t* s_out, uint32_t* s_tmp)
+{
+    uint32_t* s_in = s_tmp;
+    uint32_t* s_rank = s_tmp + kRankSamples;
+    const int lg = max(2, ceil_log2((uint32_t)n)), size = 1 << lg;
+    static_assert(kSortGroup * kSortThreads >= kRankSamples, "the first rounds hold all of them");
+#pragma unroll
+    for (int r = 0; r < kSortGroup; ++r) {
+        const int p = p0 + r * kWave;                    // (the position makes every word another)
+        if (p < size)
+            s_in[p] = p < n ? w[r] << kRankBits | (uint32_t)p : ~0u;
+    }
+    __syncthreads();
+    const int i = (int)threadIdx.x & (size - 1), part = (int)threadIdx.x >> lg, each = max(4, size * size / kSortThreads);
+    const uint32_t mine = s_in[i];
+    uint32_t before = 0;
+    for (int j = part * each; j < min((part + 1) * each, size); j += 4) {
+        const uint4 x = *reinterpret_cast<const uint4*>(s_in + j);
+        before += (x.x < mine ? 1u : 0u) + (x.y < mine ? 1u : 0u) + (x.z < mine ? 1u : 0u) + (x.w < mine ? 1u : 0u);
+    }
+    if (before > 0)
+        atomicAdd(&s_rank[i], before);
+    __syncthreads();
+    if ((int)threadIdx.x < n)
+        s_out[s_rank[threadIdx.x]] = s_in[threadIdx.x] >> kRankBits;
+    __syncthreads();
+}
+
 // MODE: a.mode (in one kernel the partition's plan took 0.3 us longer)
 template <int MODE>
 __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
@@ -602,7 +638,10 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
 #pragma unroll
     for (int r = 0; r < kSortPerThread; ++r)
         w[r] = r < rounds && wave * rounds * kWave + r * kWave + lane < S ? min(w[r], rows - 1) : ~0u;
-    block_sort(w, groups, 0, bits, s_key, s_cnt, s_wsum);
+    if (S <= kRankSamples && bits <= 32 - kRankBits)
+        rank_sort(w, S, wave * rounds * kWave + lane, s_key, reinterpret_cast<uint32_t*>(&s_cnt[0][0]));
+    else
+        block_sort(w, groups, 0, bits, s_key, s_cnt, s_wsum);
     // ---- borders: row 0, every q-th sample once, and the row after one that fills a whole stretch of samples
     // (a bucket of its own).  Thread j owns candidates 2 j and 2 j + 1.
     uint32_t cand[2], emit[2];
