@@ -29,7 +29,8 @@ constexpr int kSpanUnit = 16;             // a span of the update kernel is a mu
 constexpr int kWinMax = 16;               // most bag windows a long run is cut into
 constexpr int kWinBatch = 8;               // pieces a workgroup of window_runs_kernel claims at a time
 constexpr int kBwdThreads = 256;          // 4 wavefronts = 4 chunks per workgroup
-constexpr int kBwdUnroll = 4;             // gradient rows in flight per lane group (long runs)
+constexpr int kBwdUnroll = 4;             // gradient rows in flight per lane group (long runs) ...
+constexpr int kBwdUnrollWide = 8;         // ... and where a row takes the whole wavefront and the call is a chain of such trips
 constexpr int kShortRun = 4;              // runs up to this length are handled one per lane group
 constexpr int kMaxDim = 512;
 // dense hot rows: runs longer than the call's dense threshold are summed as (count matrix) x (gradient block)
@@ -821,7 +822,7 @@ struct Cols {
 
 // Whole-wavefront fp32 sum of the rows rowptr(i) (element type GT), i in [p0, p1), p1 > p0; rowptr must
 // be valid for every i in the range.  Afterwards every lane group holds the complete sums.
-template <typename GT, typename RowPtr>
+template <typename GT, int UNROLL = kBwdUnroll, typename RowPtr>
 __device__ __forceinline__ void wave_gather_sum(RowPtr rowptr, int p0, int p1, const float* __restrict__ zero_row_f,
                                                 const Cols& c, float (&acc)[2][4])
 {
@@ -833,23 +834,23 @@ __device__ __forceinline__ void wave_gather_sum(RowPtr rowptr, int p0, int p1, c
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             acc[k][e] = 0.f;
-    for (int i0 = p0; i0 < p1; i0 += G * kBwdUnroll) {
-        typename GIO::Vec v[kBwdUnroll][2];
-        const GT* rp[kBwdUnroll];
+    for (int i0 = p0; i0 < p1; i0 += G * UNROLL) {
+        typename GIO::Vec v[UNROLL][2];
+        const GT* rp[UNROLL];
 #pragma unroll
-        for (int u = 0; u < kBwdUnroll; ++u) {
+        for (int u = 0; u < UNROLL; ++u) {
             const int i = i0 + u * G + c.grp;
             const GT* p = rowptr(min(i, p1 - 1));
             rp[u] = i < p1 ? p : zero_row;
         }
 #pragma unroll
-        for (int u = 0; u < kBwdUnroll; ++u) {
+        for (int u = 0; u < UNROLL; ++u) {
             v[u][0] = GIO::ldv(rp[u] + c.e0);
             v[u][1] = GIO::ldv(rp[u] + c.e1);
         }
         GIO::requested();
 #pragma unroll
-        for (int u = 0; u < kBwdUnroll; ++u) {
+        for (int u = 0; u < UNROLL; ++u) {
             GIO::add(acc[0], v[u][0]);
             GIO::add(acc[1], v[u][1]);
         }
@@ -1000,7 +1001,7 @@ __device__ __forceinline__ void store_shared(float* __restrict__ dst, const floa
 }
 
 // Sum of the gradient rows of the sorted positions [p0, p1) of one table, by one wavefront; every lane group has it.
-template <typename GT>
+template <typename GT, int UNROLL = kBwdUnroll>
 __device__ __forceinline__ void sum_lookups(const BwdArgs& a, const TableMeta& m, const Cols& c, int p0, int p1, float (&acc)[2][4])
 {
     using GIO = GradIO<GT>;
@@ -1019,23 +1020,23 @@ __device__ __forceinline__ void sum_lookups(const BwdArgs& a, const TableMeta& m
     for (int base = p0; base < p1; base += kWave) {
         const int cnt = min(kWave, p1 - base);
         const int myv = vals[min(base + lane, p1 - 1)];     // 64 payloads with one coalesced load
-        for (int i0 = 0; i0 < cnt; i0 += G * kBwdUnroll) {
-            typename GIO::Vec v[kBwdUnroll][2];
-            const GT* rp[kBwdUnroll];
+        for (int i0 = 0; i0 < cnt; i0 += G * UNROLL) {
+            typename GIO::Vec v[UNROLL][2];
+            const GT* rp[UNROLL];
 #pragma unroll
-            for (int x = 0; x < kBwdUnroll; ++x) {
+            for (int x = 0; x < UNROLL; ++x) {
                 const int i = i0 + x * G + c.grp;
                 const int b = __shfl(myv, min(i, cnt - 1));
                 rp[x] = i < cnt ? gb + (int64_t)b * stride : zero_row;
             }
 #pragma unroll
-            for (int x = 0; x < kBwdUnroll; ++x) {
+            for (int x = 0; x < UNROLL; ++x) {
                 v[x][0] = GIO::ldv(rp[x] + c.e0);
                 v[x][1] = GIO::ldv(rp[x] + c.e1);
             }
             GIO::requested();
 #pragma unroll
-            for (int x = 0; x < kBwdUnroll; ++x) {
+            for (int x = 0; x < UNROLL; ++x) {
                 GIO::add(acc[0], v[x][0]);
                 GIO::add(acc[1], v[x][1]);
             }
@@ -1090,7 +1091,7 @@ __device__ __forceinline__ FoundPiece find_piece(const BwdArgs& a, int slot)
 // adds the partial rows up in their order and applies the update: whichever wavefront that is, the sum is the same.  The rows
 // are stored and loaded past the L2s; a wavefront counts its piece when its stores have arrived, and loads the others' when
 // all are counted.  (A launch of its own for the last part took 5 to 11 us, most of it its latency.)
-template <typename WT, typename GT, int OPT>
+template <typename WT, typename GT, int OPT, int UNROLL>
 __device__ __forceinline__ void piece_of_found_run(const BwdArgs& a, int slot, int run, int s, int e, int p0, int p1)
 {
     using IO = RowIO<WT, 4>;
@@ -1100,7 +1101,7 @@ __device__ __forceinline__ void piece_of_found_run(const BwdArgs& a, int slot, i
     const Cols c(m.dim, m.lpr_bwd(), lane);
     const int np = position_pieces(e - s);
     float acc[2][4];
-    sum_lookups<GT>(a, m, c, p0, p1, acc);
+    sum_lookups<GT, UNROLL>(a, m, c, p0, p1, acc);
     store_shared(a.partials + (int64_t)slot * a.dpad, acc, c);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     uint32_t* done = a.piece_done + s / kPosSlot;
@@ -1120,7 +1121,7 @@ __device__ __forceinline__ void piece_of_found_run(const BwdArgs& a, int slot, i
     OptRow<OPT> st;
     st.load(a.opt, key, wel, c);
     const SharedFloat* rows = reinterpret_cast<const SharedFloat*>(a.partials);
-    wave_gather_sum<SharedFloat>([&](int i) { return rows + (int64_t)(position_of_piece(s, e - s, np, i) / kPosSlot) * a.dpad; }, 0, np,
+    wave_gather_sum<SharedFloat, UNROLL>([&](int i) { return rows + (int64_t)(position_of_piece(s, e - s, np, i) / kPosSlot) * a.dpad; }, 0, np,
                                  a.zero_row, c, acc);
     optimizer_epilogue<WT, OPT>(wrow, wvv, acc, m.dim, c, c.grp == 0, a.opt, key, wel, st);
 }
@@ -1265,6 +1266,7 @@ enum LongRuns {
     kLongListed,       // the spans list them for other kernels
     kLongSmall,        // workgroups of this launch (a.small)
     kLongPieces,       // workgroups of this launch sum their pieces (a.piece_blocks)
+    kLongPiecesWide,   // the same, with twice the rows in flight (pieces_wide)
 };
 
 template <typename WT, typename GT, int OPT, int SPAN, int LONG>
@@ -1281,6 +1283,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     // element-wise optimizers carry whole state rows and take one run per group
     constexpr int kNB1 = OPT != kOptRowwiseAdagrad ? 1 : sizeof(WT) == 2 ? 4 : 2;   // runs of one lookup per group
     constexpr int kNB2 = OPT != kOptRowwiseAdagrad ? 1 : 2;                          // runs of two lookups per group
+    constexpr int kUnroll = LONG == kLongPiecesWide ? kBwdUnrollWide : kBwdUnroll;
     static_assert(SPAN <= 256, "run indices of a span are kept in bytes");
     static_assert(kShortRun == 4, "run_batch is instantiated for 1..4 lookups");
     __shared__ int32_t s_seg_all[kWaves][kSegCap];
@@ -1298,7 +1301,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
             return;
         }
     }
-    if constexpr (LONG == kLongPieces) {
+    if constexpr (LONG == kLongPieces || LONG == kLongPiecesWide) {
         if (block < a.piece_blocks) {
             // beside the spans: in a launch of its own after them a piece added a chain of up to 128 rows to calls that are little
             // more than such chains, and 5 us to those without long runs (40 tables of 4..512 columns, 0.17 M lookups: step of
@@ -1306,7 +1309,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
             const int slot = uniform(block * kWaves + wv);
             const FoundPiece f = find_piece(a, slot);
             if (uniform(f.found))
-                piece_of_found_run<WT, GT, OPT>(a, slot, uniform(f.run), uniform(f.s), uniform(f.e), uniform(f.p0), uniform(f.p1));
+                piece_of_found_run<WT, GT, OPT, kUnroll>(a, slot, uniform(f.run), uniform(f.s), uniform(f.e), uniform(f.p0), uniform(f.p1));
             return;
         }
         block -= a.piece_blocks;
@@ -1527,7 +1530,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
                 wvv[1] = IO::ldv(wrow + c.e1);
                 st.load(a.opt, key, m.woff + rel, c);
                 float acc[2][4];
-                wave_gather_sum<GT>([&](int p) { return gb + (int64_t)s_val[p - q0] * sumD; }, s0, s0 + len0, a.zero_row,
+                wave_gather_sum<GT, kUnroll>([&](int p) { return gb + (int64_t)s_val[p - q0] * sumD; }, s0, s0 + len0, a.zero_row,
                                     c, acc);
                 optimizer_epilogue<WT, OPT>(wrow, wvv, acc, D, c, c.grp == 0, a.opt, key, m.woff + rel, st);
             }
