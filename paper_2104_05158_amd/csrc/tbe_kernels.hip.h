@@ -604,7 +604,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_
 //     dense_rows_kernel (counts x gradient block).  Below it, while a table's gradient block fits an L2
 //     (by_position), its pieces of kPosPiece lookups are listed for window_runs_kernel right away; beyond that
 //     the run is queued, per table, for window_runs_kernel (pieces by bag window).  Those write fp32 partial
-//     rows to the workspace, and the fix-up kernel adds a run's partial rows in a fixed order and applies the update.
+//     rows to the workspace, and the fix-up kernel adds a run's partial rows in a fixed order and applies the update.  In
+//     small and middle calls workgroups of this launch do all of that (kLongSmall, kLongPieces).
 // The single-lookup rows of the tail of the index distribution move a row, its moment and one gradient row
 // each and run at the rate of the memory system; the steps of the longer runs are bound by how fast gradient
 // rows come out of the caches, so nothing here is arranged around instruction counts.

@@ -105,9 +105,11 @@ constexpr int64_t kPositionBlock = 4 << 20;
 constexpr int64_t kManyLongBytes = 16000000, kManyLongPerColumn = 65536;
 
 // Lookups up to which the long runs of a call without dense ones are found by position instead of listed: every partial row
-// there could be takes a wavefront that looks for it, which a larger call does not get back (with the sums added up in a launch of their own, step, us, listed / found: 40
+// there could be takes a wavefront that looks for it, which a larger call does not get back (step, us, listed / found, with the
+// partial rows added up in a launch of their own: 40
 // tables of 4..512 columns, 0.17 M 103 / 85; 512 columns, 0.2 M 171 / 154; 128, 0.33 M 94 / 92; uniform, 0.65 M 295 / 298;
-// 16-bit, 2 M 358 / 361, 6.2 M 688 / 694; 256 fp32 columns, 3.6 M 544 / 548; added up beside the spans, in a launch of 4096 wavefronts, 6.2 M 670 / 729).  Narrow rows (longer spans) have short chains and stay listed.
+// 16-bit, 2 M 358 / 361, 6.2 M 688 / 694; 256 fp32 columns, 3.6 M 544 / 548; found and finished by a launch of 4096 wavefronts, 16-bit, 6.2 M 670 / 729).  Narrow rows
+// (longer spans) have short chains and stay listed.
 constexpr int64_t kFoundLookups = 1 << 19;
 
 // Whether a call that finds its long runs by position keeps eight gradient rows in flight per lane group instead of four.  A row of
@@ -245,7 +247,6 @@ constexpr int64_t kSelectMean = 4 * kSelectCap, kSelectLookups = 1 << 18;
 // walk the table once more for every 12,288 of them (11 tables, one of 200,000 Zipf lookups: sort of 100 us, 62 with parts).
 // Together the rows of a table have at most lookups / kSelectPart units more than one each.
 constexpr int kSelectPart = 4096;
-constexpr int kSelectHot = (int)(kSelectLookups / kSelectPart);    // most rows with more than one
 
 TBE_BOTH int unit_parts(uint32_t sampled, int lookups, int samples, int part)
 {
