@@ -1188,7 +1188,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
 // PIECES (a.mode is kSortPieces): the unit's words are collected first, its piece of every chunk of the table in turn.  Where the
 // pieces start says how many lookups of the table go before the unit: no histogram, no second walk over the indices.  A unit
 // that does not fit is collected in memory, where its keys will be.  8 tables, 0.66 M lookups: 16.7 us instead of 14.7, for 9.1
-// of the histogram and 6.0 of the units; 64 tables, 6.2 M: 62 instead of 49, for 27 (the words of a unit are collected four a
+// of the histogram and 6.0 of the units; 64 tables, 6.2 M: 56 instead of 49, for 27 (the words of a unit are collected four a
 // thread at a time: with eight, registers spill and every reload is a trip to memory, 22 us instead of 16.7).
 constexpr int kCollect = 4;
 
