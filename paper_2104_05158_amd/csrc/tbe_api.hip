@@ -745,7 +745,6 @@ static tbe_status_t enqueue_sort(tbe_s* h, const int32_t* d_indices, const int64
     a.lut = h->ws<uint16_t>(h->off_lut);
     a.bstart = h->ws<uint32_t>(h->off_bstart);
     a.hist = h->ws<uint32_t>(h->off_hist);
-    a.starts = reinterpret_cast<uint16_t*>(a.hist);
     a.multi = h->ws<int32_t>(h->off_multi);
     a.tile_bag = h->ws<int32_t>(h->off_tile_bag);
     a.unit_runs = h->ws<uint32_t>(h->off_unit_runs);

@@ -673,6 +673,7 @@ struct BwdArgs {
     int32_t span_blocks;   // small: workgroups of spans; those of long runs follow
     int32_t piece_blocks;  // > 0: long runs are found by position, not listed; this many workgroups of the update kernel, in front of
                            // those of the spans, sum their pieces, a wavefront per partial row there could be
+    int32_t grad_bytes;    // bytes per gradient element (sizes the bag windows)
     uint32_t* piece_done;  // [n / kPosSlot] (piece_blocks) pieces summed so far of the long run that starts there (zero between updates)
     const uint32_t* small_long;   // small: indices of the long runs, their number in front
     int32_t by_position;   // long runs are cut by position (their pieces are listed by the update kernel), not by bag window
@@ -691,9 +692,10 @@ struct BwdArgs {
     // long runs (kLongRun < length <= dense_thr): queued per table, summed window by window by window_runs_kernel
     uint32_t* win_cnt;     // [T] (zero between updates)
     uint32_t* win_list;    // table t's queue starts at entry tstart[t] / kLongRun + t
-    int32_t grad_bytes;    // bytes per gradient element (sizes the bag windows)
     OptParams opt;
 };
+// (as for the sort's arguments: what the update reads of them lies in the first 256 bytes)
+static_assert(offsetof(BwdArgs, opt) + offsetof(OptParams, beta1) <= 256, "row-wise AdaGrad");
 
 struct WinPiece {        // 16 bytes: what a wavefront needs to sum one piece, in one load
     int32_t p0, p1;      // sorted positions of the piece
