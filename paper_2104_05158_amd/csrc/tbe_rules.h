@@ -284,11 +284,12 @@ inline bool use_select_sort(int64_t tables, int64_t lookups) { return lookups <=
 // single table: the units of several find theirs) a call keeps all steps of the partition, which the profile shows of it (30,000
 // lookups: 37 us for some 31).
 constexpr int kPiecesMax = 1024;
+constexpr int kPiecesChunk = 8192;         // a chunk is ordered by one workgroup at once, in LDS; its length is a power of two
 constexpr int64_t kPiecesMin = 1 << 15;
 
 inline bool use_pieces_sort(bool words32, int64_t lookups, int chunk)
 {
-    return words32 && lookups > kPiecesMin && lookups <= (int64_t)kPiecesMax * chunk;
+    return words32 && chunk <= kPiecesChunk && (chunk & (chunk - 1)) == 0 && lookups > kPiecesMin && lookups <= (int64_t)kPiecesMax * chunk;
 }
 
 // Workgroups of the bucket sort: one per unit there can be (and no fewer than are resident: tables cut by the packed range have

@@ -80,6 +80,7 @@ struct SortUnit {        // 32 bytes
     int32_t first;       // the table's first unit (they are numbered one after the other)
     uint32_t last;       // select: offset of the unit's last row from key0 (of the last unit: of any index); pieces: the table's first chunk
 };
+static_assert(kPiecesChunk == kSortTile, "sort_scatter_kernel<.., true> orders one tile");
 static_assert(sizeof(SortUnit) == 32 && kManyTables <= 65536, "");
 constexpr int kUnitContinued = 1;     // further part of a one-row bucket: its first lookup starts no run
 constexpr int kUnitNone = 2;          // (select, pieces) no bucket; until the unit is sorted its start and m are those of the table

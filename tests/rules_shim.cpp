@@ -41,6 +41,17 @@ int small_long_runs(int64_t lookups, int lanes) { return tbe::small_long_runs(lo
 
 int use_select_sort(int64_t tables, int64_t lookups) { return tbe::use_select_sort(tables, lookups); }
 
+int use_pieces_sort(int words32, int64_t lookups, int chunk) { return tbe::use_pieces_sort(words32 != 0, lookups, chunk); }
+
+int64_t sort_local_blocks(int64_t lookups, int64_t tables, int target, int tile, int64_t resident)
+{
+    return tbe::sort_local_blocks(lookups, tables, target, tile, resident);
+}
+
+int unit_parts(int sampled, int lookups, int samples, int part) { return tbe::unit_parts((uint32_t)sampled, lookups, samples, part); }
+
+int pieces_wide(int rowwise, int64_t widest) { return tbe::pieces_wide(rowwise != 0, widest); }
+
 int select_parts(int sampled, int lookups, int samples) { return tbe::select_parts((uint32_t)sampled, lookups, samples); }
 
 uint32_t select_fewer_rows(uint32_t rows, int found) { return tbe::select_fewer_rows(rows, found); }

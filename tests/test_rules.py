@@ -159,6 +159,8 @@ def test_which_long_runs_are_cut_how(rules):
         out = np.empty(4, np.int32)
         rules.long_run_rule(ctypes.c_int64(n), ctypes.c_int64(batch), ctypes.c_int64(128), ctypes.c_int(4), out.ctypes.data_as(ctypes.c_void_p))
         return bool(out[3])
+    wide = lambda rowwise, widest: bool(rules.pieces_wide(ctypes.c_int(rowwise), ctypes.c_int64(widest)))
+    assert wide(1, 257) and not wide(1, 256) and not wide(0, 512)
     assert found(1 << 19, 8192) and not found((1 << 19) + 1, 8192) and not found(1000, 8193)
     assert rule(3_999_999, 8192, 128, 4) == [1, 0, 128] and rule(4_000_000, 8192, 128, 4) == [1, 1, 512]
     assert rule(4_000_000, 8193, 128, 4) == rule(1, 8193, 128, 4) == [0, 1, 512] and rule(1, 8193, 128, 2) == [1, 0, 128]
@@ -190,6 +192,39 @@ def test_hot_rows_take_no_more_units_than_there_is_room_for(rules):
         cuts = np.sort(rng.integers(0, samples + 1, 40))
         of_rows = np.diff(np.concatenate([[0], cuts, [samples]]))
         assert sum(parts(int(k), n, samples) - 1 for k in of_rows) <= n // 4096
+
+
+def test_which_calls_have_units_that_collect_their_pieces(rules):
+    # a chunk is put in order by one workgroup at once, a unit holds the starts of all chunks and shifts by their length: a chunk
+    # of more than a tile, or of no power of two, may never take that path, whatever the host asks for
+    use = lambda words32, n, chunk: bool(rules.use_pieces_sort(ctypes.c_int(words32), ctypes.c_int64(n), ctypes.c_int(chunk)))
+    for chunk in (2048, 4096, 8192):
+        assert use(1, 1024 * chunk, chunk) and not use(1, 1024 * chunk + 1, chunk) and not use(0, 1024 * chunk, chunk)
+    for chunk in (8193, 16_384, 24_576, 32_768, 6144, 5000):
+        assert not use(1, 1_000_000, chunk) and not use(1, 1 << 24, chunk), chunk
+
+
+def test_every_unit_of_the_bucket_sort_has_a_workgroup_or_takes_a_ticket(rules):
+    rules.sort_local_blocks.restype = ctypes.c_int64
+    blocks = lambda n, tables, target: rules.sort_local_blocks(ctypes.c_int64(n), ctypes.c_int64(tables), ctypes.c_int(target),
+                                                               ctypes.c_int(8192), ctypes.c_int64(768))
+    assert blocks(32_769, 1, 1024) == 768                # no fewer than are resident
+    assert blocks(8_000_000, 1, 2841) == 2815 + 976 + 2  # a unit per bucket, one more per tile of a row, two a table
+    assert blocks(100_000, 4000, 1024) == 97 + 12 + 8000 and blocks(100_000, 4041, 1024) == 8191 and blocks(100_000, 4042, 1024) == 768
+    assert blocks(100_000_000, 64, 3500) == 768
+
+
+def test_rows_of_several_units_fit_the_units_of_their_call(rules):
+    # the plan of a call of up to 8 M lookups takes part numbers from the samples: whatever rows those are of, at most one unit
+    # more for every tile of lookups
+    rng = np.random.default_rng(12)
+    parts = lambda sampled, n, samples: rules.unit_parts(ctypes.c_int(sampled), ctypes.c_int(n), ctypes.c_int(samples), ctypes.c_int(8192))
+    for n in (32_769, 131_073, 786_433, 4_000_003, (1 << 23) - 1, 1 << 23):
+        for samples in (16, 1000, 8192):
+            assert parts(samples, n, samples) == 1 + n // 8192
+            cuts = np.sort(rng.integers(0, samples + 1, 40))
+            of_rows = np.diff(np.concatenate([[0], cuts, [samples]]))
+            assert sum(parts(int(k), n, samples) - 1 for k in of_rows) <= n // 8192
 
 
 def _parts_of_a_unit(rules, looked_up, rows):
