@@ -240,11 +240,24 @@ TBE_API tbe_status_t tbe_profile_enable(tbe_handle_t h, int32_t max_calls);
 
 /*
  * Synchronises the recorded events and returns, per slot, how often it was timed and its total duration in milliseconds
- * since the last read; then resets the pool.  A slot holds the kernels of one step of a call: "forward"; of the sort
- * "sort_plan", "sort_hist", "sort_scan", "sort_scatter" (these three once per call, or once per eight bits of the row
- * indices in the calls that are sorted digit by digit), "sort_local" (not in those; all there is in a small call) and
- * "sort_runs"; "reduce_update"; of the long runs "window_runs", "dense_rows" and "long_fixup".  names receives pointers to
- * static strings.  capacity = length of the three host arrays, at least 10; *num_slots = entries filled.
+ * since the last read; then resets the pool.  A slot holds the kernels of one step of a call, and a call has the steps
+ * that its size asks for: a slot counts 0 where no kernel of its own does the step.
+ *   "forward"
+ *   the sort        plan  hist  scan  scatter  local  runs   ("sort_plan" ... "sort_runs")
+ *     at most 8192 lookups in at most 32,768 bags
+ *                    0     0     0     0        1      0
+ *     at most 2^18 lookups, 24,576 a table on average
+ *                    1     0     0     0        1      1
+ *     at most 2^23 lookups
+ *                    1     0     0     1        1      1
+ *     more, or a table of more than 512 * 2^(32 - b) rows, where b bits hold a bag's number in the batch
+ *                    1     1     1     1        1      1
+ *     digit by digit (few tall or very many tables)
+ *                    1     once per eight bits  0      1
+ *   "reduce_update"
+ *   "window_runs", "dense_rows", "long_fixup": rows with many lookups, in calls that do not sum them in the update
+ * names receives pointers to static strings.  capacity = length of the three host arrays, at least 10; *num_slots =
+ * entries filled.
  */
 TBE_API tbe_status_t tbe_profile_read(tbe_handle_t h, int32_t capacity, const char** names,
                               int64_t* launches, double* total_ms, int32_t* num_slots);

@@ -280,16 +280,15 @@ inline bool use_select_sort(int64_t tables, int64_t lookups) { return lookups <=
 // tables, 0.66 M 48 / 47 -> 42 / 42; 16, 2.6 M 95 / 93 -> 77 / 78; 64, 2 M 73 / 69 -> 64 / 61, 6.2 M 124 / 118 -> 113 / 109, 8 M 140 /
 // 137 -> 133 / 129; 600, 2 M 105 / 103 -> 81 / 78; 16, of which one has 4 M, 140 / 145 -> 133 / 146; 64, one 8 M 234 / 252 -> 209 /
 // 231.  Beyond, a table's units read the starts of hundreds of chunks for pieces of a few words (64 tables, 19 M lookups: the
-// units 208 us, 119 and 55 for the count).  kPiecesMax is also what a workgroup holds of them in LDS.  Up to kPiecesMin lookups (of a
-// single table: the units of several find theirs) a call keeps all steps of the partition, which the profile shows of it (30,000
-// lookups: 37 us for some 31).
+// units 208 us, 119 and 55 for the count).  kPiecesMax is also what a workgroup holds of them in LDS.
+// There is no smallest call: the smallest this gets, one table of 24,577 lookups (use_select_sort has the others), takes 39 counted
+// and 33 collected, of 32,768 38 and 32 (1 M rows).
 constexpr int kPiecesMax = 1024;
 constexpr int kPiecesChunk = 8192;         // a chunk is ordered by one workgroup at once, in LDS; its length is a power of two
-constexpr int64_t kPiecesMin = 1 << 15;
 
 inline bool use_pieces_sort(bool words32, int64_t lookups, int chunk)
 {
-    return words32 && chunk <= kPiecesChunk && (chunk & (chunk - 1)) == 0 && lookups > kPiecesMin && lookups <= (int64_t)kPiecesMax * chunk;
+    return words32 && chunk <= kPiecesChunk && (chunk & (chunk - 1)) == 0 && lookups <= (int64_t)kPiecesMax * chunk;
 }
 
 // Workgroups of the bucket sort: one per unit there can be (and no fewer than are resident: tables cut by the packed range have

@@ -19,10 +19,10 @@
 //   sort_local_kernel    one workgroup per unit: sorts the words in LDS, writes keys and payloads, counts the runs
 //   sort_runs_kernel     bucket borders are run borders, so a unit's runs start at a known index: unique_keys,
 //                        seg_offsets, and the first run of every span unit
-// A call of up to 8 M lookups leaves out histogram, columns and units: its chunks are put in order of their buckets where they
-// lie, and a unit collects its piece of each (use_pieces_sort).  One of some 100,000 leaves out the partition, too:
-// sort_select_kernel sorts units that it finds itself (use_select_sort).  One of at most kSortTile lookups is sorted by (table, row) at once, by one workgroup
-// (sort_small_kernel).
+// A call of up to 8 M lookups in words of 32 bits leaves out histogram, columns and units: its chunks are put in order of
+// their buckets where they lie, and a unit collects its piece of each (use_pieces_sort).  One of up to 2^18, and few a table,
+// leaves out the partition, too: sort_select_kernel sorts units that it finds itself (use_select_sort).  One of at most
+// kSortTile lookups is sorted by (table, row) at once, by one workgroup (sort_small_kernel).
 //
 // (The runs' first index could also come from a look-back over the units' counts inside sort_local_kernel; at
 // 38,000 units its polling took 6 ms where the extra kernel takes 0.2.)

@@ -347,12 +347,13 @@ def test_profile_slots(gpu_device):
     op.close()
 
 
-@pytest.mark.parametrize("rows,n,expect", [
-    (10_000, 30_000, dict(sort_plan=1, sort_hist=1, sort_scan=1, sort_scatter=1, sort_local=1, sort_runs=1)),       # partition
-    (10_000, 1_000_000, dict(sort_plan=1, sort_hist=2, sort_scan=2, sort_scatter=2, sort_local=0, sort_runs=1)),    # two digits
+@pytest.mark.parametrize("rows,n,expect,batch", [
+    (34_000_000, 262_144, dict(sort_plan=1, sort_hist=1, sort_scan=1, sort_scatter=1, sort_local=1, sort_runs=1), 65_536),  # partition
+    (10_000, 20_000, dict(sort_plan=1, sort_hist=0, sort_scan=0, sort_scatter=0, sort_local=1, sort_runs=1), 100),  # units find lookups
+    (10_000, 30_000, dict(sort_plan=1, sort_hist=0, sort_scan=0, sort_scatter=1, sort_local=1, sort_runs=1), 100),  # units collect them
+    (10_000, 1_000_000, dict(sort_plan=1, sort_hist=2, sort_scan=2, sort_scatter=2, sort_local=0, sort_runs=1), 100),  # two digits
 ])
-def test_profile_counts_every_step_of_the_sort_once(gpu_device, rows, n, expect):
-    batch = 100
+def test_profile_counts_every_step_of_the_sort_once(gpu_device, rows, n, expect, batch):
     op = tbe.TableBatchedEmbeddingBags([rows], [4], 0, batch, n, device=gpu_device)
     idx = torch.from_numpy(np.random.default_rng(1).integers(0, rows, n).astype(np.int32)).to(gpu_device)
     off = torch.from_numpy((np.arange(batch + 1) * (n // batch)).astype(np.int64)).to(gpu_device)

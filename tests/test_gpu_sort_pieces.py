@@ -13,6 +13,8 @@ MOST = 1024 * TILE
 
 CASES = {
     # name: (rows, batch, lookups per table, per table the rows that are looked up oftenest and their shares)
+    "smallest_call": ([1_000_000], 100, [24_577], [{}]),
+    "no_more_than_a_few_chunks": ([5000], 611, [32_768], [{4999: 0.4}]),
     "quarter_tiles": ([1_000_000], 700, [1 << 17], [{}]),
     "half_tiles": ([1_000_000], 700, [(1 << 17) + 1], [{}]),
     "most_half_tiles": ([1_000_000, 5000], 4096, [(3 << 18) - 3, 3], [{}, {}]),

@@ -199,7 +199,7 @@ def test_which_calls_have_units_that_collect_their_pieces(rules):
     # of more than a tile, or of no power of two, may never take that path, whatever the host asks for
     use = lambda words32, n, chunk: bool(rules.use_pieces_sort(ctypes.c_int(words32), ctypes.c_int64(n), ctypes.c_int(chunk)))
     for chunk in (2048, 4096, 8192):
-        assert use(1, 1024 * chunk, chunk) and not use(1, 1024 * chunk + 1, chunk) and not use(0, 1024 * chunk, chunk)
+        assert use(1, 24_577, chunk) and use(1, 1024 * chunk, chunk) and not use(1, 1024 * chunk + 1, chunk) and not use(0, 1024 * chunk, chunk)
     for chunk in (8193, 16_384, 24_576, 32_768, 6144, 5000):
         assert not use(1, 1_000_000, chunk) and not use(1, 1 << 24, chunk), chunk
 
