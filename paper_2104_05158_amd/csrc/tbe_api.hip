@@ -862,8 +862,6 @@ static void launch_update(const BwdArgs& a, dim3 grid_fix, hipStream_t st, tbe_s
             const dim3 grid((unsigned)(a.span_blocks + long_blocks));
             if (a.small)
                 hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, kLongSmall>), grid, dim3(kBwdThreads), 0, st, a);
-            else if (pieces_wide(OPT == kOptRowwiseAdagrad, a.dpad))
-                hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, OPT == kOptRowwiseAdagrad ? kLongPiecesWide : kLongPieces>), grid, dim3(kBwdThreads), 0, st, a);
             else
                 hipLaunchKernelGGL((reduce_update_kernel<WT, GT, OPT, kSpanUnit, kLongPieces>), grid, dim3(kBwdThreads), 0, st, a);
             return;

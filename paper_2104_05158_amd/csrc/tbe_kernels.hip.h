@@ -29,8 +29,7 @@ constexpr int kSpanUnit = 16;             // a span of the update kernel is a mu
 constexpr int kWinMax = 16;               // most bag windows a long run is cut into
 constexpr int kWinBatch = 8;               // pieces a workgroup of window_runs_kernel claims at a time
 constexpr int kBwdThreads = 256;          // 4 wavefronts = 4 chunks per workgroup
-constexpr int kBwdUnroll = 4;             // gradient rows in flight per lane group (long runs) ...
-constexpr int kBwdUnrollWide = 8;         // ... and where a row takes the whole wavefront and the call is a chain of such trips
+constexpr int kBwdUnroll = 4;             // gradient rows in flight per lane group (long runs)
 constexpr int kShortRun = 4;              // runs up to this length are handled one per lane group
 constexpr int kMaxDim = 512;
 // dense hot rows: runs longer than the call's dense threshold are summed as (count matrix) x (gradient block)
@@ -825,7 +824,7 @@ struct Cols {
 
 // Whole-wavefront fp32 sum of the rows rowptr(i) (element type GT), i in [p0, p1), p1 > p0; rowptr must
 // be valid for every i in the range.  Afterwards every lane group holds the complete sums.
-template <typename GT, int UNROLL = kBwdUnroll, typename RowPtr>
+template <typename GT, typename RowPtr>
 __device__ __forceinline__ void wave_gather_sum(RowPtr rowptr, int p0, int p1, const float* __restrict__ zero_row_f,
                                                 const Cols& c, float (&acc)[2][4])
 {
@@ -837,23 +836,23 @@ __device__ __forceinline__ void wave_gather_sum(RowPtr rowptr, int p0, int p1, c
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             acc[k][e] = 0.f;
-    for (int i0 = p0; i0 < p1; i0 += G * UNROLL) {
-        typename GIO::Vec v[UNROLL][2];
-        const GT* rp[UNROLL];
+    for (int i0 = p0; i0 < p1; i0 += G * kBwdUnroll) {
+        typename GIO::Vec v[kBwdUnroll][2];
+        const GT* rp[kBwdUnroll];
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
+        for (int u = 0; u < kBwdUnroll; ++u) {
             const int i = i0 + u * G + c.grp;
             const GT* p = rowptr(min(i, p1 - 1));
             rp[u] = i < p1 ? p : zero_row;
         }
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
+        for (int u = 0; u < kBwdUnroll; ++u) {
             v[u][0] = GIO::ldv(rp[u] + c.e0);
             v[u][1] = GIO::ldv(rp[u] + c.e1);
         }
         GIO::requested();
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
+        for (int u = 0; u < kBwdUnroll; ++u) {
             GIO::add(acc[0], v[u][0]);
             GIO::add(acc[1], v[u][1]);
         }
@@ -864,6 +863,53 @@ __device__ __forceinline__ void wave_gather_sum(RowPtr rowptr, int p0, int p1, c
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 acc[k][e] += __shfl_xor(acc[k][e], s);
+    }
+}
+
+// The same, of the rows base + payload(i) * stride, where a row takes the whole wavefront (1 << c.lprl == kWave, rows of more than
+// 256 columns).  A run or piece of 128 such rows is a chain of trips: 32 with four rows in flight, 16 with the eight that go on
+// at once here (six of fp32).  A row is the same for all lanes, so its address is a scalar, and the rows take the registers that
+// four rows and their addresses take: the kernel keeps its wavefronts (five or six a SIMD), and the narrower tables of a call
+// lose nothing.  Update, us, four rows / these / eight with vector addresses in an instance of their own for every call with a
+// wide table, which had four wavefronts a SIMD: 4 tables of 512 fp32 columns, 70,000 Zipf lookups 39.5 / 38.7 / 35.6, uniform
+// 59.8 / 59.8 / 62.5, bf16 gradients 39.9 / 30.3 / 31.2; 4..512 columns, 0.15 M 37.1 / 34.9 / 35.6, bf16 39.2 / 31.4 / 35.3;
+// 12 tables of 64 columns, 0.48 M, beside 4 of 512 with 800, fp16 29.3 / 28.8 / 37.5 (eight fp32 rows with scalar addresses take
+// 114 registers: 35.3 for the first of these, 61.8 for the second, 54.4 for 51.6 of 4..512 columns, 0.4 M).
+template <typename GT, typename Payload>
+__device__ __forceinline__ void sum_wide_rows(Payload payload, const GT* base, int64_t stride, int p0, int p1, const GT* zero_row, const Cols& c,
+                                              float (&acc)[2][4])
+{
+    using GIO = GradIO<GT>;
+    constexpr int kRows = sizeof(GT) == 4 ? 6 : 8;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t o0 = (uint32_t)c.e0 * (uint32_t)sizeof(GT), o1 = (uint32_t)c.e1 * (uint32_t)sizeof(GT);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[k][e] = 0.f;
+    for (int first = p0; first < p1; first += kWave) {
+        const int cnt = min(kWave, p1 - first);
+        const int mine = payload(min(first + lane, p1 - 1));
+        for (int i0 = 0; i0 < cnt; i0 += kRows) {
+            typename GIO::Vec v[kRows][2];
+            uint32_t l0 = o0, l1 = o1;
+            asm volatile("" : "+v"(l0), "+v"(l1));   // (widened here, a scalar address and a 32-bit offset are one load)
+#pragma unroll
+            for (int x = 0; x < kRows; ++x) {
+                int64_t at = (int64_t)__builtin_amdgcn_readlane(mine, min(i0 + x, cnt - 1)) * stride;
+                asm volatile("" : "+s"(at));         // (no branch around the product)
+                const char* row = reinterpret_cast<const char*>(i0 + x < cnt ? base + at : zero_row);
+                v[x][0] = GIO::ldv(reinterpret_cast<const GT*>(row + l0));
+                v[x][1] = GIO::ldv(reinterpret_cast<const GT*>(row + l1));
+            }
+            GIO::requested();
+#pragma unroll
+            for (int x = 0; x < kRows; ++x) {
+                GIO::add(acc[0], v[x][0]);
+                GIO::add(acc[1], v[x][1]);
+            }
+        }
     }
 }
 
@@ -1004,7 +1050,7 @@ __device__ __forceinline__ void store_shared(float* __restrict__ dst, const floa
 }
 
 // Sum of the gradient rows of the sorted positions [p0, p1) of one table, by one wavefront; every lane group has it.
-template <typename GT, int UNROLL = kBwdUnroll>
+template <typename GT, bool WIDE = false>
 __device__ __forceinline__ void sum_lookups(const BwdArgs& a, const TableMeta& m, const Cols& c, int p0, int p1, float (&acc)[2][4])
 {
     using GIO = GradIO<GT>;
@@ -1014,6 +1060,10 @@ __device__ __forceinline__ void sum_lookups(const BwdArgs& a, const TableMeta& m
     const int32_t* __restrict__ vals = a.sorted_vals;
     const int64_t stride = a.table_major ? m.dim : a.sumD;
     const GT* gb = a.table_major ? grad_out + (int64_t)a.batch * m.col : grad_out + m.col;
+    if (WIDE && 1 << c.lprl == kWave) {
+        sum_wide_rows([&](int i) { return vals[i]; }, gb, stride, p0, p1, zero_row, c, acc);
+        return;
+    }
     const int G = kWave >> c.lprl;
 #pragma unroll
     for (int k = 0; k < 2; ++k)
@@ -1023,23 +1073,23 @@ __device__ __forceinline__ void sum_lookups(const BwdArgs& a, const TableMeta& m
     for (int base = p0; base < p1; base += kWave) {
         const int cnt = min(kWave, p1 - base);
         const int myv = vals[min(base + lane, p1 - 1)];     // 64 payloads with one coalesced load
-        for (int i0 = 0; i0 < cnt; i0 += G * UNROLL) {
-            typename GIO::Vec v[UNROLL][2];
-            const GT* rp[UNROLL];
+        for (int i0 = 0; i0 < cnt; i0 += G * kBwdUnroll) {
+            typename GIO::Vec v[kBwdUnroll][2];
+            const GT* rp[kBwdUnroll];
 #pragma unroll
-            for (int x = 0; x < UNROLL; ++x) {
+            for (int x = 0; x < kBwdUnroll; ++x) {
                 const int i = i0 + x * G + c.grp;
                 const int b = __shfl(myv, min(i, cnt - 1));
                 rp[x] = i < cnt ? gb + (int64_t)b * stride : zero_row;
             }
 #pragma unroll
-            for (int x = 0; x < UNROLL; ++x) {
+            for (int x = 0; x < kBwdUnroll; ++x) {
                 v[x][0] = GIO::ldv(rp[x] + c.e0);
                 v[x][1] = GIO::ldv(rp[x] + c.e1);
             }
             GIO::requested();
 #pragma unroll
-            for (int x = 0; x < UNROLL; ++x) {
+            for (int x = 0; x < kBwdUnroll; ++x) {
                 GIO::add(acc[0], v[x][0]);
                 GIO::add(acc[1], v[x][1]);
             }
@@ -1094,7 +1144,7 @@ __device__ __forceinline__ FoundPiece find_piece(const BwdArgs& a, int slot)
 // adds the partial rows up in their order and applies the update: whichever wavefront that is, the sum is the same.  The rows
 // are stored and loaded past the L2s; a wavefront counts its piece when its stores have arrived, and loads the others' when
 // all are counted.  (A launch of its own for the last part took 5 to 11 us, most of it its latency.)
-template <typename WT, typename GT, int OPT, int UNROLL>
+template <typename WT, typename GT, int OPT>
 __device__ __forceinline__ void piece_of_found_run(const BwdArgs& a, int slot, int run, int s, int e, int p0, int p1)
 {
     using IO = RowIO<WT, 4>;
@@ -1104,7 +1154,8 @@ __device__ __forceinline__ void piece_of_found_run(const BwdArgs& a, int slot, i
     const Cols c(m.dim, m.lpr_bwd(), lane);
     const int np = position_pieces(e - s);
     float acc[2][4];
-    sum_lookups<GT, UNROLL>(a, m, c, p0, p1, acc);
+    constexpr bool kWide = OPT == kOptRowwiseAdagrad;
+    sum_lookups<GT, kWide>(a, m, c, p0, p1, acc);
     store_shared(a.partials + (int64_t)slot * a.dpad, acc, c);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     uint32_t* done = a.piece_done + s / kPosSlot;
@@ -1117,15 +1168,18 @@ __device__ __forceinline__ void piece_of_found_run(const BwdArgs& a, int slot, i
     if (lane == 0)
         __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t wel = m.woff + (int64_t)(key - m.rbase) * m.dim;
+    const SharedFloat* rows = reinterpret_cast<const SharedFloat*>(a.partials);
+    auto slot_of = [&](int i) { return position_of_piece(s, e - s, np, i) / kPosSlot; };
     WT* wrow = static_cast<WT*>(a.weights) + wel;
     typename IO::Vec wvv[2];
+    OptRow<OPT> st;
     wvv[0] = IO::ldv(wrow + c.e0);
     wvv[1] = IO::ldv(wrow + c.e1);
-    OptRow<OPT> st;
     st.load(a.opt, key, wel, c);
-    const SharedFloat* rows = reinterpret_cast<const SharedFloat*>(a.partials);
-    wave_gather_sum<SharedFloat, UNROLL>([&](int i) { return rows + (int64_t)(position_of_piece(s, e - s, np, i) / kPosSlot) * a.dpad; }, 0, np,
-                                 a.zero_row, c, acc);
+    if (kWide && 1 << c.lprl == kWave)
+        sum_wide_rows(slot_of, rows, a.dpad, 0, np, reinterpret_cast<const SharedFloat*>(a.zero_row), c, acc);
+    else
+        wave_gather_sum<SharedFloat>([&](int i) { return rows + (int64_t)slot_of(i) * a.dpad; }, 0, np, a.zero_row, c, acc);
     optimizer_epilogue<WT, OPT>(wrow, wvv, acc, m.dim, c, c.grp == 0, a.opt, key, wel, st);
 }
 
@@ -1269,11 +1323,11 @@ enum LongRuns {
     kLongListed,       // the spans list them for other kernels
     kLongSmall,        // workgroups of this launch (a.small)
     kLongPieces,       // workgroups of this launch sum their pieces (a.piece_blocks)
-    kLongPiecesWide,   // the same, with twice the rows in flight (pieces_wide)
 };
 
 template <typename WT, typename GT, int OPT, int SPAN, int LONG>
-__global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
+// (sum_wide_rows fits the wavefronts that the kernel has without it)
+__global__ __launch_bounds__(kBwdThreads, LONG == kLongPieces && OPT == kOptRowwiseAdagrad ? (sizeof(GT) == 4 ? 5 : 6) : 1) void reduce_update_kernel(BwdArgs a)
 {
     using IO = RowIO<WT, 4>;
     const GT* __restrict__ grad_out = static_cast<const GT*>(a.grad_out);
@@ -1286,7 +1340,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
     // element-wise optimizers carry whole state rows and take one run per group
     constexpr int kNB1 = OPT != kOptRowwiseAdagrad ? 1 : sizeof(WT) == 2 ? 4 : 2;   // runs of one lookup per group
     constexpr int kNB2 = OPT != kOptRowwiseAdagrad ? 1 : 2;                          // runs of two lookups per group
-    constexpr int kUnroll = LONG == kLongPiecesWide ? kBwdUnrollWide : kBwdUnroll;
+    constexpr bool kWide = LONG == kLongPieces && OPT == kOptRowwiseAdagrad;
     static_assert(SPAN <= 256, "run indices of a span are kept in bytes");
     static_assert(kShortRun == 4, "run_batch is instantiated for 1..4 lookups");
     __shared__ int32_t s_seg_all[kWaves][kSegCap];
@@ -1304,7 +1358,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
             return;
         }
     }
-    if constexpr (LONG == kLongPieces || LONG == kLongPiecesWide) {
+    if constexpr (LONG == kLongPieces) {
         if (block < a.piece_blocks) {
             // beside the spans: in a launch of its own after them a piece added a chain of up to 128 rows to calls that are little
             // more than such chains, and 5 us to those without long runs (40 tables of 4..512 columns, 0.17 M lookups: step of
@@ -1312,7 +1366,7 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
             const int slot = uniform(block * kWaves + wv);
             const FoundPiece f = find_piece(a, slot);
             if (uniform(f.found))
-                piece_of_found_run<WT, GT, OPT, kUnroll>(a, slot, uniform(f.run), uniform(f.s), uniform(f.e), uniform(f.p0), uniform(f.p1));
+                piece_of_found_run<WT, GT, OPT>(a, slot, uniform(f.run), uniform(f.s), uniform(f.e), uniform(f.p0), uniform(f.p1));
             return;
         }
         block -= a.piece_blocks;
@@ -1529,12 +1583,16 @@ __global__ __launch_bounds__(kBwdThreads) void reduce_update_kernel(BwdArgs a)
                 WT* wrow = wtab + rel;
                 typename IO::Vec wvv[2];
                 OptRow<OPT> st;
+                float acc[2][4];
+                const bool wide = kWide && 1 << c.lprl == kWave;
                 wvv[0] = IO::ldv(wrow + c.e0);
                 wvv[1] = IO::ldv(wrow + c.e1);
                 st.load(a.opt, key, m.woff + rel, c);
-                float acc[2][4];
-                wave_gather_sum<GT, kUnroll>([&](int p) { return gb + (int64_t)s_val[p - q0] * sumD; }, s0, s0 + len0, a.zero_row,
-                                    c, acc);
+                if (wide)
+                    sum_wide_rows([&](int p) { return s_val[p - q0]; }, gb, sumD, s0, s0 + len0, reinterpret_cast<const GT*>(a.zero_row), c, acc);
+                else
+                    wave_gather_sum<GT>([&](int p) { return gb + (int64_t)s_val[p - q0] * sumD; }, s0, s0 + len0, a.zero_row,
+                                        c, acc);
                 optimizer_epilogue<WT, OPT>(wrow, wvv, acc, D, c, c.grp == 0, a.opt, key, m.woff + rel, st);
             }
             __threadfence_block();

@@ -112,13 +112,6 @@ constexpr int64_t kManyLongBytes = 16000000, kManyLongPerColumn = 65536;
 // (longer spans) have short chains and stay listed.
 constexpr int64_t kFoundLookups = 1 << 19;
 
-// Whether a call that finds its long runs by position keeps eight gradient rows in flight per lane group instead of four.  A row of
-// more than 256 columns takes the whole wavefront, and a run or piece of 128 such rows is a chain of 32 trips, or of 16; narrower
-// rows have more groups, and the registers cost them wavefronts (element-wise optimizers of any width).  Step, us, four / eight:
-// 512 columns, 70,000 lookups 99.6 / 96.0; 384, 60,000 74.2 / 70.3; 4..512, 0.17 M 79.9 / 78.3; 256, 98,000 75.0 / 75.3; 128, 0.33 M
-// 99.3 / 100.1, fp16 0.16 M 64.3 / 66.5; 64, 0.32 M 79.4 / 82.1; Adam, 128, 0.44 M 165.7 / 171.8.
-inline bool pieces_wide(bool rowwise, int64_t widest) { return rowwise && widest > 256; }
-
 constexpr int kPosPiece = 128;            // a piece by position has at most this many lookups (and fewer than that is never long) ...
 constexpr int kPosPiecesMax = 256;        // ... unless that would make more pieces of a run than this
 // Partial row of a piece: its first position / kPosSlot.  A piece has at least kPosSlot lookups, so no two share one, and a

@@ -50,8 +50,6 @@ int64_t sort_local_blocks(int64_t lookups, int64_t tables, int target, int tile,
 
 int unit_parts(int sampled, int lookups, int samples, int part) { return tbe::unit_parts((uint32_t)sampled, lookups, samples, part); }
 
-int pieces_wide(int rowwise, int64_t widest) { return tbe::pieces_wide(rowwise != 0, widest); }
-
 int select_parts(int sampled, int lookups, int samples) { return tbe::select_parts((uint32_t)sampled, lookups, samples); }
 
 uint32_t select_fewer_rows(uint32_t rows, int found) { return tbe::select_fewer_rows(rows, found); }

@@ -1,6 +1,11 @@
-"""What the compiler made of the device code built here.  The additions of 16-bit floats are written in asm, about which the
+"""What the compiler made of the device code built here.
+
+The additions of 16-bit floats are written in asm, about which the
 scheduler knows nothing: it may move them between the loads of a step, and the step then takes a trip to memory for each
-row instead of one for all.  In every kernel no basic block may load a row behind its first such addition."""
+row instead of one for all.  In every kernel no basic block may load a row behind its first such addition.
+
+The update kernel that sums long runs itself keeps more rows in flight where a row takes the whole wavefront: every table of
+a call pays for the registers, in wavefronts, unless they are those that the kernel has without it."""
 import os
 import re
 import shutil
@@ -14,8 +19,8 @@ OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """{demangled name: [basic block: its loads ('L') and mixed additions ('a') in order]} of the built library."""
+def parts(tmp_path_factory):
+    """The code objects of the built library."""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     if not os.path.exists(build.LIB):
@@ -23,9 +28,15 @@ def kernels(tmp_path_factory):
     d = tmp_path_factory.mktemp("device_code")
     shutil.copy(build.LIB, d / "libtbe.so")
     subprocess.run([OBJDUMP, "--offloading", "libtbe.so"], cwd=d, check=True, capture_output=True)
+    return [str(p) for p in sorted(d.glob("libtbe.so.*gfx950"))]
+
+
+@pytest.fixture(scope="module")
+def kernels(parts):
+    """{demangled name: [basic block: its loads ('L') and mixed additions ('a') in order]}"""
     found = {}
-    for part in sorted(d.glob("libtbe.so.*gfx950")):
-        text = subprocess.run([OBJDUMP, "-d", "-C", "--no-show-raw-insn", "--no-leading-addr", "--symbolize-operands", str(part)],
+    for part in parts:
+        text = subprocess.run([OBJDUMP, "-d", "-C", "--no-show-raw-insn", "--no-leading-addr", "--symbolize-operands", part],
                               check=True, capture_output=True, text=True).stdout
         blocks = None
         for line in text.splitlines():
@@ -49,3 +60,21 @@ def test_rows_of_a_step_are_requested_before_the_first_is_added(kernels):
         assert any(name in k for k in mixed), name
     late = [k for k, blocks in mixed.items() if any(re.search("a.*L", b) for b in blocks)]
     assert not late, late
+
+
+def test_update_that_sums_long_runs_keeps_its_wavefronts(parts):
+    registers = {}
+    for part in parts:
+        text = subprocess.run([OBJDUMP.replace("objdump", "readelf"), "--notes", part], check=True, capture_output=True, text=True).stdout
+        for kernel in text.split(".agpr_count:")[1:]:
+            value = lambda key: int(re.search(key + r":\s+(\d+)", kernel)[1])
+            registers[re.search(r"\.symbol:\s+'?([\w.]+)\.kd", kernel)[1]] = value(r"\.vgpr_count"), value(r"\.private_segment_fixed_size")
+    names = subprocess.run(["c++filt"], input="\n".join(registers), capture_output=True, text=True, check=True).stdout.split("\n")
+    seen = 0
+    for (vgprs, scratch), name in zip(registers.values(), names):
+        row = re.search(r"reduce_update_kernel<(.*), (.*), 0, 16, [2-9]>", name)     # row-wise AdaGrad; 0 and 1 leave long runs to others
+        if row:
+            # 512 registers a lane in steps of eight: five wavefronts a SIMD with rows of fp32, six with 16-bit ones
+            assert scratch == 0 and vgprs <= (96 if row[2] == "float" else 80), (name, vgprs, scratch)
+            seen += 1
+    assert seen == 6, seen

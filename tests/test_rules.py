@@ -159,8 +159,6 @@ def test_which_long_runs_are_cut_how(rules):
         out = np.empty(4, np.int32)
         rules.long_run_rule(ctypes.c_int64(n), ctypes.c_int64(batch), ctypes.c_int64(128), ctypes.c_int(4), out.ctypes.data_as(ctypes.c_void_p))
         return bool(out[3])
-    wide = lambda rowwise, widest: bool(rules.pieces_wide(ctypes.c_int(rowwise), ctypes.c_int64(widest)))
-    assert wide(1, 257) and not wide(1, 256) and not wide(0, 512)
     assert found(1 << 19, 8192) and not found((1 << 19) + 1, 8192) and not found(1000, 8193)
     assert rule(3_999_999, 8192, 128, 4) == [1, 0, 128] and rule(4_000_000, 8192, 128, 4) == [1, 1, 512]
     assert rule(4_000_000, 8193, 128, 4) == rule(1, 8193, 128, 4) == [0, 1, 512] and rule(1, 8193, 128, 2) == [1, 0, 128]
