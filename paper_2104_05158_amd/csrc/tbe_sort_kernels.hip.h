@@ -76,7 +76,7 @@ struct SortUnit {        // 32 bytes
     uint32_t key0;       // linear row id that row offset 0 stands for
     int32_t bits;        // bits of the row offsets to sort
     uint16_t t, bucket;  // (bucket: pieces)
-    int32_t flags;       // kUnit...; the part's number in the bits from 8 on
+    int32_t flags;       // kUnit...; select: the part's number in the bits from 8 on; pieces: there, and the last's from 20 on
     int32_t first;       // the table's first unit (they are numbered one after the other)
     uint32_t last;       // select: offset of the unit's last row from key0 (of the last unit: of any index); pieces: the table's first chunk
 };
@@ -84,7 +84,7 @@ static_assert(kPiecesChunk == kSortTile, "sort_scatter_kernel<.., true> orders o
 static_assert(sizeof(SortUnit) == 32 && kManyTables <= 65536, "");
 constexpr int kUnitContinued = 1;     // further part of a one-row bucket: its first lookup starts no run
 constexpr int kUnitNone = 2;          // (select, pieces) no bucket; until the unit is sorted its start and m are those of the table
-constexpr int kUnitMore = 4;          // (select, pieces) further parts follow
+constexpr int kUnitMore = 4;          // (select) further parts follow
 
 // How the lookups come to their units: by a partition with known places (histogram, units, scatter), every unit finding its
 // own among all of the table's (use_select_sort), or every chunk sorted by bucket where it lies and the units collecting
@@ -743,8 +743,9 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             SortUnit u{start, n, rbase + lo[k], ceil_log2(hi[k] - lo[k]), (uint16_t)t, (uint16_t)i, 0, (int32_t)s_sum[3], 0};
             // (an index that is no row of the table is the last bucket's)
             u.last = MODE == kSortPieces ? (uint32_t)st.chunk_base : i + 1 < nb ? hi[k] - lo[k] - 1u : ~0u - lo[k];
+            static_assert((int64_t)kPiecesMax * kPiecesChunk / kSortTile < 1 << 12, "a part's number");
             for (uint32_t j = 0; j < parts[k]; ++j) {
-                u.flags = (int32_t)(j << 8) | (j + 1 < parts[k] ? kUnitMore : 0);
+                u.flags = (int32_t)(MODE == kSortPieces ? (parts[k] - 1u) << 20 | j << 8 : j << 8 | (j + 1 < parts[k] ? (uint32_t)kUnitMore : 0u));
                 a.units[at++] = u;
             }
         }
@@ -1198,7 +1199,9 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 4 : 2) void sort_sca
 // pieces start says how many lookups of the table go before the unit: no histogram, no second walk over the indices.  A unit
 // that does not fit is collected in memory, where its keys will be.  8 tables, 0.66 M lookups: 16.7 us instead of 14.7, for 9.1
 // of the histogram and 6.0 of the units; 64 tables, 6.2 M: 56 instead of 49, for 27 (the words of a unit are collected four a
-// thread at a time: with eight, registers spill and every reload is a trip to memory, 22 us instead of 16.7).
+// thread at a time: with eight, registers spill and every reload is a trip to memory, 22 us instead of 16.7).  Collecting is
+// one pass more for a unit of several rows that does not fit: where the sample misses 1000 rows that have nearly all of
+// 0.9 M lookups, the sort takes 4.3 ms instead of 3.7.
 constexpr int kCollect = 4;
 
 template <typename W, bool PIECES>
@@ -1275,15 +1278,19 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
             __syncthreads();
             start = table_start + uniform((int)before);
             m_all = uniform((int)slots);
-            if (bits == 0) {                         // of a row with several units this one's part, the last takes the rest
-                const int part = flags >> 8;
-                from_slot = min(part * kSortTile, m_all);
-                m_all = (flags & kUnitMore ? min((part + 1) * kSortTile, m_all) : m_all) - from_slot;
+            // Of a row with several units this one's share.  Their number is the sample's guess: a tile each with the rest for
+            // the last one, that one had a few tiles too many every other time (16 tables of 300 rows, 2 M Zipf lookups 58.4 us,
+            // 54.5 with shares).  A row that the sample has missed altogether stays with one workgroup, 0.8 us for 1000
+            // lookups of it: no input whose rows do not depend on mix_bits of their positions has one.
+            if (bits == 0) {
+                const uint32_t part = (uint32_t)flags >> 8 & 0xfffu, parts = ((uint32_t)flags >> 20) + 1u;
+                from_slot = (int)((uint64_t)(uint32_t)m_all * part / parts);
+                m_all = (int)((uint64_t)(uint32_t)m_all * (part + 1u) / parts) - from_slot;
                 start += from_slot;
             }
             large = m_all > kSortTile;
-            // The words go to LDS, those of a unit that does not fit where its keys will be.  A wavefront has a stretch of the
-            // slots and walks the chunks that have them, the next 64 in its lanes.
+            // The words go to LDS, those of a unit that does not fit where its keys will be, or are keys and payloads already if they
+            // are of one row.  A wavefront has a stretch of the slots and walks the chunks that have them, the next 64 in its lanes.
 #pragma unroll 1
             for (int first = 0; first < m_all; first += kSortTile) {
                 const int m = min(kSortTile, m_all - first), rounds = group_count<kSortGroup>(m) * kSortGroup;
@@ -1325,8 +1332,12 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
                         if (r0 + r < rounds) {
                             if (!large)
                                 s_w[i] = i < m ? w[r] : ~(W)0;
-                            else if (i < m)
-                                reinterpret_cast<W*>(a.keys)[start + first + i] = w[r];
+                            else if (i < m && bits > 0)
+                                a.keys[start + first + i] = (uint32_t)w[r];
+                            else if (i < m) {
+                                a.keys[start + first + i] = key0 + (uint32_t)(w[r] >> a.vb);
+                                a.vals[start + first + i] = (int32_t)(w[r] & vmask);
+                            }
                         }
                     }
                 }
@@ -1455,7 +1466,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(W) == 4 ? 6 : 4) void sort_loc
                 heads = 1;
             }
 #pragma unroll 4
-            for (int i = opaque(tid); i < m_all; i += kSortThreads) {
+            for (int i = PIECES && bits == 0 ? m_all : opaque(tid); i < m_all; i += kSortThreads) {
                 const W x = src[i];
                 a.keys[start + i] = key0 + (uint32_t)(x >> a.vb);
                 a.vals[start + i] = (int32_t)(x & vmask);
