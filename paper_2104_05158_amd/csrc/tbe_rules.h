@@ -105,11 +105,14 @@ constexpr int64_t kPositionBlock = 4 << 20;
 constexpr int64_t kManyLongBytes = 16000000, kManyLongPerColumn = 65536;
 
 // Lookups up to which the long runs of a call without dense ones are found by position instead of listed: every partial row
-// there could be takes a wavefront that looks for it, which a larger call does not get back (step, us, listed / found, with the
-// partial rows added up in a launch of their own: 40
-// tables of 4..512 columns, 0.17 M 103 / 85; 512 columns, 0.2 M 171 / 154; 128, 0.33 M 94 / 92; uniform, 0.65 M 295 / 298;
-// 16-bit, 2 M 358 / 361, 6.2 M 688 / 694; 256 fp32 columns, 3.6 M 544 / 548; found and finished by a launch of 4096 wavefronts, 16-bit, 6.2 M 670 / 729).  Narrow rows
-// (longer spans) have short chains and stay listed.
+// there could be takes a wavefront that looks for it, and the one that sums the last piece of a run finishes it; a list takes
+// two launches more.  Update, us, listed / found: 8 tables of 128 fp32 columns, 60,000 lookups uniform 22.5 / 18.6, Zipf 1.05
+// 26.3 / 15.0; 0.5 M 121 / 116, 67.8 / 61.1; 4..512 columns, 0.15 M 51.0 / 47.3, 59.8 / 34.9; 256, 0.5 M 225 / 222, 112.6 /
+// 111.8; 64 of 128, 16-bit, 0.5 M 83.9 / 77.6, 60.3 / 47.3.  Beyond the line (uniform within the spread of the runs, Zipf):
+// 8 of 128 fp32 columns, 0.66 M 78.8 / 73.4, 1 M 109 / 107, 1.5 M 154 / 155, 3.9 M 314 / 318; 16 of 128, 1 M 134 / 128, 2 M 204 /
+// 202; 64 of 128, 16-bit, 1 M 125 / 107, 1.5 M 151 / 151; but 8 of 256, 1 M 189 / 192, 1.5 M 247 / 254.  Up to the line no call
+// loses; calls of up to 1 M and 128 columns would still gain 2 to 15 %.  Narrow rows (longer spans) have short chains and stay
+// listed.
 constexpr int64_t kFoundLookups = 1 << 19;
 
 constexpr int kPosPiece = 128;            // a piece by position has at most this many lookups (and fewer than that is never long) ...
