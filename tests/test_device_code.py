@@ -5,7 +5,8 @@ scheduler knows nothing: it may move them between the loads of a step, and the s
 row instead of one for all.  In every kernel no basic block may load a row behind its first such addition.
 
 The update kernel that sums long runs itself keeps more rows in flight where a row takes the whole wavefront: every table of
-a call pays for the registers, in wavefronts, unless they are those that the kernel has without it."""
+a call pays for the registers, in wavefronts, unless they are those that the kernel has without it.  Its wavefronts count their pieces when
+the stores of their sums have arrived, which only an instruction between them says."""
 import os
 import re
 import shutil
@@ -33,7 +34,8 @@ def parts(tmp_path_factory):
 
 @pytest.fixture(scope="module")
 def kernels(parts):
-    """{demangled name: [basic block: its loads ('L') and mixed additions ('a') in order]}"""
+    """{demangled name: [basic block: its loads ('L') and mixed additions ('a'), stores of 8 bytes past the L2s ('S'), counts ('C')
+    and waits for all of memory ('W') in order]}"""
     found = {}
     for part in parts:
         text = subprocess.run([OBJDUMP, "-d", "-C", "--no-show-raw-insn", "--no-leading-addr", "--symbolize-operands", part],
@@ -47,6 +49,12 @@ def kernels(parts):
                 blocks.append("")
             elif blocks is not None and re.match(r"\s*(global|buffer)_load", line):
                 blocks[-1] += "L"
+            elif blocks is not None and re.match(r"\s*global_store_dwordx2.* sc1", line):
+                blocks[-1] += "S"
+            elif blocks is not None and "s_waitcnt vmcnt(0)" in line:
+                blocks[-1] += "W"
+            elif blocks is not None and re.match(r"\s*global_atomic_add v.* sc0", line):
+                blocks[-1] += "C"
             elif blocks is not None and "v_fma_mix_f32" in line:
                 blocks[-1] += "a"
             elif blocks is not None and re.match(r"\s*s_(cbranch|branch)", line):
@@ -78,3 +86,11 @@ def test_update_that_sums_long_runs_keeps_its_wavefronts(parts):
             assert scratch == 0 and vgprs <= (96 if row[2] == "float" else 80), (name, vgprs, scratch)
             seen += 1
     assert seen == 6, seen
+
+
+def test_a_piece_is_counted_after_its_stores_have_arrived(kernels):
+    counting = [k for k in kernels if re.search(r"reduce_update_kernel<.*, .*, [012], 16, 2>", k)]
+    assert len(counting) == 18
+    for k in counting:
+        order = "".join(kernels[k])
+        assert re.search("S[^SWC]*W[^SWC]*C", order) and not re.search("S[^W]*C", order), k
