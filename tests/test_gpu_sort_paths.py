@@ -1,6 +1,8 @@
 """GPU test of every path of the backward's sort: the one-workgroup sort of small calls and its size limits, buckets of
 one row, crowded row ids, tables cut by the range of a packed word, 64-bit words, a bucket larger than a tile (the
-sample is made to miss its rows), more tables than lookups, empty tables and empty bags.  Keys, payloads, unique keys
+sample is made to miss its rows), more tables than lookups, empty tables and empty bags.  Words of 64 bits are partitioned here;
+those of 32 only in calls of more than 2^23 lookups (test_gpu_sort_partition.py), and the calls of this size have units that find
+(test_gpu_sort_select.py) or collect (test_gpu_sort_pieces.py) their lookups.  Keys, payloads, unique keys
 and segment offsets must equal a stable argsort by (table, row) bit for bit."""
 import numpy as np
 import pytest
@@ -68,6 +70,7 @@ CASES = {
 
 @pytest.mark.parametrize("case", sorted(CASES))
 def test_paths_of_the_partition(gpu_device, case):
+    """What the borders of the buckets have to cope with, whichever way the lookups come to them."""
     rows, batch, per_table, ids = CASES[case]
     rng = np.random.default_rng(len(case))
     lens = np.concatenate([_lens(rng, batch, n) for n in per_table])
@@ -108,7 +111,7 @@ def test_bucket_larger_than_a_tile(gpu_device, n, rows, batch):
 
 @pytest.mark.parametrize("chunks,extra", [(16, 0), (32, 0), (32, 1), (75, 0), (76, 0), (257, -1)])
 def test_tables_of_few_and_of_many_chunks(gpu_device, chunks, extra):
-    # up to 32 chunks of a tile, or 96 of all tables, a table's counts are added up where its units are made, beyond by a kernel
+    # tables on both sides of 16, 32, 75 and 256 chunks, beside short ones and an empty one
     rng = np.random.default_rng(chunks)
     rows, per_table = [150_000, 9, 700, 2_000_000], [chunks * TILE + extra, 3 * TILE, 0, 17 * TILE]
     lens = np.concatenate([_lens(rng, 300, n) for n in per_table])
