@@ -1333,7 +1333,8 @@ enum LongRuns {
 
 template <typename WT, typename GT, int OPT, int SPAN, int LONG>
 // (sum_wide_rows fits the wavefronts that the kernel has without it)
-__global__ __launch_bounds__(kBwdThreads, LONG == kLongPieces && OPT == kOptRowwiseAdagrad ? (sizeof(GT) == 4 ? 5 : 6) : 1) void reduce_update_kernel(BwdArgs a)
+__global__ __launch_bounds__(kBwdThreads, LONG == kLongPieces && OPT == kOptRowwiseAdagrad ? (sizeof(GT) == 4 ? 5 : 6) : 1)
+void reduce_update_kernel(BwdArgs a)
 {
     using IO = RowIO<WT, 4>;
     const GT* __restrict__ grad_out = static_cast<const GT*>(a.grad_out);

@@ -288,9 +288,11 @@ inline bool use_pieces_sort(bool words32, int64_t lookups, int chunk)
 }
 
 // Workgroups of the bucket sort: one per unit there can be (and no fewer than are resident: tables cut by the packed range have
-// more units) while those are at most kUnitsDispatched, otherwise as many as are resident, which take the units one by one.  An atomic on one word and a descriptor wait in front of every unit (with 768 workgroups, us, ->
-// one each: 64 tables, 2 M lookups 74 -> 64, 8 M 139 -> 133, 20 M 286 -> 283), but a workgroup's start costs more once there
-// are tens of thousands (128 tables, 100 M lookups 1285 -> 1319).
+// more units) while those are at most kUnitsDispatched, otherwise as many as are resident, which take the units one by one.  An
+// atomic on one word and a descriptor wait in front of every unit (sort, us, with 768 workgroups -> one each: 64 tables, 2 M
+// lookups 74 -> 64, 8 M 139 -> 133, 20 M 286 -> 283; words of 64 bits, 512 workgroups: 8 tables, 1 M 77 -> 74, 4 M 133 -> 127, 16 M
+// 388 -> 391, 24 M 557 -> 552; 32 tables, 2 M 100 -> 95, 8 M 207 -> 204, 20 M 455 -> 456), but a workgroup's start costs more
+// once there are tens of thousands (128 tables, 100 M lookups 1285 -> 1319).
 constexpr int64_t kUnitsDispatched = 8192;
 
 inline int64_t sort_local_blocks(int64_t lookups, int64_t tables, int target, int tile, int64_t resident)

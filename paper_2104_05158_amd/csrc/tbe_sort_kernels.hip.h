@@ -745,7 +745,8 @@ __global__ __launch_bounds__(kSortThreads) void sort_plan_kernel(SortArgs a)
             u.last = MODE == kSortPieces ? (uint32_t)st.chunk_base : i + 1 < nb ? hi[k] - lo[k] - 1u : ~0u - lo[k];
             static_assert((int64_t)kPiecesMax * kPiecesChunk / kSortTile < 1 << 12, "a part's number");
             for (uint32_t j = 0; j < parts[k]; ++j) {
-                u.flags = (int32_t)(MODE == kSortPieces ? (parts[k] - 1u) << 20 | j << 8 : j << 8 | (j + 1 < parts[k] ? (uint32_t)kUnitMore : 0u));
+                const uint32_t last = MODE == kSortPieces ? (parts[k] - 1u) << 20 : j + 1 < parts[k] ? (uint32_t)kUnitMore : 0u;
+                u.flags = (int32_t)(last | j << 8);
                 a.units[at++] = u;
             }
         }
